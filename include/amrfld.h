@@ -86,7 +86,8 @@ typedef struct {
   int nsub[32];          /* substeps of level l per step of level l-1; 0 means 2 */
   int check_every;       /* PCG iterations between host convergence checks; 0 = auto */
   int true_residual;     /* 1: compute ||b - A x|| after each solve for the stats */
-  int time_sweeps;       /* N > 0: time the sweep of every N-th CG iteration with HIP events */
+  int time_sweeps;       /* N > 0: time the sweep of every N-th CG iteration with HIP events (a resident
+                            solve, see amrfld_solve_level: all its iterations, with the device's clock) */
   double inner_tol;      /* AMRFLD_MIXED: residual reduction of each FP32 inner CG segment between two
                             FP64 refinement sweeps; default 3e-3 */
   int max_outer;         /* AMRFLD_MIXED: refinement sweeps cap; default 30 */
@@ -187,7 +188,13 @@ amrfld_status amrfld_set_coeffs(amrfld_ctx* c, int level, const double* rho, con
  * fine-to-coarse face energies to the parent level's flux register in Neumann /
  * Robin mode (eq. mean_flux) and clear this level's register.  With a
  * temperature the coupling term is included and T is updated.
- * Returns AMRFLD_E_NOCONV if max_iter was reached. */
+ * Returns AMRFLD_E_NOCONV if max_iter was reached.
+ * An FP64 solve whose level fits the device's registers and LDS (about 1.3 million
+ * slots) runs in one launch that keeps the whole CG state on the chip, whatever
+ * max_blocks, form_coefs and persistent say (stats: sweep_blocks = launch_blocks = its
+ * blocks, launch_mode as asked for); the other levels run in sweeps.  Should that launch
+ * not end because its blocks do not reach the device together, the solve is repeated in
+ * sweeps. */
 amrfld_status amrfld_solve_level(amrfld_ctx* c, int level, double dt, int bc_mode, double tol);
 
 /* For callers that cannot allocate device memory (tight serving loops, harnesses

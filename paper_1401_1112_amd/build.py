@@ -10,7 +10,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libamrfld.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-SOURCES = ["tables.cpp", "setup.hip", "pcg.hip", "signal.hip", "api.hip"]
+SOURCES = ["tables.cpp", "resident_plan.cpp", "setup.hip", "pcg.hip", "resident.hip", "signal.hip", "api.hip"]
 FLAGS = [
     "-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

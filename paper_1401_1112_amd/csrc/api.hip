@@ -17,6 +17,7 @@
 
 #include "../../include/amrfld.h"
 #include "device.h"
+#include "resident.h"
 #include "signal.h"
 #include "tables.h"
 
@@ -116,8 +117,21 @@ double* scratch_of(int dev, std::string* why) {
   return g_scratch_ptr[dev];
 }
 
+// Device tables and exchange memory of a resident plan, owned.
+struct ResTables {
+  ResPlanDev d;
+
+  void release() {
+    for (const void* p : {(const void*)d.parts, (const void*)d.places, (const void*)d.partner, (const void*)d.task0,
+                          (const void*)d.task, (const void*)d.lines, (const void*)d.halo, (const void*)d.epoch})
+      dfree(const_cast<void*>(p));
+    d = ResPlanDev{};
+  }
+};
+
 struct LevelState {
   LevelTables t;
+  ResTables res;  // resident solves of this level (no tables: the level does not fit)
   int32_t *nbr = nullptr, *cnb = nullptr, *parent = nullptr, *child = nullptr;
   bool tables_uploaded = false, child_dirty = true;
   double *rho = nullptr, *E = nullptr, *T = nullptr, *K = nullptr;
@@ -152,6 +166,7 @@ struct LevelState {
     rho = E = T = K = Cp = diag = b = reg = Ch = rs = nullptr;
     mask = nullptr;
     tables_uploaded = false;
+    res.release();
   }
 };
 
@@ -236,6 +251,7 @@ struct amrfld_ctx {
   amrfld_opts o{};
   std::string err;
   int device = 0;  // current device when the context was created
+  int n_cu = 0;    // its compute units
   uint64_t param_epoch = 0;  // bumped by every call that changes what a captured step bakes in
   StepGraph step_graph;
   int finest = -1;
@@ -263,6 +279,7 @@ struct amrfld_ctx {
   hipStream_t cap_stream = nullptr;  // library stream for graph capture (default priority)
   hipEvent_t cap_ev[2] = {nullptr, nullptr};
   hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};
+  hipEvent_t gate_ev = nullptr;  // end of this context's last launch whose blocks wait for each other
   std::vector<hipEvent_t> sweep_ev;  // 4 per iteration when sweeps are timed
   std::vector<amrfld_stats> stats;
 
@@ -276,6 +293,34 @@ struct amrfld_ctx {
 };
 
 namespace {
+
+// Launches whose blocks wait for each other (resident and persistent solves) need all
+// their blocks on the device together, so two of them must not share it: a launch of
+// another context waits on the device for the last one's end.  Held for the launch.
+struct WaitingLaunch {
+  std::mutex mu;
+  const amrfld_ctx* owner = nullptr;  // of the last launch, while its context lives
+};
+WaitingLaunch g_waiting[kMaxDevices];
+
+class WaitingScope {
+ public:
+  WaitingScope(amrfld_ctx* c, hipStream_t s)
+      : c_(c), s_(s), w_(g_waiting[std::max(0, std::min(c->device, kMaxDevices - 1))]), lk_(w_.mu) {
+    if (w_.owner && w_.owner != c) check(hipStreamWaitEvent(s, w_.owner->gate_ev, 0), "launch order");
+  }
+  // after the launch
+  void launched() {
+    check(hipEventRecord(c_->gate_ev, s_), "launch order");
+    w_.owner = c_;
+  }
+
+ private:
+  amrfld_ctx* c_;
+  hipStream_t s_;
+  WaitingLaunch& w_;
+  std::lock_guard<std::mutex> lk_;
+};
 
 // Caller arrays that a kernel reads or writes must be device memory (a host
 // pointer would fault in the kernel): checked before any launch.
@@ -353,6 +398,62 @@ void ensure_workspace32(amrfld_ctx* c, int64_t n) {
   alloc_vecs(c->cg32, n, "workspace fp32");
   c->x_alt = dalloc<double>(n, "workspace x");
   c->ws32_n = n;
+}
+
+// Exchange numbers start at 1 over a cleared exchange memory (stamp 0 is never awaited).
+void reset_exchange(hipStream_t s, const ResPlanDev& d) {
+  launch_fill_u32(s, reinterpret_cast<unsigned*>(d.lines), int64_t(4) * d.n_parts * kResLine, 0u);
+  launch_fill_u32(s, reinterpret_cast<unsigned*>(d.halo), int64_t(32) * d.n_units, 0u);
+  launch_fill_u32(s, d.epoch, d.n_prob, 1u);
+  launch_fill_u32(s, d.epoch + d.n_prob, d.n_prob + 1, 0u);
+}
+
+template <class T>
+const T* upload_const(const std::vector<T>& v, const char* what, hipStream_t s) {
+  T* p = dalloc<T>(int64_t(v.size()), what);
+  const hipError_t e = hipMemcpyAsync(p, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice, s);
+  if (e != hipSuccess) dfree(p);
+  check(e, what);
+  return p;
+}
+
+// Device tables of a resident plan (none where it does not fit a resident launch); the
+// stream is synchronised before the host vectors go.
+ResTables make_res_tables(hipStream_t s, const ResPlanHost& h, int n_prob) {
+  ResTables r;
+  r.d.n_parts = int(h.parts.size());
+  r.d.n_units = int(h.partner.size());
+  r.d.n_prob = n_prob;
+  r.d.n_blocks = int(h.task0.size()) - 1;
+  r.d.max_slots = h.max_slots;
+  r.d.max_units = h.max_units;
+  if (!resident_fits(r.d)) return ResTables{};
+  try {
+    r.d.parts = upload_const(h.parts, "resident plan", s);
+    r.d.places = reinterpret_cast<const uint2*>(upload_const(h.places, "resident plan", s));
+    r.d.partner = upload_const(h.partner, "resident plan", s);
+    r.d.task0 = upload_const(h.task0, "resident plan", s);
+    r.d.task = upload_const(h.task, "resident plan", s);
+    r.d.lines = dalloc<unsigned long long>(int64_t(2) * r.d.n_parts * kResLine, "resident exchange");
+    r.d.halo = dalloc<unsigned long long>(int64_t(16) * r.d.n_units, "resident exchange");
+    r.d.epoch = dalloc<unsigned>(2 * n_prob + 1, "resident exchange");
+    reset_exchange(s, r.d);
+    check(hipStreamSynchronize(s), "resident plan");
+  } catch (...) {
+    (void)hipStreamSynchronize(s);
+    r.release();
+    throw;
+  }
+  return r;
+}
+
+// The resident plan of one level, one share per compute unit at most.
+ResTables level_res_tables(const amrfld_ctx* c, const LevelTables& t) {
+  const int g = res_group(t.n_oct, c->n_cu, kResMaxSlots, kResTargetSlots);
+  if ((t.n_oct + g - 1) / g * 8 > kResMaxSlots) return ResTables{};
+  ResProblem p;
+  p.n_oct = t.n_oct;
+  return make_res_tables(c->stream(), build_res_plan({p}, {g}, g, t.nbr.data(), t.n_oct), 1);
 }
 
 // The level's device tables: allocated all together (a failed allocation leaves
@@ -576,7 +677,12 @@ int pcg_iterations(amrfld_ctx* c, const DevLevel& D, const SweepPlan& P, const S
     const int blocks = persistent_blocks<T>(Pp, per_cu);
     if (blocks > 0) {
       launch_zero_u32(s, c->bar, kBarWords);
-      const hipError_t e = launch_pcg_persistent<T>(s, D, Pp, max_iter, Ah, v, x, sc_dev, c->partials, c->bar, per_cu);
+      hipError_t e;
+      {
+        WaitingScope order(c, s);
+        e = launch_pcg_persistent<T>(s, D, Pp, max_iter, Ah, v, x, sc_dev, c->partials, c->bar, per_cu);
+        if (e == hipSuccess) order.launched();
+      }
       if (e == hipSuccess) {
         read_scalars(c, sc_host, sc_dev, np);
         unsigned aborted = 0;
@@ -811,7 +917,13 @@ void pcg_mixed(amrfld_ctx* c, const DevLevel& D, const SweepPlan& P, const Sweep
     const int blocks = mixed_persistent_blocks(Pp, P32p, c->o.persistent_per_cu);
     if (blocks > 0) {
       launch_zero_u32(s, c->bar, kBarWords);
-      if (launch_mixed_persistent(s, D, Pp, P32p, M, c->o.persistent_per_cu) == hipSuccess) {
+      hipError_t e;
+      {
+        WaitingScope order(c, s);
+        e = launch_mixed_persistent(s, D, Pp, P32p, M, c->o.persistent_per_cu);
+        if (e == hipSuccess) order.launched();
+      }
+      if (e == hipSuccess) {
         unsigned aborted = 0;
         check(hipMemcpyAsync(&aborted, c->bar + kBarAbort, sizeof(unsigned), hipMemcpyDeviceToHost, s), "abort flag");
         check(hipStreamSynchronize(s), "abort flag");
@@ -853,6 +965,60 @@ void pcg_mixed(amrfld_ctx* c, const DevLevel& D, const SweepPlan& P, const Sweep
   if (x_cur != A.x) launch_copy_f64(s, A.x, x_cur, A.n);
 }
 
+// FP64 solves of levels whose state fits the device's registers and LDS run resident;
+// the other forms (mixed precision, larger levels) in sweeps.
+bool use_resident(const amrfld_ctx* c, const LevelState& L) {
+  return c->o.precision == AMRFLD_FP64 && resident_fits(L.res.d);
+}
+
+ResArgs resident_args(const amrfld_ctx* c, const LevelState& L, double dt, double tol, PcgScalars* sc) {
+  ResArgs a;
+  a.Cp = L.Cp;
+  a.Cm = L.Ch;
+  a.diag = L.diag;
+  a.b = L.b;
+  a.x = L.E;
+  a.sc = sc;
+  a.tol = tol;
+  a.abs_floor = c->o.abs_floor;
+  a.max_iter = c->o.max_iter;
+  a.linf_test = c->o.linf_test;
+  a.true_residual = c->o.true_residual;
+  a.cp = cparams(c, L);
+  a.rho = L.rho;
+  a.T_out = L.T;
+  a.dt = dt;
+  a.spin_limit = kResSpinLimit;
+  return a;
+}
+
+// Launches a resident solve in its turn; false: not launchable here.
+bool run_resident(amrfld_ctx* c, hipStream_t s, const DevLevel& D, const ResPlanDev& R, const ResArgs& a) {
+  if (R.n_blocks == 1) {  // waits for nobody
+    if (launch_resident(s, D, R, a) == hipSuccess) return true;
+  } else {
+    WaitingScope order(c, s);
+    if (launch_resident(s, D, R, a) == hipSuccess) {
+      order.launched();
+      return true;
+    }
+  }
+  (void)hipGetLastError();
+  return false;
+}
+
+// A resident launch that ended without its result because a wait between its blocks
+// timed out: clears the exchange for the next launch.  Returns false when no block had
+// begun to write its result (the caller solves in sweeps); throws otherwise.
+bool resident_timed_out(amrfld_ctx* c, hipStream_t s, const ResPlanDev& d) {
+  unsigned w[2] = {0, 0};  // one problem: its number and the number at its last write
+  check(hipMemcpyAsync(w, d.epoch, sizeof(w), hipMemcpyDeviceToHost, s), "resident flags");
+  check(hipStreamSynchronize(s), "resident flags");
+  reset_exchange(s, d);
+  if (w[0] == w[1]) throw HipError("resident solve: an exchange between blocks timed out");
+  return false;
+}
+
 // One backward-Euler step of one level (Sect. 3.3.4).
 amrfld_status solve_one(amrfld_ctx* c, int level, double dt, int mode, double tol) {
   const hipStream_t s = c->stream();
@@ -872,38 +1038,63 @@ amrfld_status solve_one(amrfld_ctx* c, int level, double dt, int mode, double to
   launch_cell_K(s, D, L.E, L.rho, Lc ? Lc->E : nullptr, kparams(L), outer_bc(c), L.K);
   const double w = mode == AMRFLD_BC_DIRICHLET ? 1.0 : mode == AMRFLD_BC_NEUMANN ? 0.0 : c->o.robin_alpha;
   const CouplingParams cp = cparams(c, L);
+  double* Cm = use_resident(c, L) ? L.Ch : nullptr;  // the sweeps' scaled operator is not formed then
   launch_assemble(s, D, L.K, Lc ? Lc->K : nullptr, L.E, Lc ? Lc->E : nullptr, L.rho, L.reg, dt, w,
-                  c->o.robin_alpha, cp, kparams(L), outer_bc(c), L.Cp, L.mask, L.diag, L.b);
+                  c->o.robin_alpha, cp, kparams(L), outer_bc(c), L.Cp, L.mask, L.diag, L.b, Cm);
   const double scale = dt / (D.dx * D.dx);
   if (c->o.theta != 1.0)
     launch_theta_step(s, D, c->o.theta, L.E, face_coefs(c, L.Cp, L.K, L.mask, scale, 1.0, false), L.Cp, L.diag,
-                      L.b);
-  const FaceCoefs<double> Aop = face_coefs(c, L.Cp, L.K, L.mask, scale, c->o.theta, false);
-  const ScaledOp<double> Ah = scale_operator(c, s, D, Aop, L.Cp, L.diag, L.rs, L.Ch);
-
+                      L.b, Cm);
+  ensure_scalars(c, 1);
   const int n_tiles = tiles_of(D.n_slots);
   const SweepPlan P = level_plan(c, n_tiles);
-  ensure_scalars(c, 1);
   LoopStats ls;
   ls.iters.assign(1, 0);
-  const SolveArrays A{Aop, L.diag, L.b, L.E, D.n_slots, Ah};
-  if (c->o.precision == AMRFLD_MIXED) {
-    pcg_mixed(c, D, P, level_plan(c, n_tiles, kMaxTilesPerBlock32), A, tol, &ls);
-  } else {
-    pcg_fp64(c, D, P, A, tol, &ls, L.last_iters);
+  const bool registers = Lc && (mode == AMRFLD_BC_NEUMANN || mode == AMRFLD_BC_ROBIN);
+  double* reg_c = registers ? ensure_reg(c, *Lc) : nullptr;
+  bool resident = use_resident(c, L);
+  if (resident) {
+    check(hipEventRecord(c->ev[1], s), "event");
+    if (run_resident(c, s, D, L.res.d, resident_args(c, L, dt, tol, c->sc))) {
+      check(hipEventRecord(c->ev[2], s), "event");
+      if (registers)
+        launch_flux_register(s, D, L.K, Lc->K, L.E, Lc->E, dt, reg_c, int(Lc->t.n_slots()), &c->sc->done);
+      if (L.reg) launch_fill(s, L.reg, 6 * L.t.n_slots(), 0.0);
+      check(hipEventRecord(c->ev[3], s), "event");
+      read_scalars(c, c->h_sc, c->sc, 1);
+      check(hipGetLastError(), "kernels");
+      if (!c->h_sc->done) resident = resident_timed_out(c, s, L.res.d);
+      ls.persistent = c->o.persistent != 0;
+      ls.launch_blocks = L.res.d.n_blocks;
+      if (c->o.time_sweeps > 0) {
+        ls.n_timed = c->h_sc->iter;
+        ls.sweep_ms = c->h_sc->loop_ms;
+      }
+    } else {
+      resident = false;  // not launchable here: sweeps instead
+    }
   }
-  check(hipEventRecord(c->ev[2], s), "event");
-  if (c->o.true_residual && c->o.precision != AMRFLD_MIXED)
-    launch_true_residual(s, D, P, Ah, L.b, L.E, c->sc, c->partials);
-  launch_post_solve(s, D, P, L.E, L.rho, cp, dt, L.T, c->sc, c->partials);
-  if (Lc && (mode == AMRFLD_BC_NEUMANN || mode == AMRFLD_BC_ROBIN)) {
-    double* reg = ensure_reg(c, *Lc);
-    launch_flux_register(s, D, L.K, Lc->K, L.E, Lc->E, dt, reg, int(Lc->t.n_slots()));
+  if (!resident) {
+    const FaceCoefs<double> Aop = face_coefs(c, L.Cp, L.K, L.mask, scale, c->o.theta, false);
+    const ScaledOp<double> Ah = scale_operator(c, s, D, Aop, L.Cp, L.diag, L.rs, L.Ch);
+    const SolveArrays A{Aop, L.diag, L.b, L.E, D.n_slots, Ah};
+    ls = LoopStats{};
+    ls.iters.assign(1, 0);
+    if (c->o.precision == AMRFLD_MIXED) {
+      pcg_mixed(c, D, P, level_plan(c, n_tiles, kMaxTilesPerBlock32), A, tol, &ls);
+    } else {
+      pcg_fp64(c, D, P, A, tol, &ls, L.last_iters);
+    }
+    check(hipEventRecord(c->ev[2], s), "event");
+    if (c->o.true_residual && c->o.precision != AMRFLD_MIXED)
+      launch_true_residual(s, D, P, Ah, L.b, L.E, c->sc, c->partials);
+    launch_post_solve(s, D, P, L.E, L.rho, cp, dt, L.T, c->sc, c->partials);
+    if (registers) launch_flux_register(s, D, L.K, Lc->K, L.E, Lc->E, dt, reg_c, int(Lc->t.n_slots()));
+    if (L.reg) launch_fill(s, L.reg, 6 * L.t.n_slots(), 0.0);
+    check(hipEventRecord(c->ev[3], s), "event");
+    read_scalars(c, c->h_sc, c->sc, 1);
+    check(hipGetLastError(), "kernels");
   }
-  if (L.reg) launch_fill(s, L.reg, 6 * L.t.n_slots(), 0.0);
-  check(hipEventRecord(c->ev[3], s), "event");
-  read_scalars(c, c->h_sc, c->sc, 1);
-  check(hipGetLastError(), "kernels");
 
   const PcgScalars& h = *c->h_sc;
   if (c->o.precision != AMRFLD_MIXED) L.last_iters = h.iter;
@@ -925,8 +1116,8 @@ amrfld_status solve_one(amrfld_ctx* c, int level, double dt, int mode, double to
   st.dt = dt;
   st.rnorm0 = h.rnorm0;
   st.bnorm = h.bnorm;
-  st.sweep_blocks = P.G;
-  st.launch_blocks = ls.persistent ? ls.launch_blocks : P.G;
+  st.sweep_blocks = resident ? L.res.d.n_parts : P.G;
+  st.launch_blocks = resident || ls.persistent ? ls.launch_blocks : P.G;
   st.launch_mode = ls.persistent ? 1 : 0;
   float ms = 0.f, pms = 0.f;
   check(hipEventSynchronize(c->ev[3]), "event");  // passed already: the scalars were read after it
@@ -983,12 +1174,21 @@ hipError_t record_solve(amrfld_ctx* c, hipStream_t st, int level, double dt, int
   launch_cell_K(st, D, L.E, L.rho, Lc ? Lc->E : nullptr, kparams(L), outer_bc(c), L.K);
   const double w = mode == AMRFLD_BC_DIRICHLET ? 1.0 : mode == AMRFLD_BC_NEUMANN ? 0.0 : c->o.robin_alpha;
   const CouplingParams cp = cparams(c, L);
+  double* Cm = use_resident(c, L) ? L.Ch : nullptr;  // the sweeps' scaled operator is not formed then
   launch_assemble(st, D, L.K, Lc ? Lc->K : nullptr, L.E, Lc ? Lc->E : nullptr, L.rho, L.reg, dt, w,
-                  c->o.robin_alpha, cp, kparams(L), outer_bc(c), L.Cp, L.mask, L.diag, L.b);
+                  c->o.robin_alpha, cp, kparams(L), outer_bc(c), L.Cp, L.mask, L.diag, L.b, Cm);
   const double scale = dt / (D.dx * D.dx);
   if (c->o.theta != 1.0)
     launch_theta_step(st, D, c->o.theta, L.E, face_coefs(c, L.Cp, L.K, L.mask, scale, 1.0, false), L.Cp, L.diag,
-                      L.b);
+                      L.b, Cm);
+  const bool registers = Lc && (mode == AMRFLD_BC_NEUMANN || mode == AMRFLD_BC_ROBIN);
+  if (use_resident(c, L)) {
+    const hipError_t e = launch_resident(st, D, L.res.d, resident_args(c, L, dt, tol, sc));
+    if (e != hipSuccess) return e;
+    if (registers) launch_flux_register(st, D, L.K, Lc->K, L.E, Lc->E, dt, Lc->reg, int(Lc->t.n_slots()), &sc->done);
+    if (L.reg) launch_fill(st, L.reg, 6 * L.t.n_slots(), 0.0);
+    return hipGetLastError();
+  }
   const FaceCoefs<double> Aop = face_coefs(c, L.Cp, L.K, L.mask, scale, c->o.theta, false);
   const ScaledOp<double> Ah = scale_operator(c, st, D, Aop, L.Cp, L.diag, L.rs, L.Ch);
   const SolveArrays A{Aop, L.diag, L.b, L.E, D.n_slots, Ah};
@@ -1014,7 +1214,7 @@ hipError_t record_solve(amrfld_ctx* c, hipStream_t st, int level, double dt, int
   if (e != hipSuccess) return e;
   if (c->o.true_residual && !mixed) launch_true_residual(st, D, P, Ah, L.b, L.E, sc, c->partials);
   launch_post_solve(st, D, P, L.E, L.rho, cp, dt, L.T, sc, c->partials);
-  if (Lc && (mode == AMRFLD_BC_NEUMANN || mode == AMRFLD_BC_ROBIN))
+  if (registers)
     launch_flux_register(st, D, L.K, Lc->K, L.E, Lc->E, dt, Lc->reg, int(Lc->t.n_slots()));
   if (L.reg) launch_fill(st, L.reg, 6 * L.t.n_slots(), 0.0);
   return hipGetLastError();
@@ -1090,7 +1290,11 @@ amrfld_status advance_graph(amrfld_ctx* c, double dt_coarse, int mode, double to
     sg.param_epoch = c->param_epoch;
   }
   check(hipEventRecord(c->ev[0], us), "event");
-  check(hipGraphLaunch(sg.ex, us), "graph launch");
+  {
+    WaitingScope order(c, us);
+    check(hipGraphLaunch(sg.ex, us), "graph launch");
+    order.launched();
+  }
   check(hipEventRecord(c->ev[3], us), "event");
   check(hipStreamSynchronize(us), "sync");
   float total_ms = 0.f;
@@ -1105,6 +1309,11 @@ amrfld_status advance_graph(amrfld_ctx* c, double dt_coarse, int mode, double to
     const LevelState& L = c->L(sched[k].level);
     const int nt = tiles_of(L.t.n_slots());
     const SweepPlan P = level_plan(c, nt);
+    const bool resident = use_resident(c, L);
+    if (resident && !h.done) {
+      aborted = 1;
+      reset_exchange(us, L.res.d);
+    }
     amrfld_stats st{};
     st.level = sched[k].level;
     st.iters = mixed ? h.inner_total : h.iter;
@@ -1120,10 +1329,11 @@ amrfld_status advance_graph(amrfld_ctx* c, double dt_coarse, int mode, double to
     st.pcg_ms = -1.0;
     st.rnorm0 = h.rnorm0;
     st.bnorm = h.bnorm;
-    st.sweep_blocks = P.G;
-    st.launch_blocks = mixed ? mixed_persistent_blocks(P, level_plan(c, nt, kMaxTilesPerBlock32),
-                                                       c->o.persistent_per_cu)
-                             : persistent_blocks<double>(P, c->o.persistent_per_cu);
+    st.sweep_blocks = resident ? L.res.d.n_parts : P.G;
+    st.launch_blocks = resident ? L.res.d.n_blocks
+                       : mixed  ? mixed_persistent_blocks(P, level_plan(c, nt, kMaxTilesPerBlock32),
+                                                          c->o.persistent_per_cu)
+                                : persistent_blocks<double>(P, c->o.persistent_per_cu);
     st.launch_mode = 2;
     st.status = h.nonfinite ? AMRFLD_E_NONFINITE : (h.converged ? AMRFLD_OK : AMRFLD_E_NOCONV);
     if (st.status != AMRFLD_OK && worst == AMRFLD_OK) {
@@ -1369,9 +1579,10 @@ amrfld_status solve_composite(amrfld_ctx* c, double dt, double tol) {
   CouplingParams cp = cparams(c, c->L(base));
   cp.T = coupled ? C.T : nullptr;
   const DevLevel D = C.dev();
-  launch_assemble_composite(s, D, C.K, C.x, C.rho, cp, outer_bc(c), dt, C.Cp, C.cif, C.c2f, C.diag, C.b);
-  const ScaledOp<double> Ah = scale_operator(c, s, D, stored_face_coefs(C.Cp), C.Cp, C.diag, C.rs, C.Ch);
-  launch_interface_values(s, D, C.n_if_entries, C.cif, C.rs, C.if_val);
+  // a single level is that level's system (rows times the volume): solved as it is
+  bool resident = C.n_levels == 1 && resident_fits(c->L(base).res.d);
+  launch_assemble_composite(s, D, C.K, C.x, C.rho, cp, outer_bc(c), dt, C.Cp, C.cif, C.c2f, C.diag, C.b,
+                            resident ? C.Ch : nullptr);
   const int n_tiles = tiles_of(C.n_slots);
   const int B = c->o.max_blocks > 0 ? c->o.max_blocks : 1024;
   SweepPlan P = single_plan(sweep_blocks(n_tiles, B), n_tiles);
@@ -1381,9 +1592,37 @@ amrfld_status solve_composite(amrfld_ctx* c, double dt, double tol) {
   }
   LoopStats ls;
   ls.iters.assign(1, 0);
-  pcg_fp64(c, D, P, SolveArrays{stored_face_coefs(C.Cp), C.diag, C.b, C.x, C.n_slots, Ah}, tol, &ls);
+  if (resident) {
+    const ResPlanDev& R = c->L(base).res.d;
+    ResArgs a = resident_args(c, c->L(base), dt, tol, c->sc);
+    a.Cp = C.Cp;
+    a.Cm = C.Ch;
+    a.diag = C.diag;
+    a.b = C.b;
+    a.x = C.x;
+    a.cp.T = nullptr;  // the post-solve below updates T
+    check(hipEventRecord(c->ev[1], s), "event");
+    if (run_resident(c, s, D, R, a)) {
+      read_scalars(c, c->h_sc, c->sc, 1);
+      if (!c->h_sc->done) resident = resident_timed_out(c, s, R);
+      if (c->o.time_sweeps > 0) {
+        ls.n_timed = c->h_sc->iter;
+        ls.sweep_ms = c->h_sc->loop_ms;
+      }
+    } else {
+      resident = false;
+    }
+  }
+  if (!resident) {
+    ls = LoopStats{};
+    ls.iters.assign(1, 0);
+    const ScaledOp<double> Ah = scale_operator(c, s, D, stored_face_coefs(C.Cp), C.Cp, C.diag, C.rs, C.Ch);
+    launch_interface_values(s, D, C.n_if_entries, C.cif, C.rs, C.if_val);
+    pcg_fp64(c, D, P, SolveArrays{stored_face_coefs(C.Cp), C.diag, C.b, C.x, C.n_slots, Ah}, tol, &ls);
+  }
   check(hipEventRecord(c->ev[2], s), "event");
-  if (c->o.true_residual) launch_true_residual(s, D, P, stored_face_coefs(C.Cp), C.diag, C.b, C.x, c->sc, c->partials);
+  if (c->o.true_residual && !resident)
+    launch_true_residual(s, D, P, stored_face_coefs(C.Cp), C.diag, C.b, C.x, c->sc, c->partials);
   int64_t n_leaf = 0;
   for (int k = 0; k < C.n_levels; ++k) {
     LevelState& L = c->L(base + k);
@@ -1414,8 +1653,7 @@ amrfld_status solve_composite(amrfld_ctx* c, double dt, double tol) {
   st.dt = dt;
   st.rnorm0 = h.rnorm0;
   st.bnorm = h.bnorm;
-  st.sweep_blocks = P.G;
-  st.launch_blocks = P.G;
+  st.sweep_blocks = st.launch_blocks = resident ? c->L(base).res.d.n_blocks : P.G;
   float ms = 0.f, pms = 0.f;
   check(hipEventSynchronize(c->ev[3]), "event");  // passed already: the scalars were read after it
   check(hipEventElapsedTime(&ms, c->ev[0], c->ev[3]), "event");
@@ -1640,7 +1878,11 @@ amrfld_status solve_batch_persistent(amrfld_ctx* c, const std::vector<amrfld_pat
       mode = 1;
     } else {
       check(hipEventRecord(c->cap_ev[0], c->cap_stream), "event");
-      check(hipGraphLaunch(ex, c->cap_stream), "graph launch");
+      {
+        WaitingScope order(c, c->cap_stream);
+        check(hipGraphLaunch(ex, c->cap_stream), "graph launch");
+        order.launched();
+      }
       check(hipEventRecord(c->cap_ev[1], c->cap_stream), "event");
       check(hipStreamSynchronize(c->cap_stream), "graph");
       check(hipEventElapsedTime(&total_ms, c->cap_ev[0], c->cap_ev[1]), "event");
@@ -1650,7 +1892,11 @@ amrfld_status solve_batch_persistent(amrfld_ctx* c, const std::vector<amrfld_pat
   }
   if (mode == 1) {
     check(hipEventRecord(c->ev[0], us), "event");
-    check(record(us), "persistent launch");
+    {
+      WaitingScope order(c, us);
+      check(record(us), "persistent launch");
+      order.launched();
+    }
     check(hipEventRecord(c->ev[3], us), "event");
     check(hipStreamSynchronize(us), "sync");
     check(hipEventElapsedTime(&total_ms, c->ev[0], c->ev[3]), "event");
@@ -1923,9 +2169,11 @@ amrfld_status amrfld_create(const amrfld_opts* o, amrfld_ctx** out) {
     c->o = *o;
     c->lev.resize(o->max_level - o->base_level + 1);
     check(hipGetDevice(&c->device), "device");
+    check(hipDeviceGetAttribute(&c->n_cu, hipDeviceAttributeMultiprocessorCount, c->device), "device");
     resolve_scratch(c->device);
     ensure_scalars(c, 1);
     for (auto& e : c->ev) check(hipEventCreate(&e), "event");
+    check(hipEventCreateWithFlags(&c->gate_ev, hipEventDisableTiming), "event");
     c->stats.reserve(64);
   } catch (const std::exception& e) {
     g_create_error = e.what();
@@ -1939,6 +2187,15 @@ amrfld_status amrfld_create(const amrfld_opts* o, amrfld_ctx** out) {
 void amrfld_destroy(amrfld_ctx* c) {
   if (!c) return;
   (void)hipStreamSynchronize(c->stream());
+  if (c->gate_ev) {
+    WaitingLaunch& w = g_waiting[std::max(0, std::min(c->device, kMaxDevices - 1))];
+    std::lock_guard<std::mutex> lk(w.mu);
+    if (w.owner == c) {
+      (void)hipEventSynchronize(c->gate_ev);
+      w.owner = nullptr;
+    }
+    (void)hipEventDestroy(c->gate_ev);
+  }
   c->step_graph.reset();
   for (auto& L : c->lev) L.release();
   if (c->batch) {
@@ -1999,6 +2256,7 @@ amrfld_status amrfld_build_level(amrfld_ctx* c, int level, int64_t n_oct, const 
       fresh.Ch = dalloc<double>(3 * n, "fields");
       fresh.rs = dalloc<double>(n, "fields");
       upload_tables(c, fresh);
+      fresh.res = level_res_tables(c, fresh.t);
     } catch (...) {
       (void)hipStreamSynchronize(c->stream());
       fresh.release();

@@ -53,6 +53,7 @@ struct PcgScalars {
   // last iteration in buffer cont - 1 (gam[1], alpha[1] hold that iteration's scalars)
   int cont;
   int pad_;
+  double loop_ms;  // resident CG: device time of the iterations
 };
 
 // Parameters of one independent patch of a batch: a box of cells of size dx
@@ -203,25 +204,29 @@ void launch_cell_K(hipStream_t s, const DevLevel& L, const double* E, const doub
 // w: weight of the coarse-to-fine Dirichlet part (1 D, 0 N, alpha R); alpha: Robin
 // weight of batch patch faces whose mode is Robin; kp and ob: the diffusivity law and
 // the box faces' Dirichlet values (no patch table).
-// mask: bit d of slot i set when its face in direction d couples two leaves.
+// mask: bit d of slot i set when its face in direction d couples two leaves.  Cm
+// (optional): the coefficients of the - faces, zero unless both sides are leaves.
 void launch_assemble(hipStream_t s, const DevLevel& L, const double* K, const double* K_coarse,
                      const double* E, const double* E_coarse, const double* rho, const double* reg,
                      double dt, double w, double alpha, const CouplingParams& cp, const CellKParams& kp,
-                     const OuterBC& ob, double* Cp, uint8_t* mask, double* diag, double* b);
+                     const OuterBC& ob, double* Cp, uint8_t* mask, double* diag, double* b,
+                     double* Cm = nullptr);
 // Theta-weighted step (Crank-Nicolson at 1/2) from an assembled backward-Euler
 // level system: b -= (1 - theta) (A E - E) on the leaves, then A = I + theta (A - I).
 void launch_theta_step(hipStream_t s, const DevLevel& L, double theta, const double* E,
-                       const FaceCoefs<double>& A1, double* Cp, double* diag, double* b);
+                       const FaceCoefs<double>& A1, double* Cp, double* diag, double* b, double* Cm = nullptr);
 // Composite system of all levels advanced with one dt (unique time step): per slot
 // the volume-scaled same-level coefficients Cp, interface coefficients cif, the
 // refined-neighbour mask c2f, diagonal and right-hand side; E is the concatenated
 // energy, K the concatenated diffusivity of every level.
 void launch_assemble_composite(hipStream_t s, const DevLevel& C, const double* K, const double* E,
                                const double* rho, const CouplingParams& cp, const OuterBC& ob, double dt,
-                               double* Cp, double* cif, uint8_t* c2f, double* diag, double* b);
+                               double* Cp, double* cif, uint8_t* c2f, double* diag, double* b,
+                               double* Cm = nullptr);
+// done (optional): nothing is added unless this flag of the solve's record is set.
 void launch_flux_register(hipStream_t s, const DevLevel& F, const double* K_f, const double* K_c,
                           const double* E_f, const double* E_c, double dt, double* reg_c,
-                          int n_slots_c);
+                          int n_slots_c, const int* done = nullptr);
 void launch_restrict(hipStream_t s, const DevLevel& F, const double* E_f, double* E_c);
 void launch_fill(hipStream_t s, double* p, int64_t n, double v);
 // dst[i] = src[i] for n device doubles (a plain streaming copy; the runtime's
@@ -301,6 +306,7 @@ template <typename T>
 hipError_t launch_pcg_persistent(hipStream_t s, const DevLevel& L, const SweepPlan& P, int max_iter,
                                  const ScaledOp<T>& Ah, const CgVecs<T>& v, T* x, PcgScalars* sc, double* part,
                                  unsigned* bar, int per_cu_cap);
+void launch_fill_u32(hipStream_t s, unsigned* p, int64_t n, unsigned v);
 void launch_zero_u32(hipStream_t s, unsigned* p, int n);
 // Copies count scalar records between device memory and the device-mapped view of
 // pinned host memory (to_host: then makes the stores visible to the host), so that

@@ -1057,9 +1057,9 @@ __global__ __launch_bounds__(kBlock) void k_copy_scalars(const uint64_t* __restr
   if (to_host) __threadfence_system();
 }
 
-__global__ __launch_bounds__(kBlock) void k_zero_u32(unsigned* p, int n) {
-  const int i = int(blockIdx.x * kBlock + threadIdx.x);
-  if (i < n) p[i] = 0u;
+__global__ __launch_bounds__(kBlock) void k_fill_u32(unsigned* p, int64_t n, unsigned v) {
+  const int64_t i = int64_t(blockIdx.x) * kBlock + threadIdx.x;
+  if (i < n) p[i] = v;
 }
 
 // Scaled interface coefficients of the composite system, one thread per listed row.
@@ -1178,9 +1178,12 @@ void launch_copy_scalars(hipStream_t s, const PcgScalars* src, PcgScalars* dst, 
                      to_host ? 1 : 0);
 }
 
-void launch_zero_u32(hipStream_t s, unsigned* p, int n) {
-  hipLaunchKernelGGL(k_zero_u32, dim3((n + kBlock - 1) / kBlock), dim3(kBlock), 0, s, p, n);
+void launch_fill_u32(hipStream_t s, unsigned* p, int64_t n, unsigned v) {
+  if (n <= 0) return;
+  hipLaunchKernelGGL(k_fill_u32, dim3(unsigned((n + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, p, n, v);
 }
+
+void launch_zero_u32(hipStream_t s, unsigned* p, int n) { launch_fill_u32(s, p, n, 0u); }
 
 // Resident blocks of a cooperative kernel with the iteration sweep's LDS for this
 // plan on this device (0 if unknown or not supported).

@@ -1,0 +1,63 @@
+// Resident CG: the whole solve of a problem in one launch, its state in registers and
+// LDS, one exchange of face values and partial sums between blocks per iteration.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include "device.h"
+#include "resident_plan.h"
+
+namespace amrfld {
+
+constexpr int kResThreads = 512;
+constexpr int kResMaxSlots = 10 * kResThreads;  // of one share
+constexpr int kResTargetSlots = 1024;  // of one share where the level has several
+// polls of a wait before a block gives up (about a microsecond each)
+constexpr unsigned kResSpinLimit = 1u << 18;
+constexpr int kResWords = 7;  // a share's partial sums: words of 48 bits and a 16-bit stamp
+constexpr int kResLine = 8;   // words of the line they lie in
+
+// Device tables of a plan and its exchange memory.
+struct ResPlanDev {
+  const ResPart* parts = nullptr;
+  const uint2* places = nullptr;  // per pair of slots: see ResPlanHost
+  const int32_t* partner = nullptr;
+  const int32_t* task0 = nullptr;
+  const int32_t* task = nullptr;
+  unsigned long long* lines = nullptr;  // [2][n_parts][kResLine]
+  unsigned long long* halo = nullptr;   // [2][n_units][4][2]
+  // [n_prob] next exchange number of each problem, advanced when its solve is complete;
+  // [n_prob] that number once a block has begun to write the result of a solve; then the
+  // flag of a wait that timed out
+  unsigned* epoch = nullptr;
+  int n_parts = 0, n_units = 0, n_prob = 0;
+  int n_blocks = 0;
+  int max_slots = 0, max_units = 0;
+};
+
+struct ResArgs {
+  const double* Cp = nullptr;    // assembled coefficients of the + faces
+  const double* Cm = nullptr;    // and of the - faces
+  const double* diag = nullptr;
+  const double* b = nullptr;
+  double* x = nullptr;           // x_0 on entry, the result on return
+  PcgScalars* sc = nullptr;      // one record per problem, written whole
+  double tol = 0.0, abs_floor = 0.0;
+  int max_iter = 0, linf_test = 0, true_residual = 0;
+  // post-solve: T update of the coupling term
+  CouplingParams cp{};
+  const double* rho = nullptr;
+  double* T_out = nullptr;
+  double dt = 0.0;
+  unsigned spin_limit = 0;
+};
+
+// Whether a block's share of this plan fits its registers and LDS.
+bool resident_fits(const ResPlanDev& R);
+// All blocks have to be on the device together (at most one per compute unit): no other
+// kernel whose blocks wait for each other may run meanwhile.  An ordinary launch: a
+// cooperative one goes through a hardware queue of its own, which costs 20 to 130 us of
+// waits between the queues on a solve of 300 us.
+hipError_t launch_resident(hipStream_t s, const DevLevel& L, const ResPlanDev& R, const ResArgs& A);
+
+}  // namespace amrfld

@@ -1,0 +1,825 @@
+// Resident CG (Sect. 3.3.4): see resident.h.
+//
+// A block holds a contiguous share of a problem's slots for the whole solve: the scaled
+// face coefficients, the iterate, the residual and s^ = A^ p^ in registers, the search
+// direction p^ and the diagonal in LDS.  Nothing of the system is read from memory again
+// after the start.  Between blocks an iteration exchanges only the s^ of the cells on
+// faces between shares (each block keeps copies of its outer neighbours' r^ and p^ and
+// updates them with the arithmetic of their owner, so the copies are the owner's bits)
+// and four partial sums per share.
+//
+// A thread holds pairs of slots that are neighbours in x, four threads an oct: the
+// sibling in x is the thread's own, those in y and z come by quad permutes, and the
+// out-of-oct neighbours in y and z of both slots are one 16-byte LDS read.
+//
+// The recurrences are those of CG on the Jacobi-scaled system with one reduction per
+// iteration: s^_k = A^ p^_k, alpha_k = (r^,r^) / (p^,s^), and the next residual norm
+// that beta_k needs is formed from the sums of the same exchange,
+//   (r^_{k+1}, r^_{k+1}) = alpha^2 (s^,s^) - (r^,r^)
+// ((r^,s^) = (p^,s^), p^ being conjugate to its predecessor), while
+// (r^_{k+1}, r^_{k+1}) itself is summed with the next exchange and used for alpha_{k+1}:
+// the step along p^ stays a line search, and no error is carried on.
+//
+// Every exchanged word carries the number of its exchange (a 64-bit word holds data
+// and stamp), so a reader polls the data itself: no barrier, no flag after the data and
+// no cache write-back stand between a value's store and its use.  Two buffers
+// alternate: a block stores into a buffer again only after it has seen every block's
+// sums of the exchange between, and so after every block has read it.  Every wait is
+// bounded; a block that gives up sets the abort flag and leaves, the others then time
+// out in turn, and the iterate in memory is untouched.
+#include "resident.h"
+
+#include <algorithm>
+
+#include "common.h"
+
+namespace amrfld {
+
+namespace {
+
+typedef unsigned long long u64;
+
+constexpr int kWaves = kResThreads / 64;
+constexpr int kSums = 4;
+constexpr u64 kMask48 = 0xffffffffffffull;
+
+__device__ __forceinline__ u64 ld_word(const u64* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void st_word(u64* p, u64 v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void st_word32(unsigned* p, unsigned v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ u64 bits_of(double v) { return u64(__double_as_longlong(v)); }
+__device__ __forceinline__ double of_bits(u64 w) { return __longlong_as_double((long long)w); }
+__device__ __forceinline__ double of_words(unsigned lo, unsigned hi) { return of_bits((u64(hi) << 32) | lo); }
+
+// The thread's number, recomputed where it is used: addresses derived from it are not
+// kept in registers from one phase to the next.
+__device__ __forceinline__ int tid() {
+  int t = int(threadIdx.x);
+  asm volatile("" : "+v"(t));
+  return t;
+}
+
+// The value is formed here: not later, where its inputs would have to be kept as well.
+template <typename T>
+__device__ __forceinline__ void keep(T& v) {
+  asm volatile("" : "+v"(v));
+}
+
+// v of the lane that kCtrl names, `old` where there is none.
+template <int kCtrl>
+__device__ __forceinline__ double dpp(double old, double v) {
+  const u64 w = bits_of(v), o = bits_of(old);
+  return of_words(
+      unsigned(__builtin_amdgcn_update_dpp(int(unsigned(o)), int(unsigned(w)), kCtrl, 0xf, 0xf, false)),
+      unsigned(__builtin_amdgcn_update_dpp(int(unsigned(o >> 32)), int(unsigned(w >> 32)), kCtrl, 0xf, 0xf, false)));
+}
+template <int kCtrl>
+__device__ __forceinline__ float dpp(float old, float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(old), __float_as_int(v), kCtrl, 0xf, 0xf, false));
+}
+constexpr int kQuadXor1 = 0xB1, kQuadXor2 = 0x4E, kRowShr1 = 0x111, kRowShr2 = 0x112, kRowShr4 = 0x114,
+              kRowShr8 = 0x118;
+
+// a + b after the upper half wave of a has changed places with the lower half of b: a
+// summed over lane pairs 32 apart in the lower half, b in the upper half.
+__device__ __forceinline__ double fold32(double a, double b) {
+  const u64 x = bits_of(a), y = bits_of(b);
+  const auto lo = __builtin_amdgcn_permlane32_swap(unsigned(x), unsigned(y), false, false);
+  const auto hi = __builtin_amdgcn_permlane32_swap(unsigned(x >> 32), unsigned(y >> 32), false, false);
+  return of_words(lo[0], hi[0]) + of_words(lo[1], hi[1]);
+}
+// The same with the odd rows of 16 lanes of a and the even rows of b.
+__device__ __forceinline__ double fold16(double a, double b) {
+  const u64 x = bits_of(a), y = bits_of(b);
+  const auto lo = __builtin_amdgcn_permlane16_swap(unsigned(x), unsigned(y), false, false);
+  const auto hi = __builtin_amdgcn_permlane16_swap(unsigned(x >> 32), unsigned(y >> 32), false, false);
+  return of_words(lo[0], hi[0]) + of_words(lo[1], hi[1]);
+}
+// Wave-wide sums of four values: the last lane of row 0, 1, 2, 3 returns that of v[0],
+// v[2], v[1], v[3].  Folding halves the values with the lanes: 7 additions, not 24.
+__device__ __forceinline__ double wave_sums(const double (&v)[kSums]) {
+  double a = fold16(fold32(v[0], v[1]), fold32(v[2], v[3]));
+  a += dpp<kRowShr1>(0.0, a);
+  a += dpp<kRowShr2>(0.0, a);
+  a += dpp<kRowShr4>(0.0, a);
+  a += dpp<kRowShr8>(0.0, a);
+  return a;
+}
+__device__ __forceinline__ double wave_max(double a) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) a = fmax(a, __shfl_xor(a, o, 64));
+  return a;
+}
+
+// LDS of a block.
+struct Shared {
+  double part[kWaves][kSums + 1];   // per wave: this share's sums and maximum
+  double total[kWaves][kSums + 1];  // per wave: over the shares' words
+  int failed;
+};
+
+struct Exchange {
+  const ResPlanDev& R;
+  const ResPart& me;
+  int my_part;
+  unsigned epoch;  // number of the next exchange
+  unsigned spin_limit;
+
+  // the words of share `part`: a 64-byte line that one store fills
+  __device__ __forceinline__ u64* words(int part) const {
+    return R.lines + (size_t(epoch & 1u) * R.n_parts + part) * kResLine;
+  }
+  __device__ __forceinline__ u64* halo(int unit) const {
+    return R.halo + (size_t(epoch & 1u) * R.n_units + unit) * 8;
+  }
+};
+
+// Words of one value in the halo memory, and of the four of a unit.
+template <typename T>
+constexpr int kValueWords = int(sizeof(T) / 4);
+
+__device__ __forceinline__ unsigned half(double v, int h) { return unsigned(bits_of(v) >> (32 * h)); }
+__device__ __forceinline__ unsigned half(float v, int) { return unsigned(__float_as_int(v)); }
+
+// The export list to the partners' halo memory: consecutive lanes store consecutive
+// words, so that one store fills a unit's line.
+template <typename T>
+__device__ __forceinline__ void put_halo(const Exchange& X, const T* ex, const int* partner) {
+  constexpr int kW = kValueWords<T>, kUnit = 4 * kW;
+  const u64 st = u64(X.epoch) << 32;
+  for (int w = tid(); w < kUnit * X.me.n_units; w += kResThreads)
+    st_word(X.halo(partner[w / kUnit]) + w % kUnit, st | half(ex[w / kW], w % kW));
+}
+
+// The halo values of this exchange to sh, a word per lane.  Every value is stored by the
+// thread that exported the one at the same place, so sh and ex are the same memory.
+// false: a wait timed out.
+template <typename T>
+__device__ __forceinline__ bool get_halo(const Exchange& X, T* sh) {
+  constexpr int kW = kValueWords<T>, kBatch = 8;
+  const int nw = 4 * kW * X.me.n_units;
+  const u64* h = X.halo(X.me.unit0);
+  unsigned polls = 0;
+  for (int w0 = tid(); w0 < nw; w0 += kBatch * kResThreads) {
+    u64 c[kBatch];
+#pragma unroll
+    for (int k = 0; k < kBatch; ++k)
+      c[k] = w0 + k * kResThreads < nw ? ld_word(h + w0 + k * kResThreads) : u64(X.epoch) << 32;
+    for (;;) {  // words that are not there yet are read again, and no others
+      bool all = true;
+#pragma unroll
+      for (int k = 0; k < kBatch; ++k)
+        if (unsigned(c[k] >> 32) != X.epoch) {
+          all = false;
+          c[k] = ld_word(h + w0 + k * kResThreads);
+        }
+      if (all) break;
+      if (++polls > X.spin_limit) return false;
+    }
+#pragma unroll
+    for (int k = 0; k < kBatch; ++k) {
+      const int w = w0 + k * kResThreads;
+      const unsigned mine = unsigned(c[k]);
+      if constexpr (kW == 1) {
+        if (w < nw) sh[w] = __int_as_float(int(mine));
+      } else {  // the other half is in the neighbour lane
+        const unsigned other = unsigned(__builtin_amdgcn_update_dpp(0, int(mine), kQuadXor1, 0xf, 0xf, false));
+        if (w < nw && !(w & 1)) sh[w >> 1] = of_words(mine, other);
+      }
+    }
+  }
+  return true;
+}
+
+// The sums (k < kSums) and the maximum over the first n of the waves' rows, the same in
+// every thread: lanes 8 k .. 8 k + 7 hold value k of the rows and add them up.
+__device__ __forceinline__ void row_totals(const double (&rows)[kWaves][kSums + 1], int n, bool wide,
+                                           double (&v)[kSums], double& m) {
+  const int lane = tid() & 63;
+  const bool in = (lane & 7) < n;
+  double c = lane < 8 * kSums && in ? rows[lane & 7][lane >> 3] : 0.0;
+  c += dpp<kRowShr1>(0.0, c);
+  c += dpp<kRowShr2>(0.0, c);
+  c += dpp<kRowShr4>(0.0, c);
+  const u64 w = bits_of(c);
+#pragma unroll
+  for (int k = 0; k < kSums; ++k)
+    v[k] = of_words(unsigned(__builtin_amdgcn_readlane(int(unsigned(w)), 8 * k + 7)),
+                    unsigned(__builtin_amdgcn_readlane(int(unsigned(w >> 32)), 8 * k + 7)));
+  if (wide) {
+    double x = in ? rows[lane & 7][kSums] : -DBL_MAX;
+    x = fmax(x, dpp<kRowShr1>(x, x));
+    x = fmax(x, dpp<kRowShr2>(x, x));
+    x = fmax(x, dpp<kRowShr4>(x, x));
+    const u64 e = bits_of(x);
+    m = of_words(unsigned(__builtin_amdgcn_readlane(int(unsigned(e)), 7)),
+                 unsigned(__builtin_amdgcn_readlane(int(unsigned(e >> 32)), 7)));
+  }
+}
+
+// This share's sums v and (wide) maximum m published, and its export list ex (null:
+// none); a problem of one share: the sums returned to every thread.
+template <typename T>
+__device__ __forceinline__ void put_sums(const Exchange& X, double (&v)[kSums], double& m, bool wide, Shared& S,
+                                         const T* ex, const int* partner) {
+  const int t = tid(), lane = t & 63, wid = t >> 6;
+  const double a = wave_sums(v);
+  if ((lane & 15) == 15) S.part[wid][((lane >> 5) & 1) | ((lane >> 3) & 2)] = a;
+  if (wide) {
+    const double b = wave_max(m);
+    if (lane == 0) S.part[wid][kSums] = b;
+  }
+  __syncthreads();
+  if (X.me.group == 1) {
+    row_totals(S.part, kWaves, wide, v, m);
+    __syncthreads();
+    return;
+  }
+  if (ex) put_halo(X, ex, partner);
+  if (wid == 0) {
+    double x = 0.0;
+    row_totals(S.part, kWaves, wide, v, x);
+    const u64 d0 = bits_of(v[0]), d1 = bits_of(v[1]), d2 = bits_of(v[2]), d3 = bits_of(v[3]), e = bits_of(x);
+    // 48 bits of data to a word
+    u64 word = d0;
+    word = lane == 1 ? (d0 >> 48) | (d1 << 16) : word;
+    word = lane == 2 ? (d1 >> 32) | (d2 << 32) : word;
+    word = lane == 3 ? d2 >> 16 : word;
+    word = lane == 4 ? d3 : word;
+    word = lane == 5 ? (d3 >> 48) | (e << 16) : word;
+    word = lane == 6 ? e >> 32 : word;
+    word = (word & kMask48) | (u64(X.epoch & 0xffffu) << 48);
+    if (lane < (wide ? kResWords : kResWords - 1)) st_word(X.words(X.my_part) + lane, word);
+  }
+}
+
+// The sums (and maximum) over the whole problem to every thread, and the halo values
+// that the neighbour shares published for this exchange to sh (null: none).  false: a
+// wait timed out.
+template <typename T>
+__device__ __forceinline__ bool collect(Exchange& X, double (&v)[kSums], double& m, bool wide, Shared& S, T* sh) {
+  const int t = tid(), lane = t & 63, wid = t >> 6, G = X.me.group;
+  if (G == 1) {
+    ++X.epoch;
+    return true;
+  }
+  const int n_waves = (G + 63) >> 6;
+  bool ok = !sh || get_halo(X, sh);
+  if (wid < n_waves) {
+    u64 w[kResWords];
+#pragma unroll
+    for (int k = 0; k < kResWords; ++k) w[k] = 0;
+    if (t < G && ok) {
+      const unsigned st = X.epoch & 0xffffu;
+      const u64* ln = X.words(X.me.part0 + t);
+      unsigned polls = 0;
+      for (;;) {
+        bool all = true;
+#pragma unroll
+        for (int k = 0; k < kResWords; ++k)
+          if (k < kResWords - 1 || wide) w[k] = ld_word(ln + k);
+#pragma unroll
+        for (int k = 0; k < kResWords; ++k)
+          if (k < kResWords - 1 || wide) all = all && unsigned(w[k] >> 48) == st;
+        if (all) break;
+        if (++polls > X.spin_limit) {
+          ok = false;
+          break;
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < kResWords; ++k) w[k] &= kMask48;
+    }
+    v[0] = of_bits(w[0] | (w[1] << 48));
+    v[1] = of_bits((w[1] >> 16) | (w[2] << 32));
+    v[2] = of_bits((w[2] >> 32) | (w[3] << 16));
+    v[3] = of_bits(w[4] | (w[5] << 48));
+    const double a = wave_sums(v);
+    if ((lane & 15) == 15) S.total[wid][((lane >> 5) & 1) | ((lane >> 3) & 2)] = a;
+    if (wide) {
+      const double b = wave_max(t < G ? of_bits((w[5] >> 16) | (w[6] << 32)) : -DBL_MAX);
+      if (lane == 0) S.total[wid][kSums] = b;
+    }
+  }
+  if (!ok) S.failed = 1;
+  __syncthreads();
+  row_totals(S.total, n_waves, wide, v, m);
+  ++X.epoch;
+  return S.failed == 0;
+}
+
+
+template <typename T>
+struct Pair;
+template <>
+struct Pair<double> {
+  typedef double2 type;
+};
+template <>
+struct Pair<float> {
+  typedef float2 type;
+};
+
+// A share's state in registers, NP pairs of slots per thread (thread t holds pairs
+// t + 512 u of the share).  Coefficients: within the oct cix, ciy, ciz (that in x is the
+// same for both slots), out of the oct cox, coy, coz.  Places in p: of the out-of-oct
+// neighbours in x of both slots (px, 16 bits each) and of the pairs in y and z (pyz).
+template <typename T, int NP>
+struct Regs {
+  T cix[NP], ciy[NP][2], ciz[NP][2], cox[NP][2], coy[NP][2], coz[NP][2];
+  T x[NP][2], r[NP][2], s[NP][2];
+  unsigned px[NP], pyz[NP];
+  unsigned face;  // bit u: pair u has a cell on a face between shares
+};
+
+// LDS arrays of a share.
+template <typename T>
+struct Lds {
+  T* p;         // [cap + 4 units]: p^ of the share, then of its halo cells
+  T* d;         // [cap]: the diagonal
+  T* rh;        // [4 units]: r^ of the halo cells
+  T* ex;        // [4 units]: this share's cells on the same faces, then the halo cells'
+                // values of the current exchange
+  int* partner; // [units]
+};
+
+// (A^ v) of pair u, v in p.
+template <typename T, int NP>
+__device__ __forceinline__ void apply(const Regs<T, NP>& q, const T* p, int u, T (&pv)[2], T (&av)[2]) {
+  typedef typename Pair<T>::type T2;
+  const int l = 2 * (tid() + u * kResThreads);
+  const T2 own = *reinterpret_cast<const T2*>(p + l);
+  const T2 ny = *reinterpret_cast<const T2*>(p + (q.pyz[u] & 0xffffu));
+  const T2 nz = *reinterpret_cast<const T2*>(p + (q.pyz[u] >> 16));
+  const T nx0 = p[q.px[u] & 0xffffu], nx1 = p[q.px[u] >> 16];
+  pv[0] = own.x;
+  pv[1] = own.y;
+  T a0 = own.x, a1 = own.y;
+  a0 = fma(-q.cix[u], own.y, a0);
+  a1 = fma(-q.cix[u], own.x, a1);
+  a0 = fma(-q.ciy[u][0], dpp<kQuadXor1>(own.x, own.x), a0);
+  a1 = fma(-q.ciy[u][1], dpp<kQuadXor1>(own.y, own.y), a1);
+  a0 = fma(-q.ciz[u][0], dpp<kQuadXor2>(own.x, own.x), a0);
+  a1 = fma(-q.ciz[u][1], dpp<kQuadXor2>(own.y, own.y), a1);
+  a0 = fma(-q.cox[u][0], nx0, a0);
+  a1 = fma(-q.cox[u][1], nx1, a1);
+  a0 = fma(-q.coy[u][0], ny.x, a0);
+  a1 = fma(-q.coy[u][1], ny.y, a1);
+  a0 = fma(-q.coz[u][0], nz.x, a0);
+  a1 = fma(-q.coz[u][1], nz.y, a1);
+  av[0] = a0;
+  av[1] = a1;
+}
+
+// The values of pair u that lie on faces between shares to the block's export list
+// (ordered like its halo cells).
+template <typename T, int NP>
+__device__ __forceinline__ void stage(const Regs<T, NP>& q, T* ex, int u, T v0, T v1) {
+  constexpr int kCap = 2 * NP * kResThreads;
+  typedef typename Pair<T>::type T2;
+  if (!((q.face >> u) & 1u)) return;
+  const int x0 = int(q.px[u] & 0xffffu) - kCap, x1 = int(q.px[u] >> 16) - kCap;
+  const int y = int(q.pyz[u] & 0xffffu) - kCap, z = int(q.pyz[u] >> 16) - kCap;
+  if (x0 >= 0) ex[x0] = v0;
+  if (x1 >= 0) ex[x1] = v1;
+  T2 w;
+  w.x = v0;
+  w.y = v1;
+  if (y >= 0) *reinterpret_cast<T2*>(ex + y) = w;
+  if (z >= 0) *reinterpret_cast<T2*>(ex + z) = w;
+}
+
+template <typename T>
+__device__ __forceinline__ bool exchange(Exchange& X, double (&v)[kSums], double& m, bool wide, Shared& S,
+                                         const Lds<T>& lds) {
+  put_sums(X, v, m, wide, S, lds.ex, lds.partner);
+  return collect(X, v, m, wide, S, lds.ex);
+}
+
+struct CgResult {
+  double rn, linf;
+  int iters;
+  bool fin, conv;
+};
+
+// CG iterations from r^ = q.r, p^ in lds.p (own and halo), r^ of the halo in lds.rh.
+// thresh, tol, max_iter, linf_test: the stopping rule of Sect. 3.3.4; dmin: smallest
+// diagonal entry.  false: a wait timed out.
+template <typename T, int NP>
+__device__ __forceinline__ bool cg_loop(Exchange& X, Regs<T, NP>& q, const Lds<T>& lds, Shared& S, double thresh,
+                                        double tol, int max_iter, bool linf_test, double dmin, CgResult& out) {
+  typedef typename Pair<T>::type T2;
+  constexpr int kCap = 2 * NP * kResThreads;
+  const int nh = 4 * X.me.n_units;
+  double rr = 0.0, rrd = 0.0, linf = 0.0;
+#pragma unroll
+  for (int u = 0; u < NP; ++u) {
+    const T2 d = *reinterpret_cast<const T2*>(lds.d + 2 * (tid() + u * kResThreads));
+    const double a0 = double(q.r[u][0]) * double(q.r[u][0]), a1 = double(q.r[u][1]) * double(q.r[u][1]);
+    rr += a0 + a1;
+    rrd = fma(a0, double(d.x), fma(a1, double(d.y), rrd));
+  }
+  bool wide = false;  // the next exchange carries the largest relative change too
+  const double stop2 = 1.000001 * thresh * thresh;
+  for (int k = 0;; ++k) {
+    double v[kSums] = {0.0, 0.0, rr, rrd};
+#pragma unroll
+    for (int u = 0; u < NP; ++u) {
+      // (opaque: nothing derived from the places is kept in registers across iterations)
+      asm volatile("" : "+v"(q.px[u]), "+v"(q.pyz[u]));
+      __builtin_amdgcn_sched_barrier(0);
+      T pv[2], av[2];
+      apply(q, lds.p, u, pv, av);
+      q.s[u][0] = av[0];
+      q.s[u][1] = av[1];
+      stage(q, lds.ex, u, av[0], av[1]);
+      v[0] = fma(double(pv[0]), double(av[0]), fma(double(pv[1]), double(av[1]), v[0]));
+      v[1] = fma(double(av[0]), double(av[0]), fma(double(av[1]), double(av[1]), v[1]));
+    }
+    if (!exchange(X, v, linf, wide, S, lds)) return false;
+    // the stopping test of iterate k
+    if (k >= 1) {
+      // (the root only where it can matter: it is a long chain before alpha)
+      out.fin = isfinite(v[3]) && isfinite(v[0]) && isfinite(v[2]);
+      if (!out.fin || v[3] <= stop2 || k >= max_iter) {
+        out.rn = sqrt(v[3]);
+        out.linf = linf;
+        out.iters = k;
+        out.conv = out.fin && ((out.rn <= thresh && (!linf_test || (wide && linf < tol))) || out.rn == 0.0);
+        if (!out.fin || out.conv || k >= max_iter) return true;
+      }
+    }
+    // alpha = gam / (p^,s^); beta = (alpha^2 (s^,s^) - gam) / gam
+    const double gam = v[2];
+    const double inv = 1.0 / v[0], alpha = gam * inv;
+    const double ratio = fma(alpha * inv, v[1], -1.0);
+    const double beta = ratio > 0.0 ? ratio : 0.0;
+    const double gnext = beta * gam;
+    if (!isfinite(alpha) || !isfinite(ratio)) {
+      out.rn = sqrt(v[3]);
+      out.fin = out.conv = false;
+      out.iters = k;
+      return true;
+    }
+    // ||r_{k+1}||^2 >= dmin (r^,r^)_{k+1}: where that is above the threshold (with a
+    // margin for the rounding of the prediction) iterate k + 1 cannot be the last, and its
+    // relative change, a division per cell, is not formed
+    wide = k + 1 >= max_iter || !(gnext * dmin > 4.0 * thresh * thresh);
+    const T ta = T(alpha), tb = T(beta);
+    rr = rrd = linf = 0.0;
+#pragma unroll
+    for (int u = 0; u < NP; ++u) {
+      __builtin_amdgcn_sched_barrier(0);
+      const int l = 2 * (tid() + u * kResThreads);
+      const T2 po = *reinterpret_cast<const T2*>(lds.p + l);
+      const T2 d = *reinterpret_cast<const T2*>(lds.d + l);
+      if (wide) {
+        const T x0 = fabs(q.x[u][0]), x1 = fabs(q.x[u][1]), e0 = fabs(ta * po.x), e1 = fabs(ta * po.y);
+        linf = fmax(linf, fmax(double(x0 > T(0) ? e0 / x0 : e0), double(x1 > T(0) ? e1 / x1 : e1)));
+      }
+      q.x[u][0] = fma(ta, po.x, q.x[u][0]);
+      q.x[u][1] = fma(ta, po.y, q.x[u][1]);
+      q.r[u][0] = fma(-ta, q.s[u][0], q.r[u][0]);
+      q.r[u][1] = fma(-ta, q.s[u][1], q.r[u][1]);
+      T2 pn;
+      pn.x = fma(tb, po.x, q.r[u][0]);
+      pn.y = fma(tb, po.y, q.r[u][1]);
+      *reinterpret_cast<T2*>(lds.p + l) = pn;
+      const double a0 = double(q.r[u][0]) * double(q.r[u][0]), a1 = double(q.r[u][1]) * double(q.r[u][1]);
+      rr += a0 + a1;
+      rrd = fma(a0, double(d.x), fma(a1, double(d.y), rrd));
+    }
+    for (int h = tid(); h < nh; h += kResThreads) {
+      const T rn = fma(-ta, lds.ex[h], lds.rh[h]);
+      lds.rh[h] = rn;
+      lds.p[kCap + h] = fma(tb, lds.p[kCap + h], rn);
+    }
+    __syncthreads();
+  }
+}
+
+// The FP64 solve of one share of one problem.  false: a wait timed out.
+template <int NP>
+__device__ __forceinline__ bool solve_part(const DevLevel& L, const ResPlanDev& R, const ResArgs& A, int my_part,
+                                           unsigned char* dyn, Shared& S) {
+  constexpr int kCap = 2 * NP * kResThreads;
+  const ResPart me = R.parts[my_part];
+  const int ns = me.n_slots, n = L.n_slots;
+  const int nh = 4 * R.max_units;
+  Lds<double> lds;
+  lds.p = reinterpret_cast<double*>(dyn);
+  lds.d = lds.p + kCap + nh;
+  lds.rh = lds.d + kCap;
+  lds.ex = lds.rh + nh;
+  lds.partner = reinterpret_cast<int*>(lds.ex + nh);
+  const unsigned epoch0 = R.epoch[me.prob];
+  Exchange X{R, me, my_part, epoch0, A.spin_limit};
+  for (int u = tid(); u < me.n_units; u += kResThreads) lds.partner[u] = R.partner[me.unit0 + u];
+  if (threadIdx.x == 0) {
+    S.failed = 0;
+    if (my_part == me.part0) A.sc[me.prob].done = 0;  // set again when the whole record is written
+  }
+  auto take_halo = [&](double* dst) {  // the received values as the halo part of a vector
+    for (int h = tid(); h < 4 * me.n_units; h += kResThreads) dst[h] = lds.ex[h];
+  };
+
+  // start: rs = diag^-1/2 exchanged, the scaled operator; x^_0 = x_0 / rs exchanged,
+  // r^_0 = rs b - A^ x^_0 exchanged.  Every array is read once, in order; a thread's pairs
+  // past the share's end read its first pair and get rs = 0, hence a zero operator.
+  Regs<double, NP> q;
+  q.face = 0;
+  double v[kSums] = {0.0, 0.0, 0.0, 0.0}, m = -DBL_MAX;
+  auto slot = [&](int l) -> int64_t { return me.slot0 + (l < ns ? l : 0); };
+  auto pair = [&](const double* a, int64_t i) { return *reinterpret_cast<const double2*>(a + i); };
+  auto at = [&](int l) { return *reinterpret_cast<const double2*>(lds.p + l); };
+  {
+    double2 d[NP];
+    uint2 pl[NP];
+#pragma unroll
+    for (int u = 0; u < NP; ++u) {
+      const int64_t i = slot(2 * (tid() + u * kResThreads));
+      d[u] = pair(A.diag, i);
+      pl[u] = R.places[i >> 1];
+    }
+#pragma unroll
+    for (int u = 0; u < NP; ++u) {
+      const int l = 2 * (tid() + u * kResThreads);
+      const bool valid = l < ns;
+      const double2 rs{valid ? 1.0 / sqrt(d[u].x) : 0.0, valid ? 1.0 / sqrt(d[u].y) : 0.0};
+      m = fmax(m, fmax(-d[u].x, -d[u].y));
+      *reinterpret_cast<double2*>(lds.d + l) = d[u];
+      *reinterpret_cast<double2*>(lds.p + l) = rs;
+      auto place = [&](unsigned c, unsigned own) {
+        if (!valid) return own;
+        return (c & kResHalo) ? unsigned(kCap) + (c & ~kResHalo) : c;
+      };
+      const unsigned x0 = place(pl[u].x & 0xffffu, l), x1 = place(pl[u].x >> 16, l + 1);
+      const unsigned y = place(pl[u].y & 0xffffu, l), z = place(pl[u].y >> 16, l);
+      q.px[u] = x0 | (x1 << 16);
+      q.pyz[u] = y | (z << 16);
+      if (max(max(x0, x1), max(y, z)) >= unsigned(kCap)) q.face |= 1u << u;
+      keep(q.px[u]);
+      keep(q.pyz[u]);
+      stage(q, lds.ex, u, rs.x, rs.y);
+    }
+  }
+  __syncthreads();
+  if (!exchange(X, v, m, true, S, lds)) return false;
+  const double dmin = -m;
+  take_halo(lds.p + kCap);
+  __syncthreads();
+  // (one axis after the other, so that the loads in flight are few registers)
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    double2 cp[NP], cm[NP];
+#pragma unroll
+    for (int u = 0; u < NP; ++u) {
+      const int64_t i = int64_t(a) * n + slot(2 * (tid() + u * kResThreads));
+      cp[u] = pair(A.Cp, i);
+      cm[u] = pair(A.Cm, i);
+    }
+#pragma unroll
+    for (int u = 0; u < NP; ++u) {
+      const int tt = tid(), l = 2 * (tt + u * kResThreads);
+      const double2 rs = at(l);
+      if (a == 0) {
+        q.cix[u] = cp[u].x * (rs.x * rs.y);
+        q.cox[u][0] = cm[u].x * (rs.x * lds.p[q.px[u] & 0xffffu]);
+        q.cox[u][1] = cp[u].y * (rs.y * lds.p[q.px[u] >> 16]);
+        keep(q.cix[u]);
+        keep(q.cox[u][0]);
+        keep(q.cox[u][1]);
+        continue;
+      }
+      const bool up = tt & a;  // on the + side of its oct
+      const double2 in = up ? cm[u] : cp[u], out = up ? cp[u] : cm[u];
+      const double2 rn = at(a == 1 ? q.pyz[u] & 0xffffu : q.pyz[u] >> 16);
+      const double sx = a == 1 ? dpp<kQuadXor1>(rs.x, rs.x) : dpp<kQuadXor2>(rs.x, rs.x);
+      const double sy = a == 1 ? dpp<kQuadXor1>(rs.y, rs.y) : dpp<kQuadXor2>(rs.y, rs.y);
+      double(&ci)[2] = a == 1 ? q.ciy[u] : q.ciz[u];
+      double(&co)[2] = a == 1 ? q.coy[u] : q.coz[u];
+      ci[0] = in.x * (rs.x * sx);
+      ci[1] = in.y * (rs.y * sy);
+      co[0] = out.x * (rs.x * rn.x);
+      co[1] = out.y * (rs.y * rn.y);
+      keep(ci[0]);
+      keep(ci[1]);
+      keep(co[0]);
+      keep(co[1]);
+    }
+  }
+  {
+    double2 x0[NP];
+#pragma unroll
+    for (int u = 0; u < NP; ++u) x0[u] = pair(A.x, slot(2 * (tid() + u * kResThreads)));
+#pragma unroll
+    for (int u = 0; u < NP; ++u) {
+      const int l = 2 * (tid() + u * kResThreads);
+      const double2 rs = at(l);
+      q.s[u][0] = rs.x;
+      q.s[u][1] = rs.y;
+      q.x[u][0] = l < ns ? x0[u].x / rs.x : 0.0;
+      q.x[u][1] = l < ns ? x0[u].y / rs.y : 0.0;
+      keep(q.x[u][0]);
+      keep(q.x[u][1]);
+      stage(q, lds.ex, u, q.x[u][0], q.x[u][1]);
+    }
+  }
+  v[0] = v[1] = v[2] = v[3] = 0.0;
+  __syncthreads();  // rs read everywhere
+#pragma unroll
+  for (int u = 0; u < NP; ++u)
+    *reinterpret_cast<double2*>(lds.p + 2 * (tid() + u * kResThreads)) = double2{q.x[u][0], q.x[u][1]};
+  if (!exchange(X, v, m, false, S, lds)) return false;
+  take_halo(lds.p + kCap);
+  __syncthreads();
+  v[0] = v[1] = v[2] = v[3] = 0.0;
+  {
+    double2 b[NP];
+    int2 ch[NP];
+#pragma unroll
+    for (int u = 0; u < NP; ++u) {
+      const int64_t i = slot(2 * (tid() + u * kResThreads));
+      b[u] = pair(A.b, i);
+      ch[u] = *reinterpret_cast<const int2*>(L.child + i);
+    }
+#pragma unroll
+    for (int u = 0; u < NP; ++u) {
+      __builtin_amdgcn_sched_barrier(0);
+      const int l = 2 * (tid() + u * kResThreads);
+      double pv[2], av[2];
+      apply(q, lds.p, u, pv, av);
+      const double2 d = *reinterpret_cast<const double2*>(lds.d + l);
+      q.r[u][0] = q.s[u][0] * b[u].x - av[0];
+      q.r[u][1] = q.s[u][1] * b[u].y - av[1];
+      keep(q.r[u][0]);
+      keep(q.r[u][1]);
+      v[0] += q.r[u][0] * q.r[u][0] * d.x + q.r[u][1] * q.r[u][1] * d.y;
+      if (l < ns && ch[u].x == -1) v[1] += b[u].x * b[u].x;
+      if (l < ns && ch[u].y == -1) v[1] += b[u].y * b[u].y;
+      stage(q, lds.ex, u, q.r[u][0], q.r[u][1]);
+    }
+  }
+  __syncthreads();  // x^ read everywhere
+#pragma unroll
+  for (int u = 0; u < NP; ++u)
+    *reinterpret_cast<double2*>(lds.p + 2 * (tid() + u * kResThreads)) = double2{q.r[u][0], q.r[u][1]};
+  if (!exchange(X, v, m, false, S, lds)) return false;
+  take_halo(lds.rh);
+  take_halo(lds.p + kCap);
+  __syncthreads();
+  const double rnorm0 = sqrt(v[0]), bnorm = sqrt(v[1]);
+  const double floor_b = A.abs_floor * bnorm, thresh = fmax(A.tol * rnorm0, floor_b);
+  CgResult res;
+  res.rn = rnorm0;
+  res.linf = 0.0;
+  res.iters = 0;
+  res.fin = isfinite(rnorm0) && isfinite(bnorm);
+  res.conv = res.fin && rnorm0 <= floor_b;
+  const long long clk0 = wall_clock64();
+  if (res.fin && !res.conv &&
+      !cg_loop(X, q, lds, S, thresh, A.tol, A.max_iter, A.linf_test != 0, dmin, res))
+    return false;
+  const long long clk1 = wall_clock64();
+
+  // the unscaled iterate, the T update of the coupling term (linearised emission), the
+  // true residual b - (A^ x^) / rs and the smallest leaf energy
+  v[0] = v[1] = v[2] = v[3] = 0.0;
+  m = -DBL_MAX;
+  if (threadIdx.x == 0) st_word32(R.epoch + R.n_prob + me.prob, epoch0);
+#pragma unroll
+  for (int u = 0; u < NP; ++u) {
+    __builtin_amdgcn_sched_barrier(0);
+    const int l = 2 * (tid() + u * kResThreads);
+    if (l < ns) {
+      const int64_t i = me.slot0 + l;
+      const double2 d = *reinterpret_cast<const double2*>(lds.d + l);
+      const double rs[2] = {1.0 / sqrt(d.x), 1.0 / sqrt(d.y)};
+      double2 xi{q.x[u][0] * rs[0], q.x[u][1] * rs[1]};
+      if (res.iters > 0) *reinterpret_cast<double2*>(A.x + i) = xi;
+      else xi = pair(A.x, i);
+      const int2 ch = *reinterpret_cast<const int2*>(L.child + i);
+      if (ch.x == -1) m = fmax(m, -xi.x);
+      if (ch.y == -1) m = fmax(m, -xi.y);
+      if (A.cp.T) {
+#pragma unroll 1
+        for (int e = 0; e < 2; ++e)
+          if ((e ? ch.y : ch.x) == -1) {
+            const double T = A.cp.T[i + e], rr = A.rho[i + e], xe = e ? xi.y : xi.x;
+            const double eta = A.cp.kappa_P * rr * A.cp.c_light * A.dt;
+            const double bT = 4.0 * A.cp.a_rad * T * T * T;
+            A.T_out[i + e] = T + eta * (xe - A.cp.a_rad * (T * T * T * T)) / (rr * A.cp.c_v + eta * bT);
+          }
+      }
+      q.x[u][0] = xi.x / rs[0];
+      q.x[u][1] = xi.y / rs[1];
+    }
+    if (A.true_residual) {
+      *reinterpret_cast<double2*>(lds.p + l) = double2{q.x[u][0], q.x[u][1]};
+      stage(q, lds.ex, u, q.x[u][0], q.x[u][1]);
+    }
+  }
+  if (A.true_residual) {
+    double none = 0.0;
+    __syncthreads();
+    if (!exchange(X, v, none, false, S, lds)) return false;
+    take_halo(lds.p + kCap);
+    __syncthreads();
+    v[0] = v[1] = v[2] = v[3] = 0.0;
+#pragma unroll
+    for (int u = 0; u < NP; ++u) {
+      const int l = 2 * (tid() + u * kResThreads);
+      double pv[2], av[2];
+      apply(q, lds.p, u, pv, av);
+      if (l < ns) {
+        const double2 b = *reinterpret_cast<const double2*>(A.b + me.slot0 + l);
+        const double2 d = *reinterpret_cast<const double2*>(lds.d + l);
+        const double r0 = b.x - av[0] * sqrt(d.x), r1 = b.y - av[1] * sqrt(d.y);
+        v[0] = fma(r0, r0, fma(r1, r1, v[0]));
+      }
+    }
+  }
+  put_sums(X, v, m, true, S, static_cast<const double*>(nullptr), lds.partner);
+  if (my_part != me.part0) return true;
+  if (!collect(X, v, m, true, S, static_cast<double*>(nullptr))) return false;
+  if (threadIdx.x == 0) {
+    R.epoch[me.prob] = X.epoch;
+    PcgScalars z{};
+    z.rnorm0 = rnorm0;
+    z.bnorm = bnorm;
+    z.thresh = thresh;
+    z.tol = A.tol;
+    z.abs_floor = A.abs_floor;
+    z.rnorm = res.rn;
+    z.linf = res.linf;
+    z.true_rnorm = sqrt(v[0]);
+    z.min_E = -m;
+    z.iter = res.iters;
+    z.done = 1;
+    z.converged = res.conv ? 1 : 0;
+    z.nonfinite = res.fin ? 0 : 1;
+    z.max_iter = A.max_iter;
+    z.linf_test = A.linf_test;
+    z.loop_ms = double(clk1 - clk0) * 1e-5;  // the constant 100 MHz counter
+    A.sc[me.prob] = z;
+  }
+  return true;
+}
+
+template <int NP>
+__global__ __launch_bounds__(kResThreads) void k_cg_resident(DevLevel L, ResPlanDev R, ResArgs A) {
+  extern __shared__ __align__(16) unsigned char res_lds[];
+  __shared__ Shared S;
+  const int b = int(blockIdx.x);
+  for (int k = R.task0[b]; k < R.task0[b + 1]; ++k) {
+    if (!solve_part<NP>(L, R, A, R.task[k], res_lds, S)) {
+      if (threadIdx.x == 0) st_word32(R.epoch + 2 * R.n_prob, 1u);
+      return;
+    }
+    __syncthreads();
+  }
+}
+
+constexpr size_t kLdsLimit = 160 * 1024 - sizeof(Shared) - 256;
+
+size_t dyn_lds(const ResPlanDev& R, int NP) {
+  const size_t nh = 4 * size_t(R.max_units);
+  return (4 * size_t(NP) * kResThreads + 3 * nh) * sizeof(double) + size_t(R.max_units) * sizeof(int);
+}
+
+// Pairs of slots per thread.
+int pairs_of(const ResPlanDev& R) { return (R.max_slots + 2 * kResThreads - 1) / (2 * kResThreads); }
+
+template <int NP>
+hipError_t launch_np(hipStream_t s, const DevLevel& L, const ResPlanDev& R, const ResArgs& A) {
+  const size_t lds = dyn_lds(R, NP);
+  const void* f = reinterpret_cast<const void*>(&k_cg_resident<NP>);
+  const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_cg_resident<NP>, dim3(R.n_blocks), dim3(kResThreads), lds, s, L, R, A);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+bool resident_fits(const ResPlanDev& R) {
+  return R.n_parts > 0 && R.max_slots <= kResMaxSlots && dyn_lds(R, pairs_of(R)) <= kLdsLimit;
+}
+
+hipError_t launch_resident(hipStream_t s, const DevLevel& L, const ResPlanDev& R, const ResArgs& A) {
+  switch (pairs_of(R)) {
+    case 1: return launch_np<1>(s, L, R, A);
+    case 2: return launch_np<2>(s, L, R, A);
+    case 3: return launch_np<3>(s, L, R, A);
+    case 4: return launch_np<4>(s, L, R, A);
+    case 5: return launch_np<5>(s, L, R, A);
+  }
+  return hipErrorNotSupported;
+}
+
+}  // namespace amrfld

@@ -1,0 +1,100 @@
+// Shares and halo faces of the resident CG (host).
+#include "resident_plan.h"
+
+#include <algorithm>
+
+namespace amrfld {
+
+int res_group(int64_t n_oct, int max_blocks, int max_slots, int target_slots) {
+  if (8 * n_oct <= max_slots) return 1;
+  const int64_t want = (8 * n_oct + target_slots - 1) / target_slots;
+  int64_t g = std::max<int64_t>(1, std::min<int64_t>({want, n_oct, int64_t(max_blocks)}));
+  if (g > 8) g = std::min<int64_t>((g + 7) / 8 * 8, max_blocks);  // as many blocks on every XCD
+  return int(std::min<int64_t>(g, n_oct));
+}
+
+ResPlanHost build_res_plan(const std::vector<ResProblem>& probs, const std::vector<int>& group, int n_blocks,
+                           const int32_t* nbr, int64_t n_oct_table) {
+  ResPlanHost h;
+  std::vector<int32_t> part_of(n_oct_table, -1);
+  for (size_t q = 0; q < probs.size(); ++q) {
+    const int64_t m = probs[q].n_oct;
+    const int g = group[q], p0 = int(h.parts.size());
+    for (int r = 0; r < g; ++r) {
+      const int64_t o0 = probs[q].oct0 + m * r / g, o1 = probs[q].oct0 + m * (r + 1) / g;
+      ResPart p{};
+      p.slot0 = int(8 * o0);
+      p.n_slots = int(8 * (o1 - o0));
+      p.prob = int(q);
+      p.part0 = p0;
+      p.group = g;
+      for (int64_t o = o0; o < o1; ++o) part_of[o] = int32_t(h.parts.size());
+      h.max_slots = std::max(h.max_slots, p.n_slots);
+      h.parts.push_back(p);
+    }
+  }
+  h.unit_of.assign(6 * n_oct_table, -1);
+  int32_t n_units = 0;
+  for (ResPart& p : h.parts) {
+    p.unit0 = n_units;
+    const int32_t me = part_of[p.slot0 / 8];
+    for (int64_t o = p.slot0 / 8; o < (int64_t(p.slot0) + p.n_slots) / 8; ++o)
+      for (int d = 0; d < 6; ++d) {
+        const int32_t nb = nbr[6 * o + d];
+        if (nb >= 0 && part_of[nb] != me) h.unit_of[6 * o + d] = n_units++;
+      }
+    p.n_units = n_units - p.unit0;
+    h.max_units = std::max(h.max_units, p.n_units);
+  }
+  h.partner.assign(n_units, -1);
+  for (const ResPart& p : h.parts)
+    for (int64_t o = p.slot0 / 8; o < (int64_t(p.slot0) + p.n_slots) / 8; ++o)
+      for (int d = 0; d < 6; ++d) {
+        const int32_t u = h.unit_of[6 * o + d];
+        if (u >= 0) h.partner[u] = h.unit_of[6 * int64_t(nbr[6 * o + d]) + (d ^ 1)];
+      }
+  h.places.assign(8 * n_oct_table, 0);
+  for (const ResPart& p : h.parts)
+    for (int64_t o = p.slot0 / 8; o < (int64_t(p.slot0) + p.n_slots) / 8; ++o)
+      for (int k = 0; k < 4; ++k) {  // pair k of the oct: y = k & 1, z = k >> 1
+        const unsigned own = unsigned(8 * o + 2 * k - p.slot0);
+        auto place = [&](int d, unsigned self, unsigned inside, unsigned cell) -> unsigned {
+          const int32_t nb = nbr[6 * o + d], u = h.unit_of[6 * o + d];
+          if (nb < 0) return self;
+          return u >= 0 ? kResHalo | unsigned(4 * (u - p.unit0)) + cell : unsigned(8 * int64_t(nb) - p.slot0) + inside;
+        };
+        const int y = k & 1, z = k >> 1;
+        const unsigned x0 = place(0, own, unsigned(2 * k + 1), unsigned(k)), x1 = place(1, own + 1, unsigned(2 * k), unsigned(k));
+        const unsigned py = place(2 + y, own, unsigned(2 * (k ^ 1)), unsigned(2 * z));
+        const unsigned pz = place(4 + z, own, unsigned(2 * (k ^ 2)), unsigned(2 * y));
+        h.places[8 * o + 2 * k] = x0 | (x1 << 16);
+        h.places[8 * o + 2 * k + 1] = py | (pz << 16);
+      }
+  // Blocks: each problem goes to the `group` least loaded blocks.  Every block works on
+  // its shares in the order of the problems, so the first unfinished problem always has
+  // all its blocks on it: no block waits for one that waits for it.
+  std::vector<std::vector<int32_t>> list(n_blocks);
+  std::vector<std::pair<int64_t, int>> load(n_blocks);  // (slots, block)
+  for (int b = 0; b < n_blocks; ++b) load[b] = {0, b};
+  for (size_t q = 0, at = 0; q < probs.size(); at += size_t(group[q]), ++q) {
+    const int g = group[q];
+    std::partial_sort(load.begin(), load.begin() + g, load.end());
+    // blocks are dealt to the XCDs round-robin: neighbouring shares on the same XCD
+    if (probs.size() == 1 && g % 8 == 0)
+      std::sort(load.begin(), load.begin() + g, [](const std::pair<int64_t, int>& a, const std::pair<int64_t, int>& b) {
+        return std::make_pair(a.second % 8, a.second) < std::make_pair(b.second % 8, b.second);
+      });
+    for (int r = 0; r < g; ++r) {
+      list[load[r].second].push_back(int32_t(at + r));
+      load[r].first += h.parts[at + r].n_slots;
+    }
+  }
+  h.task0.assign(1, 0);
+  for (int b = 0; b < n_blocks; ++b) {
+    h.task.insert(h.task.end(), list[b].begin(), list[b].end());
+    h.task0.push_back(int32_t(h.task.size()));
+  }
+  return h;
+}
+
+}  // namespace amrfld

@@ -1,0 +1,60 @@
+// How the octs of independent problems are dealt to the blocks of the resident CG
+// (host side, no device code): contiguous shares of octs, and the faces between them.
+#pragma once
+
+#include <cstdint>
+#include <vector>
+
+namespace amrfld {
+
+constexpr unsigned kResHalo = 0x8000u;
+
+// One block's share of a problem: a contiguous range of its slots.
+struct ResPart {
+  int slot0, n_slots;  // its slots (whole octs)
+  int unit0, n_units;  // its halo units: faces of its octs whose neighbour oct lies in another share
+  int prob;            // the problem
+  int part0, group;    // the problem's shares are [part0, part0 + group)
+  int pad_;
+};
+
+struct ResPlanHost {
+  std::vector<ResPart> parts;
+  // unit_of[6 o + d]: number of the halo unit of oct o's face d, or -1.  Units are
+  // numbered share by share, so a share's units are contiguous.
+  std::vector<int32_t> unit_of;
+  // places[2 k], places[2 k + 1] of the slots 2 k and 2 k + 1, neighbours in x: where a
+  // share's block finds their out-of-oct neighbours, 16 bits each.  Low and high half of
+  // the first word: the neighbour in x of either slot; of the second: the pair of
+  // neighbours in y, in z.  A position in the share, or kResHalo and a position among
+  // its halo cells (four per unit); the slot or pair itself where there is none.
+  std::vector<uint32_t> places;
+  // partner[u]: the unit of the same face seen from the other side (the neighbour
+  // share writes its four cells there)
+  std::vector<int32_t> partner;
+  // blocks: block b works on the shares task[task0[b] .. task0[b + 1]) in that order
+  std::vector<int32_t> task0, task;
+  int max_slots = 0, max_units = 0;  // of one share
+};
+
+// A problem's octs: [oct0, oct0 + n_oct) of the neighbour table.
+struct ResProblem {
+  int64_t oct0 = 0, n_oct = 0;
+};
+
+// Shares of a problem of n_oct octs: one where it fits a block (max_slots), else about
+// target_slots each, at most max_blocks.  One block waits for nobody: 4096 slots take
+// 2.5 us an iteration in one block and 4.1 us in four.  From two blocks on an iteration
+// is the exchange (3 to 4 us) and 0.5 us per 1024 slots of a share, and the exchange
+// grows slowly with the blocks: 16 k slots take 5.9, 4.9, 4.3 and 4.4 us in 4, 8, 16 and
+// 32 blocks, 88 k slots 5.6, 5.2 and 5.4 us in 48, 88 and 176.
+int res_group(int64_t n_oct, int max_blocks, int max_slots, int target_slots);
+
+// Plans problems (listed in the order the blocks work on them) on n_blocks blocks;
+// group[q] shares of problem q, all on different blocks.  nbr: 6 per oct, as in
+// LevelTables (the neighbour of o in direction d has o as its neighbour in d ^ 1).
+// n_oct_table: rows of nbr.
+ResPlanHost build_res_plan(const std::vector<ResProblem>& probs, const std::vector<int>& group, int n_blocks,
+                           const int32_t* nbr, int64_t n_oct_table);
+
+}  // namespace amrfld

@@ -103,11 +103,14 @@ __global__ __launch_bounds__(kBlock) void k_theta_rhs(DevLevel L, FaceCoefs<doub
 
 // ... the matrix becomes I + theta (A1 - I) (identity rows stay identity rows).
 __global__ __launch_bounds__(kBlock) void k_theta_scale(int n, double theta, double* __restrict__ Cp,
-                                                        double* __restrict__ diag) {
+                                                        double* __restrict__ Cm, double* __restrict__ diag) {
   const int i = blockIdx.x * kBlock + threadIdx.x;
   if (i >= n) return;
 #pragma unroll
-  for (int a = 0; a < 3; ++a) Cp[size_t(a) * n + i] *= theta;
+  for (int a = 0; a < 3; ++a) {
+    Cp[size_t(a) * n + i] *= theta;
+    if (Cm) Cm[size_t(a) * n + i] *= theta;
+  }
   diag[i] = 1.0 + theta * (diag[i] - 1.0);
 }
 
@@ -115,8 +118,8 @@ __global__ __launch_bounds__(kBlock) void k_assemble(
     DevLevel L, const double* __restrict__ K, const double* __restrict__ Kc,
     const double* __restrict__ E, const double* __restrict__ Ec, const double* __restrict__ rho,
     const double* __restrict__ reg, double coef, double w, double alpha, CouplingParams cp, CellKParams kp,
-    OuterBC ob, double dt, double* __restrict__ Cp, uint8_t* __restrict__ mask, double* __restrict__ diag,
-    double* __restrict__ b) {
+    OuterBC ob, double dt, double* __restrict__ Cp, double* __restrict__ Cm, uint8_t* __restrict__ mask,
+    double* __restrict__ diag, double* __restrict__ b) {
   const int i = blockIdx.x * kBlock + threadIdx.x;
   const int n = L.n_slots;
   if (i >= n) return;
@@ -124,6 +127,7 @@ __global__ __launch_bounds__(kBlock) void k_assemble(
     Cp[i] = 0.0;
     Cp[size_t(n) + i] = 0.0;
     Cp[2 * size_t(n) + i] = 0.0;
+    if (Cm) Cm[i] = Cm[size_t(n) + i] = Cm[2 * size_t(n) + i] = 0.0;
     mask[i] = 0;
     diag[i] = 1.0;
     b[i] = E[i];
@@ -133,7 +137,7 @@ __global__ __launch_bounds__(kBlock) void k_assemble(
   if (pp) coef = pp->coef;
   const double Ki = K[i];
   double d = 1.0, bb = E[i];
-  double cplus[3] = {0.0, 0.0, 0.0};
+  double cplus[3] = {0.0, 0.0, 0.0}, cminus[3] = {0.0, 0.0, 0.0};
   unsigned m = 0;
 #pragma unroll
   for (int dir = 0; dir < 6; ++dir) {
@@ -148,6 +152,7 @@ __global__ __launch_bounds__(kBlock) void k_assemble(
         d += C;
         m |= 1u << dir;
         if (dir & 1) cplus[dir >> 1] = C;
+        else cminus[dir >> 1] = C;
       }
     } else {
       const int c = L.cnb[(i >> 3) * 6 + dir];
@@ -182,6 +187,11 @@ __global__ __launch_bounds__(kBlock) void k_assemble(
   Cp[i] = cplus[0];
   Cp[size_t(n) + i] = cplus[1];
   Cp[2 * size_t(n) + i] = cplus[2];
+  if (Cm) {
+    Cm[i] = cminus[0];
+    Cm[size_t(n) + i] = cminus[1];
+    Cm[2 * size_t(n) + i] = cminus[2];
+  }
   mask[i] = uint8_t(m);
   diag[i] = d;
   b[i] = bb;
@@ -195,8 +205,8 @@ __global__ __launch_bounds__(kBlock) void k_assemble(
 // (V_f (2/3) A_f, equal to V_c A_c / 3), and read by both rows.
 __global__ __launch_bounds__(kBlock) void k_assemble_composite(
     DevLevel L, const double* __restrict__ K, const double* __restrict__ E, const double* __restrict__ rho,
-    CouplingParams cp, OuterBC ob, double dt, double* __restrict__ Cp, double* __restrict__ cif,
-    uint8_t* __restrict__ c2f, double* __restrict__ diag, double* __restrict__ b) {
+    CouplingParams cp, OuterBC ob, double dt, double* __restrict__ Cp, double* __restrict__ Cm,
+    double* __restrict__ cif, uint8_t* __restrict__ c2f, double* __restrict__ diag, double* __restrict__ b) {
   const int i = blockIdx.x * kBlock + threadIdx.x;
   const int n = L.n_slots;
   if (i >= n) return;
@@ -204,6 +214,7 @@ __global__ __launch_bounds__(kBlock) void k_assemble_composite(
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
       Cp[size_t(a) * n + i] = 0.0;
+      if (Cm) Cm[size_t(a) * n + i] = 0.0;
       cif[size_t(a) * n + i] = 0.0;
     }
     c2f[i] = 0;
@@ -214,7 +225,7 @@ __global__ __launch_bounds__(kBlock) void k_assemble_composite(
   const PatchParams& P = L.pp[L.oct_prob[i >> 3]];
   const double coef = P.coef, V = P.vol, Ki = K[i];
   double d = 1.0, bb = E[i];
-  double cplus[3] = {0.0, 0.0, 0.0}, cf[3] = {0.0, 0.0, 0.0};
+  double cplus[3] = {0.0, 0.0, 0.0}, cminus[3] = {0.0, 0.0, 0.0}, cf[3] = {0.0, 0.0, 0.0};
   unsigned mask = 0;
   for (int dir = 0; dir < 6; ++dir) {
     const int a = dir >> 1, side = dir & 1;
@@ -233,6 +244,7 @@ __global__ __launch_bounds__(kBlock) void k_assemble_composite(
         const double C = harmonic(Ki, K[j]) * coef;
         d += C;
         if (side) cplus[a] = V * C;
+        else cminus[a] = V * C;
       }
     } else {
       const int c = L.cnb[(i >> 3) * 6 + dir];
@@ -261,6 +273,7 @@ __global__ __launch_bounds__(kBlock) void k_assemble_composite(
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
     Cp[size_t(a) * n + i] = cplus[a];
+    if (Cm) Cm[size_t(a) * n + i] = cminus[a];
     cif[size_t(a) * n + i] = cf[a];
   }
   c2f[i] = uint8_t(mask);
@@ -276,7 +289,8 @@ __global__ __launch_bounds__(kBlock) void k_flux_register(DevLevel F, const doub
                                                           const double* __restrict__ Ef,
                                                           const double* __restrict__ Ec,
                                                           double coef, double* __restrict__ reg_c,
-                                                          int n_slots_c) {
+                                                          int n_slots_c, const int* done) {
+  if (done && !*done) return;
   const int t = blockIdx.x * kBlock + threadIdx.x;
   if (t >= F.n_oct * 6) return;
   const int o = t / 6, dir = t % 6;
@@ -413,31 +427,31 @@ void launch_cell_K(hipStream_t s, const DevLevel& L, const double* E, const doub
 void launch_assemble(hipStream_t s, const DevLevel& L, const double* K, const double* K_coarse,
                      const double* E, const double* E_coarse, const double* rho, const double* reg,
                      double dt, double w, double alpha, const CouplingParams& cp, const CellKParams& kp,
-                     const OuterBC& ob, double* Cp, uint8_t* mask, double* diag, double* b) {
+                     const OuterBC& ob, double* Cp, uint8_t* mask, double* diag, double* b, double* Cm) {
   const double coef = dt / (L.dx * L.dx);
   hipLaunchKernelGGL(k_assemble, dim3(grid_for(L.n_slots)), dim3(kBlock), 0, s, L, K, K_coarse, E,
-                     E_coarse, rho, reg, coef, w, alpha, cp, kp, ob, dt, Cp, mask, diag, b);
+                     E_coarse, rho, reg, coef, w, alpha, cp, kp, ob, dt, Cp, Cm, mask, diag, b);
 }
 
 void launch_assemble_composite(hipStream_t s, const DevLevel& C, const double* K, const double* E,
                                const double* rho, const CouplingParams& cp, const OuterBC& ob, double dt,
-                               double* Cp, double* cif, uint8_t* c2f, double* diag, double* b) {
+                               double* Cp, double* cif, uint8_t* c2f, double* diag, double* b, double* Cm) {
   hipLaunchKernelGGL(k_assemble_composite, dim3(grid_for(C.n_slots)), dim3(kBlock), 0, s, C, K, E, rho, cp, ob, dt,
-                     Cp, cif, c2f, diag, b);
+                     Cp, Cm, cif, c2f, diag, b);
 }
 
 void launch_theta_step(hipStream_t s, const DevLevel& L, double theta, const double* E,
-                       const FaceCoefs<double>& A1, double* Cp, double* diag, double* b) {
+                       const FaceCoefs<double>& A1, double* Cp, double* diag, double* b, double* Cm) {
   hipLaunchKernelGGL(k_theta_rhs, dim3(grid_for(L.n_slots)), dim3(kBlock), 0, s, L, A1, diag, E, theta, b);
-  hipLaunchKernelGGL(k_theta_scale, dim3(grid_for(L.n_slots)), dim3(kBlock), 0, s, L.n_slots, theta, Cp, diag);
+  hipLaunchKernelGGL(k_theta_scale, dim3(grid_for(L.n_slots)), dim3(kBlock), 0, s, L.n_slots, theta, Cp, Cm, diag);
 }
 
 void launch_flux_register(hipStream_t s, const DevLevel& F, const double* K_f, const double* K_c,
                           const double* E_f, const double* E_c, double dt, double* reg_c,
-                          int n_slots_c) {
+                          int n_slots_c, const int* done) {
   const double coef = dt / (F.dx * F.dx);
   hipLaunchKernelGGL(k_flux_register, dim3(grid_for(int64_t(F.n_oct) * 6)), dim3(kBlock), 0, s, F,
-                     K_f, K_c, E_f, E_c, coef, reg_c, n_slots_c);
+                     K_f, K_c, E_f, E_c, coef, reg_c, n_slots_c, done);
 }
 
 void launch_restrict(hipStream_t s, const DevLevel& F, const double* E_f, double* E_c) {

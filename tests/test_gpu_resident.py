@@ -1,0 +1,124 @@
+"""The resident CG of FP64 level solves (csrc/resident.hip) against the oracle at the
+sizes where its shares change: one oct, the largest share of one block and one oct more,
+whole and ragged last pairs of a thread, one and several waves of share words, faces
+between shares on every side; and contexts on several streams and threads at once, whose
+launches have to take turns on the device.
+
+Bar: relative L2 <= 1e-12 with equal iteration counts (a near-tie of a residual with its
+threshold: both sides again with tol 0 at the larger count)."""
+import threading
+
+import numpy as np
+import pytest
+
+from _util import align, oracle_from_problem
+import oracle as ora
+from synth.configs import config_uniform
+from synth.hierarchy import Hierarchy
+
+pytestmark = pytest.mark.gpu
+
+
+def _problem(k, seed=1, base=4, compact=False):
+    """A uniform base level and one finer level of k octs: the first k base cells in
+    Morton-like blocks (compact) or k cells drawn at random."""
+    p = config_uniform(base, kmode="lp", seed=seed)
+    n = 1 << base
+    rng = np.random.default_rng(seed)
+    cells = np.array([[i, j, l] for i in range(n) for j in range(n) for l in range(n)], dtype=np.int32)
+    pick = np.arange(k) if compact else rng.permutation(len(cells))[:k]
+    p.hierarchy = Hierarchy(base, {base: p.hierarchy.octs[base], base + 1: np.ascontiguousarray(cells[pick])})
+    return p
+
+
+def _solve(p, level, dt, tol, max_iter=10000, **kw):
+    from paper_1401_1112_amd.solver import solver_from_problem, to_numpy
+    s = solver_from_problem(p, max_iter=max_iter, **kw)
+    s.solve_level(level, dt, 0, tol, raise_on_error=False)
+    out = to_numpy(s.E(level)), s.cells(level), s.stats()[0]
+    s.close()
+    return out
+
+
+def _check(p, level, dt, tol):
+    o = oracle_from_problem(p)
+    h = o.solve_level(level, dt, ora.DIRICHLET, tol)
+    e, cells, st = _solve(p, level, dt, tol)
+    if st["iters"] != h["iters"]:  # near-tie: the larger count on both sides
+        n = max(st["iters"], h["iters"])
+        o = oracle_from_problem(p, max_iter=n, abs_floor=0.0)
+        h = o.solve_level(level, dt, ora.DIRICHLET, 0.0)
+        e, cells, st = _solve(p, level, dt, 0.0, max_iter=n, abs_floor=0.0)
+    assert st["iters"] == h["iters"]
+    ref = align(level, o.cells(level), o.E[level], cells)
+    assert np.linalg.norm(e - ref) <= 1e-12 * np.linalg.norm(ref)
+    assert np.isclose(st["min_E"], h["min_E"], rtol=1e-10)
+    assert abs(st["true_rel_res"] * st["rnorm0"] - h["true_res"]) <= 0.05 * h["true_res"] + 1e-14 * h["bnorm"]
+    return st
+
+
+@pytest.mark.parametrize("k", [1, 2, 127, 128, 129, 640, 641, 1000, 2049, 4095])
+@pytest.mark.parametrize("compact", [False, True])
+def test_sizes_against_oracle(k, compact):
+    p = _problem(k, seed=k, compact=compact)
+    st = _check(p, 5, 12.0 / 32 ** 2, 1e-10)
+    assert (st["sweep_blocks"] == 1) == (k <= 640)
+
+
+@pytest.mark.parametrize("level", [1, 2, 3, 6])
+def test_uniform_levels_against_oracle(level):
+    p = config_uniform(level, kmode="lp", seed=level)
+    _check(p, level, 12.0 / 4 ** level, 1e-10)
+
+
+def test_fixed_counts_and_no_linf_test():
+    p = _problem(700, seed=5)
+    for kw in ({"linf_test": False}, {"true_residual": False}):
+        o = oracle_from_problem(p, **({"linf_test": False} if "linf_test" in kw else {}))
+        h = o.solve_level(5, 12.0 / 32 ** 2, ora.DIRICHLET, 1e-8)
+        e, cells, st = _solve(p, 5, 12.0 / 32 ** 2, 1e-8, **kw)
+        assert st["iters"] == h["iters"]
+        ref = align(5, o.cells(5), o.E[5], cells)
+        assert np.linalg.norm(e - ref) <= 1e-12 * np.linalg.norm(ref)
+        assert (st["true_rel_res"] == -1.0) == ("true_residual" in kw)
+
+
+def test_contexts_on_streams_and_threads():
+    # several contexts, each with a stream and a thread of its own, on levels of many
+    # blocks: their launches wait for each other on the device and every result is the
+    # one of the context alone, bit for bit
+    import torch
+    from paper_1401_1112_amd.solver import solver_from_problem, to_numpy
+    ps = [_problem(k, seed=20 + k) for k in (3000, 4096, 900, 4000)]
+    alone = [_solve(p, 5, 12.0 / 32 ** 2, 1e-10)[0] for p in ps]
+    streams = [torch.cuda.Stream() for _ in ps]
+    solvers = []
+    for p, st in zip(ps, streams):
+        with torch.cuda.stream(st):
+            solvers.append(solver_from_problem(p, stream=st))
+    torch.cuda.synchronize()
+    out, errors = [None] * len(ps), []
+
+    def work(k):
+        try:
+            p, s = ps[k], solvers[k]
+            with torch.cuda.stream(streams[k]):
+                for _ in range(4):
+                    for l in (4, 5):
+                        c = s.cells(l)
+                        s.set_fields(l, p.rho(l, c), p.E(l, c), kmode=1)
+                    s.solve_level(5, 12.0 / 32 ** 2, 0, 1e-10)
+                out[k] = s.E(5)
+            streams[k].synchronize()
+        except Exception as e:  # reported below, in the main thread
+            errors.append((k, e))
+
+    threads = [threading.Thread(target=work, args=(k,)) for k in range(len(ps))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not errors, errors
+    for k, s in enumerate(solvers):
+        assert np.array_equal(to_numpy(out[k]), alone[k]), k
+        s.close()

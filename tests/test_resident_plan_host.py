@@ -1,0 +1,163 @@
+"""Plan of the resident CG (csrc/resident_plan.cpp) on the CPU: shares cover every
+problem's octs once, every face between two shares has one unit on each side and the two
+name each other, the place of each of a face's four cells is the same seen from both
+sides, and no order of execution of the blocks' lists can make two blocks wait for each
+other.  Plain build and with AddressSanitizer and UndefinedBehaviorSanitizer."""
+import os
+import shutil
+import struct
+import subprocess
+
+import numpy as np
+import pytest
+
+from synth.hierarchy import random_balanced_hierarchy
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_1401_1112_amd", "csrc")
+OFF = [(-1, 0, 0), (1, 0, 0), (0, -1, 0), (0, 1, 0), (0, 0, -1), (0, 0, 1)]
+SANITIZE = ["-g", "-fno-omit-frame-pointer", "-fsanitize=address,undefined", "-fno-sanitize-recover=all"]
+
+pytestmark = pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+
+
+@pytest.fixture(scope="module", params=["plain", "asan_ubsan"])
+def harness(request, tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("plan") / f"plan_dump_{request.param}")
+    extra = SANITIZE if request.param == "asan_ubsan" else []
+    subprocess.run(["g++", "-O1", "-std=c++17"] + extra + ["-I", CSRC,
+                    os.path.join(ROOT, "tests", "host", "resident_plan_dump.cpp"),
+                    os.path.join(CSRC, "resident_plan.cpp"), "-o", exe], check=True)
+    return exe
+
+
+def _morton(o):
+    k = np.zeros(len(o), dtype=np.int64)
+    for b in range(10):
+        for a in range(3):
+            k |= ((o[:, a].astype(np.int64) >> b) & 1) << (3 * b + a)
+    return k
+
+
+def _table(octs):
+    """Neighbour octs of Morton-sorted octs, -1 where absent."""
+    octs = np.asarray(octs, dtype=np.int64)
+    octs = octs[np.argsort(_morton(octs))]
+    at = {tuple(o): i for i, o in enumerate(octs.tolist())}
+    return np.array([[at.get((o[0] + d[0], o[1] + d[1], o[2] + d[2]), -1) for d in OFF] for o in octs.tolist()],
+                    dtype=np.int32)
+
+
+def _box(m):
+    return np.array([[i, j, k] for i in range(m) for j in range(m) for k in range(m)])
+
+
+def _plan(harness, tmp_path, tables, n_blocks, target):
+    """Problems one after another, with a gap of unused rows between them."""
+    rows, probs, at = [], [], 0
+    for t in tables:
+        probs.append((at, len(t)))
+        rows.append(np.where(t >= 0, t + at, -1))
+        rows.append(np.full((3, 6), -1))
+        at += len(t) + 3
+    nbr = np.concatenate(rows).astype(np.int32)
+    path = tmp_path / "p.bin"
+    with open(path, "wb") as f:
+        f.write(struct.pack("<iii", len(probs), n_blocks, target))
+        for p in probs:
+            f.write(struct.pack("<qq", *p))
+        f.write(struct.pack("<q", len(nbr)))
+        f.write(nbr.tobytes())
+    run = subprocess.run([harness, str(path)], capture_output=True, text=True)
+    assert run.returncode == 0, run.stderr[-3000:]
+    arr = [np.array(x.split(), dtype=np.int64) for x in run.stdout.splitlines()]
+    return probs, nbr, arr[0].reshape(-1, 7), arr[1].reshape(-1, 6), arr[2], arr[3], arr[4], arr[5], arr[6]
+
+
+CASES = {
+    "one_oct": lambda: ([_box(1)], 256, 64),
+    "one_share": lambda: ([_box(4)], 256, 2048),
+    "many_shares": lambda: ([_box(8)], 24, 64),
+    "every_oct_a_share": lambda: ([_box(3)], 256, 8),
+    "irregular": lambda: ([random_balanced_hierarchy(3, 3, 5, 0.5).octs[5]], 16, 128),
+    "batch": lambda: ([_box(m) for m in (6, 5, 4, 4, 3, 2, 1, 1)], 8, 256),
+    "batch_whole_chip": lambda: ([_box(m) for m in (7, 7, 6, 2, 1)], 5, 100),
+}
+
+
+@pytest.mark.parametrize("case", list(CASES))
+def test_plan(harness, tmp_path, case):
+    octs, n_blocks, target = CASES[case]()
+    probs, nbr, parts, unit_of, partner, task0, task, most, places = _plan(
+        harness, tmp_path, [_table(o) for o in octs], n_blocks, target)
+    part_of = np.full(len(nbr), -1)
+    for k, (s0, ns, u0, nu, q, p0, g) in enumerate(parts):
+        assert s0 % 8 == 0 and ns % 8 == 0 and ns > 0
+        assert np.all(part_of[s0 // 8:(s0 + ns) // 8] == -1)
+        part_of[s0 // 8:(s0 + ns) // 8] = k
+        assert p0 <= k < p0 + g and g <= n_blocks
+        assert np.all(parts[p0:p0 + g, 4] == q)
+    for o0, m in probs:
+        assert np.all(part_of[o0:o0 + m] >= 0)
+    assert int((part_of >= 0).sum()) == sum(m for _, m in probs)
+    assert most[0] == parts[:, 1].max() and most[1] == parts[:, 3].max()
+
+    seen = set()
+    for o in range(len(nbr)):
+        for d in range(6):
+            u, nb = unit_of[o, d], nbr[o, d]
+            cross = part_of[o] >= 0 and nb >= 0 and part_of[nb] != part_of[o]
+            assert (u >= 0) == cross
+            if not cross:
+                continue
+            seen.add(int(u))
+            k = part_of[o]
+            assert parts[k, 2] <= u < parts[k, 2] + parts[k, 3]
+            assert partner[u] == unit_of[nb, d ^ 1] and partner[partner[u]] == u
+    assert seen == set(range(len(partner)))
+
+    # every share once; a problem's shares on different blocks; lists in the problems'
+    # order, so that the first unfinished problem always has all its blocks
+    assert sorted(task) == list(range(len(parts))) and len(task0) == n_blocks + 1
+    for b in range(n_blocks):
+        mine = parts[task[task0[b]:task0[b + 1]], 4]
+        assert np.all(np.diff(mine) > 0)
+
+    # what a thread reads for the out-of-oct neighbours of its pairs: the slots of its own
+    # share directly; halo cells through the export list of the neighbour share, whose
+    # entry 4 u + c is filled with the cell whose own place is that entry
+    places = (places & 0xffffffff).reshape(-1, 2)
+    filled = {}
+
+    def entries(o, k):
+        p0, p1 = (int(v) for v in places[4 * o + k])
+        s = 8 * o + 2 * k
+        out = [(s, 0, k, p0 & 0xffff, 1), (s + 1, 1, k, p0 >> 16, 1)]
+        return out + [(s, 2 + (k & 1), k, p1 & 0xffff, 2), (s, 4 + (k >> 1), k, p1 >> 16, 2)]
+
+    rows = [o for o in range(len(nbr)) if part_of[o] >= 0]
+    for o in rows:
+        for k in range(4):
+            for s, d, _, place, w in entries(o, k):
+                if place & 0x8000:
+                    for j in range(w):
+                        key = (int(part_of[o]), (place & 0x7fff) + j)
+                        assert key not in filled
+                        filled[key] = s + j
+    assert len(filled) == 4 * len(partner)
+    for o in rows:
+        me = parts[part_of[o]]
+        for k in range(4):
+            for s, d, _, place, w in entries(o, k):
+                nb = nbr[o, d]
+                for j in range(w):
+                    pos = (s + j) & 7
+                    want = 8 * nb + (pos ^ (1 << (d >> 1))) if nb >= 0 else s + j
+                    if place & 0x8000:
+                        cell = (place & 0x7fff) + j
+                        other = partner[me[2] + cell // 4]
+                        owner = part_of[nb]
+                        got = filled[(int(owner), int(4 * (other - parts[owner, 2]) + cell % 4))]
+                    else:
+                        got = me[0] + place + j
+                    assert got == want, (case, o, k, d)
