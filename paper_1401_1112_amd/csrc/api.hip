@@ -189,8 +189,22 @@ struct BatchState {
   uint8_t* mask = nullptr;
   PatchParams* pp = nullptr;
   const double** src = nullptr;  // device array of n_prob pointers
+  // Patches solved resident (FP64) and the plan of the sweeps over the others: no block
+  // for a resident patch.  E0: the energies at the start of a step, restored if the
+  // resident launch does not end.
+  ResTables res;
+  std::vector<ResProblem> res_probs;
+  std::vector<char> is_resident;  // per patch
+  int n_big = 0;  // patches that the sweeps solve
+  int G_big = 0;
+  int32_t *big_blk_prob = nullptr, *big_blk0 = nullptr;
+  double* E0 = nullptr;
 
   void release() {
+    res.release();
+    for (void* p : {(void*)big_blk_prob, (void*)big_blk0, (void*)E0}) dfree(p);
+    big_blk_prob = big_blk0 = nullptr;
+    E0 = nullptr;
     for (void* p : {(void*)nbr, (void*)cnb, (void*)child, (void*)oct_prob, (void*)idx, (void*)blk_prob,
                     (void*)blk0, (void*)tile0, (void*)d_out_off, (void*)E, (void*)rho, (void*)K, (void*)Cp,
                     (void*)diag, (void*)b, (void*)pp, (void*)src, (void*)mask, (void*)Ch, (void*)rs})
@@ -226,6 +240,16 @@ struct BatchState {
     p.blk0 = blk0;
     p.tile0 = tile0;
     p.done_count = nullptr;
+    p.n_active = n_prob;
+    return p;
+  }
+  // the sweeps of the patches that are not solved resident
+  SweepPlan big_plan() const {
+    SweepPlan p = plan();
+    p.G = G_big;
+    p.blk_prob = big_blk_prob;
+    p.blk0 = big_blk0;
+    p.n_active = n_big;
     return p;
   }
 };
@@ -868,7 +892,7 @@ void pcg_fp64(amrfld_ctx* c, const DevLevel& D, const SweepPlan& P, const SolveA
   const hipStream_t s = c->stream();
   const int np = P.n_prob;
   for (int q = 0; q < np; ++q) c->h_sc[q] = make_scalars(tol, c->o.abs_floor, c->o.max_iter, c->o.linf_test);
-  launch_init_scalars(s, c->sc, np, tol, c->o.abs_floor, c->o.max_iter, c->o.linf_test);
+  launch_init_scalars(s, c->sc, np, tol, c->o.abs_floor, c->o.max_iter, c->o.linf_test, P.blk0);
   cg_start(c, s, D, P, A, c->sc);
   check(hipEventRecord(c->ev[1], s), "event");
   pcg_iterations<double>(c, D, P, A.Ah, c->cg, A.x, c->sc, c->h_sc, c->o.max_iter, ls,
@@ -903,7 +927,7 @@ void pcg_mixed(amrfld_ctx* c, const DevLevel& D, const SweepPlan& P, const Sweep
     c->h_sc[q] = make_scalars(tol, c->o.abs_floor, c->o.max_iter, c->o.linf_test);
     c->h_sc[np + q] = make_scalars(c->o.inner_tol, 0.0, c->o.max_iter, 0);
   }
-  launch_init_scalars(s, c->sc, np, tol, c->o.abs_floor, c->o.max_iter, c->o.linf_test);
+  launch_init_scalars(s, c->sc, np, tol, c->o.abs_floor, c->o.max_iter, c->o.linf_test, P.blk0);
   launch_init_scalars(s, c->sc + np, np, c->o.inner_tol, 0.0, c->o.max_iter, 0);
   check(hipEventRecord(c->ev[1], s), "event");
   PcgScalars* out = c->sc;
@@ -1763,21 +1787,66 @@ void build_batch_into(amrfld_ctx* c, BatchState* B, const std::vector<int>& size
       }
     }
   }
-  // blocks: at most tpb tiles per block, about >= 1024 blocks in total
-  const int64_t total_tiles = tile0[B->n_prob];
-  const int max_blocks = c->o.max_blocks > 0 ? c->o.max_blocks : 1024;
-  const int tpb = int(std::max<int64_t>(1, std::min<int64_t>(kMaxTilesPerBlock, total_tiles / max_blocks)));
-  std::vector<int32_t> blk0(B->n_prob + 1, 0), t0v(B->n_prob + 1, 0), blk_prob;
-  int tpb_max = 1;
+  // patches that fit a resident solve, the largest first; in shares as large as a block
+  // holds once the patches fill the device, else about even
+  std::vector<int> order;
   for (int q = 0; q < B->n_prob; ++q) {
-    const int64_t tiles = tile0[q + 1] - tile0[q];
-    const int64_t g = (tiles + tpb - 1) / tpb;
-    blk0[q + 1] = int32_t(blk0[q] + g);
-    t0v[q + 1] = int32_t(tile0[q + 1]);
-    tpb_max = std::max<int>(tpb_max, int((tiles + g - 1) / g));
-    for (int64_t k = 0; k < g; ++k) blk_prob.push_back(q);
+    const int64_t m = sizes[q] / 2;
+    if ((m * m * m + c->n_cu - 1) / c->n_cu * 8 <= kResMaxSlots) order.push_back(q);
   }
+  std::sort(order.begin(), order.end(), [&](int a, int b2) { return sizes[a] != sizes[b2] ? sizes[a] > sizes[b2] : a < b2; });
+  std::vector<char>& is_res = B->is_resident;
+  is_res.assign(B->n_prob, 0);
+  B->res_probs.clear();
+  if (!order.empty()) {
+    int64_t slots = 0, shares = 0;
+    for (int q : order) slots += int64_t(sizes[q]) * sizes[q] * sizes[q];
+    const int target =
+        int(std::max<int64_t>(kResTargetSlots, std::min<int64_t>(kResMaxSlots, (slots + c->n_cu - 1) / c->n_cu)));
+    std::vector<ResProblem> probs;
+    std::vector<int> group;
+    for (int q : order) {
+      const int64_t m = sizes[q] / 2;
+      ResProblem p;
+      p.oct0 = oct0[q];
+      p.n_oct = m * m * m;
+      p.id = q;
+      probs.push_back(p);
+      group.push_back(res_group(p.n_oct, c->n_cu, kResMaxSlots, target));
+      shares += group.back();
+    }
+    const int n_blocks = int(std::min<int64_t>(c->n_cu, shares));
+    B->res = make_res_tables(c->stream(), build_res_plan(probs, group, n_blocks, nbr.data(), B->n_oct), B->n_prob);
+    if (B->res.d.parts) {
+      for (int q : order) is_res[q] = 1;
+      B->res_probs = probs;
+    }
+  }
+  // blocks of the sweeps: at most tpb tiles per block, about >= 1024 blocks in total
+  const int max_blocks = c->o.max_blocks > 0 ? c->o.max_blocks : 1024;
+  std::vector<int32_t> t0v(B->n_prob + 1, 0);
+  int tpb_max = 1;
+  auto deal = [&](bool all, std::vector<int32_t>& blk0, std::vector<int32_t>& blk_prob) {
+    int64_t total = 0;
+    for (int q = 0; q < B->n_prob; ++q)
+      if (all || !is_res[q]) total += tile0[q + 1] - tile0[q];
+    const int tpb = int(std::max<int64_t>(1, std::min<int64_t>(kMaxTilesPerBlock, total / max_blocks)));
+    blk0.assign(B->n_prob + 1, 0);
+    for (int q = 0; q < B->n_prob; ++q) {
+      const int64_t tiles = tile0[q + 1] - tile0[q];
+      const int64_t g = all || !is_res[q] ? (tiles + tpb - 1) / tpb : 0;
+      blk0[q + 1] = int32_t(blk0[q] + g);
+      t0v[q + 1] = int32_t(tile0[q + 1]);
+      if (g > 0) tpb_max = std::max<int>(tpb_max, int((tiles + g - 1) / g));
+      for (int64_t k = 0; k < g; ++k) blk_prob.push_back(q);
+    }
+  };
+  std::vector<int32_t> blk0, blk_prob, big_blk0, big_blk_prob;
+  deal(true, blk0, blk_prob);
+  deal(false, big_blk0, big_blk_prob);
   B->G = blk0[B->n_prob];
+  B->G_big = big_blk0[B->n_prob];
+  B->n_big = B->n_prob - int(std::count(is_res.begin(), is_res.end(), char(1)));
   B->tpb_max = tpb_max;
   std::vector<int32_t> cnb(6 * B->n_oct, -1);
   upload(c, &B->nbr, nbr, "batch tables");
@@ -1787,9 +1856,12 @@ void build_batch_into(amrfld_ctx* c, BatchState* B, const std::vector<int>& size
   upload(c, &B->idx, idx, "batch tables");
   upload(c, &B->blk_prob, blk_prob, "batch tables");
   upload(c, &B->blk0, blk0, "batch tables");
+  upload(c, &B->big_blk_prob, big_blk_prob, "batch tables");
+  upload(c, &B->big_blk0, big_blk0, "batch tables");
   upload(c, &B->tile0, t0v, "batch tables");
   upload(c, &B->d_out_off, B->out_off, "batch tables");
   B->E = dalloc<double>(B->n_slots, "batch fields");
+  if (B->res.d.parts) B->E0 = dalloc<double>(B->n_slots, "batch fields");
   B->rho = dalloc<double>(B->n_slots, "batch fields");
   B->K = dalloc<double>(B->n_slots, "batch fields");
   B->Cp = dalloc<double>(3 * B->n_slots, "batch fields");
@@ -1803,6 +1875,28 @@ void build_batch_into(amrfld_ctx* c, BatchState* B, const std::vector<int>& size
   check(hipStreamSynchronize(c->stream()), "batch tables");
 }
 
+// Patches of a step that are solved resident in this precision.
+bool batch_resident(const BatchState& B, int precision) {
+  return B.res.d.parts && precision == AMRFLD_FP64;
+}
+
+ResArgs batch_resident_args(const amrfld_ctx* c, const BatchState& B, double tol, PcgScalars* sc) {
+  ResArgs a;
+  a.Cp = B.Cp;
+  a.Cm = B.Ch;
+  a.diag = B.diag;
+  a.b = B.b;
+  a.x = B.E;
+  a.sc = sc;
+  a.tol = tol;
+  a.abs_floor = c->o.abs_floor;
+  a.max_iter = c->o.max_iter;
+  a.linf_test = c->o.linf_test;
+  a.true_residual = c->o.true_residual;
+  a.spin_limit = kResSpinLimitBatch;
+  return a;
+}
+
 // All steps of a batch with one cooperative launch per step for the PCG
 // iterations, optionally captured in one hipGraph.  Returns AMRFLD_E_STATE when
 // the device cannot run the cooperative launch (the caller then polls).
@@ -1811,13 +1905,17 @@ amrfld_status solve_batch_persistent(amrfld_ctx* c, const std::vector<amrfld_pat
   BatchState& B = *c->batch;
   const int np = B.n_prob;
   const DevLevel D = B.dev();
-  SweepPlan P = B.plan();
+  const bool resident = batch_resident(B, precision);
+  SweepPlan P = resident ? B.big_plan() : B.plan();
   if (!c->bar) c->bar = dalloc<unsigned>(kBarWords, "barrier");
   P.done_count = c->bar + kBarDone;
   const unsigned* abort_flag = c->bar + kBarAbort;
   const int per_cu = c->o.persistent_per_cu;
   const bool mixed = precision == AMRFLD_MIXED;
-  if ((mixed ? mixed_persistent_blocks(P, P, per_cu) : persistent_blocks<double>(P, per_cu)) <= 0) return AMRFLD_E_STATE;
+  const int blocks = P.G == 0 ? B.res.d.n_blocks
+                     : mixed  ? mixed_persistent_blocks(P, P, per_cu)
+                              : persistent_blocks<double>(P, per_cu);
+  if (blocks <= 0) return AMRFLD_E_STATE;
   // one record per (step, patch), then the inner records of the mixed form (shared by the steps)
   ensure_scalars(c, n_steps * np + np);
   if (mixed) ensure_workspace32(c, B.n_slots);
@@ -1833,10 +1931,15 @@ amrfld_status solve_batch_persistent(amrfld_ctx* c, const std::vector<amrfld_pat
       PcgScalars* sc = c->sc + int64_t(step) * np;
       launch_cell_K(st, D, B.E, B.rho, nullptr, kp, OuterBC{}, B.K);
       launch_assemble(st, D, B.K, nullptr, B.E, nullptr, B.rho, nullptr, 1.0, 1.0, c->o.robin_alpha, cp, kp,
-                      OuterBC{}, B.Cp, B.mask, B.diag, B.b);
+                      OuterBC{}, B.Cp, B.mask, B.diag, B.b, resident ? B.Ch : nullptr);
+      if (resident) {
+        const hipError_t e = launch_resident(st, D, B.res.d, batch_resident_args(c, B, tol, sc));
+        if (e != hipSuccess) return e;
+        if (P.G == 0) continue;
+      }
       const ScaledOp<double> Ah = scale_operator(c, st, D, Aop, B.Cp, B.diag, B.rs, B.Ch);
       const SolveArrays A{Aop, B.diag, B.b, B.E, B.n_slots, Ah};
-      launch_init_scalars(st, sc, np, tol, c->o.abs_floor, c->o.max_iter, c->o.linf_test);
+      launch_init_scalars(st, sc, np, tol, c->o.abs_floor, c->o.max_iter, c->o.linf_test, P.blk0);
       launch_zero_u32(st, c->bar, kBarAbort);
       hipError_t e;
       if (mixed) {
@@ -1909,6 +2012,7 @@ amrfld_status solve_batch_persistent(amrfld_ctx* c, const std::vector<amrfld_pat
   for (int step = 0; step < n_steps; ++step) {
     for (int q = 0; q < np; ++q) {
       const PcgScalars& h = c->h_sc[int64_t(step) * np + q];
+      if (resident && !h.done) aborted = 1;
       amrfld_stats st{};
       st.level = q;
       st.iters = mixed ? h.inner_total : h.iter;
@@ -1926,8 +2030,8 @@ amrfld_status solve_batch_persistent(amrfld_ctx* c, const std::vector<amrfld_pat
       st.launch_mode = mode;
       st.rnorm0 = h.rnorm0;
       st.bnorm = h.bnorm;
-      st.sweep_blocks = P.G;
-      st.launch_blocks = mixed ? mixed_persistent_blocks(P, P, per_cu) : persistent_blocks<double>(P, per_cu);
+      st.sweep_blocks = P.G == 0 ? B.res.d.n_blocks : P.G;
+      st.launch_blocks = blocks;
       st.status = h.nonfinite ? AMRFLD_E_NONFINITE : (h.converged ? AMRFLD_OK : AMRFLD_E_NOCONV);
       if (st.status != AMRFLD_OK && worst == AMRFLD_OK) {
         worst = amrfld_status(st.status);
@@ -1937,6 +2041,7 @@ amrfld_status solve_batch_persistent(amrfld_ctx* c, const std::vector<amrfld_pat
       c->stats.push_back(st);
     }
   }
+  if (aborted && resident) reset_exchange(us, B.res.d);
   if (aborted) return fail(c, AMRFLD_E_DEVICE, "persistent sweep: a grid barrier timed out");
   if (worst != AMRFLD_OK) return fail(c, worst, worst_msg);
   return AMRFLD_OK;
@@ -1983,7 +2088,7 @@ amrfld_status solve_batch(amrfld_ctx* c, const std::vector<amrfld_patch>& pt, in
     c->stats.clear();  // the device cannot run it: poll instead
   }
   ensure_scalars(c, np);
-  const SweepPlan P = B.plan();
+  bool resident = batch_resident(B, precision);
   // the batch's precision for this call only, restored on every way out
   struct PrecisionScope {
     amrfld_opts& o;
@@ -2001,22 +2106,46 @@ amrfld_status solve_batch(amrfld_ctx* c, const std::vector<amrfld_patch>& pt, in
     CouplingParams cp{};
     cp.T = nullptr;
     launch_assemble(s, D, B.K, nullptr, B.E, nullptr, B.rho, nullptr, 1.0, 1.0, c->o.robin_alpha, cp, kp,
-                    OuterBC{}, B.Cp, B.mask, B.diag, B.b);
+                    OuterBC{}, B.Cp, B.mask, B.diag, B.b, resident ? B.Ch : nullptr);
     LoopStats ls;
     ls.iters.assign(np, 0);
-    const FaceCoefs<double> Aop = face_coefs(c, B.Cp, B.K, B.mask, 1.0, 1.0, true);
-    const ScaledOp<double> Ah = scale_operator(c, s, D, Aop, B.Cp, B.diag, B.rs, B.Ch);
-    const SolveArrays A{Aop, B.diag, B.b, B.E, B.n_slots, Ah};
-    if (precision == AMRFLD_MIXED) {
-      pcg_mixed(c, D, P, P, A, tol, &ls);  // one plan for the batch's FP64 and FP32 sweeps
-    } else {
-      pcg_fp64(c, D, P, A, tol, &ls, hint);
-      hint = *std::max_element(ls.iters.begin(), ls.iters.end());
+    check(hipEventRecord(c->ev[1], s), "event");
+    if (resident) {
+      launch_copy_f64(s, B.E0, B.E, B.n_slots);
+      resident = run_resident(c, s, D, B.res.d, batch_resident_args(c, B, tol, c->sc));
+      if (resident) {
+        read_scalars(c, c->h_sc, c->sc, np);
+        // a launch that did not end: the step again in sweeps, from its first energies
+        bool ended = true;
+        for (const ResProblem& p : B.res_probs) ended = ended && c->h_sc[p.id].done;
+        if (!ended) {
+          reset_exchange(s, B.res.d);
+          launch_copy_f64(s, B.E, B.E0, B.n_slots);
+          resident = false;
+        }
+      }
     }
-    check(hipEventRecord(c->ev[2], s), "event");
-    if (c->o.true_residual && precision != AMRFLD_MIXED)
-      launch_true_residual(s, D, P, Ah, B.b, B.E, c->sc, c->partials);
-    launch_post_solve(s, D, P, B.E, B.rho, cp, 0.0, nullptr, c->sc, c->partials);
+    const SweepPlan P = resident ? B.big_plan() : B.plan();
+    if (P.G > 0) {
+      const FaceCoefs<double> Aop = face_coefs(c, B.Cp, B.K, B.mask, 1.0, 1.0, true);
+      const ScaledOp<double> Ah = scale_operator(c, s, D, Aop, B.Cp, B.diag, B.rs, B.Ch);
+      const SolveArrays A{Aop, B.diag, B.b, B.E, B.n_slots, Ah};
+      if (precision == AMRFLD_MIXED) {
+        pcg_mixed(c, D, P, P, A, tol, &ls);  // one plan for the batch's FP64 and FP32 sweeps
+      } else {
+        pcg_fp64(c, D, P, A, tol, &ls, hint);  // (counts the resident patches' records too)
+        hint = 0;
+        for (int q = 0; q < np; ++q)
+          if (!resident || !B.is_resident[q]) hint = std::max(hint, ls.iters[q]);
+      }
+      check(hipEventRecord(c->ev[2], s), "event");
+      if (c->o.true_residual && precision != AMRFLD_MIXED)
+        launch_true_residual(s, D, P, Ah, B.b, B.E, c->sc, c->partials);
+      launch_post_solve(s, D, P, B.E, B.rho, cp, 0.0, nullptr, c->sc, c->partials);
+    } else {
+      check(hipEventRecord(c->ev[2], s), "event");
+      for (int q = 0; q < np; ++q) ls.iters[q] = c->h_sc[q].iter;
+    }
     check(hipEventRecord(c->ev[3], s), "event");
     read_scalars(c, c->h_sc, c->sc, np);
     check(hipGetLastError(), "kernels");
@@ -2040,13 +2169,15 @@ amrfld_status solve_batch(amrfld_ctx* c, const std::vector<amrfld_patch>& pt, in
       st.dt = pt[q].dt;
       st.ms = ms;
       st.pcg_ms = pms;
-      st.n_timed = ls.n_timed;
-      st.sweep_ms = ls.sweep_ms;
+      if (!(resident && B.is_resident[q])) {  // the timed sweeps are those of the other patches
+        st.n_timed = ls.n_timed;
+        st.sweep_ms = ls.sweep_ms;
+      }
       st.spare_ms = 0.0;
       st.rnorm0 = h.rnorm0;
       st.bnorm = h.bnorm;
-      st.sweep_blocks = P.G;
-      st.launch_blocks = ls.persistent ? ls.launch_blocks : P.G;
+      st.sweep_blocks = P.G > 0 ? P.G : B.res.d.n_blocks;
+      st.launch_blocks = ls.persistent ? ls.launch_blocks : st.sweep_blocks;
       st.launch_mode = ls.persistent ? 1 : 0;
       st.status = h.nonfinite ? AMRFLD_E_NONFINITE : (h.converged ? AMRFLD_OK : AMRFLD_E_NOCONV);
       if (st.status != AMRFLD_OK && worst == AMRFLD_OK) {

@@ -105,6 +105,7 @@ struct DevLevel {
 // and scalars are per problem.
 struct SweepPlan {
   int n_prob = 1;
+  int n_active = 1;                   // problems that own blocks (the others are solved elsewhere)
   int G = 1;                          // total blocks
   int n_tiles = 0;                    // used when the arrays are null (one problem)
   int tpb_max = 1;                    // largest tile count of one block (sizes the LDS of the staged sweeps)
@@ -313,8 +314,9 @@ void launch_zero_u32(hipStream_t s, unsigned* p, int n);
 // reading or setting the scalars costs one small kernel instead of a copy engine
 // transfer.
 void launch_copy_scalars(hipStream_t s, const PcgScalars* src, PcgScalars* dst, int count, bool to_host);
+// blk0 (optional): a plan's block offsets; records of problems without blocks are left alone.
 void launch_init_scalars(hipStream_t s, PcgScalars* sc, int n, double tol, double abs_floor, int max_iter,
-                         int linf_test);
+                         int linf_test, const int32_t* blk0 = nullptr);
 // The same with the scaled operator, staged in LDS, for solves without couplings to
 // other levels.
 void launch_true_residual(hipStream_t s, const DevLevel& L, const SweepPlan& P, const ScaledOp<double>& Ah,

@@ -639,7 +639,7 @@ __device__ __forceinline__ void body_check(int prob, SweepPlan P, int it_last, P
   int b0, Gp;
   problem_blocks(P, prob, b0, Gp);
   PcgScalars* sc = scs + prob;
-  if (sc->done) return;
+  if (sc->done || Gp == 0) return;
   double red[4];
   const bool mx[4] = {false, false, false, true};
   reduce_partials_all<4>(part_of(part, P, it_last) + 4 * b0, Gp, mx, red, lds);
@@ -702,6 +702,7 @@ __device__ __forceinline__ void body_finish(int prob, SweepPlan P, int kind, con
   int b0, Gp;
   problem_blocks(P, prob, b0, Gp);
   PcgScalars* sc = scs + prob;
+  if (Gp == 0) return;  // solved elsewhere
   double v[1];
   const bool mx[1] = {kind == 1};
   reduce_partials_all<1>(part + b0, Gp, mx, v, lds);
@@ -780,7 +781,7 @@ __device__ __forceinline__ void body_ir_finish(int prob, SweepPlan P, int first,
   problem_blocks(P, prob, b0, Gp);
   PcgScalars* out = outs + prob;
   PcgScalars* in = ins + prob;
-  if (out->done) {
+  if (out->done || Gp == 0) {
     if (threadIdx.x == 0) {
       in->done = 1;
       in->iter = 0;
@@ -971,7 +972,7 @@ __global__ __launch_bounds__(kBlock) void k_pcg_persistent(DevLevel L, SweepPlan
     }
     if (threadIdx.x == 0) n_done = __hip_atomic_load(P.done_count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
-    if (n_done >= unsigned(P.n_prob)) break;
+    if (n_done >= unsigned(P.n_active)) break;
   }
 }
 
@@ -1019,7 +1020,7 @@ __global__ __launch_bounds__(kBlock) void k_mixed_persistent(DevLevel L, SweepPl
     if (blockIdx.x == 0 && threadIdx.x == 0)
       __hip_atomic_store(inner_done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (!sync()) return;
-    if (read_count(outer_done) >= unsigned(P.n_prob)) break;
+    if (read_count(outer_done) >= unsigned(P.n_active)) break;
     for (int vb = int(blockIdx.x); vb < P32.G; vb += int(nb))
       body_inner_init(vb, L, P32, M.Ah32, M.r32, M.d32, M.v32, M.outer, M.inner, M.part);
     if (!sync()) return;
@@ -1028,7 +1029,7 @@ __global__ __launch_bounds__(kBlock) void k_mixed_persistent(DevLevel L, SweepPl
         body_cg_sweep<float>(vb, L, P32, it, M.Ah32, M.v32, M.d32, M.inner, M.part);
       if (!sync()) return;
       // stops are counted only at the sweep heads (see k_pcg_persistent)
-      if (read_count(inner_done) >= unsigned(P32.n_prob)) break;
+      if (read_count(inner_done) >= unsigned(P32.n_active)) break;
     }
   }
   // the last refinement sweep wrote x_cur: make it the caller's iterate
@@ -1039,9 +1040,9 @@ __global__ __launch_bounds__(kBlock) void k_mixed_persistent(DevLevel L, SweepPl
 }
 
 __global__ __launch_bounds__(kBlock) void k_init_scalars(PcgScalars* sc, int n, double tol, double abs_floor,
-                                                         int max_iter, int linf_test) {
+                                                         int max_iter, int linf_test, const int32_t* blk0) {
   const int i = int(blockIdx.x * kBlock + threadIdx.x);
-  if (i >= n) return;
+  if (i >= n || (blk0 && blk0[i + 1] == blk0[i])) return;
   PcgScalars z{};
   z.tol = tol;
   z.abs_floor = abs_floor;
@@ -1164,9 +1165,9 @@ void launch_inner_init(hipStream_t s, const DevLevel& L, const SweepPlan& P, con
 }
 
 void launch_init_scalars(hipStream_t s, PcgScalars* sc, int n, double tol, double abs_floor, int max_iter,
-                         int linf_test) {
+                         int linf_test, const int32_t* blk0) {
   hipLaunchKernelGGL(k_init_scalars, dim3((n + kBlock - 1) / kBlock), dim3(kBlock), 0, s, sc, n, tol, abs_floor,
-                     max_iter, linf_test);
+                     max_iter, linf_test, blk0);
 }
 
 void launch_copy_scalars(hipStream_t s, const PcgScalars* src, PcgScalars* dst, int count, bool to_host) {

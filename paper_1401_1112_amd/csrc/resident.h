@@ -14,6 +14,8 @@ constexpr int kResMaxSlots = 10 * kResThreads;  // of one share
 constexpr int kResTargetSlots = 1024;  // of one share where the level has several
 // polls of a wait before a block gives up (about a microsecond each)
 constexpr unsigned kResSpinLimit = 1u << 18;
+// of a batch, where a block may wait for others to come to a patch from their earlier ones
+constexpr unsigned kResSpinLimitBatch = 1u << 22;
 constexpr int kResWords = 7;  // a share's partial sums: words of 48 bits and a 16-bit stamp
 constexpr int kResLine = 8;   // words of the line they lie in
 

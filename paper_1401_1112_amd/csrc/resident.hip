@@ -785,6 +785,30 @@ __global__ __launch_bounds__(kResThreads) void k_cg_resident(DevLevel L, ResPlan
   }
 }
 
+// Shares of several sizes in one launch: each runs with as many pairs per thread as it
+// needs (a small share in the loops of a large one would mostly iterate over nothing).
+__global__ __launch_bounds__(kResThreads) void k_cg_resident_batch(DevLevel L, ResPlanDev R, ResArgs A) {
+  extern __shared__ __align__(16) unsigned char res_lds[];
+  __shared__ Shared S;
+  const int b = int(blockIdx.x);
+  for (int k = R.task0[b]; k < R.task0[b + 1]; ++k) {
+    const int part = R.task[k];
+    bool ok;
+    switch ((R.parts[part].n_slots + 2 * kResThreads - 1) / (2 * kResThreads)) {
+      case 1: ok = solve_part<1>(L, R, A, part, res_lds, S); break;
+      case 2: ok = solve_part<2>(L, R, A, part, res_lds, S); break;
+      case 3: ok = solve_part<3>(L, R, A, part, res_lds, S); break;
+      case 4: ok = solve_part<4>(L, R, A, part, res_lds, S); break;
+      default: ok = solve_part<5>(L, R, A, part, res_lds, S);
+    }
+    if (!ok) {
+      if (threadIdx.x == 0) st_word32(R.epoch + 2 * R.n_prob, 1u);
+      return;
+    }
+    __syncthreads();
+  }
+}
+
 constexpr size_t kLdsLimit = 160 * 1024 - sizeof(Shared) - 256;
 
 size_t dyn_lds(const ResPlanDev& R, int NP) {
@@ -812,6 +836,14 @@ bool resident_fits(const ResPlanDev& R) {
 }
 
 hipError_t launch_resident(hipStream_t s, const DevLevel& L, const ResPlanDev& R, const ResArgs& A) {
+  if (R.n_prob > 1) {
+    const size_t lds = dyn_lds(R, pairs_of(R));
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_cg_resident_batch),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_cg_resident_batch, dim3(R.n_blocks), dim3(kResThreads), lds, s, L, R, A);
+    return hipGetLastError();
+  }
   switch (pairs_of(R)) {
     case 1: return launch_np<1>(s, L, R, A);
     case 2: return launch_np<2>(s, L, R, A);

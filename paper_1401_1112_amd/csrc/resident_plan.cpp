@@ -13,6 +13,10 @@ int res_group(int64_t n_oct, int max_blocks, int max_slots, int target_slots) {
   return int(std::min<int64_t>(g, n_oct));
 }
 
+double res_cost(int n_slots, int group) {
+  return 0.6 + 0.0005 * n_slots + (group > 1 ? 2.5 + 0.012 * group : 0.0);
+}
+
 ResPlanHost build_res_plan(const std::vector<ResProblem>& probs, const std::vector<int>& group, int n_blocks,
                            const int32_t* nbr, int64_t n_oct_table) {
   ResPlanHost h;
@@ -25,7 +29,7 @@ ResPlanHost build_res_plan(const std::vector<ResProblem>& probs, const std::vect
       ResPart p{};
       p.slot0 = int(8 * o0);
       p.n_slots = int(8 * (o1 - o0));
-      p.prob = int(q);
+      p.prob = probs[q].id;
       p.part0 = p0;
       p.group = g;
       for (int64_t o = o0; o < o1; ++o) part_of[o] = int32_t(h.parts.size());
@@ -74,19 +78,22 @@ ResPlanHost build_res_plan(const std::vector<ResProblem>& probs, const std::vect
   // its shares in the order of the problems, so the first unfinished problem always has
   // all its blocks on it: no block waits for one that waits for it.
   std::vector<std::vector<int32_t>> list(n_blocks);
-  std::vector<std::pair<int64_t, int>> load(n_blocks);  // (slots, block)
-  for (int b = 0; b < n_blocks; ++b) load[b] = {0, b};
+  std::vector<std::pair<double, int>> load(n_blocks);  // (time, block)
+  for (int b = 0; b < n_blocks; ++b) load[b] = {0.0, b};
   for (size_t q = 0, at = 0; q < probs.size(); at += size_t(group[q]), ++q) {
     const int g = group[q];
     std::partial_sort(load.begin(), load.begin() + g, load.end());
     // blocks are dealt to the XCDs round-robin: neighbouring shares on the same XCD
     if (probs.size() == 1 && g % 8 == 0)
-      std::sort(load.begin(), load.begin() + g, [](const std::pair<int64_t, int>& a, const std::pair<int64_t, int>& b) {
+      std::sort(load.begin(), load.begin() + g, [](const std::pair<double, int>& a, const std::pair<double, int>& b) {
         return std::make_pair(a.second % 8, a.second) < std::make_pair(b.second % 8, b.second);
       });
+    double end = 0.0;  // the problem begins when the last of its blocks is free
+    for (int r = 0; r < g; ++r) end = std::max(end, load[r].first);
+    end += res_cost(h.parts[at].n_slots, g);
     for (int r = 0; r < g; ++r) {
       list[load[r].second].push_back(int32_t(at + r));
-      load[r].first += h.parts[at + r].n_slots;
+      load[r].first = end;
     }
   }
   h.task0.assign(1, 0);

@@ -37,9 +37,10 @@ struct ResPlanHost {
   int max_slots = 0, max_units = 0;  // of one share
 };
 
-// A problem's octs: [oct0, oct0 + n_oct) of the neighbour table.
+// A problem's octs: [oct0, oct0 + n_oct) of the neighbour table; id: its scalar record.
 struct ResProblem {
   int64_t oct0 = 0, n_oct = 0;
+  int id = 0;
 };
 
 // Shares of a problem of n_oct octs: one where it fits a block (max_slots), else about
@@ -49,6 +50,9 @@ struct ResProblem {
 // grows slowly with the blocks: 16 k slots take 5.9, 4.9, 4.3 and 4.4 us in 4, 8, 16 and
 // 32 blocks, 88 k slots 5.6, 5.2 and 5.4 us in 48, 88 and 176.
 int res_group(int64_t n_oct, int max_blocks, int max_slots, int target_slots);
+
+// About what an iteration of a share of n_slots slots takes in a group (us).
+double res_cost(int n_slots, int group);
 
 // Plans problems (listed in the order the blocks work on them) on n_blocks blocks;
 // group[q] shares of problem q, all on different blocks.  nbr: 6 per oct, as in

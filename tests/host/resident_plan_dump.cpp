@@ -21,6 +21,7 @@ int main(int argc, char** argv) {
     if (std::fread(v, 8, 2, f) != 2) return 2;
     p.oct0 = v[0];
     p.n_oct = v[1];
+    p.id = int(&p - probs.data());
     group.push_back(amrfld::res_group(p.n_oct, head[1], head[2], head[2]));
   }
   int64_t rows = 0;
