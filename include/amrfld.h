@@ -69,7 +69,9 @@ typedef enum { AMRFLD_BC_DIRICHLET = 0, AMRFLD_BC_NEUMANN = 1, AMRFLD_BC_ROBIN =
  * b - A x and applies the solution update in FP64 and decides the stop with the
  * rule of Sect. 3.3.4 on that residual.  Between two refinement sweeps the FP32 CG
  * reduces its residual by inner_tol; after each sweep it continues from the new
- * residual with its search direction kept (residual replacement). */
+ * residual with its search direction kept (residual replacement).  Levels and patches that
+ * are solved resident on the chip (see amrfld_solve_level) keep the refinement and its
+ * stopping rule, with an inner CG in FP64. */
 typedef enum { AMRFLD_FP64 = 0, AMRFLD_MIXED = 1 } amrfld_precision;
 typedef enum { AMRFLD_K_CONST = 0, AMRFLD_K_LP = 1, AMRFLD_K_MINERBO = 2, AMRFLD_K_POWER = 3 } amrfld_kmode;
 
@@ -189,10 +191,10 @@ amrfld_status amrfld_set_coeffs(amrfld_ctx* c, int level, const double* rho, con
  * Robin mode (eq. mean_flux) and clear this level's register.  With a
  * temperature the coupling term is included and T is updated.
  * Returns AMRFLD_E_NOCONV if max_iter was reached.
- * An FP64 solve whose level fits the device's registers and LDS (about 1.3 million
- * slots) runs in one launch that keeps the whole CG state on the chip, whatever
- * max_blocks, form_coefs and persistent say (stats: sweep_blocks = launch_blocks = its
- * blocks, launch_mode as asked for); the other levels run in sweeps.  Should that launch
+ * A solve whose level fits the device's registers and LDS (about 1.3 million slots) runs
+ * resident: one launch that keeps the whole CG state on the chip, whatever max_blocks,
+ * form_coefs, persistent and inner_tol say (stats: launch_blocks = its blocks,
+ * launch_mode as asked for); the other levels run in sweeps.  Should that launch
  * not end because its blocks do not reach the device together, the solve is repeated in
  * sweeps. */
 amrfld_status amrfld_solve_level(amrfld_ctx* c, int level, double dt, int bc_mode, double tol);

@@ -986,13 +986,22 @@ void pcg_mixed(amrfld_ctx* c, const DevLevel& D, const SweepPlan& P, const Sweep
     for (int q = 0; q < np && expect_stop; ++q)
       expect_stop = c->h_sc[q].done || c->h_sc[np + q].rnorm <= 0.5 * c->h_sc[q].thresh;
   }
-  if (x_cur != A.x) launch_copy_f64(s, A.x, x_cur, A.n);
+  if (x_cur != A.x) launch_copy_plan(s, P, int(A.n), A.x, x_cur);
 }
 
-// FP64 solves of levels whose state fits the device's registers and LDS run resident;
-// the other forms (mixed precision, larger levels) in sweeps.
-bool use_resident(const amrfld_ctx* c, const LevelState& L) {
-  return c->o.precision == AMRFLD_FP64 && resident_fits(L.res.d);
+// Solves of levels whose state fits the device's registers and LDS run resident, the
+// others in sweeps.  The mixed form runs there with its refinement but an FP64 inner CG:
+// FP32 halves the bytes of a sweep, and a resident iteration reads none.
+bool use_resident(const LevelState& L) { return resident_fits(L.res.d); }
+
+// Launches that may resume a refined solve after its first one.
+int resident_resumes(const amrfld_ctx* c, int precision) {
+  if (precision != AMRFLD_MIXED) return 0;
+  return std::min(kResResumes, (c->o.max_outer > 0 ? c->o.max_outer : 30) - 1);
+}
+
+bool resume_wanted(const amrfld_ctx* c, const PcgScalars& h) {
+  return h.done && !h.converged && !h.nonfinite && h.inner_total < c->o.max_iter;
 }
 
 ResArgs resident_args(const amrfld_ctx* c, const LevelState& L, double dt, double tol, PcgScalars* sc) {
@@ -1007,8 +1016,9 @@ ResArgs resident_args(const amrfld_ctx* c, const LevelState& L, double dt, doubl
   a.abs_floor = c->o.abs_floor;
   a.max_iter = c->o.max_iter;
   a.linf_test = c->o.linf_test;
-  a.true_residual = c->o.true_residual;
-  a.cp = cparams(c, L);
+  a.refine = c->o.precision == AMRFLD_MIXED;
+  a.true_residual = c->o.true_residual || a.refine;
+  if (!a.refine) a.cp = cparams(c, L);  // (a refined solve's T is updated after its last launch)
   a.rho = L.rho;
   a.T_out = L.T;
   a.dt = dt;
@@ -1062,7 +1072,7 @@ amrfld_status solve_one(amrfld_ctx* c, int level, double dt, int mode, double to
   launch_cell_K(s, D, L.E, L.rho, Lc ? Lc->E : nullptr, kparams(L), outer_bc(c), L.K);
   const double w = mode == AMRFLD_BC_DIRICHLET ? 1.0 : mode == AMRFLD_BC_NEUMANN ? 0.0 : c->o.robin_alpha;
   const CouplingParams cp = cparams(c, L);
-  double* Cm = use_resident(c, L) ? L.Ch : nullptr;  // the sweeps' scaled operator is not formed then
+  double* Cm = use_resident(L) ? L.Ch : nullptr;  // the sweeps' scaled operator is not formed then
   launch_assemble(s, D, L.K, Lc ? Lc->K : nullptr, L.E, Lc ? Lc->E : nullptr, L.rho, L.reg, dt, w,
                   c->o.robin_alpha, cp, kparams(L), outer_bc(c), L.Cp, L.mask, L.diag, L.b, Cm);
   const double scale = dt / (D.dx * D.dx);
@@ -1076,11 +1086,21 @@ amrfld_status solve_one(amrfld_ctx* c, int level, double dt, int mode, double to
   ls.iters.assign(1, 0);
   const bool registers = Lc && (mode == AMRFLD_BC_NEUMANN || mode == AMRFLD_BC_ROBIN);
   double* reg_c = registers ? ensure_reg(c, *Lc) : nullptr;
-  bool resident = use_resident(c, L);
+  bool resident = use_resident(L);
   if (resident) {
     check(hipEventRecord(c->ev[1], s), "event");
-    if (run_resident(c, s, D, L.res.d, resident_args(c, L, dt, tol, c->sc))) {
+    ResArgs ra = resident_args(c, L, dt, tol, c->sc);
+    if (run_resident(c, s, D, L.res.d, ra)) {
+      if (ra.refine) {
+        read_scalars(c, c->h_sc, c->sc, 1);
+        ra.resume = 1;
+        for (int k = resident_resumes(c, c->o.precision); k > 0 && resume_wanted(c, *c->h_sc); --k) {
+          if (!run_resident(c, s, D, L.res.d, ra)) break;
+          read_scalars(c, c->h_sc, c->sc, 1);
+        }
+      }
       check(hipEventRecord(c->ev[2], s), "event");
+      if (ra.refine && cp.T) launch_post_solve(s, D, P, L.E, L.rho, cp, dt, L.T, c->sc, c->partials);
       if (registers)
         launch_flux_register(s, D, L.K, Lc->K, L.E, Lc->E, dt, reg_c, int(Lc->t.n_slots()), &c->sc->done);
       if (L.reg) launch_fill(s, L.reg, 6 * L.t.n_slots(), 0.0);
@@ -1091,7 +1111,7 @@ amrfld_status solve_one(amrfld_ctx* c, int level, double dt, int mode, double to
       ls.persistent = c->o.persistent != 0;
       ls.launch_blocks = L.res.d.n_blocks;
       if (c->o.time_sweeps > 0) {
-        ls.n_timed = c->h_sc->iter;
+        ls.n_timed = c->o.precision == AMRFLD_MIXED ? c->h_sc->inner_total : c->h_sc->iter;
         ls.sweep_ms = c->h_sc->loop_ms;
       }
     } else {
@@ -1140,7 +1160,7 @@ amrfld_status solve_one(amrfld_ctx* c, int level, double dt, int mode, double to
   st.dt = dt;
   st.rnorm0 = h.rnorm0;
   st.bnorm = h.bnorm;
-  st.sweep_blocks = resident ? L.res.d.n_parts : P.G;
+  st.sweep_blocks = P.G;
   st.launch_blocks = resident || ls.persistent ? ls.launch_blocks : P.G;
   st.launch_mode = ls.persistent ? 1 : 0;
   float ms = 0.f, pms = 0.f;
@@ -1198,7 +1218,7 @@ hipError_t record_solve(amrfld_ctx* c, hipStream_t st, int level, double dt, int
   launch_cell_K(st, D, L.E, L.rho, Lc ? Lc->E : nullptr, kparams(L), outer_bc(c), L.K);
   const double w = mode == AMRFLD_BC_DIRICHLET ? 1.0 : mode == AMRFLD_BC_NEUMANN ? 0.0 : c->o.robin_alpha;
   const CouplingParams cp = cparams(c, L);
-  double* Cm = use_resident(c, L) ? L.Ch : nullptr;  // the sweeps' scaled operator is not formed then
+  double* Cm = use_resident(L) ? L.Ch : nullptr;  // the sweeps' scaled operator is not formed then
   launch_assemble(st, D, L.K, Lc ? Lc->K : nullptr, L.E, Lc ? Lc->E : nullptr, L.rho, L.reg, dt, w,
                   c->o.robin_alpha, cp, kparams(L), outer_bc(c), L.Cp, L.mask, L.diag, L.b, Cm);
   const double scale = dt / (D.dx * D.dx);
@@ -1206,9 +1226,15 @@ hipError_t record_solve(amrfld_ctx* c, hipStream_t st, int level, double dt, int
     launch_theta_step(st, D, c->o.theta, L.E, face_coefs(c, L.Cp, L.K, L.mask, scale, 1.0, false), L.Cp, L.diag,
                       L.b, Cm);
   const bool registers = Lc && (mode == AMRFLD_BC_NEUMANN || mode == AMRFLD_BC_ROBIN);
-  if (use_resident(c, L)) {
-    const hipError_t e = launch_resident(st, D, L.res.d, resident_args(c, L, dt, tol, sc));
+  if (use_resident(L)) {
+    ResArgs ra = resident_args(c, L, dt, tol, sc);
+    hipError_t e = launch_resident(st, D, L.res.d, ra);
+    ra.resume = 1;
+    for (int k = resident_resumes(c, c->o.precision); k > 0 && e == hipSuccess; --k)
+      e = launch_resident(st, D, L.res.d, ra);
     if (e != hipSuccess) return e;
+    if (ra.refine && cp.T)
+      launch_post_solve(st, D, level_plan(c, tiles_of(D.n_slots)), L.E, L.rho, cp, dt, L.T, sc, c->partials);
     if (registers) launch_flux_register(st, D, L.K, Lc->K, L.E, Lc->E, dt, Lc->reg, int(Lc->t.n_slots()), &sc->done);
     if (L.reg) launch_fill(st, L.reg, 6 * L.t.n_slots(), 0.0);
     return hipGetLastError();
@@ -1333,7 +1359,7 @@ amrfld_status advance_graph(amrfld_ctx* c, double dt_coarse, int mode, double to
     const LevelState& L = c->L(sched[k].level);
     const int nt = tiles_of(L.t.n_slots());
     const SweepPlan P = level_plan(c, nt);
-    const bool resident = use_resident(c, L);
+    const bool resident = use_resident(L);
     if (resident && !h.done) {
       aborted = 1;
       reset_exchange(us, L.res.d);
@@ -1353,7 +1379,7 @@ amrfld_status advance_graph(amrfld_ctx* c, double dt_coarse, int mode, double to
     st.pcg_ms = -1.0;
     st.rnorm0 = h.rnorm0;
     st.bnorm = h.bnorm;
-    st.sweep_blocks = resident ? L.res.d.n_parts : P.G;
+    st.sweep_blocks = P.G;
     st.launch_blocks = resident ? L.res.d.n_blocks
                        : mixed  ? mixed_persistent_blocks(P, level_plan(c, nt, kMaxTilesPerBlock32),
                                                           c->o.persistent_per_cu)
@@ -1625,6 +1651,8 @@ amrfld_status solve_composite(amrfld_ctx* c, double dt, double tol) {
     a.b = C.b;
     a.x = C.x;
     a.cp.T = nullptr;  // the post-solve below updates T
+    a.refine = 0;      // FP64 whatever the precision option says
+    a.true_residual = c->o.true_residual;
     check(hipEventRecord(c->ev[1], s), "event");
     if (run_resident(c, s, D, R, a)) {
       read_scalars(c, c->h_sc, c->sc, 1);
@@ -1677,7 +1705,8 @@ amrfld_status solve_composite(amrfld_ctx* c, double dt, double tol) {
   st.dt = dt;
   st.rnorm0 = h.rnorm0;
   st.bnorm = h.bnorm;
-  st.sweep_blocks = st.launch_blocks = resident ? c->L(base).res.d.n_blocks : P.G;
+  st.sweep_blocks = P.G;
+  st.launch_blocks = resident ? c->L(base).res.d.n_blocks : P.G;
   float ms = 0.f, pms = 0.f;
   check(hipEventSynchronize(c->ev[3]), "event");  // passed already: the scalars were read after it
   check(hipEventElapsedTime(&ms, c->ev[0], c->ev[3]), "event");
@@ -1875,12 +1904,7 @@ void build_batch_into(amrfld_ctx* c, BatchState* B, const std::vector<int>& size
   check(hipStreamSynchronize(c->stream()), "batch tables");
 }
 
-// Patches of a step that are solved resident in this precision.
-bool batch_resident(const BatchState& B, int precision) {
-  return B.res.d.parts && precision == AMRFLD_FP64;
-}
-
-ResArgs batch_resident_args(const amrfld_ctx* c, const BatchState& B, double tol, PcgScalars* sc) {
+ResArgs batch_resident_args(const amrfld_ctx* c, const BatchState& B, double tol, int precision, PcgScalars* sc) {
   ResArgs a;
   a.Cp = B.Cp;
   a.Cm = B.Ch;
@@ -1892,7 +1916,8 @@ ResArgs batch_resident_args(const amrfld_ctx* c, const BatchState& B, double tol
   a.abs_floor = c->o.abs_floor;
   a.max_iter = c->o.max_iter;
   a.linf_test = c->o.linf_test;
-  a.true_residual = c->o.true_residual;
+  a.refine = precision == AMRFLD_MIXED;
+  a.true_residual = c->o.true_residual || a.refine;
   a.spin_limit = kResSpinLimitBatch;
   return a;
 }
@@ -1905,7 +1930,7 @@ amrfld_status solve_batch_persistent(amrfld_ctx* c, const std::vector<amrfld_pat
   BatchState& B = *c->batch;
   const int np = B.n_prob;
   const DevLevel D = B.dev();
-  const bool resident = batch_resident(B, precision);
+  const bool resident = B.res.d.parts != nullptr;
   SweepPlan P = resident ? B.big_plan() : B.plan();
   if (!c->bar) c->bar = dalloc<unsigned>(kBarWords, "barrier");
   P.done_count = c->bar + kBarDone;
@@ -1933,7 +1958,11 @@ amrfld_status solve_batch_persistent(amrfld_ctx* c, const std::vector<amrfld_pat
       launch_assemble(st, D, B.K, nullptr, B.E, nullptr, B.rho, nullptr, 1.0, 1.0, c->o.robin_alpha, cp, kp,
                       OuterBC{}, B.Cp, B.mask, B.diag, B.b, resident ? B.Ch : nullptr);
       if (resident) {
-        const hipError_t e = launch_resident(st, D, B.res.d, batch_resident_args(c, B, tol, sc));
+        ResArgs ra = batch_resident_args(c, B, tol, precision, sc);
+        hipError_t e = launch_resident(st, D, B.res.d, ra);
+        ra.resume = 1;
+        for (int k = resident_resumes(c, precision); k > 0 && e == hipSuccess; --k)
+          e = launch_resident(st, D, B.res.d, ra);
         if (e != hipSuccess) return e;
         if (P.G == 0) continue;
       }
@@ -2088,7 +2117,7 @@ amrfld_status solve_batch(amrfld_ctx* c, const std::vector<amrfld_patch>& pt, in
     c->stats.clear();  // the device cannot run it: poll instead
   }
   ensure_scalars(c, np);
-  bool resident = batch_resident(B, precision);
+  bool resident = B.res.d.parts != nullptr;
   // the batch's precision for this call only, restored on every way out
   struct PrecisionScope {
     amrfld_opts& o;
@@ -2112,9 +2141,20 @@ amrfld_status solve_batch(amrfld_ctx* c, const std::vector<amrfld_patch>& pt, in
     check(hipEventRecord(c->ev[1], s), "event");
     if (resident) {
       launch_copy_f64(s, B.E0, B.E, B.n_slots);
-      resident = run_resident(c, s, D, B.res.d, batch_resident_args(c, B, tol, c->sc));
+      ResArgs ra = batch_resident_args(c, B, tol, precision, c->sc);
+      resident = run_resident(c, s, D, B.res.d, ra);
       if (resident) {
         read_scalars(c, c->h_sc, c->sc, np);
+        ra.resume = 1;
+        auto wanted = [&] {
+          for (const ResProblem& p : B.res_probs)
+            if (resume_wanted(c, c->h_sc[p.id])) return true;
+          return false;
+        };
+        for (int k = resident_resumes(c, precision); k > 0 && wanted(); --k) {
+          if (!run_resident(c, s, D, B.res.d, ra)) break;
+          read_scalars(c, c->h_sc, c->sc, np);
+        }
         // a launch that did not end: the step again in sweeps, from its first energies
         bool ended = true;
         for (const ResProblem& p : B.res_probs) ended = ended && c->h_sc[p.id].done;

@@ -342,6 +342,8 @@ void launch_ir_sweep(hipStream_t s, const DevLevel& L, const SweepPlan& P, const
                      const PcgScalars* inner, double* part);
 void launch_ir_finish(hipStream_t s, const SweepPlan& P, int first, double inner_tol, int max_outer,
                       PcgScalars* outer, PcgScalars* inner, const double* part);
+// dst[i] = src[i] for the slots of every block of the plan (of n_slots in all).
+void launch_copy_plan(hipStream_t s, const SweepPlan& P, int n_slots, double* dst, const double* src);
 // Arrays and parameters of the whole mixed-precision solve in one persistent launch.
 struct MixedArgs {
   ScaledOp<double> Ah;  // FP64 scaled operator of the refinement sweeps

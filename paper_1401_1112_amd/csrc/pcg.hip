@@ -844,6 +844,13 @@ __device__ __forceinline__ void body_ir_finish(int prob, SweepPlan P, int first,
   in->counted = 0;
 }
 
+__device__ __forceinline__ void body_copy_plan(int vb, const SweepPlan& P, int n_slots, double* dst,
+                                               const double* src) {
+  const BlockPlan bp = block_plan(P, vb);
+  const int s1 = min(bp.t1 * kBlock, n_slots);
+  for (int i = bp.t0 * kBlock + int(threadIdx.x); i < s1; i += kBlock) dst[i] = src[i];
+}
+
 // ------------------------------------------------------------ kernels
 template <typename T>
 __global__ __launch_bounds__(kBlock) void k_cg_start_r(DevLevel L, SweepPlan P, ScaledOp<T> Ah,
@@ -1034,9 +1041,13 @@ __global__ __launch_bounds__(kBlock) void k_mixed_persistent(DevLevel L, SweepPl
   }
   // the last refinement sweep wrote x_cur: make it the caller's iterate
   if (x_cur != M.x) {
-    for (int i = int(blockIdx.x) * kBlock + int(threadIdx.x); i < L.n_slots; i += int(nb) * kBlock)
-      M.x[i] = x_cur[i];
+    for (int vb = int(blockIdx.x); vb < P.G; vb += int(nb)) body_copy_plan(vb, P, L.n_slots, M.x, x_cur);
   }
+}
+
+__global__ __launch_bounds__(kBlock) void k_copy_plan(SweepPlan P, int n_slots, double* __restrict__ dst,
+                                                      const double* __restrict__ src) {
+  body_copy_plan(int(blockIdx.x), P, n_slots, dst, src);
 }
 
 __global__ __launch_bounds__(kBlock) void k_init_scalars(PcgScalars* sc, int n, double tol, double abs_floor,
@@ -1105,6 +1116,10 @@ void launch_cg_sweep(hipStream_t s, const DevLevel& L, const SweepPlan& P, int i
                           sc, part);
   else
     hipLaunchKernelGGL(k_cg_sweep<T>, dim3(P.G), dim3(kBlock), lds, s, L, P, it, Ah, v, x, sc, part);
+}
+
+void launch_copy_plan(hipStream_t s, const SweepPlan& P, int n_slots, double* dst, const double* src) {
+  hipLaunchKernelGGL(k_copy_plan, dim3(P.G), dim3(kBlock), 0, s, P, n_slots, dst, src);
 }
 
 int interface_blocks(const DevLevel& L) { return std::max(1, (L.n_if_rows + kBlock - 1) / kBlock); }

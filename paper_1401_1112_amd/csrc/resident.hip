@@ -503,7 +503,7 @@ __device__ __forceinline__ bool cg_loop(Exchange& X, Regs<T, NP>& q, const Lds<T
   }
 }
 
-// The FP64 solve of one share of one problem.  false: a wait timed out.
+// The solve of one share of one problem.  false: a wait timed out.
 template <int NP>
 __device__ __forceinline__ bool solve_part(const DevLevel& L, const ResPlanDev& R, const ResArgs& A, int my_part,
                                            unsigned char* dyn, Shared& S) {
@@ -517,6 +517,10 @@ __device__ __forceinline__ bool solve_part(const DevLevel& L, const ResPlanDev& 
   lds.rh = lds.d + kCap;
   lds.ex = lds.rh + nh;
   lds.partner = reinterpret_cast<int*>(lds.ex + nh);
+  if (A.resume) {  // nothing left to do: decided by an earlier launch, alike for every share
+    const PcgScalars& o = A.sc[me.prob];
+    if (o.converged || o.nonfinite || o.inner_total >= A.max_iter) return true;
+  }
   const unsigned epoch0 = R.epoch[me.prob];
   Exchange X{R, me, my_part, epoch0, A.spin_limit};
   for (int u = tid(); u < me.n_units; u += kResThreads) lds.partner[u] = R.partner[me.unit0 + u];
@@ -673,17 +677,22 @@ __device__ __forceinline__ bool solve_part(const DevLevel& L, const ResPlanDev& 
   take_halo(lds.rh);
   take_halo(lds.p + kCap);
   __syncthreads();
-  const double rnorm0 = sqrt(v[0]), bnorm = sqrt(v[1]);
-  const double floor_b = A.abs_floor * bnorm, thresh = fmax(A.tol * rnorm0, floor_b);
+  // (a resumed solve keeps the norms and the threshold of its first launch)
+  const double start2 = v[0];
+  const double rnorm0 = A.resume ? A.sc[me.prob].rnorm0 : sqrt(v[0]), bnorm = sqrt(v[1]);
+  const double floor_b = A.abs_floor * bnorm, thresh = A.resume ? A.sc[me.prob].thresh : fmax(A.tol * rnorm0, floor_b);
+  const int before = A.resume ? A.sc[me.prob].inner_total : 0;
   CgResult res;
-  res.rn = rnorm0;
+  res.rn = sqrt(start2);
   res.linf = 0.0;
   res.iters = 0;
-  res.fin = isfinite(rnorm0) && isfinite(bnorm);
-  res.conv = res.fin && rnorm0 <= floor_b;
+  res.fin = isfinite(start2) && isfinite(bnorm);
+  res.conv = res.fin && res.rn <= floor_b;
   const long long clk0 = wall_clock64();
+  // (a refined solve aims a little below the threshold, so that the true residual, which
+  // differs from the recursive one by rounding, is below it at the first check)
   if (res.fin && !res.conv &&
-      !cg_loop(X, q, lds, S, thresh, A.tol, A.max_iter, A.linf_test != 0, dmin, res))
+      !cg_loop(X, q, lds, S, A.refine ? 0.9 * thresh : thresh, A.tol, A.max_iter - before, A.linf_test != 0, dmin, res))
     return false;
   const long long clk1 = wall_clock64();
 
@@ -750,6 +759,13 @@ __device__ __forceinline__ bool solve_part(const DevLevel& L, const ResPlanDev& 
   if (threadIdx.x == 0) {
     R.epoch[me.prob] = X.epoch;
     PcgScalars z{};
+    const int outer = A.resume ? A.sc[me.prob].iter : 0;
+    if (A.refine && res.iters > 0) {
+      // the stop is decided on the true residual; a start at the floor needed no sweep
+      res.rn = sqrt(v[0]);
+      res.fin = res.fin && isfinite(res.rn);
+      res.conv = res.fin && ((res.rn <= thresh && (!A.linf_test || res.linf < A.tol)) || res.rn == 0.0);
+    }
     z.rnorm0 = rnorm0;
     z.bnorm = bnorm;
     z.thresh = thresh;
@@ -759,7 +775,8 @@ __device__ __forceinline__ bool solve_part(const DevLevel& L, const ResPlanDev& 
     z.linf = res.linf;
     z.true_rnorm = sqrt(v[0]);
     z.min_E = -m;
-    z.iter = res.iters;
+    z.iter = A.refine ? outer + (res.iters > 0 ? 1 : 0) : res.iters;
+    z.inner_total = A.refine ? before + res.iters : 0;
     z.done = 1;
     z.converged = res.conv ? 1 : 0;
     z.nonfinite = res.fin ? 0 : 1;
@@ -819,13 +836,13 @@ size_t dyn_lds(const ResPlanDev& R, int NP) {
 // Pairs of slots per thread.
 int pairs_of(const ResPlanDev& R) { return (R.max_slots + 2 * kResThreads - 1) / (2 * kResThreads); }
 
-template <int NP>
-hipError_t launch_np(hipStream_t s, const DevLevel& L, const ResPlanDev& R, const ResArgs& A) {
-  const size_t lds = dyn_lds(R, NP);
-  const void* f = reinterpret_cast<const void*>(&k_cg_resident<NP>);
-  const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
+hipError_t launch_kernel(void (*f)(DevLevel, ResPlanDev, ResArgs), hipStream_t s, const DevLevel& L,
+                         const ResPlanDev& R, const ResArgs& A) {
+  const size_t lds = dyn_lds(R, pairs_of(R));
+  const hipError_t e =
+      hipFuncSetAttribute(reinterpret_cast<const void*>(f), hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_cg_resident<NP>, dim3(R.n_blocks), dim3(kResThreads), lds, s, L, R, A);
+  hipLaunchKernelGGL(f, dim3(R.n_blocks), dim3(kResThreads), lds, s, L, R, A);
   return hipGetLastError();
 }
 
@@ -836,20 +853,13 @@ bool resident_fits(const ResPlanDev& R) {
 }
 
 hipError_t launch_resident(hipStream_t s, const DevLevel& L, const ResPlanDev& R, const ResArgs& A) {
-  if (R.n_prob > 1) {
-    const size_t lds = dyn_lds(R, pairs_of(R));
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_cg_resident_batch),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_cg_resident_batch, dim3(R.n_blocks), dim3(kResThreads), lds, s, L, R, A);
-    return hipGetLastError();
-  }
+  if (R.n_prob > 1) return launch_kernel(&k_cg_resident_batch, s, L, R, A);
   switch (pairs_of(R)) {
-    case 1: return launch_np<1>(s, L, R, A);
-    case 2: return launch_np<2>(s, L, R, A);
-    case 3: return launch_np<3>(s, L, R, A);
-    case 4: return launch_np<4>(s, L, R, A);
-    case 5: return launch_np<5>(s, L, R, A);
+    case 1: return launch_kernel(&k_cg_resident<1>, s, L, R, A);
+    case 2: return launch_kernel(&k_cg_resident<2>, s, L, R, A);
+    case 3: return launch_kernel(&k_cg_resident<3>, s, L, R, A);
+    case 4: return launch_kernel(&k_cg_resident<4>, s, L, R, A);
+    case 5: return launch_kernel(&k_cg_resident<5>, s, L, R, A);
   }
   return hipErrorNotSupported;
 }

@@ -62,7 +62,7 @@ def _check(p, level, dt, tol):
 def test_sizes_against_oracle(k, compact):
     p = _problem(k, seed=k, compact=compact)
     st = _check(p, 5, 12.0 / 32 ** 2, 1e-10)
-    assert (st["sweep_blocks"] == 1) == (k <= 640)
+    assert (st["launch_blocks"] == 1) == (k <= 640)
 
 
 @pytest.mark.parametrize("level", [1, 2, 3, 6])
@@ -122,3 +122,32 @@ def test_contexts_on_streams_and_threads():
     for k, s in enumerate(solvers):
         assert np.array_equal(to_numpy(out[k]), alone[k]), k
         s.close()
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("graph", [False, True])
+def test_batch_of_resident_and_swept_patches(precision, graph):
+    # one patch above the resident size (112^3 cells) among small ones, two steps: the
+    # small ones against the oracle, the large one by its true residual; no sweep of the
+    # large patch may touch the others' energies
+    from oracle.patch_oracle import patch_advance
+    from paper_1401_1112_amd import FP64, MIXED
+    from paper_1401_1112_amd.solver import BatchSolver
+    from synth.configs import patch_batch
+    small, alpha = patch_batch(5100, 6, n_min=2, n_max=40)
+    big, _ = patch_batch(5200, 1, n_min=112, n_max=112)
+    patches = small[:3] + big + small[3:]
+    s = BatchSolver(robin_alpha=alpha, persistent=graph, graph=graph)
+    res, status = s.solve(patches, 2, 1e-10, precision=MIXED if precision == "mixed" else FP64)
+    st = s.stats()
+    s.close()
+    assert status == 0 and all(x["converged"] == 1 for x in st)
+    for x in st:
+        thr = max(1e-10 * x["rnorm0"], 1e-14 * x["bnorm"])
+        assert x["true_rel_res"] * x["rnorm0"] <= (1.0 + 1e-12 if precision == "mixed" else 2.5) * thr
+    for q, p in enumerate(patches):
+        if p.n > 100:
+            assert np.isfinite(res[q]).all()
+            continue
+        e, _ = patch_advance(p.rho, p.E, p.dx, p.dt, p.face_mode, p.face_ghost, p.face_flux, 2, 1e-10, alpha=alpha)
+        assert np.linalg.norm(res[q] - e) <= 1e-9 * np.linalg.norm(e), q
