@@ -123,7 +123,8 @@ struct ResTables {
 
   void release() {
     for (const void* p : {(const void*)d.parts, (const void*)d.places, (const void*)d.partner, (const void*)d.task0,
-                          (const void*)d.task, (const void*)d.lines, (const void*)d.halo, (const void*)d.epoch})
+                          (const void*)d.task, (const void*)d.lines, (const void*)d.halo, (const void*)d.epoch,
+                          (const void*)d.coefs})
       dfree(const_cast<void*>(p));
     d = ResPlanDev{};
   }
@@ -450,7 +451,7 @@ ResTables make_res_tables(hipStream_t s, const ResPlanHost& h, int n_prob) {
   r.d.n_prob = n_prob;
   r.d.n_blocks = int(h.task0.size()) - 1;
   r.d.max_slots = h.max_slots;
-  r.d.max_units = h.max_units;
+  r.d.lds = resident_lds(h.parts, h.max_slots, n_prob);
   if (!resident_fits(r.d)) return ResTables{};
   try {
     r.d.parts = upload_const(h.parts, "resident plan", s);
@@ -461,6 +462,7 @@ ResTables make_res_tables(hipStream_t s, const ResPlanHost& h, int n_prob) {
     r.d.lines = dalloc<unsigned long long>(int64_t(2) * r.d.n_parts * kResLine, "resident exchange");
     r.d.halo = dalloc<unsigned long long>(int64_t(16) * r.d.n_units, "resident exchange");
     r.d.epoch = dalloc<unsigned>(2 * n_prob + 1, "resident exchange");
+    if (const size_t nc = resident_coefs(r.d)) r.d.coefs = dalloc<double>(int64_t(nc), "resident coefficients");
     reset_exchange(s, r.d);
     check(hipStreamSynchronize(s), "resident plan");
   } catch (...) {
@@ -473,7 +475,7 @@ ResTables make_res_tables(hipStream_t s, const ResPlanHost& h, int n_prob) {
 
 // The resident plan of one level, one share per compute unit at most.
 ResTables level_res_tables(const amrfld_ctx* c, const LevelTables& t) {
-  const int g = res_group(t.n_oct, c->n_cu, kResMaxSlots, kResTargetSlots);
+  const int g = res_group(t.n_oct, c->n_cu, kResBlockSlots, kResTargetSlots);
   if ((t.n_oct + g - 1) / g * 8 > kResMaxSlots) return ResTables{};
   ResProblem p;
   p.n_oct = t.n_oct;
@@ -1816,22 +1818,25 @@ void build_batch_into(amrfld_ctx* c, BatchState* B, const std::vector<int>& size
       }
     }
   }
-  // patches that fit a resident solve, the largest first; in shares as large as a block
-  // holds once the patches fill the device, else about even
-  std::vector<int> order;
-  for (int q = 0; q < B->n_prob; ++q) {
-    const int64_t m = sizes[q] / 2;
-    if ((m * m * m + c->n_cu - 1) / c->n_cu * 8 <= kResMaxSlots) order.push_back(q);
-  }
-  std::sort(order.begin(), order.end(), [&](int a, int b2) { return sizes[a] != sizes[b2] ? sizes[a] > sizes[b2] : a < b2; });
+  // patches that fit a resident solve, the largest first (without those of streamed
+  // coefficients should the halo of one be too large for LDS); in shares as large as a
+  // block holds once the patches fill the device, else about even
   std::vector<char>& is_res = B->is_resident;
   is_res.assign(B->n_prob, 0);
   B->res_probs.clear();
-  if (!order.empty()) {
+  for (const int most : {kResMaxSlots, kResBlockSlots}) {
+    std::vector<int> order;
+    for (int q = 0; q < B->n_prob; ++q) {
+      const int64_t m = sizes[q] / 2;
+      if ((m * m * m + c->n_cu - 1) / c->n_cu * 8 <= most) order.push_back(q);
+    }
+    if (order.empty()) break;
+    std::sort(order.begin(), order.end(),
+              [&](int a, int b2) { return sizes[a] != sizes[b2] ? sizes[a] > sizes[b2] : a < b2; });
     int64_t slots = 0, shares = 0;
     for (int q : order) slots += int64_t(sizes[q]) * sizes[q] * sizes[q];
     const int target =
-        int(std::max<int64_t>(kResTargetSlots, std::min<int64_t>(kResMaxSlots, (slots + c->n_cu - 1) / c->n_cu)));
+        int(std::max<int64_t>(kResTargetSlots, std::min<int64_t>(kResBlockSlots, (slots + c->n_cu - 1) / c->n_cu)));
     std::vector<ResProblem> probs;
     std::vector<int> group;
     for (int q : order) {
@@ -1841,7 +1846,7 @@ void build_batch_into(amrfld_ctx* c, BatchState* B, const std::vector<int>& size
       p.n_oct = m * m * m;
       p.id = q;
       probs.push_back(p);
-      group.push_back(res_group(p.n_oct, c->n_cu, kResMaxSlots, target));
+      group.push_back(res_group(p.n_oct, c->n_cu, kResBlockSlots, target));
       shares += group.back();
     }
     const int n_blocks = int(std::min<int64_t>(c->n_cu, shares));
@@ -1849,6 +1854,7 @@ void build_batch_into(amrfld_ctx* c, BatchState* B, const std::vector<int>& size
     if (B->res.d.parts) {
       for (int q : order) is_res[q] = 1;
       B->res_probs = probs;
+      break;
     }
   }
   // blocks of the sweeps: at most tpb tiles per block, about >= 1024 blocks in total

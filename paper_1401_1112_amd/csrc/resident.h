@@ -4,13 +4,20 @@
 
 #include <hip/hip_runtime.h>
 
+#include <vector>
+
 #include "device.h"
 #include "resident_plan.h"
 
 namespace amrfld {
 
 constexpr int kResThreads = 512;
-constexpr int kResMaxSlots = 10 * kResThreads;  // of one share
+// Pairs of slots a thread holds with their coefficients, and the slots of a block then;
+// larger shares, up to kResMaxSlots, read the coefficients in every iteration.
+constexpr int kResPairs = 5;
+constexpr int kResBlockSlots = 2 * kResPairs * kResThreads;
+constexpr int kResMaxSlots = 16 * kResThreads;
+constexpr int kResStreamDoubles = 11 * kResMaxSlots / 2;  // the coefficients of a block
 constexpr int kResTargetSlots = 1024;  // of one share where the level has several
 // polls of a wait before a block gives up (about a microsecond each)
 constexpr unsigned kResSpinLimit = 1u << 18;
@@ -33,9 +40,11 @@ struct ResPlanDev {
   // [n_prob] that number once a block has begun to write the result of a solve; then the
   // flag of a wait that timed out
   unsigned* epoch = nullptr;
+  double* coefs = nullptr;              // streamed coefficients, resident_coefs() of them
   int n_parts = 0, n_units = 0, n_prob = 0;
   int n_blocks = 0;
-  int max_slots = 0, max_units = 0;
+  int max_slots = 0;
+  size_t lds = 0;  // bytes of LDS, resident_lds()
 };
 
 struct ResArgs {
@@ -61,6 +70,9 @@ struct ResArgs {
 
 // Whether a block's share of this plan fits its registers and LDS.
 bool resident_fits(const ResPlanDev& R);
+size_t resident_lds(const std::vector<ResPart>& parts, int max_slots, int n_prob);
+// Doubles of the streamed coefficients of a plan (0: none of its shares streams them).
+size_t resident_coefs(const ResPlanDev& R);
 // All blocks have to be on the device together (at most one per compute unit): no other
 // kernel whose blocks wait for each other may run meanwhile.  An ordinary launch: a
 // cooperative one goes through a hardware queue of its own, which costs 20 to 130 us of

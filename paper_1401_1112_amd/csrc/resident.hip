@@ -325,23 +325,97 @@ struct Pair<float> {
   typedef float2 type;
 };
 
+// Scaled face coefficients of a pair: within the oct cix (the same for both slots), ciy,
+// ciz; out of the oct cox, coy, coz.
+template <typename T>
+struct Coefs {
+  T cix, ciy[2], ciz[2], cox[2], coy[2], coz[2];
+};
+
 // A share's state in registers, NP pairs of slots per thread (thread t holds pairs
-// t + 512 u of the share).  Coefficients: within the oct cix, ciy, ciz (that in x is the
-// same for both slots), out of the oct cox, coy, coz.  Places in p: of the out-of-oct
-// neighbours in x of both slots (px, 16 bits each) and of the pairs in y and z (pyz).
+// t + 512 u of the share).  Places in p: of the out-of-oct neighbours in x of both slots
+// (px, 16 bits each) and of the pairs in y and z (pyz).
 template <typename T, int NP>
-struct Regs {
-  T cix[NP], ciy[NP][2], ciz[NP][2], cox[NP][2], coy[NP][2], coz[NP][2];
+struct State {
   T x[NP][2], r[NP][2], s[NP][2];
   unsigned px[NP], pyz[NP];
   unsigned face;  // bit u: pair u has a cell on a face between shares
+};
+
+// With the coefficients in registers too and the diagonal in LDS, or (kStream: shares of
+// more than 5120 slots, whose coefficients do not fit) with the diagonal in registers and
+// the coefficients read in every iteration, from memory that this block alone uses: 44
+// bytes per slot that L2 and the last-level cache largely hold, against the 115 of a
+// sweep.  What ends it at 8192 slots is the register file.  256 patches of 16.9 M cells,
+// the 7.8 M of five of them in streamed shares (128^3 and less): 42.8 ms for two steps
+// against 69 with sweeps of those five.
+template <typename T, int NP, bool kStream>
+struct Regs;
+
+template <typename T, int NP>
+struct Regs<T, NP, false> : State<T, NP> {
+  typedef typename Pair<T>::type T2;
+  Coefs<T> c[NP];
+  T* d;
+
+  __device__ __forceinline__ Coefs<T> coefs(int u) const { return c[u]; }
+  __device__ __forceinline__ void put_axis(int u, int a, T ci0, T ci1, T co0, T co1) {
+    T(&ci)[2] = a == 1 ? c[u].ciy : c[u].ciz;
+    T(&co)[2] = a == 0 ? c[u].cox : a == 1 ? c[u].coy : c[u].coz;
+    if (a == 0) {
+      c[u].cix = ci0;
+      keep(c[u].cix);
+    } else {
+      ci[0] = ci0;
+      ci[1] = ci1;
+      keep(ci[0]);
+      keep(ci[1]);
+    }
+    co[0] = co0;
+    co[1] = co1;
+    keep(co[0]);
+    keep(co[1]);
+  }
+  __device__ __forceinline__ T2 diag(int u) const {
+    return *reinterpret_cast<const T2*>(d + 2 * (tid() + u * kResThreads));
+  }
+  __device__ __forceinline__ void put_diag(int u, T2 v) {
+    *reinterpret_cast<T2*>(d + 2 * (tid() + u * kResThreads)) = v;
+  }
+};
+
+template <typename T, int NP>
+struct Regs<T, NP, true> : State<T, NP> {
+  typedef typename Pair<T>::type T2;
+  T dr[NP][2];
+  T2* cs;  // five arrays of NP * 512 pairs (ciy, ciz, cox, coy, coz), then cix
+
+  __device__ __forceinline__ T2* at(int k, int u) const { return cs + (k * NP + u) * kResThreads + tid(); }
+  __device__ __forceinline__ T* x_at(int u) const {
+    return reinterpret_cast<T*>(cs + 5 * NP * kResThreads) + u * kResThreads + tid();
+  }
+  __device__ __forceinline__ Coefs<T> coefs(int u) const {
+    const T2 iy = *at(0, u), iz = *at(1, u), ox = *at(2, u), oy = *at(3, u), oz = *at(4, u);
+    return Coefs<T>{*x_at(u), {iy.x, iy.y}, {iz.x, iz.y}, {ox.x, ox.y}, {oy.x, oy.y}, {oz.x, oz.y}};
+  }
+  __device__ __forceinline__ void put_axis(int u, int a, T ci0, T ci1, T co0, T co1) {
+    if (a == 0) *x_at(u) = ci0;
+    else *at(a - 1, u) = T2{ci0, ci1};
+    *at(2 + a, u) = T2{co0, co1};
+  }
+  __device__ __forceinline__ T2 diag(int u) const { return T2{dr[u][0], dr[u][1]}; }
+  __device__ __forceinline__ void put_diag(int u, T2 v) {
+    dr[u][0] = v.x;
+    dr[u][1] = v.y;
+    keep(dr[u][0]);
+    keep(dr[u][1]);
+  }
 };
 
 // LDS arrays of a share.
 template <typename T>
 struct Lds {
   T* p;         // [cap + 4 units]: p^ of the share, then of its halo cells
-  T* d;         // [cap]: the diagonal
   T* rh;        // [4 units]: r^ of the halo cells
   T* ex;        // [4 units]: this share's cells on the same faces, then the halo cells'
                 // values of the current exchange
@@ -350,7 +424,8 @@ struct Lds {
 
 // (A^ v) of pair u, v in p.
 template <typename T, int NP>
-__device__ __forceinline__ void apply(const Regs<T, NP>& q, const T* p, int u, T (&pv)[2], T (&av)[2]) {
+__device__ __forceinline__ void apply(const State<T, NP>& q, const Coefs<T>& c, const T* p, int u, T (&pv)[2],
+                                      T (&av)[2]) {
   typedef typename Pair<T>::type T2;
   const int l = 2 * (tid() + u * kResThreads);
   const T2 own = *reinterpret_cast<const T2*>(p + l);
@@ -360,26 +435,42 @@ __device__ __forceinline__ void apply(const Regs<T, NP>& q, const T* p, int u, T
   pv[0] = own.x;
   pv[1] = own.y;
   T a0 = own.x, a1 = own.y;
-  a0 = fma(-q.cix[u], own.y, a0);
-  a1 = fma(-q.cix[u], own.x, a1);
-  a0 = fma(-q.ciy[u][0], dpp<kQuadXor1>(own.x, own.x), a0);
-  a1 = fma(-q.ciy[u][1], dpp<kQuadXor1>(own.y, own.y), a1);
-  a0 = fma(-q.ciz[u][0], dpp<kQuadXor2>(own.x, own.x), a0);
-  a1 = fma(-q.ciz[u][1], dpp<kQuadXor2>(own.y, own.y), a1);
-  a0 = fma(-q.cox[u][0], nx0, a0);
-  a1 = fma(-q.cox[u][1], nx1, a1);
-  a0 = fma(-q.coy[u][0], ny.x, a0);
-  a1 = fma(-q.coy[u][1], ny.y, a1);
-  a0 = fma(-q.coz[u][0], nz.x, a0);
-  a1 = fma(-q.coz[u][1], nz.y, a1);
+  a0 = fma(-c.cix, own.y, a0);
+  a1 = fma(-c.cix, own.x, a1);
+  a0 = fma(-c.ciy[0], dpp<kQuadXor1>(own.x, own.x), a0);
+  a1 = fma(-c.ciy[1], dpp<kQuadXor1>(own.y, own.y), a1);
+  a0 = fma(-c.ciz[0], dpp<kQuadXor2>(own.x, own.x), a0);
+  a1 = fma(-c.ciz[1], dpp<kQuadXor2>(own.y, own.y), a1);
+  a0 = fma(-c.cox[0], nx0, a0);
+  a1 = fma(-c.cox[1], nx1, a1);
+  a0 = fma(-c.coy[0], ny.x, a0);
+  a1 = fma(-c.coy[1], ny.y, a1);
+  a0 = fma(-c.coz[0], nz.x, a0);
+  a1 = fma(-c.coz[1], nz.y, a1);
   av[0] = a0;
   av[1] = a1;
+}
+
+// f(u, v, A^ v) for every pair; streamed coefficients are loaded one pair ahead.
+template <typename T, int NP, bool kStream, class F>
+__device__ __forceinline__ void apply_all(const Regs<T, NP, kStream>& q, const T* p, F f) {
+  Coefs<T> c = q.coefs(0);
+#pragma unroll
+  for (int u = 0; u < NP; ++u) {
+    __builtin_amdgcn_sched_barrier(0);
+    Coefs<T> next;
+    if (kStream && u + 1 < NP) next = q.coefs(u + 1);
+    T pv[2], av[2];
+    apply(q, c, p, u, pv, av);
+    f(u, pv, av);
+    if (u + 1 < NP) c = kStream ? next : q.coefs(u + 1);
+  }
 }
 
 // The values of pair u that lie on faces between shares to the block's export list
 // (ordered like its halo cells).
 template <typename T, int NP>
-__device__ __forceinline__ void stage(const Regs<T, NP>& q, T* ex, int u, T v0, T v1) {
+__device__ __forceinline__ void stage(const State<T, NP>& q, T* ex, int u, T v0, T v1) {
   constexpr int kCap = 2 * NP * kResThreads;
   typedef typename Pair<T>::type T2;
   if (!((q.face >> u) & 1u)) return;
@@ -410,8 +501,8 @@ struct CgResult {
 // CG iterations from r^ = q.r, p^ in lds.p (own and halo), r^ of the halo in lds.rh.
 // thresh, tol, max_iter, linf_test: the stopping rule of Sect. 3.3.4; dmin: smallest
 // diagonal entry.  false: a wait timed out.
-template <typename T, int NP>
-__device__ __forceinline__ bool cg_loop(Exchange& X, Regs<T, NP>& q, const Lds<T>& lds, Shared& S, double thresh,
+template <typename T, int NP, bool kStream>
+__device__ __forceinline__ bool cg_loop(Exchange& X, Regs<T, NP, kStream>& q, const Lds<T>& lds, Shared& S, double thresh,
                                         double tol, int max_iter, bool linf_test, double dmin, CgResult& out) {
   typedef typename Pair<T>::type T2;
   constexpr int kCap = 2 * NP * kResThreads;
@@ -419,7 +510,7 @@ __device__ __forceinline__ bool cg_loop(Exchange& X, Regs<T, NP>& q, const Lds<T
   double rr = 0.0, rrd = 0.0, linf = 0.0;
 #pragma unroll
   for (int u = 0; u < NP; ++u) {
-    const T2 d = *reinterpret_cast<const T2*>(lds.d + 2 * (tid() + u * kResThreads));
+    const T2 d = q.diag(u);
     const double a0 = double(q.r[u][0]) * double(q.r[u][0]), a1 = double(q.r[u][1]) * double(q.r[u][1]);
     rr += a0 + a1;
     rrd = fma(a0, double(d.x), fma(a1, double(d.y), rrd));
@@ -428,19 +519,16 @@ __device__ __forceinline__ bool cg_loop(Exchange& X, Regs<T, NP>& q, const Lds<T
   const double stop2 = 1.000001 * thresh * thresh;
   for (int k = 0;; ++k) {
     double v[kSums] = {0.0, 0.0, rr, rrd};
+    // (opaque: nothing derived from the places is kept in registers across iterations)
 #pragma unroll
-    for (int u = 0; u < NP; ++u) {
-      // (opaque: nothing derived from the places is kept in registers across iterations)
-      asm volatile("" : "+v"(q.px[u]), "+v"(q.pyz[u]));
-      __builtin_amdgcn_sched_barrier(0);
-      T pv[2], av[2];
-      apply(q, lds.p, u, pv, av);
+    for (int u = 0; u < NP; ++u) asm volatile("" : "+v"(q.px[u]), "+v"(q.pyz[u]));
+    apply_all(q, lds.p, [&](int u, const T(&pv)[2], const T(&av)[2]) {
       q.s[u][0] = av[0];
       q.s[u][1] = av[1];
       stage(q, lds.ex, u, av[0], av[1]);
       v[0] = fma(double(pv[0]), double(av[0]), fma(double(pv[1]), double(av[1]), v[0]));
       v[1] = fma(double(av[0]), double(av[0]), fma(double(av[1]), double(av[1]), v[1]));
-    }
+    });
     if (!exchange(X, v, linf, wide, S, lds)) return false;
     // the stopping test of iterate k
     if (k >= 1) {
@@ -477,7 +565,7 @@ __device__ __forceinline__ bool cg_loop(Exchange& X, Regs<T, NP>& q, const Lds<T
       __builtin_amdgcn_sched_barrier(0);
       const int l = 2 * (tid() + u * kResThreads);
       const T2 po = *reinterpret_cast<const T2*>(lds.p + l);
-      const T2 d = *reinterpret_cast<const T2*>(lds.d + l);
+      const T2 d = q.diag(u);
       if (wide) {
         const T x0 = fabs(q.x[u][0]), x1 = fabs(q.x[u][1]), e0 = fabs(ta * po.x), e1 = fabs(ta * po.y);
         linf = fmax(linf, fmax(double(x0 > T(0) ? e0 / x0 : e0), double(x1 > T(0) ? e1 / x1 : e1)));
@@ -504,19 +592,19 @@ __device__ __forceinline__ bool cg_loop(Exchange& X, Regs<T, NP>& q, const Lds<T
 }
 
 // The solve of one share of one problem.  false: a wait timed out.
-template <int NP>
+template <int NP, bool kStream>
 __device__ __forceinline__ bool solve_part(const DevLevel& L, const ResPlanDev& R, const ResArgs& A, int my_part,
                                            unsigned char* dyn, Shared& S) {
   constexpr int kCap = 2 * NP * kResThreads;
   const ResPart me = R.parts[my_part];
   const int ns = me.n_slots, n = L.n_slots;
-  const int nh = 4 * R.max_units;
+  const int nh = 4 * me.n_units;
   Lds<double> lds;
   lds.p = reinterpret_cast<double*>(dyn);
-  lds.d = lds.p + kCap + nh;
-  lds.rh = lds.d + kCap;
+  lds.rh = lds.p + kCap + nh;
   lds.ex = lds.rh + nh;
   lds.partner = reinterpret_cast<int*>(lds.ex + nh);
+  double* const lds_d = reinterpret_cast<double*>(lds.partner + ((me.n_units + 1) & ~1));
   if (A.resume) {  // nothing left to do: decided by an earlier launch, alike for every share
     const PcgScalars& o = A.sc[me.prob];
     if (o.converged || o.nonfinite || o.inner_total >= A.max_iter) return true;
@@ -535,8 +623,11 @@ __device__ __forceinline__ bool solve_part(const DevLevel& L, const ResPlanDev& 
   // start: rs = diag^-1/2 exchanged, the scaled operator; x^_0 = x_0 / rs exchanged,
   // r^_0 = rs b - A^ x^_0 exchanged.  Every array is read once, in order; a thread's pairs
   // past the share's end read its first pair and get rs = 0, hence a zero operator.
-  Regs<double, NP> q;
+  Regs<double, NP, kStream> q;
   q.face = 0;
+  if constexpr (kStream)
+    q.cs = reinterpret_cast<double2*>(R.coefs + size_t(blockIdx.x) * kResStreamDoubles);
+  else q.d = lds_d;
   double v[kSums] = {0.0, 0.0, 0.0, 0.0}, m = -DBL_MAX;
   auto slot = [&](int l) -> int64_t { return me.slot0 + (l < ns ? l : 0); };
   auto pair = [&](const double* a, int64_t i) { return *reinterpret_cast<const double2*>(a + i); };
@@ -556,7 +647,7 @@ __device__ __forceinline__ bool solve_part(const DevLevel& L, const ResPlanDev& 
       const bool valid = l < ns;
       const double2 rs{valid ? 1.0 / sqrt(d[u].x) : 0.0, valid ? 1.0 / sqrt(d[u].y) : 0.0};
       m = fmax(m, fmax(-d[u].x, -d[u].y));
-      *reinterpret_cast<double2*>(lds.d + l) = d[u];
+      q.put_diag(u, d[u]);
       *reinterpret_cast<double2*>(lds.p + l) = rs;
       auto place = [&](unsigned c, unsigned own) {
         if (!valid) return own;
@@ -592,12 +683,8 @@ __device__ __forceinline__ bool solve_part(const DevLevel& L, const ResPlanDev& 
       const int tt = tid(), l = 2 * (tt + u * kResThreads);
       const double2 rs = at(l);
       if (a == 0) {
-        q.cix[u] = cp[u].x * (rs.x * rs.y);
-        q.cox[u][0] = cm[u].x * (rs.x * lds.p[q.px[u] & 0xffffu]);
-        q.cox[u][1] = cp[u].y * (rs.y * lds.p[q.px[u] >> 16]);
-        keep(q.cix[u]);
-        keep(q.cox[u][0]);
-        keep(q.cox[u][1]);
+        q.put_axis(u, 0, cp[u].x * (rs.x * rs.y), 0.0, cm[u].x * (rs.x * lds.p[q.px[u] & 0xffffu]),
+                   cp[u].y * (rs.y * lds.p[q.px[u] >> 16]));
         continue;
       }
       const bool up = tt & a;  // on the + side of its oct
@@ -605,16 +692,7 @@ __device__ __forceinline__ bool solve_part(const DevLevel& L, const ResPlanDev& 
       const double2 rn = at(a == 1 ? q.pyz[u] & 0xffffu : q.pyz[u] >> 16);
       const double sx = a == 1 ? dpp<kQuadXor1>(rs.x, rs.x) : dpp<kQuadXor2>(rs.x, rs.x);
       const double sy = a == 1 ? dpp<kQuadXor1>(rs.y, rs.y) : dpp<kQuadXor2>(rs.y, rs.y);
-      double(&ci)[2] = a == 1 ? q.ciy[u] : q.ciz[u];
-      double(&co)[2] = a == 1 ? q.coy[u] : q.coz[u];
-      ci[0] = in.x * (rs.x * sx);
-      ci[1] = in.y * (rs.y * sy);
-      co[0] = out.x * (rs.x * rn.x);
-      co[1] = out.y * (rs.y * rn.y);
-      keep(ci[0]);
-      keep(ci[1]);
-      keep(co[0]);
-      keep(co[1]);
+      q.put_axis(u, a, in.x * (rs.x * sx), in.y * (rs.y * sy), out.x * (rs.x * rn.x), out.y * (rs.y * rn.y));
     }
   }
   {
@@ -652,13 +730,9 @@ __device__ __forceinline__ bool solve_part(const DevLevel& L, const ResPlanDev& 
       b[u] = pair(A.b, i);
       ch[u] = *reinterpret_cast<const int2*>(L.child + i);
     }
-#pragma unroll
-    for (int u = 0; u < NP; ++u) {
-      __builtin_amdgcn_sched_barrier(0);
+    apply_all(q, lds.p, [&](int u, const double(&)[2], const double(&av)[2]) {
       const int l = 2 * (tid() + u * kResThreads);
-      double pv[2], av[2];
-      apply(q, lds.p, u, pv, av);
-      const double2 d = *reinterpret_cast<const double2*>(lds.d + l);
+      const double2 d = q.diag(u);
       q.r[u][0] = q.s[u][0] * b[u].x - av[0];
       q.r[u][1] = q.s[u][1] * b[u].y - av[1];
       keep(q.r[u][0]);
@@ -667,7 +741,7 @@ __device__ __forceinline__ bool solve_part(const DevLevel& L, const ResPlanDev& 
       if (l < ns && ch[u].x == -1) v[1] += b[u].x * b[u].x;
       if (l < ns && ch[u].y == -1) v[1] += b[u].y * b[u].y;
       stage(q, lds.ex, u, q.r[u][0], q.r[u][1]);
-    }
+    });
   }
   __syncthreads();  // x^ read everywhere
 #pragma unroll
@@ -707,7 +781,7 @@ __device__ __forceinline__ bool solve_part(const DevLevel& L, const ResPlanDev& 
     const int l = 2 * (tid() + u * kResThreads);
     if (l < ns) {
       const int64_t i = me.slot0 + l;
-      const double2 d = *reinterpret_cast<const double2*>(lds.d + l);
+      const double2 d = q.diag(u);
       const double rs[2] = {1.0 / sqrt(d.x), 1.0 / sqrt(d.y)};
       double2 xi{q.x[u][0] * rs[0], q.x[u][1] * rs[1]};
       if (res.iters > 0) *reinterpret_cast<double2*>(A.x + i) = xi;
@@ -740,19 +814,17 @@ __device__ __forceinline__ bool solve_part(const DevLevel& L, const ResPlanDev& 
     take_halo(lds.p + kCap);
     __syncthreads();
     v[0] = v[1] = v[2] = v[3] = 0.0;
-#pragma unroll
-    for (int u = 0; u < NP; ++u) {
+    apply_all(q, lds.p, [&](int u, const double(&)[2], const double(&av)[2]) {
       const int l = 2 * (tid() + u * kResThreads);
-      double pv[2], av[2];
-      apply(q, lds.p, u, pv, av);
       if (l < ns) {
         const double2 b = *reinterpret_cast<const double2*>(A.b + me.slot0 + l);
-        const double2 d = *reinterpret_cast<const double2*>(lds.d + l);
+        const double2 d = q.diag(u);
         const double r0 = b.x - av[0] * sqrt(d.x), r1 = b.y - av[1] * sqrt(d.y);
         v[0] = fma(r0, r0, fma(r1, r1, v[0]));
       }
-    }
+    });
   }
+  v[1] = v[2] = v[3] = 0.0;
   put_sums(X, v, m, true, S, static_cast<const double*>(nullptr), lds.partner);
   if (my_part != me.part0) return true;
   if (!collect(X, v, m, true, S, static_cast<double*>(nullptr))) return false;
@@ -788,13 +860,13 @@ __device__ __forceinline__ bool solve_part(const DevLevel& L, const ResPlanDev& 
   return true;
 }
 
-template <int NP>
+template <int NP, bool kStream>
 __global__ __launch_bounds__(kResThreads) void k_cg_resident(DevLevel L, ResPlanDev R, ResArgs A) {
   extern __shared__ __align__(16) unsigned char res_lds[];
   __shared__ Shared S;
   const int b = int(blockIdx.x);
   for (int k = R.task0[b]; k < R.task0[b + 1]; ++k) {
-    if (!solve_part<NP>(L, R, A, R.task[k], res_lds, S)) {
+    if (!solve_part<NP, kStream>(L, R, A, R.task[k], res_lds, S)) {
       if (threadIdx.x == 0) st_word32(R.epoch + 2 * R.n_prob, 1u);
       return;
     }
@@ -812,11 +884,13 @@ __global__ __launch_bounds__(kResThreads) void k_cg_resident_batch(DevLevel L, R
     const int part = R.task[k];
     bool ok;
     switch ((R.parts[part].n_slots + 2 * kResThreads - 1) / (2 * kResThreads)) {
-      case 1: ok = solve_part<1>(L, R, A, part, res_lds, S); break;
-      case 2: ok = solve_part<2>(L, R, A, part, res_lds, S); break;
-      case 3: ok = solve_part<3>(L, R, A, part, res_lds, S); break;
-      case 4: ok = solve_part<4>(L, R, A, part, res_lds, S); break;
-      default: ok = solve_part<5>(L, R, A, part, res_lds, S);
+      case 1: ok = solve_part<1, false>(L, R, A, part, res_lds, S); break;
+      case 2: ok = solve_part<2, false>(L, R, A, part, res_lds, S); break;
+      case 3: ok = solve_part<3, false>(L, R, A, part, res_lds, S); break;
+      case 4: ok = solve_part<4, false>(L, R, A, part, res_lds, S); break;
+      case 5: ok = solve_part<5, false>(L, R, A, part, res_lds, S); break;
+      case 6: ok = solve_part<6, true>(L, R, A, part, res_lds, S); break;
+      default: ok = solve_part<8, true>(L, R, A, part, res_lds, S);
     }
     if (!ok) {
       if (threadIdx.x == 0) st_word32(R.epoch + 2 * R.n_prob, 1u);
@@ -828,38 +902,56 @@ __global__ __launch_bounds__(kResThreads) void k_cg_resident_batch(DevLevel L, R
 
 constexpr size_t kLdsLimit = 160 * 1024 - sizeof(Shared) - 256;
 
-size_t dyn_lds(const ResPlanDev& R, int NP) {
-  const size_t nh = 4 * size_t(R.max_units);
-  return (4 * size_t(NP) * kResThreads + 3 * nh) * sizeof(double) + size_t(R.max_units) * sizeof(int);
+// Pairs of slots per thread of a share (a batch has no loops of 7: see its kernel).
+int pairs_of(int n_slots, int n_prob) {
+  const int np = (n_slots + 2 * kResThreads - 1) / (2 * kResThreads);
+  return n_prob > 1 && np == 7 ? 8 : np;
 }
-
-// Pairs of slots per thread.
-int pairs_of(const ResPlanDev& R) { return (R.max_slots + 2 * kResThreads - 1) / (2 * kResThreads); }
 
 hipError_t launch_kernel(void (*f)(DevLevel, ResPlanDev, ResArgs), hipStream_t s, const DevLevel& L,
                          const ResPlanDev& R, const ResArgs& A) {
-  const size_t lds = dyn_lds(R, pairs_of(R));
   const hipError_t e =
-      hipFuncSetAttribute(reinterpret_cast<const void*>(f), hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
+      hipFuncSetAttribute(reinterpret_cast<const void*>(f), hipFuncAttributeMaxDynamicSharedMemorySize, int(R.lds));
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(f, dim3(R.n_blocks), dim3(kResThreads), lds, s, L, R, A);
+  hipLaunchKernelGGL(f, dim3(R.n_blocks), dim3(kResThreads), R.lds, s, L, R, A);
   return hipGetLastError();
 }
 
 }  // namespace
 
+// Of one share: the places of a vector and its halo, r^ and exchanged values of the halo,
+// the partner units and, where the coefficients are in registers, the diagonal.  The
+// shares of one problem run with as many pairs as its largest.
+size_t resident_lds(const std::vector<ResPart>& parts, int max_slots, int n_prob) {
+  size_t most = 0;
+  for (const ResPart& p : parts) {
+    const int np = pairs_of(n_prob > 1 ? p.n_slots : max_slots, n_prob);
+    const size_t cap = 2 * size_t(np) * kResThreads, nh = 4 * size_t(p.n_units);
+    most = std::max(most, (cap + 3 * nh + (np <= kResPairs ? cap : 0)) * sizeof(double) +
+                              size_t((p.n_units + 1) & ~1) * sizeof(int));
+  }
+  return most;
+}
+
+size_t resident_coefs(const ResPlanDev& R) {
+  return R.max_slots > kResBlockSlots ? size_t(R.n_blocks) * kResStreamDoubles : 0;
+}
+
 bool resident_fits(const ResPlanDev& R) {
-  return R.n_parts > 0 && R.max_slots <= kResMaxSlots && dyn_lds(R, pairs_of(R)) <= kLdsLimit;
+  return R.n_parts > 0 && R.max_slots <= kResMaxSlots && R.lds <= kLdsLimit;
 }
 
 hipError_t launch_resident(hipStream_t s, const DevLevel& L, const ResPlanDev& R, const ResArgs& A) {
   if (R.n_prob > 1) return launch_kernel(&k_cg_resident_batch, s, L, R, A);
-  switch (pairs_of(R)) {
-    case 1: return launch_kernel(&k_cg_resident<1>, s, L, R, A);
-    case 2: return launch_kernel(&k_cg_resident<2>, s, L, R, A);
-    case 3: return launch_kernel(&k_cg_resident<3>, s, L, R, A);
-    case 4: return launch_kernel(&k_cg_resident<4>, s, L, R, A);
-    case 5: return launch_kernel(&k_cg_resident<5>, s, L, R, A);
+  switch (pairs_of(R.max_slots, 1)) {
+    case 1: return launch_kernel(&k_cg_resident<1, false>, s, L, R, A);
+    case 2: return launch_kernel(&k_cg_resident<2, false>, s, L, R, A);
+    case 3: return launch_kernel(&k_cg_resident<3, false>, s, L, R, A);
+    case 4: return launch_kernel(&k_cg_resident<4, false>, s, L, R, A);
+    case 5: return launch_kernel(&k_cg_resident<5, false>, s, L, R, A);
+    case 6: return launch_kernel(&k_cg_resident<6, true>, s, L, R, A);
+    case 7: return launch_kernel(&k_cg_resident<7, true>, s, L, R, A);
+    case 8: return launch_kernel(&k_cg_resident<8, true>, s, L, R, A);
   }
   return hipErrorNotSupported;
 }

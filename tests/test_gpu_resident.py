@@ -124,18 +124,32 @@ def test_contexts_on_streams_and_threads():
         s.close()
 
 
+@pytest.mark.parametrize("k", [163841, 200000, 262144])
+def test_streamed_coefficients_against_oracle(k):
+    # shares of six to eight pairs per thread, the last one full
+    p = _problem(k, seed=3, base=6, compact=True)
+    kw = dict(max_iter=20, abs_floor=0.0)
+    o = oracle_from_problem(p, **kw)
+    h = o.solve_level(7, 12.0 / 128 ** 2, ora.DIRICHLET, 0.0)
+    e, cells, st = _solve(p, 7, 12.0 / 128 ** 2, 0.0, **kw)
+    assert st["iters"] == h["iters"] == 20 and st["launch_blocks"] == 256
+    ref = align(7, o.cells(7), o.E[7], cells)
+    assert np.linalg.norm(e - ref) <= 1e-12 * np.linalg.norm(ref)
+
+
 @pytest.mark.parametrize("precision", ["fp64", "mixed"])
 @pytest.mark.parametrize("graph", [False, True])
-def test_batch_of_resident_and_swept_patches(precision, graph):
-    # one patch above the resident size (112^3 cells) among small ones, two steps: the
-    # small ones against the oracle, the large one by its true residual; no sweep of the
-    # large patch may touch the others' energies
+@pytest.mark.parametrize("n_big", [112, 136])
+def test_batch_of_resident_and_swept_patches(precision, graph, n_big):
+    # one patch of streamed coefficients (112^3 cells) or above the resident size (136^3)
+    # among small ones, two steps: the small ones against the oracle, the large one by its
+    # true residual; no sweep of the large patch may touch the others' energies
     from oracle.patch_oracle import patch_advance
     from paper_1401_1112_amd import FP64, MIXED
     from paper_1401_1112_amd.solver import BatchSolver
     from synth.configs import patch_batch
     small, alpha = patch_batch(5100, 6, n_min=2, n_max=40)
-    big, _ = patch_batch(5200, 1, n_min=112, n_max=112)
+    big, _ = patch_batch(5200, 1, n_min=n_big, n_max=n_big)
     patches = small[:3] + big + small[3:]
     s = BatchSolver(robin_alpha=alpha, persistent=graph, graph=graph)
     res, status = s.solve(patches, 2, 1e-10, precision=MIXED if precision == "mixed" else FP64)
