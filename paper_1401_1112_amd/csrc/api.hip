@@ -124,7 +124,7 @@ struct ResTables {
   void release() {
     for (const void* p : {(const void*)d.parts, (const void*)d.places, (const void*)d.partner, (const void*)d.task0,
                           (const void*)d.task, (const void*)d.lines, (const void*)d.halo, (const void*)d.epoch,
-                          (const void*)d.coefs})
+                          (const void*)d.extra})
       dfree(const_cast<void*>(p));
     d = ResPlanDev{};
   }
@@ -457,12 +457,16 @@ ResTables make_res_tables(hipStream_t s, const ResPlanHost& h, int n_prob) {
     r.d.parts = upload_const(h.parts, "resident plan", s);
     r.d.places = reinterpret_cast<const uint2*>(upload_const(h.places, "resident plan", s));
     r.d.partner = upload_const(h.partner, "resident plan", s);
+    std::vector<uint32_t> c(h.couplings);
+    c.insert(c.end(), h.coarse.begin(), h.coarse.end());
+    r.d.coupled = !c.empty();
+    if (r.d.coupled) r.d.extra = const_cast<uint32_t*>(upload_const(c, "resident plan", s));
     r.d.task0 = upload_const(h.task0, "resident plan", s);
     r.d.task = upload_const(h.task, "resident plan", s);
     r.d.lines = dalloc<unsigned long long>(int64_t(2) * r.d.n_parts * kResLine, "resident exchange");
     r.d.halo = dalloc<unsigned long long>(int64_t(16) * r.d.n_units, "resident exchange");
     r.d.epoch = dalloc<unsigned>(2 * n_prob + 1, "resident exchange");
-    if (const size_t nc = resident_coefs(r.d)) r.d.coefs = dalloc<double>(int64_t(nc), "resident coefficients");
+    if (const size_t nc = resident_coefs(r.d)) r.d.extra = dalloc<double>(int64_t(nc), "resident coefficients");
     reset_exchange(s, r.d);
     check(hipStreamSynchronize(s), "resident plan");
   } catch (...) {
@@ -1437,6 +1441,7 @@ struct CompositeState {
   int n_if_rows = 0, n_if_entries = 0;
   int32_t *if_row = nullptr, *if_ptr = nullptr, *if_col = nullptr, *if_src = nullptr;
   double *if_val = nullptr, *if_part = nullptr;
+  ResTables res;  // of several levels that fit a resident solve together
 
   DevLevel dev() const {
     DevLevel d;
@@ -1463,6 +1468,7 @@ struct CompositeState {
                     (void*)T, (void*)Cp, (void*)cif, (void*)diag, (void*)b, (void*)c2f, (void*)if_row,
                     (void*)if_ptr, (void*)if_col, (void*)if_src, (void*)if_val, (void*)if_part, (void*)Ch, (void*)rs})
       dfree(p);
+    res.release();
   }
 };
 
@@ -1592,6 +1598,13 @@ void build_composite_into(amrfld_ctx* c, CompositeState* C) {
   C->Ch = dalloc<double>(3 * n, "composite system");
   C->rs = dalloc<double>(n, "composite system");
   C->c2f = dalloc<uint8_t>(n, "composite system");
+  if (C->n_levels > 1 && n <= int64_t(c->n_cu) * kResBlockSlots) {
+    ResProblem p;
+    p.n_oct = C->n_oct;
+    // (at least two blocks: couplings go through the exchange, also those within a share)
+    const int g = std::max(2, res_group(C->n_oct, c->n_cu, 0, kResTargetSlots));
+    C->res = make_res_tables(c->stream(), build_res_plan({p}, {g}, g, nbr.data(), C->n_oct, cnb.data(), child.data()), 1);
+  }
   launch_fill(c->stream(), C->x, n, 0.0);  // padding slots keep x = 0 (identity rows)
   launch_fill(c->stream(), C->rho, n, 1.0);
   launch_fill(c->stream(), C->T, n, 1.0);
@@ -1632,7 +1645,8 @@ amrfld_status solve_composite(amrfld_ctx* c, double dt, double tol) {
   cp.T = coupled ? C.T : nullptr;
   const DevLevel D = C.dev();
   // a single level is that level's system (rows times the volume): solved as it is
-  bool resident = C.n_levels == 1 && resident_fits(c->L(base).res.d);
+  const ResPlanDev& R = C.n_levels == 1 ? c->L(base).res.d : C.res.d;
+  bool resident = resident_fits(R);
   launch_assemble_composite(s, D, C.K, C.x, C.rho, cp, outer_bc(c), dt, C.Cp, C.cif, C.c2f, C.diag, C.b,
                             resident ? C.Ch : nullptr);
   const int n_tiles = tiles_of(C.n_slots);
@@ -1645,7 +1659,6 @@ amrfld_status solve_composite(amrfld_ctx* c, double dt, double tol) {
   LoopStats ls;
   ls.iters.assign(1, 0);
   if (resident) {
-    const ResPlanDev& R = c->L(base).res.d;
     ResArgs a = resident_args(c, c->L(base), dt, tol, c->sc);
     a.Cp = C.Cp;
     a.Cm = C.Ch;
@@ -1670,6 +1683,8 @@ amrfld_status solve_composite(amrfld_ctx* c, double dt, double tol) {
   if (!resident) {
     ls = LoopStats{};
     ls.iters.assign(1, 0);
+    if (resident_fits(R))  // without the couplings among the face coefficients
+      launch_assemble_composite(s, D, C.K, C.x, C.rho, cp, outer_bc(c), dt, C.Cp, C.cif, C.c2f, C.diag, C.b, nullptr);
     const ScaledOp<double> Ah = scale_operator(c, s, D, stored_face_coefs(C.Cp), C.Cp, C.diag, C.rs, C.Ch);
     launch_interface_values(s, D, C.n_if_entries, C.cif, C.rs, C.if_val);
     pcg_fp64(c, D, P, SolveArrays{stored_face_coefs(C.Cp), C.diag, C.b, C.x, C.n_slots, Ah}, tol, &ls);
@@ -1708,7 +1723,7 @@ amrfld_status solve_composite(amrfld_ctx* c, double dt, double tol) {
   st.rnorm0 = h.rnorm0;
   st.bnorm = h.bnorm;
   st.sweep_blocks = P.G;
-  st.launch_blocks = resident ? c->L(base).res.d.n_blocks : P.G;
+  st.launch_blocks = resident ? R.n_blocks : P.G;
   float ms = 0.f, pms = 0.f;
   check(hipEventSynchronize(c->ev[3]), "event");  // passed already: the scalars were read after it
   check(hipEventElapsedTime(&ms, c->ev[0], c->ev[3]), "event");

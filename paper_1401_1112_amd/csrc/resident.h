@@ -40,11 +40,15 @@ struct ResPlanDev {
   // [n_prob] that number once a block has begun to write the result of a solve; then the
   // flag of a wait that timed out
   unsigned* epoch = nullptr;
-  double* coefs = nullptr;              // streamed coefficients, resident_coefs() of them
+  // streamed coefficients, resident_coefs() of them; of a system with couplings between
+  // levels (coupled) ResPlanHost::couplings, then ::coarse.  (One pointer and the sizes in
+  // 32 bits: with larger arguments the compiler spills more of the loops.)
+  void* extra = nullptr;
   int n_parts = 0, n_units = 0, n_prob = 0;
   int n_blocks = 0;
   int max_slots = 0;
-  size_t lds = 0;  // bytes of LDS, resident_lds()
+  int lds = 0;  // bytes of LDS, resident_lds()
+  int coupled = 0;
 };
 
 struct ResArgs {
@@ -70,7 +74,7 @@ struct ResArgs {
 
 // Whether a block's share of this plan fits its registers and LDS.
 bool resident_fits(const ResPlanDev& R);
-size_t resident_lds(const std::vector<ResPart>& parts, int max_slots, int n_prob);
+int resident_lds(const std::vector<ResPart>& parts, int max_slots, int n_prob);
 // Doubles of the streamed coefficients of a plan (0: none of its shares streams them).
 size_t resident_coefs(const ResPlanDev& R);
 // All blocks have to be on the device together (at most one per compute unit): no other

@@ -20,6 +20,14 @@
 // (r^_{k+1}, r^_{k+1}) itself is summed with the next exchange and used for alpha_{k+1}:
 // the step along p^ stays a line search, and no error is carried on.
 //
+// The composite system of several levels: a finer cell's face towards a coarser leaf is
+// an out-of-oct face like any other, its halo cell the leaf's value; a leaf's face
+// towards finer cells is a unit with their four values, added to its row by its thread
+// with coefficients from LDS.  All couplings go through the exchange, also those within
+// a share.  Four levels of 353 k slots, 400 iterations in four solves: 13.1 ms with
+// sweeps and a kernel for the couplings, 4.7 so (10.5 us per iteration, of which the
+// exchange of about four times the faces of a level of this size is the largest part).
+//
 // Every exchanged word carries the number of its exchange (a 64-bit word holds data
 // and stamp), so a reader polls the data itself: no barrier, no flag after the data and
 // no cache write-back stand between a value's store and its use.  Two buffers
@@ -342,18 +350,21 @@ struct State {
   unsigned face;  // bit u: pair u has a cell on a face between shares
 };
 
-// With the coefficients in registers too and the diagonal in LDS, or (kStream: shares of
+// What a share's loops hold where.
+enum ResMode { kHeld, kStreamed, kCoupled };
+
+// With the coefficients in registers too and the diagonal in LDS, or (kStreamed: shares of
 // more than 5120 slots, whose coefficients do not fit) with the diagonal in registers and
 // the coefficients read in every iteration, from memory that this block alone uses: 44
 // bytes per slot that L2 and the last-level cache largely hold, against the 115 of a
 // sweep.  What ends it at 8192 slots is the register file.  256 patches of 16.9 M cells,
 // the 7.8 M of five of them in streamed shares (128^3 and less): 42.8 ms for two steps
 // against 69 with sweeps of those five.
-template <typename T, int NP, bool kStream>
+template <typename T, int NP, ResMode kMode>
 struct Regs;
 
 template <typename T, int NP>
-struct Regs<T, NP, false> : State<T, NP> {
+struct Regs<T, NP, kHeld> : State<T, NP> {
   typedef typename Pair<T>::type T2;
   Coefs<T> c[NP];
   T* d;
@@ -385,7 +396,7 @@ struct Regs<T, NP, false> : State<T, NP> {
 };
 
 template <typename T, int NP>
-struct Regs<T, NP, true> : State<T, NP> {
+struct Regs<T, NP, kStreamed> : State<T, NP> {
   typedef typename Pair<T>::type T2;
   T dr[NP][2];
   T2* cs;  // five arrays of NP * 512 pairs (ciy, ciz, cox, coy, coz), then cix
@@ -410,6 +421,14 @@ struct Regs<T, NP, true> : State<T, NP> {
     keep(dr[u][0]);
     keep(dr[u][1]);
   }
+};
+
+// As kHeld, and couplings to finer cells.
+template <typename T, int NP>
+struct Regs<T, NP, kCoupled> : Regs<T, NP, kHeld> {
+  unsigned cu[NP];  // of a pair: first of its coarse units (16 bits), units of either slot (8 bits each)
+  T* cv;            // [4 coarse units]: scaled coefficients of their finer cells (in LDS)
+  int uc0;          // halo position of the first coarse unit
 };
 
 // LDS arrays of a share.
@@ -452,27 +471,48 @@ __device__ __forceinline__ void apply(const State<T, NP>& q, const Coefs<T>& c, 
 }
 
 // f(u, v, A^ v) for every pair; streamed coefficients are loaded one pair ahead.
-template <typename T, int NP, bool kStream, class F>
-__device__ __forceinline__ void apply_all(const Regs<T, NP, kStream>& q, const T* p, F f) {
+template <typename T, int NP, ResMode kMode, class F>
+__device__ __forceinline__ void apply_all(const Regs<T, NP, kMode>& q, const T* p, F f) {
   Coefs<T> c = q.coefs(0);
 #pragma unroll
   for (int u = 0; u < NP; ++u) {
     __builtin_amdgcn_sched_barrier(0);
     Coefs<T> next;
-    if (kStream && u + 1 < NP) next = q.coefs(u + 1);
+    if (kMode == kStreamed && u + 1 < NP) next = q.coefs(u + 1);
     T pv[2], av[2];
     apply(q, c, p, u, pv, av);
+    if constexpr (kMode == kCoupled) {
+      if (q.cu[u]) {
+        const int k1 = int(q.cu[u] & 0xffffu) + int((q.cu[u] >> 16) & 0xffu), k2 = k1 + int(q.cu[u] >> 24);
+        const T* ph = p + 2 * NP * kResThreads + q.uc0;
+        for (int k = int(q.cu[u] & 0xffffu); k < k2; ++k) {
+          T t = T(0);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) t = fma(q.cv[4 * k + e], ph[4 * k + e], t);
+          if (k < k1) av[0] -= t;
+          else av[1] -= t;
+        }
+      }
+    }
     f(u, pv, av);
-    if (u + 1 < NP) c = kStream ? next : q.coefs(u + 1);
+    if (u + 1 < NP) c = kMode == kStreamed ? next : q.coefs(u + 1);
   }
 }
 
 // The values of pair u that lie on faces between shares to the block's export list
 // (ordered like its halo cells).
-template <typename T, int NP>
-__device__ __forceinline__ void stage(const State<T, NP>& q, T* ex, int u, T v0, T v1) {
+template <typename T, int NP, ResMode kMode>
+__device__ __forceinline__ void stage(const Regs<T, NP, kMode>& q, T* ex, int u, T v0, T v1) {
   constexpr int kCap = 2 * NP * kResThreads;
   typedef typename Pair<T>::type T2;
+  if constexpr (kMode == kCoupled) {
+    if (q.cu[u]) {
+      const int k1 = int(q.cu[u] & 0xffffu) + int((q.cu[u] >> 16) & 0xffu), k2 = k1 + int(q.cu[u] >> 24);
+      for (int k = int(q.cu[u] & 0xffffu); k < k2; ++k)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) ex[q.uc0 + 4 * k + e] = k < k1 ? v0 : v1;
+    }
+  }
   if (!((q.face >> u) & 1u)) return;
   const int x0 = int(q.px[u] & 0xffffu) - kCap, x1 = int(q.px[u] >> 16) - kCap;
   const int y = int(q.pyz[u] & 0xffffu) - kCap, z = int(q.pyz[u] >> 16) - kCap;
@@ -501,8 +541,8 @@ struct CgResult {
 // CG iterations from r^ = q.r, p^ in lds.p (own and halo), r^ of the halo in lds.rh.
 // thresh, tol, max_iter, linf_test: the stopping rule of Sect. 3.3.4; dmin: smallest
 // diagonal entry.  false: a wait timed out.
-template <typename T, int NP, bool kStream>
-__device__ __forceinline__ bool cg_loop(Exchange& X, Regs<T, NP, kStream>& q, const Lds<T>& lds, Shared& S, double thresh,
+template <typename T, int NP, ResMode kMode>
+__device__ __forceinline__ bool cg_loop(Exchange& X, Regs<T, NP, kMode>& q, const Lds<T>& lds, Shared& S, double thresh,
                                         double tol, int max_iter, bool linf_test, double dmin, CgResult& out) {
   typedef typename Pair<T>::type T2;
   constexpr int kCap = 2 * NP * kResThreads;
@@ -592,15 +632,20 @@ __device__ __forceinline__ bool cg_loop(Exchange& X, Regs<T, NP, kStream>& q, co
 }
 
 // The solve of one share of one problem.  false: a wait timed out.
-template <int NP, bool kStream>
+template <int NP, ResMode kMode>
 __device__ __forceinline__ bool solve_part(const DevLevel& L, const ResPlanDev& R, const ResArgs& A, int my_part,
                                            unsigned char* dyn, Shared& S) {
   constexpr int kCap = 2 * NP * kResThreads;
-  const ResPart me = R.parts[my_part];
+  my_part = __builtin_amdgcn_readfirstlane(my_part);
+  ResPart me;  // (alike in every lane, which the compiler does not see of loaded values)
+#pragma unroll
+  for (int k = 0; k < int(sizeof(ResPart) / sizeof(int)); ++k)
+    reinterpret_cast<int*>(&me)[k] = __builtin_amdgcn_readfirstlane(reinterpret_cast<const int*>(R.parts + my_part)[k]);
   const int ns = me.n_slots, n = L.n_slots;
   const int nh = 4 * me.n_units;
   Lds<double> lds;
   lds.p = reinterpret_cast<double*>(dyn);
+
   lds.rh = lds.p + kCap + nh;
   lds.ex = lds.rh + nh;
   lds.partner = reinterpret_cast<int*>(lds.ex + nh);
@@ -623,11 +668,15 @@ __device__ __forceinline__ bool solve_part(const DevLevel& L, const ResPlanDev& 
   // start: rs = diag^-1/2 exchanged, the scaled operator; x^_0 = x_0 / rs exchanged,
   // r^_0 = rs b - A^ x^_0 exchanged.  Every array is read once, in order; a thread's pairs
   // past the share's end read its first pair and get rs = 0, hence a zero operator.
-  Regs<double, NP, kStream> q;
+  Regs<double, NP, kMode> q;
   q.face = 0;
-  if constexpr (kStream)
-    q.cs = reinterpret_cast<double2*>(R.coefs + size_t(blockIdx.x) * kResStreamDoubles);
+  if constexpr (kMode == kStreamed)
+    q.cs = reinterpret_cast<double2*>(static_cast<double*>(R.extra) + size_t(blockIdx.x) * kResStreamDoubles);
   else q.d = lds_d;
+  if constexpr (kMode == kCoupled) {
+    q.cv = lds_d + kCap;
+    q.uc0 = 4 * (me.n_units - me.n_coarse);
+  }
   double v[kSums] = {0.0, 0.0, 0.0, 0.0}, m = -DBL_MAX;
   auto slot = [&](int l) -> int64_t { return me.slot0 + (l < ns ? l : 0); };
   auto pair = [&](const double* a, int64_t i) { return *reinterpret_cast<const double2*>(a + i); };
@@ -658,6 +707,10 @@ __device__ __forceinline__ bool solve_part(const DevLevel& L, const ResPlanDev& 
       q.px[u] = x0 | (x1 << 16);
       q.pyz[u] = y | (z << 16);
       if (max(max(x0, x1), max(y, z)) >= unsigned(kCap)) q.face |= 1u << u;
+      if constexpr (kMode == kCoupled) {
+        q.cu[u] = valid ? static_cast<const unsigned*>(R.extra)[(me.slot0 + l) >> 1] : 0u;
+        keep(q.cu[u]);
+      }
       keep(q.px[u]);
       keep(q.pyz[u]);
       stage(q, lds.ex, u, rs.x, rs.y);
@@ -668,6 +721,15 @@ __device__ __forceinline__ bool solve_part(const DevLevel& L, const ResPlanDev& 
   const double dmin = -m;
   take_halo(lds.p + kCap);
   __syncthreads();
+  if constexpr (kMode == kCoupled) {
+    for (int k = tid(); k < 4 * me.n_coarse; k += kResThreads) {
+      const int2 c = reinterpret_cast<const int2*>(static_cast<const unsigned*>(R.extra) + n / 2)[me.unit0 + me.n_units - me.n_coarse + (k >> 2)];
+      const int d = c.y & 7, a = d >> 1, t0 = a == 0 ? 1 : 0, t1 = a == 2 ? 1 : 2;
+      const int f = (c.y & ~7) | ((d & 1) << a) | ((k & 1) << t0) | (((k >> 1) & 1) << t1);
+      q.cv[k] = L.cif[size_t(a) * n + f] * (lds.p[c.x] * lds.p[kCap + q.uc0 + k]);
+    }
+    __syncthreads();
+  }
   // (one axis after the other, so that the loads in flight are few registers)
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
@@ -860,13 +922,13 @@ __device__ __forceinline__ bool solve_part(const DevLevel& L, const ResPlanDev& 
   return true;
 }
 
-template <int NP, bool kStream>
+template <int NP, ResMode kMode>
 __global__ __launch_bounds__(kResThreads) void k_cg_resident(DevLevel L, ResPlanDev R, ResArgs A) {
   extern __shared__ __align__(16) unsigned char res_lds[];
   __shared__ Shared S;
   const int b = int(blockIdx.x);
   for (int k = R.task0[b]; k < R.task0[b + 1]; ++k) {
-    if (!solve_part<NP, kStream>(L, R, A, R.task[k], res_lds, S)) {
+    if (!solve_part<NP, kMode>(L, R, A, R.task[k], res_lds, S)) {
       if (threadIdx.x == 0) st_word32(R.epoch + 2 * R.n_prob, 1u);
       return;
     }
@@ -884,13 +946,13 @@ __global__ __launch_bounds__(kResThreads) void k_cg_resident_batch(DevLevel L, R
     const int part = R.task[k];
     bool ok;
     switch ((R.parts[part].n_slots + 2 * kResThreads - 1) / (2 * kResThreads)) {
-      case 1: ok = solve_part<1, false>(L, R, A, part, res_lds, S); break;
-      case 2: ok = solve_part<2, false>(L, R, A, part, res_lds, S); break;
-      case 3: ok = solve_part<3, false>(L, R, A, part, res_lds, S); break;
-      case 4: ok = solve_part<4, false>(L, R, A, part, res_lds, S); break;
-      case 5: ok = solve_part<5, false>(L, R, A, part, res_lds, S); break;
-      case 6: ok = solve_part<6, true>(L, R, A, part, res_lds, S); break;
-      default: ok = solve_part<8, true>(L, R, A, part, res_lds, S);
+      case 1: ok = solve_part<1, kHeld>(L, R, A, part, res_lds, S); break;
+      case 2: ok = solve_part<2, kHeld>(L, R, A, part, res_lds, S); break;
+      case 3: ok = solve_part<3, kHeld>(L, R, A, part, res_lds, S); break;
+      case 4: ok = solve_part<4, kHeld>(L, R, A, part, res_lds, S); break;
+      case 5: ok = solve_part<5, kHeld>(L, R, A, part, res_lds, S); break;
+      case 6: ok = solve_part<6, kStreamed>(L, R, A, part, res_lds, S); break;
+      default: ok = solve_part<8, kStreamed>(L, R, A, part, res_lds, S);
     }
     if (!ok) {
       if (threadIdx.x == 0) st_word32(R.epoch + 2 * R.n_prob, 1u);
@@ -911,7 +973,7 @@ int pairs_of(int n_slots, int n_prob) {
 hipError_t launch_kernel(void (*f)(DevLevel, ResPlanDev, ResArgs), hipStream_t s, const DevLevel& L,
                          const ResPlanDev& R, const ResArgs& A) {
   const hipError_t e =
-      hipFuncSetAttribute(reinterpret_cast<const void*>(f), hipFuncAttributeMaxDynamicSharedMemorySize, int(R.lds));
+      hipFuncSetAttribute(reinterpret_cast<const void*>(f), hipFuncAttributeMaxDynamicSharedMemorySize, R.lds);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(f, dim3(R.n_blocks), dim3(kResThreads), R.lds, s, L, R, A);
   return hipGetLastError();
@@ -920,17 +982,18 @@ hipError_t launch_kernel(void (*f)(DevLevel, ResPlanDev, ResArgs), hipStream_t s
 }  // namespace
 
 // Of one share: the places of a vector and its halo, r^ and exchanged values of the halo,
-// the partner units and, where the coefficients are in registers, the diagonal.  The
+// the partner units and, where the coefficients are in registers, the diagonal; the
+// coefficients of the finer cells.  The
 // shares of one problem run with as many pairs as its largest.
-size_t resident_lds(const std::vector<ResPart>& parts, int max_slots, int n_prob) {
+int resident_lds(const std::vector<ResPart>& parts, int max_slots, int n_prob) {
   size_t most = 0;
   for (const ResPart& p : parts) {
     const int np = pairs_of(n_prob > 1 ? p.n_slots : max_slots, n_prob);
     const size_t cap = 2 * size_t(np) * kResThreads, nh = 4 * size_t(p.n_units);
-    most = std::max(most, (cap + 3 * nh + (np <= kResPairs ? cap : 0)) * sizeof(double) +
+    most = std::max(most, (cap + 3 * nh + (np <= kResPairs ? cap : 0) + 4 * size_t(p.n_coarse)) * sizeof(double) +
                               size_t((p.n_units + 1) & ~1) * sizeof(int));
   }
-  return most;
+  return int(std::min<size_t>(most, 1u << 30));
 }
 
 size_t resident_coefs(const ResPlanDev& R) {
@@ -938,20 +1001,30 @@ size_t resident_coefs(const ResPlanDev& R) {
 }
 
 bool resident_fits(const ResPlanDev& R) {
-  return R.n_parts > 0 && R.max_slots <= kResMaxSlots && R.lds <= kLdsLimit;
+  return R.n_parts > 0 && R.max_slots <= kResMaxSlots && size_t(R.lds) <= kLdsLimit;
 }
 
 hipError_t launch_resident(hipStream_t s, const DevLevel& L, const ResPlanDev& R, const ResArgs& A) {
   if (R.n_prob > 1) return launch_kernel(&k_cg_resident_batch, s, L, R, A);
+  if (R.coupled) {
+    switch (pairs_of(R.max_slots, 1)) {
+      case 1: return launch_kernel(&k_cg_resident<1, kCoupled>, s, L, R, A);
+      case 2: return launch_kernel(&k_cg_resident<2, kCoupled>, s, L, R, A);
+      case 3: return launch_kernel(&k_cg_resident<3, kCoupled>, s, L, R, A);
+      case 4: return launch_kernel(&k_cg_resident<4, kCoupled>, s, L, R, A);
+      case 5: return launch_kernel(&k_cg_resident<5, kCoupled>, s, L, R, A);
+    }
+    return hipErrorNotSupported;
+  }
   switch (pairs_of(R.max_slots, 1)) {
-    case 1: return launch_kernel(&k_cg_resident<1, false>, s, L, R, A);
-    case 2: return launch_kernel(&k_cg_resident<2, false>, s, L, R, A);
-    case 3: return launch_kernel(&k_cg_resident<3, false>, s, L, R, A);
-    case 4: return launch_kernel(&k_cg_resident<4, false>, s, L, R, A);
-    case 5: return launch_kernel(&k_cg_resident<5, false>, s, L, R, A);
-    case 6: return launch_kernel(&k_cg_resident<6, true>, s, L, R, A);
-    case 7: return launch_kernel(&k_cg_resident<7, true>, s, L, R, A);
-    case 8: return launch_kernel(&k_cg_resident<8, true>, s, L, R, A);
+    case 1: return launch_kernel(&k_cg_resident<1, kHeld>, s, L, R, A);
+    case 2: return launch_kernel(&k_cg_resident<2, kHeld>, s, L, R, A);
+    case 3: return launch_kernel(&k_cg_resident<3, kHeld>, s, L, R, A);
+    case 4: return launch_kernel(&k_cg_resident<4, kHeld>, s, L, R, A);
+    case 5: return launch_kernel(&k_cg_resident<5, kHeld>, s, L, R, A);
+    case 6: return launch_kernel(&k_cg_resident<6, kStreamed>, s, L, R, A);
+    case 7: return launch_kernel(&k_cg_resident<7, kStreamed>, s, L, R, A);
+    case 8: return launch_kernel(&k_cg_resident<8, kStreamed>, s, L, R, A);
   }
   return hipErrorNotSupported;
 }

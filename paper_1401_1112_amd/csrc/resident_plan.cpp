@@ -18,7 +18,7 @@ double res_cost(int n_slots, int group) {
 }
 
 ResPlanHost build_res_plan(const std::vector<ResProblem>& probs, const std::vector<int>& group, int n_blocks,
-                           const int32_t* nbr, int64_t n_oct_table) {
+                           const int32_t* nbr, int64_t n_oct_table, const int32_t* cnb, const int32_t* child) {
   ResPlanHost h;
   std::vector<int32_t> part_of(n_oct_table, -1);
   for (size_t q = 0; q < probs.size(); ++q) {
@@ -45,8 +45,31 @@ ResPlanHost build_res_plan(const std::vector<ResProblem>& probs, const std::vect
     for (int64_t o = p.slot0 / 8; o < (int64_t(p.slot0) + p.n_slots) / 8; ++o)
       for (int d = 0; d < 6; ++d) {
         const int32_t nb = nbr[6 * o + d];
-        if (nb >= 0 && part_of[nb] != me) h.unit_of[6 * o + d] = n_units++;
+        if (nb >= 0 ? part_of[nb] != me : cnb && cnb[6 * o + d] >= 0) h.unit_of[6 * o + d] = n_units++;
       }
+    if (cnb) {
+      // the leaves' faces towards finer cells, slot by slot
+      const int32_t first = n_units;
+      h.couplings.resize(4 * n_oct_table, 0u);
+      for (int64_t i = p.slot0; i < int64_t(p.slot0) + p.n_slots; ++i) {
+        if (child[i] != -1) continue;
+        const int pos = int(i & 7);
+        for (int d = 0; d < 6; ++d) {
+          const int a = d >> 1, bit = 1 << a;
+          const int32_t nb = nbr[6 * (i >> 3) + d];
+          const int64_t j = ((pos >> a) & 1) != (d & 1) ? i ^ bit : nb >= 0 ? (int64_t(nb) << 3) | (pos ^ bit) : -1;
+          if (j < 0 || child[j] < 0) continue;
+          uint32_t& c = h.couplings[i >> 1];
+          if (c == 0) c = uint32_t(n_units - first);
+          c += i & 1 ? 1u << 24 : 1u << 16;
+          h.coarse.resize(2 * size_t(n_units) + 2, 0);
+          h.coarse[2 * size_t(n_units)] = int32_t(i - p.slot0);
+          h.coarse[2 * size_t(n_units) + 1] = 8 * child[j] + (d ^ 1);
+          ++n_units;
+        }
+      }
+      p.n_coarse = n_units - first;
+    }
     p.n_units = n_units - p.unit0;
     h.max_units = std::max(h.max_units, p.n_units);
   }
@@ -55,8 +78,15 @@ ResPlanHost build_res_plan(const std::vector<ResProblem>& probs, const std::vect
     for (int64_t o = p.slot0 / 8; o < (int64_t(p.slot0) + p.n_slots) / 8; ++o)
       for (int d = 0; d < 6; ++d) {
         const int32_t u = h.unit_of[6 * o + d];
-        if (u >= 0) h.partner[u] = h.unit_of[6 * int64_t(nbr[6 * o + d]) + (d ^ 1)];
+        if (u >= 0 && nbr[6 * o + d] >= 0) h.partner[u] = h.unit_of[6 * int64_t(nbr[6 * o + d]) + (d ^ 1)];
       }
+  if (cnb) h.coarse.resize(2 * size_t(n_units), 0);
+  for (const ResPart& p : h.parts)
+    for (int32_t u = p.unit0 + p.n_units - p.n_coarse; u < p.unit0 + p.n_units; ++u) {
+      const int32_t f = h.unit_of[6 * int64_t(h.coarse[2 * u + 1] >> 3) + (h.coarse[2 * u + 1] & 7)];
+      h.partner[u] = f;
+      h.partner[f] = u;
+    }
   h.places.assign(8 * n_oct_table, 0);
   for (const ResPart& p : h.parts)
     for (int64_t o = p.slot0 / 8; o < (int64_t(p.slot0) + p.n_slots) / 8; ++o)
@@ -64,8 +94,8 @@ ResPlanHost build_res_plan(const std::vector<ResProblem>& probs, const std::vect
         const unsigned own = unsigned(8 * o + 2 * k - p.slot0);
         auto place = [&](int d, unsigned self, unsigned inside, unsigned cell) -> unsigned {
           const int32_t nb = nbr[6 * o + d], u = h.unit_of[6 * o + d];
-          if (nb < 0) return self;
-          return u >= 0 ? kResHalo | unsigned(4 * (u - p.unit0)) + cell : unsigned(8 * int64_t(nb) - p.slot0) + inside;
+          if (u >= 0) return kResHalo | unsigned(4 * (u - p.unit0)) + cell;
+          return nb < 0 ? self : unsigned(8 * int64_t(nb) - p.slot0) + inside;
         };
         const int y = k & 1, z = k >> 1;
         const unsigned x0 = place(0, own, unsigned(2 * k + 1), unsigned(k)), x1 = place(1, own + 1, unsigned(2 * k), unsigned(k));

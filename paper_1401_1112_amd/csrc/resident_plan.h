@@ -15,7 +15,7 @@ struct ResPart {
   int unit0, n_units;  // its halo units: faces of its octs whose neighbour oct lies in another share
   int prob;            // the problem
   int part0, group;    // the problem's shares are [part0, part0 + group)
-  int pad_;
+  int n_coarse;        // the last of its units: its cells' faces towards finer cells
 };
 
 struct ResPlanHost {
@@ -32,6 +32,14 @@ struct ResPlanHost {
   // partner[u]: the unit of the same face seen from the other side (the neighbour
   // share writes its four cells there)
   std::vector<int32_t> partner;
+  // Couplings between levels (empty: none).  A unit of a face towards a coarser leaf holds
+  // that leaf's value four times and is an out-of-oct neighbour like any other.  A coarse
+  // unit holds the four finer cells on one face of a leaf: coarse[2 u] is the leaf's
+  // position in the share, coarse[2 u + 1] eight times the finer oct plus the direction
+  // of its face.  couplings[k] of the slots 2 k and 2 k + 1: the first of their coarse
+  // units (16 bits), the number of units of either (8 bits each), 0 where there is none.
+  std::vector<int32_t> coarse;
+  std::vector<uint32_t> couplings;
   // blocks: block b works on the shares task[task0[b] .. task0[b + 1]) in that order
   std::vector<int32_t> task0, task;
   int max_slots = 0, max_units = 0;  // of one share
@@ -57,8 +65,11 @@ double res_cost(int n_slots, int group);
 // Plans problems (listed in the order the blocks work on them) on n_blocks blocks;
 // group[q] shares of problem q, all on different blocks.  nbr: 6 per oct, as in
 // LevelTables (the neighbour of o in direction d has o as its neighbour in d ^ 1).
-// n_oct_table: rows of nbr.
+// n_oct_table: rows of nbr.  cnb, child (not null: a system with couplings between levels):
+// the coarser leaf behind each face without a neighbour oct, -1 where there is none; the
+// oct that refines each slot, negative where there is none, -1 where the slot is a leaf.
 ResPlanHost build_res_plan(const std::vector<ResProblem>& probs, const std::vector<int>& group, int n_blocks,
-                           const int32_t* nbr, int64_t n_oct_table);
+                           const int32_t* nbr, int64_t n_oct_table, const int32_t* cnb = nullptr,
+                           const int32_t* child = nullptr);
 
 }  // namespace amrfld

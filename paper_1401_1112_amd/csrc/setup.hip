@@ -202,7 +202,8 @@ __global__ __launch_bounds__(kBlock) void k_assemble(
 // leaf C = (2/3) A; a face shared with a refined same-level neighbour couples to its
 // four finer cells, each with 2^(3-ndim) A / 3 = A / 3 (K_f with that finer cell).
 // The coefficient of a fine-to-coarse pair is stored once, at the finer cell
-// (V_f (2/3) A_f, equal to V_c A_c / 3), and read by both rows.
+// (V_f (2/3) A_f, equal to V_c A_c / 3), and read by both rows.  With Cm (the resident
+// form) it is the coefficient of the finer cell's face as well.
 __global__ __launch_bounds__(kBlock) void k_assemble_composite(
     DevLevel L, const double* __restrict__ K, const double* __restrict__ E, const double* __restrict__ rho,
     CouplingParams cp, OuterBC ob, double dt, double* __restrict__ Cp, double* __restrict__ Cm,
@@ -252,6 +253,7 @@ __global__ __launch_bounds__(kBlock) void k_assemble_composite(
         const double C = (2.0 / 3.0) * harmonic(Ki, K[c]) * coef;
         d += C;
         cf[a] = V * C;
+        if (Cm) (side ? cplus : cminus)[a] = V * C;
       } else if ((ob.mask >> dir) & 1u) {  // Dirichlet value held at the box face, dx / 2 away
         const double v = ob.val[dir];
         const double C = 2.0 * harmonic(Ki, held_K(P.kmode, P.K_const, P.K_exp, P.kappa_R, P.c_light, rho[i], v)) *

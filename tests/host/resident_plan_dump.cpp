@@ -1,8 +1,10 @@
 // Test harness (host only): plans the resident CG of problems read from a binary file
 // and prints the plan as text.  Input: int32 n_probs, n_blocks, target slots, then per
-// problem int64 first oct and octs, then int64 rows and int32 nbr[rows][6].  Output:
+// problem int64 first oct and octs, then int64 rows and int32 nbr[rows][6], and of a
+// system with couplings between levels int32 cnb[rows][6] and child[8 rows].  Output:
 // the shares (slot0 n_slots unit0 n_units prob part0 group), unit_of, partner, task0, task,
-// the largest share and its units, places.
+// the largest share and its units, places; with couplings the shares' coarse units,
+// coarse, couplings.
 #include <cstdio>
 #include <vector>
 
@@ -28,8 +30,13 @@ int main(int argc, char** argv) {
   if (std::fread(&rows, 8, 1, f) != 1) return 2;
   std::vector<int32_t> nbr(6 * rows);
   if (std::fread(nbr.data(), 4, nbr.size(), f) != nbr.size()) return 2;
+  std::vector<int32_t> cnb(6 * rows), child(8 * rows);
+  const bool coupled = std::fread(cnb.data(), 4, cnb.size(), f) == cnb.size() &&
+                       std::fread(child.data(), 4, child.size(), f) == child.size();
   std::fclose(f);
-  const amrfld::ResPlanHost h = amrfld::build_res_plan(probs, group, head[1], nbr.data(), rows);
+  const amrfld::ResPlanHost h =
+      amrfld::build_res_plan(probs, group, head[1], nbr.data(), rows, coupled ? cnb.data() : nullptr,
+                             coupled ? child.data() : nullptr);
   auto line = [](const std::vector<int32_t>& v) {
     for (size_t i = 0; i < v.size(); ++i) std::printf(i ? " %d" : "%d", v[i]);
     std::printf("\n");
@@ -44,5 +51,12 @@ int main(int argc, char** argv) {
   line(h.task);
   std::printf("%d %d\n", h.max_slots, h.max_units);
   line(std::vector<int32_t>(h.places.begin(), h.places.end()));
+  if (coupled) {
+    std::vector<int32_t> n;
+    for (const auto& p : h.parts) n.push_back(p.n_coarse);
+    line(n);
+    line(h.coarse);
+    line(std::vector<int32_t>(h.couplings.begin(), h.couplings.end()));
+  }
   return 0;
 }

@@ -161,3 +161,92 @@ def test_plan(harness, tmp_path, case):
                     else:
                         got = me[0] + place + j
                     assert got == want, (case, o, k, d)
+
+
+def _composite_tables(h):
+    """Neighbour octs, coarser leaves and refining octs of all levels one after another,
+    each level padded to whole tiles of 256 slots."""
+    octs, base = {}, {}
+    n = 0
+    for l in h.levels:
+        o = np.asarray(h.octs[l], dtype=np.int64)
+        octs[l] = o[np.argsort(_morton(o))]
+        base[l] = n
+        n += (len(o) + 31) // 32 * 32
+    at = {l: {tuple(o): base[l] + i for i, o in enumerate(octs[l].tolist())} for l in h.levels}
+    nbr, cnb, child = np.full((n, 6), -1), np.full((n, 6), -1), np.full(8 * n, -2)
+    for l in h.levels:
+        for (x, y, z), o in at[l].items():
+            for d, (i, j, k) in enumerate(OFF):
+                cell = (x + i, y + j, z + k)  # an oct of level l is a cell of level l - 1
+                nbr[o, d] = at[l].get(cell, -1)
+                up = at[l - 1].get(tuple(c >> 1 for c in cell), -1) if l > h.base_level else -1
+                if nbr[o, d] < 0 and up >= 0 and min(cell) >= 0:
+                    cnb[o, d] = 8 * up + (cell[0] & 1) + 2 * (cell[1] & 1) + 4 * (cell[2] & 1)
+            for pos in range(8):
+                cell = (2 * x + (pos & 1), 2 * y + ((pos >> 1) & 1), 2 * z + (pos >> 2))
+                child[8 * o + pos] = at[l + 1].get(cell, -1) if l < h.max_level else -1
+    return nbr.astype(np.int32), cnb.astype(np.int32), child.astype(np.int32)
+
+
+@pytest.mark.parametrize("n_blocks,target", [(2, 4096), (7, 512), (64, 64)])
+def test_couplings_between_levels(harness, tmp_path, n_blocks, target):
+    nbr, cnb, child = _composite_tables(random_balanced_hierarchy(7, 2, 5, 0.5))
+    assert (cnb >= 0).any()
+    path = tmp_path / "c.bin"
+    with open(path, "wb") as f:
+        f.write(struct.pack("<iiiqqq", 1, n_blocks, target, 0, len(nbr), len(nbr)))
+        f.write(nbr.tobytes() + cnb.tobytes() + child.tobytes())
+    run = subprocess.run([harness, str(path)], capture_output=True, text=True)
+    assert run.returncode == 0, run.stderr[-3000:]
+    arr = [np.array(x.split(), dtype=np.int64) for x in run.stdout.splitlines()]
+    parts, unit_of, partner, places = arr[0].reshape(-1, 7), arr[1].reshape(-1, 6), arr[2], arr[6] & 0xffffffff
+    n_coarse, coarse, couplings = arr[7], arr[8].reshape(-1, 2), arr[9] & 0xffffffff
+    part_of = np.concatenate([np.full(p[1], k) for k, p in enumerate(parts)])
+    assert np.array_equal(partner[partner], np.arange(len(partner)))
+
+    # the slots whose values a unit sends, in its order: a finer face's four cells by the
+    # places that name the unit, a coarse unit's leaf four times
+    sends = np.full((len(partner), 4), -1)
+    reads = []  # (slot, direction, unit, cell)
+    for s in range(8 * len(nbr)):
+        k, pos, o = s >> 1, s & 7, s >> 3
+        p0, p1 = int(places[2 * k]), int(places[2 * k + 1])
+        place = [p0 >> 16 if pos & 1 else p0 & 0xffff, (p1 & 0xffff) + (pos & 1), (p1 >> 16) + (pos & 1)]
+        for a in range(3):
+            d = 2 * a + ((pos >> a) & 1)
+            assert bool(place[a] & 0x8000) == (unit_of[o, d] >= 0)
+            if place[a] & 0x8000:
+                u, c = parts[part_of[s], 2] + (place[a] & 0x7fff) // 4, place[a] & 3
+                assert u == unit_of[o, d] and sends[u, c] == -1
+                sends[u, c] = s
+                reads.append((s, d, u, c))
+    want = set()
+    for k, (p, nc) in enumerate(zip(parts, n_coarse)):
+        first = p[2] + p[3] - nc
+        for s in range(p[0], p[0] + p[1], 2):
+            w = int(couplings[s >> 1])
+            u = first + (w & 0xffff)
+            for e, m in ((s, (w >> 16) & 0xff), (s + 1, w >> 24)):
+                for v in range(u, u + m):
+                    assert coarse[v, 0] == e - p[0]
+                    sends[v] = e
+                    want.add(v)
+                u += m
+        assert want >= set(range(first, p[2] + p[3]))
+    assert len(want) == n_coarse.sum() and (sends >= 0).all()
+    for s, d, u, c in reads:
+        a = d >> 1
+        other = 8 * nbr[s >> 3, d] + ((s & 7) ^ (1 << a)) if nbr[s >> 3, d] >= 0 else cnb[s >> 3, d]
+        assert sends[partner[u], c] == other
+    # a coarse unit receives the cells on the near face of the oct that refines the leaf's
+    # neighbour, and every such face of every leaf has one
+    faces = set()
+    for v in want:
+        f, d = coarse[v, 1] >> 3, coarse[v, 1] & 7
+        a, leaf = d >> 1, sends[v, 0]
+        t = [b for b in range(3) if b != a]
+        cells = [8 * f + ((d & 1) << a) + ((c & 1) << t[0]) + ((c >> 1) << t[1]) for c in range(4)]
+        assert list(sends[partner[v]]) == cells and cnb[f, d] == leaf
+        faces.add((f, d))
+    assert len(faces) == len(want) == int((cnb >= 0).sum())
