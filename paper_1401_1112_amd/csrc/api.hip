@@ -428,7 +428,7 @@ void ensure_workspace32(amrfld_ctx* c, int64_t n) {
 // Exchange numbers start at 1 over a cleared exchange memory (stamp 0 is never awaited).
 void reset_exchange(hipStream_t s, const ResPlanDev& d) {
   launch_fill_u32(s, reinterpret_cast<unsigned*>(d.lines), int64_t(4) * d.n_parts * kResLine, 0u);
-  launch_fill_u32(s, reinterpret_cast<unsigned*>(d.halo), int64_t(32) * d.n_units, 0u);
+  launch_fill_u32(s, reinterpret_cast<unsigned*>(d.halo), 32 * d.all_units(), 0u);
   launch_fill_u32(s, d.epoch, d.n_prob, 1u);
   launch_fill_u32(s, d.epoch + d.n_prob, d.n_prob + 1, 0u);
 }
@@ -448,6 +448,7 @@ ResTables make_res_tables(hipStream_t s, const ResPlanHost& h, int n_prob) {
   ResTables r;
   r.d.n_parts = int(h.parts.size());
   r.d.n_units = int(h.partner.size());
+  r.d.n_near = h.n_near;
   r.d.n_prob = n_prob;
   r.d.n_blocks = int(h.task0.size()) - 1;
   r.d.max_slots = h.max_slots;
@@ -456,7 +457,10 @@ ResTables make_res_tables(hipStream_t s, const ResPlanHost& h, int n_prob) {
   try {
     r.d.parts = upload_const(h.parts, "resident plan", s);
     r.d.places = reinterpret_cast<const uint2*>(upload_const(h.places, "resident plan", s));
-    r.d.partner = upload_const(h.partner, "resident plan", s);
+    std::vector<int32_t> pp(h.partner);
+    pp.resize(r.d.far_units());
+    pp.insert(pp.end(), h.peers.begin(), h.peers.end());
+    r.d.partner = upload_const(pp, "resident plan", s);
     std::vector<uint32_t> c(h.couplings);
     c.insert(c.end(), h.coarse.begin(), h.coarse.end());
     r.d.coupled = !c.empty();
@@ -464,7 +468,7 @@ ResTables make_res_tables(hipStream_t s, const ResPlanHost& h, int n_prob) {
     r.d.task0 = upload_const(h.task0, "resident plan", s);
     r.d.task = upload_const(h.task, "resident plan", s);
     r.d.lines = dalloc<unsigned long long>(int64_t(2) * r.d.n_parts * kResLine, "resident exchange");
-    r.d.halo = dalloc<unsigned long long>(int64_t(16) * r.d.n_units, "resident exchange");
+    r.d.halo = dalloc<unsigned long long>(16 * r.d.all_units(), "resident exchange");
     r.d.epoch = dalloc<unsigned>(2 * n_prob + 1, "resident exchange");
     if (const size_t nc = resident_coefs(r.d)) r.d.extra = dalloc<double>(int64_t(nc), "resident coefficients");
     reset_exchange(s, r.d);
@@ -483,7 +487,7 @@ ResTables level_res_tables(const amrfld_ctx* c, const LevelTables& t) {
   if ((t.n_oct + g - 1) / g * 8 > kResMaxSlots) return ResTables{};
   ResProblem p;
   p.n_oct = t.n_oct;
-  return make_res_tables(c->stream(), build_res_plan({p}, {g}, g, t.nbr.data(), t.n_oct), 1);
+  return make_res_tables(c->stream(), build_res_plan({p}, {g}, res_blocks(g, c->n_cu), t.nbr.data(), t.n_oct), 1);
 }
 
 // The level's device tables: allocated all together (a failed allocation leaves
@@ -1115,7 +1119,7 @@ amrfld_status solve_one(amrfld_ctx* c, int level, double dt, int mode, double to
       check(hipGetLastError(), "kernels");
       if (!c->h_sc->done) resident = resident_timed_out(c, s, L.res.d);
       ls.persistent = c->o.persistent != 0;
-      ls.launch_blocks = L.res.d.n_blocks;
+      ls.launch_blocks = L.res.d.n_parts;
       if (c->o.time_sweeps > 0) {
         ls.n_timed = c->o.precision == AMRFLD_MIXED ? c->h_sc->inner_total : c->h_sc->iter;
         ls.sweep_ms = c->h_sc->loop_ms;
@@ -1386,7 +1390,7 @@ amrfld_status advance_graph(amrfld_ctx* c, double dt_coarse, int mode, double to
     st.rnorm0 = h.rnorm0;
     st.bnorm = h.bnorm;
     st.sweep_blocks = P.G;
-    st.launch_blocks = resident ? L.res.d.n_blocks
+    st.launch_blocks = resident ? L.res.d.n_parts
                        : mixed  ? mixed_persistent_blocks(P, level_plan(c, nt, kMaxTilesPerBlock32),
                                                           c->o.persistent_per_cu)
                                 : persistent_blocks<double>(P, c->o.persistent_per_cu);
@@ -1603,7 +1607,9 @@ void build_composite_into(amrfld_ctx* c, CompositeState* C) {
     p.n_oct = C->n_oct;
     // (at least two blocks: couplings go through the exchange, also those within a share)
     const int g = std::max(2, res_group(C->n_oct, c->n_cu, 0, kResTargetSlots));
-    C->res = make_res_tables(c->stream(), build_res_plan({p}, {g}, g, nbr.data(), C->n_oct, cnb.data(), child.data()), 1);
+    C->res = make_res_tables(c->stream(), build_res_plan({p}, {g}, res_blocks(g, c->n_cu), nbr.data(), C->n_oct, cnb.data(),
+                                              child.data()),
+                          1);
   }
   launch_fill(c->stream(), C->x, n, 0.0);  // padding slots keep x = 0 (identity rows)
   launch_fill(c->stream(), C->rho, n, 1.0);
@@ -1723,7 +1729,7 @@ amrfld_status solve_composite(amrfld_ctx* c, double dt, double tol) {
   st.rnorm0 = h.rnorm0;
   st.bnorm = h.bnorm;
   st.sweep_blocks = P.G;
-  st.launch_blocks = resident ? R.n_blocks : P.G;
+  st.launch_blocks = resident ? R.n_parts : P.G;
   float ms = 0.f, pms = 0.f;
   check(hipEventSynchronize(c->ev[3]), "event");  // passed already: the scalars were read after it
   check(hipEventElapsedTime(&ms, c->ev[0], c->ev[3]), "event");

@@ -18,7 +18,7 @@ constexpr int kResPairs = 5;
 constexpr int kResBlockSlots = 2 * kResPairs * kResThreads;
 constexpr int kResMaxSlots = 16 * kResThreads;
 constexpr int kResStreamDoubles = 11 * kResMaxSlots / 2;  // the coefficients of a block
-constexpr int kResTargetSlots = 1024;  // of one share where the level has several
+constexpr int kResTargetSlots = 512;  // of one share where the level has several
 // polls of a wait before a block gives up (about a microsecond each)
 constexpr unsigned kResSpinLimit = 1u << 18;
 // of a batch, where a block may wait for others to come to a patch from their earlier ones
@@ -31,11 +31,13 @@ constexpr int kResLine = 8;   // words of the line they lie in
 struct ResPlanDev {
   const ResPart* parts = nullptr;
   const uint2* places = nullptr;  // per pair of slots: see ResPlanHost
-  const int32_t* partner = nullptr;
+  const int32_t* partner = nullptr;  // ResPlanHost::partner, then ::peers
   const int32_t* task0 = nullptr;
   const int32_t* task = nullptr;
   unsigned long long* lines = nullptr;  // [2][n_parts][kResLine]
-  unsigned long long* halo = nullptr;   // [2][n_units][4][2]
+  // [2][all_units()][4][2]: the units by their first number, padded to whole lines, where
+  // the two shares run on different XCDs, then by their second where on the same
+  unsigned long long* halo = nullptr;
   // [n_prob] next exchange number of each problem, advanced when its solve is complete;
   // [n_prob] that number once a block has begun to write the result of a solve; then the
   // flag of a wait that timed out
@@ -49,6 +51,10 @@ struct ResPlanDev {
   int max_slots = 0;
   int lds = 0;  // bytes of LDS, resident_lds()
   int coupled = 0;
+  int n_near = 0;
+
+  __host__ __device__ int far_units() const { return (n_units + 1) & ~1; }
+  __host__ __device__ int64_t all_units() const { return int64_t(far_units()) + n_near; }
 };
 
 struct ResArgs {

@@ -25,8 +25,8 @@
 // towards finer cells is a unit with their four values, added to its row by its thread
 // with coefficients from LDS.  All couplings go through the exchange, also those within
 // a share.  Four levels of 353 k slots, 400 iterations in four solves: 13.1 ms with
-// sweeps and a kernel for the couplings, 4.7 so (10.5 us per iteration, of which the
-// exchange of about four times the faces of a level of this size is the largest part).
+// sweeps and a kernel for the couplings, 4.7 so (10.5 us per iteration: shares of 1380
+// slots have 340 to 630 units, as many as shares of 4880 slots of one level).
 //
 // Every exchanged word carries the number of its exchange (a 64-bit word holds data
 // and stamp), so a reader polls the data itself: no barrier, no flag after the data and
@@ -49,11 +49,18 @@ typedef unsigned long long u64;
 
 constexpr int kWaves = kResThreads / 64;
 constexpr int kSums = 4;
+constexpr int kMaxShares = kResThreads;  // of a problem: a thread reads the words of one
 constexpr u64 kMask48 = 0xffffffffffffull;
 
 __device__ __forceinline__ u64 ld_word(const u64* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+// A store that only this XCD has to see: into its L2, which agent-scope loads on the XCD
+// read as well, and no further.
+__device__ __forceinline__ void st_word_near(u64* p, u64 v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+__device__ __forceinline__ unsigned xcc_id() { return __builtin_amdgcn_s_getreg(20 | (0 << 6) | (3 << 11)); }
 __device__ __forceinline__ void st_word(u64* p, u64 v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -129,6 +136,7 @@ struct Shared {
   double part[kWaves][kSums + 1];   // per wave: this share's sums and maximum
   double total[kWaves][kSums + 1];  // per wave: over the shares' words
   int failed;
+  unsigned char xcc[kMaxShares];  // where the problem's shares run, from the first exchange on
 };
 
 struct Exchange {
@@ -137,13 +145,15 @@ struct Exchange {
   int my_part;
   unsigned epoch;  // number of the next exchange
   unsigned spin_limit;
+  unsigned near;  // bit k: this thread's k-th word of the halo is among the near ones
+  bool one_xcd;   // all shares of the only problem run on one XCD
 
   // the words of share `part`: a 64-byte line that one store fills
   __device__ __forceinline__ u64* words(int part) const {
     return R.lines + (size_t(epoch & 1u) * R.n_parts + part) * kResLine;
   }
   __device__ __forceinline__ u64* halo(int unit) const {
-    return R.halo + (size_t(epoch & 1u) * R.n_units + unit) * 8;
+    return R.halo + (size_t(epoch & 1u) * R.all_units() + unit) * 8;
   }
 };
 
@@ -155,38 +165,67 @@ __device__ __forceinline__ unsigned half(double v, int h) { return unsigned(bits
 __device__ __forceinline__ unsigned half(float v, int) { return unsigned(__float_as_int(v)); }
 
 // The export list to the partners' halo memory: consecutive lanes store consecutive
-// words, so that one store fills a unit's line.
+// words, so that one store fills a unit's line.  Units whose partner runs on the same XCD
+// lie past far_units() and stay in its L2: 256 blocks that exchange 340 units each take
+// 3.0 us so and 5.7 through memory, 600 units 3.4 and 7.2.  (The two kinds never share a
+// cache line, nor do near units of two shares: a line is written from one XCD only.)
+// A step of four levels to 1.25 M slots: 12.1 ms with all units through memory, 10.9 so.
 template <typename T>
 __device__ __forceinline__ void put_halo(const Exchange& X, const T* ex, const int* partner) {
   constexpr int kW = kValueWords<T>, kUnit = 4 * kW;
   const u64 st = u64(X.epoch) << 32;
-  for (int w = tid(); w < kUnit * X.me.n_units; w += kResThreads)
-    st_word(X.halo(partner[w / kUnit]) + w % kUnit, st | half(ex[w / kW], w % kW));
+  u64* const h = X.halo(0);
+  const int far = X.R.far_units();
+  constexpr int kBatch = 4;  // words of a thread at a time, so that their LDS reads overlap
+  const int nw = kUnit * X.me.n_units;
+  for (int w0 = tid(); w0 < nw; w0 += kBatch * kResThreads) {
+    int to[kBatch];
+    unsigned d[kBatch];
+#pragma unroll
+    for (int k = 0; k < kBatch; ++k) {
+      const int w = min(w0 + k * kResThreads, nw - 1);
+      to[k] = partner[w / kUnit];
+      d[k] = half(ex[w / kW], w % kW);
+    }
+#pragma unroll
+    for (int k = 0; k < kBatch; ++k) {
+      u64* const p = h + (size_t(to[k]) * 8 + w0 % kUnit);
+      if (w0 + k * kResThreads >= nw) break;
+      if (to[k] >= far) st_word_near(p, st | d[k]);
+      else st_word(p, st | d[k]);
+    }
+  }
 }
 
-// The halo values of this exchange to sh, a word per lane.  Every value is stored by the
-// thread that exported the one at the same place, so sh and ex are the same memory.
-// false: a wait timed out.
-template <typename T>
+// The halo values of this exchange to sh, a word per lane, kBatch words of a thread in
+// flight.  Every value is stored by the thread that exported the one at the same place,
+// so sh and ex are the same memory.  false: a wait timed out.
+template <int kBatch, typename T>
 __device__ __forceinline__ bool get_halo(const Exchange& X, T* sh) {
-  constexpr int kW = kValueWords<T>, kBatch = 8;
+  constexpr int kW = kValueWords<T>;
   const int nw = 4 * kW * X.me.n_units;
   const u64* h = X.halo(X.me.unit0);
-  unsigned polls = 0;
+  // from a unit's place among the far ones to that among the near ones (near_base)
+  const unsigned to_near = 8u * unsigned(X.R.far_units() + ((X.me.unit0 + X.my_part + 1) & ~1) - X.me.unit0);
+  unsigned polls = 0, near = X.near;
   for (int w0 = tid(); w0 < nw; w0 += kBatch * kResThreads) {
     u64 c[kBatch];
+    // (a lane past the end polls the last word, so no lane is masked)
+    auto word = [&](int k) {
+      return ld_word(h + (unsigned(min(w0 + k * kResThreads, nw - 1)) + ((0u - ((near >> k) & 1u)) & to_near)));
+    };
 #pragma unroll
-    for (int k = 0; k < kBatch; ++k)
-      c[k] = w0 + k * kResThreads < nw ? ld_word(h + w0 + k * kResThreads) : u64(X.epoch) << 32;
+    for (int k = 0; k < kBatch; ++k) c[k] = word(k);
     for (;;) {  // words that are not there yet are read again, and no others
-      bool all = true;
+      asm volatile("" : "+v"(near));  // (no masks kept from one round to the next)
+      unsigned missing = 0;
 #pragma unroll
-      for (int k = 0; k < kBatch; ++k)
-        if (unsigned(c[k] >> 32) != X.epoch) {
-          all = false;
-          c[k] = ld_word(h + w0 + k * kResThreads);
-        }
-      if (all) break;
+      for (int k = 0; k < kBatch; ++k) {
+        const unsigned miss = unsigned(c[k] >> 32) ^ X.epoch;
+        missing |= miss;
+        if (miss) c[k] = word(k);
+      }
+      if (!missing) break;
       if (++polls > X.spin_limit) return false;
     }
 #pragma unroll
@@ -200,8 +239,16 @@ __device__ __forceinline__ bool get_halo(const Exchange& X, T* sh) {
         if (w < nw && !(w & 1)) sh[w >> 1] = of_words(mine, other);
       }
     }
+    near >>= kBatch;
   }
   return true;
+}
+template <typename T>
+__device__ __forceinline__ bool get_halo(const Exchange& X, T* sh) {
+  const int nw = 4 * kValueWords<T> * X.me.n_units;
+  if (nw <= 2 * kResThreads) return get_halo<2>(X, sh);
+  if (nw <= 4 * kResThreads) return get_halo<4>(X, sh);
+  return get_halo<8>(X, sh);
 }
 
 // The sums (k < kSums) and the maximum over the first n of the waves' rows, the same in
@@ -260,9 +307,12 @@ __device__ __forceinline__ void put_sums(const Exchange& X, double (&v)[kSums], 
     word = lane == 3 ? d2 >> 16 : word;
     word = lane == 4 ? d3 : word;
     word = lane == 5 ? (d3 >> 48) | (e << 16) : word;
-    word = lane == 6 ? e >> 32 : word;
+    word = lane == 6 ? (e >> 32) | (u64(xcc_id()) << 32) : word;
     word = (word & kMask48) | (u64(X.epoch & 0xffffu) << 48);
-    if (lane < (wide ? kResWords : kResWords - 1)) st_word(X.words(X.my_part) + lane, word);
+    if (lane < (wide ? kResWords : kResWords - 1)) {
+      if (X.one_xcd) st_word_near(X.words(X.my_part) + lane, word);
+      else st_word(X.words(X.my_part) + lane, word);
+    }
   }
 }
 
@@ -310,6 +360,7 @@ __device__ __forceinline__ bool collect(Exchange& X, double (&v)[kSums], double&
     const double a = wave_sums(v);
     if ((lane & 15) == 15) S.total[wid][((lane >> 5) & 1) | ((lane >> 3) & 2)] = a;
     if (wide) {
+      if (t < G) S.xcc[t] = (unsigned char)(w[6] >> 32);
       const double b = wave_max(t < G ? of_bits((w[5] >> 16) | (w[6] << 32)) : -DBL_MAX);
       if (lane == 0) S.total[wid][kSums] = b;
     }
@@ -622,10 +673,15 @@ __device__ __forceinline__ bool cg_loop(Exchange& X, Regs<T, NP, kMode>& q, cons
       rr += a0 + a1;
       rrd = fma(a0, double(d.x), fma(a1, double(d.y), rrd));
     }
-    for (int h = tid(); h < nh; h += kResThreads) {
-      const T rn = fma(-ta, lds.ex[h], lds.rh[h]);
-      lds.rh[h] = rn;
-      lds.p[kCap + h] = fma(tb, lds.p[kCap + h], rn);
+    for (int h = 2 * tid(); h < nh; h += 2 * kResThreads) {
+      const T2 sn = *reinterpret_cast<const T2*>(lds.ex + h);
+      T2 rn = *reinterpret_cast<const T2*>(lds.rh + h), pn = *reinterpret_cast<const T2*>(lds.p + kCap + h);
+      rn.x = fma(-ta, sn.x, rn.x);
+      rn.y = fma(-ta, sn.y, rn.y);
+      pn.x = fma(tb, pn.x, rn.x);
+      pn.y = fma(tb, pn.y, rn.y);
+      *reinterpret_cast<T2*>(lds.rh + h) = rn;
+      *reinterpret_cast<T2*>(lds.p + kCap + h) = pn;
     }
     __syncthreads();
   }
@@ -655,7 +711,7 @@ __device__ __forceinline__ bool solve_part(const DevLevel& L, const ResPlanDev& 
     if (o.converged || o.nonfinite || o.inner_total >= A.max_iter) return true;
   }
   const unsigned epoch0 = R.epoch[me.prob];
-  Exchange X{R, me, my_part, epoch0, A.spin_limit};
+  Exchange X{R, me, my_part, epoch0, A.spin_limit, 0u, false};
   for (int u = tid(); u < me.n_units; u += kResThreads) lds.partner[u] = R.partner[me.unit0 + u];
   if (threadIdx.x == 0) {
     S.failed = 0;
@@ -720,6 +776,21 @@ __device__ __forceinline__ bool solve_part(const DevLevel& L, const ResPlanDev& 
   if (!exchange(X, v, m, true, S, lds)) return false;
   const double dmin = -m;
   take_halo(lds.p + kCap);
+  // from here on units between shares on the same XCD go through its L2
+  for (int u = tid(); u < me.n_units; u += kResThreads) {
+    const int2 peer = reinterpret_cast<const int2*>(R.partner + R.far_units())[me.unit0 + u];
+    if (S.xcc[peer.y] == (unsigned char)xcc_id()) lds.partner[u] = R.far_units() + peer.x;
+  }
+  // (more than one XCD's compute units are needed where shares are larger)
+  if constexpr (NP <= 2)
+    if (R.n_prob == 1 && me.group > 1)
+      X.one_xcd = __builtin_amdgcn_readfirstlane(
+                      __syncthreads_and(tid() >= me.group || S.xcc[tid()] == (unsigned char)xcc_id())) != 0;
+  for (int k = 0; k < 32 && nh > 0 && k * kResThreads < 2 * nh + 8 * kResThreads; ++k) {
+    const int unit = min(tid() + k * kResThreads, 2 * nh - 1) >> 3;  // (the last word's past the end, as it is read there)
+    const int2 peer = reinterpret_cast<const int2*>(R.partner + R.far_units())[me.unit0 + unit];
+    if (S.xcc[peer.y] == (unsigned char)xcc_id()) X.near |= 1u << k;
+  }
   __syncthreads();
   if constexpr (kMode == kCoupled) {
     for (int k = tid(); k < 4 * me.n_coarse; k += kResThreads) {

@@ -13,6 +13,12 @@ int res_group(int64_t n_oct, int max_blocks, int max_slots, int target_slots) {
   return int(std::min<int64_t>(g, n_oct));
 }
 
+int res_blocks(int g, int n_cu) {
+  const int per = std::max(1, n_cu / 8);  // compute units of an XCD
+  const int n_xcd = (g + per - 1) / per;
+  return g == 1 ? 1 : std::min(n_cu, 8 * ((g + n_xcd - 1) / n_xcd));
+}
+
 double res_cost(int n_slots, int group) {
   return 0.6 + 0.0005 * n_slots + (group > 1 ? 2.5 + 0.012 * group : 0.0);
 }
@@ -87,6 +93,17 @@ ResPlanHost build_res_plan(const std::vector<ResProblem>& probs, const std::vect
       h.partner[u] = f;
       h.partner[f] = u;
     }
+  std::vector<int32_t> share_of(n_units);
+  for (size_t k = 0; k < h.parts.size(); ++k)
+    std::fill_n(share_of.begin() + h.parts[k].unit0, h.parts[k].n_units, int32_t(k));
+  h.n_near = ResPlanHost::near_base(n_units, int32_t(h.parts.size()));
+  h.peers.resize(2 * size_t(n_units));
+  for (int32_t u = 0; u < n_units; ++u) {
+    const int32_t k = share_of[h.partner[u]];
+    const ResPart& p = h.parts[k];
+    h.peers[2 * size_t(u)] = ResPlanHost::near_base(p.unit0, k) + (h.partner[u] - p.unit0);
+    h.peers[2 * size_t(u) + 1] = k - p.part0;
+  }
   h.places.assign(8 * n_oct_table, 0);
   for (const ResPart& p : h.parts)
     for (int64_t o = p.slot0 / 8; o < (int64_t(p.slot0) + p.n_slots) / 8; ++o)
@@ -107,23 +124,57 @@ ResPlanHost build_res_plan(const std::vector<ResProblem>& probs, const std::vect
   // Blocks: each problem goes to the `group` least loaded blocks.  Every block works on
   // its shares in the order of the problems, so the first unfinished problem always has
   // all its blocks on it: no block waits for one that waits for it.
+  // Blocks are dealt to the XCDs round-robin, and shares on the same XCD exchange through
+  // its L2: neighbouring shares go to the same XCD, as far as the loads allow.
+  struct Block {
+    double time;
+    int id;
+  };
+  auto by_xcd = [](const Block& a, const Block& b) {
+    return std::make_pair(a.id % 8, a.id) < std::make_pair(b.id % 8, b.id);
+  };
+  auto by_load = [&](const Block& a, const Block& b) { return a.time != b.time ? a.time < b.time : by_xcd(a, b); };
+  // The order in which a problem's shares are dealt to its blocks: theirs, which puts
+  // neighbours on a level on one XCD (80 to 90 % of the units of a refined level), and
+  // with couplings between levels the one that grows clusters of an XCD's size by the
+  // units shared (in order a share of the finest level has 20 % of its units there).
+  std::vector<int32_t> deal(h.parts.size());
+  for (size_t k = 0; k < deal.size(); ++k) deal[k] = int32_t(k);
+  if (cnb) {
+    const int g = int(deal.size()), size = (g + 7) / 8;
+    std::vector<std::vector<std::pair<int32_t, int32_t>>> near(g);
+    std::vector<int32_t> count(g, 0);
+    for (int k = 0; k < g; ++k) {
+      const ResPart& p = h.parts[k];
+      for (int32_t u = p.unit0; u < p.unit0 + p.n_units; ++u) ++count[share_of[h.partner[u]]];
+      for (int j = 0; j < g; ++j)
+        if (count[j]) near[k].push_back({j, count[j]}), count[j] = 0;
+    }
+    std::vector<char> used(g, 0);
+    std::vector<int64_t> gain(g, 0);
+    for (int n = 0; n < g; ++n) {
+      if (n % size == 0) std::fill(gain.begin(), gain.end(), 0);
+      int best = -1;
+      for (int k = 0; k < g; ++k)
+        if (!used[k] && (best < 0 || gain[k] > gain[best])) best = k;
+      used[best] = 1;
+      deal[n] = best;
+      for (const auto& e : near[best]) gain[e.first] += e.second;
+    }
+  }
   std::vector<std::vector<int32_t>> list(n_blocks);
-  std::vector<std::pair<double, int>> load(n_blocks);  // (time, block)
+  std::vector<Block> load(n_blocks);
   for (int b = 0; b < n_blocks; ++b) load[b] = {0.0, b};
   for (size_t q = 0, at = 0; q < probs.size(); at += size_t(group[q]), ++q) {
     const int g = group[q];
-    std::partial_sort(load.begin(), load.begin() + g, load.end());
-    // blocks are dealt to the XCDs round-robin: neighbouring shares on the same XCD
-    if (probs.size() == 1 && g % 8 == 0)
-      std::sort(load.begin(), load.begin() + g, [](const std::pair<double, int>& a, const std::pair<double, int>& b) {
-        return std::make_pair(a.second % 8, a.second) < std::make_pair(b.second % 8, b.second);
-      });
+    std::partial_sort(load.begin(), load.begin() + g, load.end(), by_load);
+    std::sort(load.begin(), load.begin() + g, by_xcd);
     double end = 0.0;  // the problem begins when the last of its blocks is free
-    for (int r = 0; r < g; ++r) end = std::max(end, load[r].first);
+    for (int r = 0; r < g; ++r) end = std::max(end, load[r].time);
     end += res_cost(h.parts[at].n_slots, g);
     for (int r = 0; r < g; ++r) {
-      list[load[r].second].push_back(int32_t(at + r));
-      load[r].first = end;
+      list[load[r].id].push_back(deal[at + r]);
+      load[r].time = end;
     }
   }
   h.task0.assign(1, 0);

@@ -32,6 +32,12 @@ struct ResPlanHost {
   // partner[u]: the unit of the same face seen from the other side (the neighbour
   // share writes its four cells there)
   std::vector<int32_t> partner;
+  // A second numbering of the units, each share's from a multiple of two on (two units
+  // fill a cache line): share k's begin at near_base(unit0, k).
+  static int32_t near_base(int32_t unit0, int32_t share) { return (unit0 + share + 1) & ~1; }
+  int32_t n_near = 0;
+  // peers[2 u], peers[2 u + 1]: the partner's number in it, and its share within the group
+  std::vector<int32_t> peers;
   // Couplings between levels (empty: none).  A unit of a face towards a coarser leaf holds
   // that leaf's value four times and is an out-of-oct neighbour like any other.  A coarse
   // unit holds the four finer cells on one face of a leaf: coarse[2 u] is the leaf's
@@ -53,11 +59,16 @@ struct ResProblem {
 
 // Shares of a problem of n_oct octs: one where it fits a block (max_slots), else about
 // target_slots each, at most max_blocks.  One block waits for nobody: 4096 slots take
-// 2.5 us an iteration in one block and 4.1 us in four.  From two blocks on an iteration
-// is the exchange (3 to 4 us) and 0.5 us per 1024 slots of a share, and the exchange
-// grows slowly with the blocks: 16 k slots take 5.9, 4.9, 4.3 and 4.4 us in 4, 8, 16 and
-// 32 blocks, 88 k slots 5.6, 5.2 and 5.4 us in 48, 88 and 176.
+// 2.5 us an iteration in one block and 3.5 in eight.  From two blocks on an iteration is
+// the exchange (3 to 4 us) and 0.5 us per 1024 slots of a share; on one XCD the exchange
+// is cheap enough for small shares: 16 k slots take 4.0 us in 16 blocks and 3.7 in 32
+// (4.5 in 16 spread over the XCDs), 88 k slots 5.2 us in 88 and 5.1 in 176.
 int res_group(int64_t n_oct, int max_blocks, int max_slots, int target_slots);
+
+// Blocks to launch for one problem in g shares on n_cu compute units of 8 XCDs, to which
+// blocks are dealt round-robin: as many as it takes for its shares to lie on as few XCDs
+// as hold them (the other blocks have no share and end at once).
+int res_blocks(int g, int n_cu);
 
 // About what an iteration of a share of n_slots slots takes in a group (us).
 double res_cost(int n_slots, int group);

@@ -4,7 +4,7 @@
 // system with couplings between levels int32 cnb[rows][6] and child[8 rows].  Output:
 // the shares (slot0 n_slots unit0 n_units prob part0 group), unit_of, partner, task0, task,
 // the largest share and its units, places; with couplings the shares' coarse units,
-// coarse, couplings.
+// coarse, couplings; last the peers and the length of the near numbering.
 #include <cstdio>
 #include <vector>
 
@@ -58,5 +58,8 @@ int main(int argc, char** argv) {
     line(h.coarse);
     line(std::vector<int32_t>(h.couplings.begin(), h.couplings.end()));
   }
+  std::vector<int32_t> peers(h.peers);
+  peers.push_back(h.n_near);
+  line(peers);
   return 0;
 }

@@ -71,7 +71,27 @@ def _plan(harness, tmp_path, tables, n_blocks, target):
     run = subprocess.run([harness, str(path)], capture_output=True, text=True)
     assert run.returncode == 0, run.stderr[-3000:]
     arr = [np.array(x.split(), dtype=np.int64) for x in run.stdout.splitlines()]
+    _check_peers(arr[0].reshape(-1, 7), arr[2], arr[-1])
     return probs, nbr, arr[0].reshape(-1, 7), arr[1].reshape(-1, 6), arr[2], arr[3], arr[4], arr[5], arr[6]
+
+
+def _check_peers(parts, partner, peers):
+    """The second numbering of the units: every unit its own number, a share's contiguous
+    and from a multiple of two on, so that no line of two units belongs to two shares."""
+    n_near, peers = peers[-1], peers[:-1].reshape(-1, 2)
+    share = np.concatenate([np.full(p[3], k) for k, p in enumerate(parts)] + [np.zeros(0, dtype=int)])
+    near = np.full(len(partner), -1)
+    near[partner] = peers[:, 0]
+    assert len(np.unique(near)) == len(near) and (near >= 0).all() and (near < n_near).all()
+    for k, (s0, ns, u0, nu, q, p0, g) in enumerate(parts):
+        if nu:
+            base = (u0 + k + 1) & ~1
+            assert np.array_equal(near[u0:u0 + nu], base + np.arange(nu))
+    owner = {}
+    for n, k in zip(near, share):
+        assert owner.setdefault(n // 2, k) == k
+    for u, v in enumerate(partner):
+        assert peers[u, 1] == share[v] - parts[share[v], 5]
 
 
 CASES = {
@@ -202,6 +222,7 @@ def test_couplings_between_levels(harness, tmp_path, n_blocks, target):
     arr = [np.array(x.split(), dtype=np.int64) for x in run.stdout.splitlines()]
     parts, unit_of, partner, places = arr[0].reshape(-1, 7), arr[1].reshape(-1, 6), arr[2], arr[6] & 0xffffffff
     n_coarse, coarse, couplings = arr[7], arr[8].reshape(-1, 2), arr[9] & 0xffffffff
+    _check_peers(parts, partner, arr[-1])
     part_of = np.concatenate([np.full(p[1], k) for k, p in enumerate(parts)])
     assert np.array_equal(partner[partner], np.arange(len(partner)))
 
