@@ -191,7 +191,7 @@ amrfld_status amrfld_set_coeffs(amrfld_ctx* c, int level, const double* rho, con
  * Robin mode (eq. mean_flux) and clear this level's register.  With a
  * temperature the coupling term is included and T is updated.
  * Returns AMRFLD_E_NOCONV if max_iter was reached.
- * A solve whose level fits the device's registers and LDS (about 1.3 million slots) runs
+ * A solve whose level fits the device's registers and LDS (about 2.1 million slots) runs
  * resident: one launch that keeps the whole CG state on the chip, whatever max_blocks,
  * form_coefs, persistent and inner_tol say (stats: launch_blocks = its blocks,
  * launch_mode as asked for); the other levels run in sweeps.  Should that launch
@@ -258,7 +258,8 @@ typedef struct {
 /* Advance n_prob independent patches by n_steps backward-Euler steps each, all
  * patches in the same sweeps: every PCG sweep covers the tiles of all patches,
  * with per-patch reductions, scalars and convergence (a converged patch's
- * blocks return at once).  precision: AMRFLD_FP64 or AMRFLD_MIXED; tol as in
+ * blocks return at once).  Patches that fit the device as a level would are solved
+ * resident instead, all of them in one launch per step.  precision: AMRFLD_FP64 or AMRFLD_MIXED; tol as in
  * amrfld_solve_level.  E_out: DEVICE float64 array receiving the final energies
  * of all patches concatenated in patch order (sum of n^3 values, x fastest),
  * written by a kernel enqueued on opts.stream before return (stream-ordered).
@@ -278,9 +279,9 @@ amrfld_status amrfld_solve_batch(amrfld_ctx* c, int n_prob, const amrfld_patch* 
  * each of its four finer cells with 2^(3-ndim) A / 3; every row is multiplied by
  * its cell volume, which makes the matrix symmetric (and the total energy exactly
  * conserved with zero-flux outer faces).  After each solve T is updated and the
- * finer levels are restricted into their parents.  Runs in FP64 with host-polled
- * sweeps whatever opts.precision and opts.persistent say; no flux registers are
- * involved.  Stats: one entry per composite solve, with level = -1.  Errors: as
+ * finer levels are restricted into their parents.  Runs in FP64, resident up to about
+ * 1.3 million slots and else with host-polled sweeps, whatever opts.precision and
+ * opts.persistent say; no flux registers are involved.  Stats: one entry per composite solve, with level = -1.  Errors: as
  * amrfld_advance_subcycled; E_STATE when T is set on some levels only. */
 amrfld_status amrfld_advance_unique(amrfld_ctx* c, double dt_coarse, double tol);
 

@@ -1607,9 +1607,9 @@ void build_composite_into(amrfld_ctx* c, CompositeState* C) {
     p.n_oct = C->n_oct;
     // (at least two blocks: couplings go through the exchange, also those within a share)
     const int g = std::max(2, res_group(C->n_oct, c->n_cu, 0, kResTargetSlots));
-    C->res = make_res_tables(c->stream(), build_res_plan({p}, {g}, res_blocks(g, c->n_cu), nbr.data(), C->n_oct, cnb.data(),
-                                              child.data()),
-                          1);
+    const ResPlanHost h =
+        build_res_plan({p}, {g}, res_blocks(g, c->n_cu), nbr.data(), C->n_oct, cnb.data(), child.data());
+    if (h.max_slots <= kResBlockSlots) C->res = make_res_tables(c->stream(), h, 1);
   }
   launch_fill(c->stream(), C->x, n, 0.0);  // padding slots keep x = 0 (identity rows)
   launch_fill(c->stream(), C->rho, n, 1.0);

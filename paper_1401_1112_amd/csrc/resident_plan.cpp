@@ -30,8 +30,26 @@ ResPlanHost build_res_plan(const std::vector<ResProblem>& probs, const std::vect
   for (size_t q = 0; q < probs.size(); ++q) {
     const int64_t m = probs[q].n_oct;
     const int g = group[q], p0 = int(h.parts.size());
+    // even shares; with couplings between levels even in slots and, counted twice, in faces
+    // towards finer cells (a share of 1400 slots beside a refined region has up to as many,
+    // whose halo would not fit LDS and whose exchange every other share waits for)
+    std::vector<int64_t> first(g + 1);
+    for (int r = 0; r <= g; ++r) first[r] = probs[q].oct0 + m * r / g;
+    if (cnb) {
+      std::vector<int64_t> w(m, 8);
+      for (int64_t o = 0; o < n_oct_table; ++o)
+        for (int d = 0; d < 6; ++d)
+          if (nbr[6 * o + d] < 0 && cnb[6 * o + d] >= 0) w[cnb[6 * o + d] / 8 - probs[q].oct0] += 2;
+      int64_t total = 0, sum = 0;
+      for (int64_t x : w) total += x;
+      for (int64_t o = 0, r = 1; o < m && r < g; ++o) {
+        sum += w[o];
+        // (at least one oct to every share, before and after)
+        if ((sum * g >= total * r && o + 1 >= r) || m - (o + 1) <= g - r) first[r++] = probs[q].oct0 + o + 1;
+      }
+    }
     for (int r = 0; r < g; ++r) {
-      const int64_t o0 = probs[q].oct0 + m * r / g, o1 = probs[q].oct0 + m * (r + 1) / g;
+      const int64_t o0 = first[r], o1 = first[r + 1];
       ResPart p{};
       p.slot0 = int(8 * o0);
       p.n_slots = int(8 * (o1 - o0));
