@@ -258,6 +258,8 @@ def _roofline(stats, bytes_per_cell, kernel, note, traffic=None, active=None):
     recorded: the method's bytes per cell x the cells of each timed launch over the
     summed launch time.  active(st) -> cells of one timed launch (default: the solve's
     leaves)."""
+    # (solves that ran resident among them took no part in the sweeps)
+    stats = [st for st in stats if st.get("launch_blocks") == st.get("sweep_blocks")] or stats
     ms = sum(st["sweep_ms"] for st in stats)
     n = sum(st["n_timed"] for st in stats)
     if ms <= 0 or n == 0:
@@ -958,7 +960,18 @@ def main(argv=None):
                          "the 7-point operator on the new r, two dot products)",
                          "the levels (about 150 MB each) sit in the 256 MB Infinity Cache: cache-assisted, the "
                          "HBM gate is judged on the batch and collapse workloads (roofline_gate)")
-    if roofline is not None:
+    if roofline is not None and all(st["launch_blocks"] != st["sweep_blocks"] for st in flat):
+        # resident solves: no iteration reads the system from memory, so the method's bytes
+        # over the time are no memory rate and have no fraction of the HBM peak
+        roofline.update({
+            "bound": "latency", "frac": None, "kernel": "k_cg_resident (the whole CG state on the chip)",
+            "note": "levels up to 2.1 M slots are solved in one launch with their state in registers and LDS: "
+                    "`achieved` is the rate at which streaming sweeps would have to move the method's bytes to "
+                    "be as fast; an iteration is bound by the exchange between the blocks.  The HBM gate is "
+                    "judged on the collapse workload (roofline_gate)",
+            "timing": "device clock around the iterations of each resident launch",
+            "copy_GBs_achievable": round(_copy_bandwidth(), 1)})
+    elif roofline is not None:
         n_a = roofline["timed_launches"]
         a_ms = sum(st["sweep_ms"] for st in flat)
         moved = sum((SWEEP_BYTES_FORMED if args.form_coefs else SWEEP_BYTES) * slots[st["level"]] * st["n_timed"]
