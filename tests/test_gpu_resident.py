@@ -165,3 +165,29 @@ def test_batch_of_resident_and_swept_patches(precision, graph, n_big):
             continue
         e, _ = patch_advance(p.rho, p.E, p.dx, p.dt, p.face_mode, p.face_ghost, p.face_flux, 2, 1e-10, alpha=alpha)
         assert np.linalg.norm(res[q] - e) <= 1e-9 * np.linalg.norm(e), q
+
+
+@pytest.mark.parametrize("base,top,refine", [(2, 3, 0.2), (3, 5, 0.5), (4, 6, 0.4)])
+def test_composite_of_levels_against_oracle(base, top, refine):
+    # couplings within a share, between shares of one and of several XCDs; fixed counts
+    from paper_1401_1112_amd.solver import solver_from_problem, to_numpy
+    from synth.configs import config_tiny
+    p = config_tiny(11, base_level=base, max_level=top, p_refine=refine, kmode="lp", tol=1e-12)
+    o = oracle_from_problem(p, max_iter=25, abs_floor=0.0)
+    o.advance_unique(p.dt_coarse, 0.0)
+    s = solver_from_problem(p, max_iter=25, abs_floor=0.0)
+    s.advance_unique(p.dt_coarse, 0.0, raise_on_error=False)
+    st = s.stats()
+    assert all(x["iters"] == 25 for x in st)
+    slots = sum(-(-8 * len(p.hierarchy.octs[l]) // 256) * 256 for l in p.hierarchy.levels)
+    assert all(x["launch_blocks"] == max(2, min(256, shares(slots))) for x in st)
+    for l in p.hierarchy.levels:
+        e = to_numpy(s.E(l))
+        ref = align(l, o.cells(l), o.E[l], s.cells(l))
+        assert np.linalg.norm(e - ref) <= 1e-12 * np.linalg.norm(ref)
+    s.close()
+
+
+def shares(slots):
+    n = -(-slots // 512)  # about 512 slots each, as many on every XCD from nine on
+    return n if n <= 8 else -(-n // 8) * 8
