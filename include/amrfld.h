@@ -316,6 +316,15 @@ amrfld_status amrfld_set_launch(amrfld_ctx* c, int max_blocks, int persistent, i
  * (0, 1) or max_outer < 1: AMRFLD_E_INVALID, nothing changes. */
 amrfld_status amrfld_set_refinement(amrfld_ctx* c, double inner_tol, int max_outer);
 
+/* Whether solves that fit the chip run resident (amrfld_solve_level) for the following
+ * calls on this context: 1 (default) or 0, every solve in sweeps.  A resident launch has
+ * all its blocks on the device at once, where they wait for each other, so a caller
+ * whose other work holds compute units for long may prefer sweeps.  wait_limit: polls,
+ * of about a microsecond each, after which a block of a resident launch gives up a wait
+ * (0: the library's own bounds).  Other values: AMRFLD_E_INVALID, nothing changes.  The
+ * two forms group their sums differently, so results may differ in the last bits. */
+amrfld_status amrfld_set_resident(amrfld_ctx* c, int resident, int wait_limit);
+
 /* Message of the last failure on this context ("" if none). */
 const char* amrfld_last_error(const amrfld_ctx* c);
 

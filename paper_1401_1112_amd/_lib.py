@@ -87,6 +87,7 @@ SIGNATURES = [
     ("amrfld_last_stats", _I, [_P, ctypes.POINTER(amrfld_stats), _I, ctypes.POINTER(_I)]),
     ("amrfld_set_launch", _I, [_P, _I, _I, _I, _I]),
     ("amrfld_set_refinement", _I, [_P, ctypes.c_double, _I]),
+    ("amrfld_set_resident", _I, [_P, _I, _I]),
     ("amrfld_last_error", ctypes.c_char_p, [_P]),
     ("amrfld_create_error", ctypes.c_char_p, []),
 ]
@@ -212,6 +213,10 @@ def amrfld_last_stats(ctx, max_n=None):
 
 def amrfld_set_refinement(ctx, inner_tol, max_outer):
     return load().amrfld_set_refinement(ctx, float(inner_tol), int(max_outer))
+
+
+def amrfld_set_resident(ctx, resident, wait_limit=0):
+    return load().amrfld_set_resident(ctx, int(resident), int(wait_limit))
 
 
 def amrfld_set_launch(ctx, max_blocks, persistent, persistent_per_cu, form_coefs):

@@ -277,6 +277,8 @@ struct amrfld_ctx {
   std::string err;
   int device = 0;  // current device when the context was created
   int n_cu = 0;    // its compute units
+  bool resident_on = true;  // solves that fit run resident
+  int wait_limit = 0;       // polls of a wait between blocks; 0: the launch's own
   uint64_t param_epoch = 0;  // bumped by every call that changes what a captured step bakes in
   StepGraph step_graph;
   int finest = -1;
@@ -1002,7 +1004,8 @@ void pcg_mixed(amrfld_ctx* c, const DevLevel& D, const SweepPlan& P, const Sweep
 // Solves of levels whose state fits the device's registers and LDS run resident, the
 // others in sweeps.  The mixed form runs there with its refinement but an FP64 inner CG:
 // FP32 halves the bytes of a sweep, and a resident iteration reads none.
-bool use_resident(const LevelState& L) { return resident_fits(L.res.d); }
+bool use_resident(const amrfld_ctx* c, const ResPlanDev& R) { return c->resident_on && resident_fits(R); }
+bool use_resident(const amrfld_ctx* c, const LevelState& L) { return use_resident(c, L.res.d); }
 
 // Launches that may resume a refined solve after its first one.
 int resident_resumes(const amrfld_ctx* c, int precision) {
@@ -1032,7 +1035,7 @@ ResArgs resident_args(const amrfld_ctx* c, const LevelState& L, double dt, doubl
   a.rho = L.rho;
   a.T_out = L.T;
   a.dt = dt;
-  a.spin_limit = kResSpinLimit;
+  a.spin_limit = c->wait_limit > 0 ? unsigned(c->wait_limit) : kResSpinLimit;
   return a;
 }
 
@@ -1082,7 +1085,7 @@ amrfld_status solve_one(amrfld_ctx* c, int level, double dt, int mode, double to
   launch_cell_K(s, D, L.E, L.rho, Lc ? Lc->E : nullptr, kparams(L), outer_bc(c), L.K);
   const double w = mode == AMRFLD_BC_DIRICHLET ? 1.0 : mode == AMRFLD_BC_NEUMANN ? 0.0 : c->o.robin_alpha;
   const CouplingParams cp = cparams(c, L);
-  double* Cm = use_resident(L) ? L.Ch : nullptr;  // the sweeps' scaled operator is not formed then
+  double* Cm = use_resident(c, L) ? L.Ch : nullptr;  // the sweeps' scaled operator is not formed then
   launch_assemble(s, D, L.K, Lc ? Lc->K : nullptr, L.E, Lc ? Lc->E : nullptr, L.rho, L.reg, dt, w,
                   c->o.robin_alpha, cp, kparams(L), outer_bc(c), L.Cp, L.mask, L.diag, L.b, Cm);
   const double scale = dt / (D.dx * D.dx);
@@ -1096,7 +1099,7 @@ amrfld_status solve_one(amrfld_ctx* c, int level, double dt, int mode, double to
   ls.iters.assign(1, 0);
   const bool registers = Lc && (mode == AMRFLD_BC_NEUMANN || mode == AMRFLD_BC_ROBIN);
   double* reg_c = registers ? ensure_reg(c, *Lc) : nullptr;
-  bool resident = use_resident(L);
+  bool resident = use_resident(c, L);
   if (resident) {
     check(hipEventRecord(c->ev[1], s), "event");
     ResArgs ra = resident_args(c, L, dt, tol, c->sc);
@@ -1228,7 +1231,7 @@ hipError_t record_solve(amrfld_ctx* c, hipStream_t st, int level, double dt, int
   launch_cell_K(st, D, L.E, L.rho, Lc ? Lc->E : nullptr, kparams(L), outer_bc(c), L.K);
   const double w = mode == AMRFLD_BC_DIRICHLET ? 1.0 : mode == AMRFLD_BC_NEUMANN ? 0.0 : c->o.robin_alpha;
   const CouplingParams cp = cparams(c, L);
-  double* Cm = use_resident(L) ? L.Ch : nullptr;  // the sweeps' scaled operator is not formed then
+  double* Cm = use_resident(c, L) ? L.Ch : nullptr;  // the sweeps' scaled operator is not formed then
   launch_assemble(st, D, L.K, Lc ? Lc->K : nullptr, L.E, Lc ? Lc->E : nullptr, L.rho, L.reg, dt, w,
                   c->o.robin_alpha, cp, kparams(L), outer_bc(c), L.Cp, L.mask, L.diag, L.b, Cm);
   const double scale = dt / (D.dx * D.dx);
@@ -1236,7 +1239,7 @@ hipError_t record_solve(amrfld_ctx* c, hipStream_t st, int level, double dt, int
     launch_theta_step(st, D, c->o.theta, L.E, face_coefs(c, L.Cp, L.K, L.mask, scale, 1.0, false), L.Cp, L.diag,
                       L.b, Cm);
   const bool registers = Lc && (mode == AMRFLD_BC_NEUMANN || mode == AMRFLD_BC_ROBIN);
-  if (use_resident(L)) {
+  if (use_resident(c, L)) {
     ResArgs ra = resident_args(c, L, dt, tol, sc);
     hipError_t e = launch_resident(st, D, L.res.d, ra);
     ra.resume = 1;
@@ -1369,7 +1372,7 @@ amrfld_status advance_graph(amrfld_ctx* c, double dt_coarse, int mode, double to
     const LevelState& L = c->L(sched[k].level);
     const int nt = tiles_of(L.t.n_slots());
     const SweepPlan P = level_plan(c, nt);
-    const bool resident = use_resident(L);
+    const bool resident = use_resident(c, L);
     if (resident && !h.done) {
       aborted = 1;
       reset_exchange(us, L.res.d);
@@ -1652,7 +1655,8 @@ amrfld_status solve_composite(amrfld_ctx* c, double dt, double tol) {
   const DevLevel D = C.dev();
   // a single level is that level's system (rows times the volume): solved as it is
   const ResPlanDev& R = C.n_levels == 1 ? c->L(base).res.d : C.res.d;
-  bool resident = resident_fits(R);
+  const bool fits = use_resident(c, R);
+  bool resident = fits;
   launch_assemble_composite(s, D, C.K, C.x, C.rho, cp, outer_bc(c), dt, C.Cp, C.cif, C.c2f, C.diag, C.b,
                             resident ? C.Ch : nullptr);
   const int n_tiles = tiles_of(C.n_slots);
@@ -1689,7 +1693,7 @@ amrfld_status solve_composite(amrfld_ctx* c, double dt, double tol) {
   if (!resident) {
     ls = LoopStats{};
     ls.iters.assign(1, 0);
-    if (resident_fits(R))  // without the couplings among the face coefficients
+    if (fits)  // without the couplings among the face coefficients
       launch_assemble_composite(s, D, C.K, C.x, C.rho, cp, outer_bc(c), dt, C.Cp, C.cif, C.c2f, C.diag, C.b, nullptr);
     const ScaledOp<double> Ah = scale_operator(c, s, D, stored_face_coefs(C.Cp), C.Cp, C.diag, C.rs, C.Ch);
     launch_interface_values(s, D, C.n_if_entries, C.cif, C.rs, C.if_val);
@@ -1945,7 +1949,7 @@ ResArgs batch_resident_args(const amrfld_ctx* c, const BatchState& B, double tol
   a.linf_test = c->o.linf_test;
   a.refine = precision == AMRFLD_MIXED;
   a.true_residual = c->o.true_residual || a.refine;
-  a.spin_limit = kResSpinLimitBatch;
+  a.spin_limit = c->wait_limit > 0 ? unsigned(c->wait_limit) : kResSpinLimitBatch;
   return a;
 }
 
@@ -1957,7 +1961,7 @@ amrfld_status solve_batch_persistent(amrfld_ctx* c, const std::vector<amrfld_pat
   BatchState& B = *c->batch;
   const int np = B.n_prob;
   const DevLevel D = B.dev();
-  const bool resident = B.res.d.parts != nullptr;
+  const bool resident = use_resident(c, B.res.d);
   SweepPlan P = resident ? B.big_plan() : B.plan();
   if (!c->bar) c->bar = dalloc<unsigned>(kBarWords, "barrier");
   P.done_count = c->bar + kBarDone;
@@ -2144,7 +2148,7 @@ amrfld_status solve_batch(amrfld_ctx* c, const std::vector<amrfld_patch>& pt, in
     c->stats.clear();  // the device cannot run it: poll instead
   }
   ensure_scalars(c, np);
-  bool resident = B.res.d.parts != nullptr;
+  bool resident = use_resident(c, B.res.d);
   // the batch's precision for this call only, restored on every way out
   struct PrecisionScope {
     amrfld_opts& o;
@@ -2714,6 +2718,19 @@ amrfld_status amrfld_set_refinement(amrfld_ctx* c, double inner_tol, int max_out
   }
   c->o.inner_tol = inner_tol;
   c->o.max_outer = max_outer;
+  ++c->param_epoch;
+  c->err.clear();
+  return AMRFLD_OK;
+}
+
+amrfld_status amrfld_set_resident(amrfld_ctx* c, int resident, int wait_limit) {
+  if (!c) return AMRFLD_E_INVALID;
+  if (resident < 0 || resident > 1 || wait_limit < 0) {
+    c->err = "set_resident: resident 0 or 1 and wait_limit >= 0 are required";
+    return AMRFLD_E_INVALID;
+  }
+  c->resident_on = resident != 0;
+  c->wait_limit = wait_limit;
   ++c->param_epoch;
   c->err.clear();
   return AMRFLD_OK;

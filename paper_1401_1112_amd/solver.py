@@ -135,6 +135,9 @@ class HierarchySolver:
         self._check(L.amrfld_set_launch(self.ctx, max_blocks, int(bool(persistent)), persistent_per_cu,
                                         int(bool(form_coefs))))
 
+    def set_resident(self, resident=True, wait_limit=0):
+        self._check(L.amrfld_set_resident(self.ctx, resident, wait_limit))
+
     def set_refinement(self, inner_tol, max_outer=30):
         self._check(L.amrfld_set_refinement(self.ctx, inner_tol, max_outer))
 
@@ -256,6 +259,11 @@ class BatchSolver:
 
     def last_error(self):
         return L.amrfld_last_error(self.ctx)
+
+    def set_resident(self, resident=True, wait_limit=0):
+        st = L.amrfld_set_resident(self.ctx, resident, wait_limit)
+        if st != L.OK:
+            raise L.AmrfldError(st, L.amrfld_last_error(self.ctx))
 
     def set_refinement(self, inner_tol, max_outer=30):
         st = L.amrfld_set_refinement(self.ctx, inner_tol, max_outer)
