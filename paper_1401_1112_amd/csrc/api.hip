@@ -1113,7 +1113,8 @@ amrfld_status solve_one(amrfld_ctx* c, int level, double dt, int mode, double to
         }
       }
       check(hipEventRecord(c->ev[2], s), "event");
-      if (ra.refine && cp.T) launch_post_solve(s, D, P, L.E, L.rho, cp, dt, L.T, c->sc, c->partials);
+      if (ra.refine && cp.T)
+        launch_post_solve(s, D, P, L.E, L.rho, cp, dt, L.T, c->sc, c->partials, &c->sc->done);
       if (registers)
         launch_flux_register(s, D, L.K, Lc->K, L.E, Lc->E, dt, reg_c, int(Lc->t.n_slots()), &c->sc->done);
       if (L.reg) launch_fill(s, L.reg, 6 * L.t.n_slots(), 0.0);
@@ -1247,7 +1248,8 @@ hipError_t record_solve(amrfld_ctx* c, hipStream_t st, int level, double dt, int
       e = launch_resident(st, D, L.res.d, ra);
     if (e != hipSuccess) return e;
     if (ra.refine && cp.T)
-      launch_post_solve(st, D, level_plan(c, tiles_of(D.n_slots)), L.E, L.rho, cp, dt, L.T, sc, c->partials);
+      launch_post_solve(st, D, level_plan(c, tiles_of(D.n_slots)), L.E, L.rho, cp, dt, L.T, sc, c->partials,
+                        &sc->done);
     if (registers) launch_flux_register(st, D, L.K, Lc->K, L.E, Lc->E, dt, Lc->reg, int(Lc->t.n_slots()), &sc->done);
     if (L.reg) launch_fill(st, L.reg, 6 * L.t.n_slots(), 0.0);
     return hipGetLastError();

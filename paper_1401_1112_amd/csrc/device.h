@@ -324,9 +324,10 @@ void launch_true_residual(hipStream_t s, const DevLevel& L, const SweepPlan& P, 
 void launch_true_residual(hipStream_t s, const DevLevel& L, const SweepPlan& P, const FaceCoefs<double>& A,
                           const double* diag, const double* b, const double* x, PcgScalars* sc,
                           double* part);
+// done (optional): T is left alone unless this flag of the solve's record is set.
 void launch_post_solve(hipStream_t s, const DevLevel& L, const SweepPlan& P, const double* E,
                        const double* rho, const CouplingParams& cp, double dt, double* T_out,
-                       PcgScalars* sc, double* part);
+                       PcgScalars* sc, double* part, const int* done = nullptr);
 
 // ------------------------------------------- mixed precision (FP32 inner solve)
 // Outer sweep: x_new = x_old + d (d in FP32, may be null), r = b - A x_new in

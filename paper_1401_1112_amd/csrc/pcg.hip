@@ -671,19 +671,22 @@ __device__ __forceinline__ void body_true_residual(int vb, DevLevel L, SweepPlan
   write_partials<1>(v, mx, part, lds, vb);
 }
 
-// T update of the coupling term (linearised emission) and smallest leaf energy.
+// T update of the coupling term (linearised emission; none unless the flag done, where
+// given, is set) and smallest leaf energy.
 __device__ __forceinline__ void body_post_solve(int vb, DevLevel L, SweepPlan P, const double* __restrict__ E,
                                                        const double* __restrict__ rho, CouplingParams cp,
-                                                       double dt, double* __restrict__ T_out, double* part) {
+                                                       double dt, double* __restrict__ T_out, double* part,
+                                                       const int* done) {
   __shared__ double lds[kLds];
   const BlockPlan bp = block_plan(P, vb);
+  const bool update = cp.T && (!done || *done);
   double v[1] = {-DBL_MAX};
   for (int t = bp.t0; t < bp.t1; ++t) {
     const int i = t * kBlock + int(threadIdx.x);
     if (i < L.n_slots && L.child[i] == -1) {
       const double e = E[i];
       v[0] = fmax(v[0], -e);
-      if (cp.T) {
+      if (update) {
         const double T = cp.T[i], r = rho[i];
         const double eta = cp.kappa_P * r * cp.c_light * dt;
         const double bT = 4.0 * cp.a_rad * T * T * T;
@@ -923,8 +926,9 @@ __global__ __launch_bounds__(kBlock) void k_true_residual_staged(DevLevel L, Swe
 
 __global__ __launch_bounds__(kBlock) void k_post_solve(DevLevel L, SweepPlan P, const double* __restrict__ E,
                                                        const double* __restrict__ rho, CouplingParams cp,
-                                                       double dt, double* __restrict__ T_out, double* part) {
-  body_post_solve(int(blockIdx.x), L, P, E, rho, cp, dt, T_out, part);
+                                                       double dt, double* __restrict__ T_out, double* part,
+                                                       const int* done) {
+  body_post_solve(int(blockIdx.x), L, P, E, rho, cp, dt, T_out, part, done);
 }
 
 __global__ __launch_bounds__(kBlock) void k_ir_sweep(DevLevel L, SweepPlan P, ScaledOp<double> Ah,
@@ -1153,8 +1157,9 @@ void launch_true_residual(hipStream_t s, const DevLevel& L, const SweepPlan& P, 
 }
 
 void launch_post_solve(hipStream_t s, const DevLevel& L, const SweepPlan& P, const double* E, const double* rho,
-                       const CouplingParams& cp, double dt, double* T_out, PcgScalars* sc, double* part) {
-  hipLaunchKernelGGL(k_post_solve, dim3(P.G), dim3(kBlock), 0, s, L, P, E, rho, cp, dt, T_out, part);
+                       const CouplingParams& cp, double dt, double* T_out, PcgScalars* sc, double* part,
+                       const int* done) {
+  hipLaunchKernelGGL(k_post_solve, dim3(P.G), dim3(kBlock), 0, s, L, P, E, rho, cp, dt, T_out, part, done);
   hipLaunchKernelGGL(k_finish, dim3(P.n_prob), dim3(kBlock), 0, s, P, 1, part, sc);
 }
 

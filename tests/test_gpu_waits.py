@@ -1,0 +1,69 @@
+"""Resident launches whose blocks give up their waits for each other: the bound on the
+waits is set to one poll, every kernel leaves normally, and the call's answer is that of
+the sweeps, which repeat the solve from the state before it."""
+import numpy as np
+import pytest
+
+from synth.configs import config_uniform
+from synth.hierarchy import Hierarchy
+
+pytestmark = pytest.mark.gpu
+
+
+def _problem(k=1200, base=5, coupled=True, seed=7):
+    """A uniform base level and one finer level of k octs drawn at random: both levels in
+    several shares, which have to wait for each other."""
+    p = config_uniform(base, kmode="lp", seed=seed)
+    n = 1 << base
+    cells = np.stack(np.meshgrid(*[np.arange(n, dtype=np.int32)] * 3, indexing="ij"), -1).reshape(-1, 3)
+    pick = np.random.default_rng(seed).permutation(len(cells))[:k]
+    p.hierarchy = Hierarchy(base, {base: p.hierarchy.octs[base], base + 1: np.ascontiguousarray(cells[pick])})
+    if coupled:
+        E = p.E
+        p.T = lambda level, ijk: E(level, ijk) ** 0.25
+    return p
+
+
+def _fields(s, p):
+    from paper_1401_1112_amd.solver import to_numpy
+    out = []
+    for l in p.hierarchy.levels:
+        if p.T is None:
+            out.append(to_numpy(s.E(l)))
+        else:
+            out += [to_numpy(x) for x in s.E(l, with_T=True)]
+    return out
+
+
+def _levels(p, mode, resident, wait_limit, precision, unique=False, steps=1, **kw):
+    from paper_1401_1112_amd.solver import solver_from_problem
+    s = solver_from_problem(p, precision=precision, **kw)
+    s.set_resident(resident, wait_limit)
+    st = []
+    for _ in range(steps):
+        if unique:
+            s.advance_unique(p.dt_coarse, 1e-10)
+        else:
+            s.advance(p.dt_coarse, mode, 1e-10)
+        st += s.stats()
+    out = _fields(s, p), st
+    s.close()
+    return out
+
+
+def _swept(st):
+    return [x["launch_blocks"] == x["sweep_blocks"] for x in st]
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("mode", [0, 2])
+@pytest.mark.parametrize("coupled", [False, True])
+def test_level_solves_that_give_up_equal_sweeps(precision, mode, coupled):
+    # energies, temperatures and (through the coarse solve) the flux register, bit for bit
+    p = _problem(coupled=coupled)
+    ref, st_ref = _levels(p, mode, False, 0, precision)
+    got, st = _levels(p, mode, True, 1, precision)
+    assert all(_swept(st_ref)) and all(_swept(st))
+    assert [x["iters"] for x in st] == [x["iters"] for x in st_ref]
+    for a, b in zip(got, ref):
+        assert np.array_equal(a, b)
