@@ -1370,13 +1370,14 @@ amrfld_status advance_graph(amrfld_ctx* c, double dt_coarse, int mode, double to
   amrfld_status worst = AMRFLD_OK;
   std::string worst_msg;
   for (int k = 0; k < n; ++k) {
-    const PcgScalars& h = c->h_sc[k];
+    PcgScalars& h = c->h_sc[k];
     const LevelState& L = c->L(sched[k].level);
     const int nt = tiles_of(L.t.n_slots());
     const SweepPlan P = level_plan(c, nt);
     const bool resident = use_resident(c, L);
     if (resident && !h.done) {
       aborted = 1;
+      h = PcgScalars{};  // of another replay, or of none
       reset_exchange(us, L.res.d);
     }
     amrfld_stats st{};
@@ -2073,8 +2074,11 @@ amrfld_status solve_batch_persistent(amrfld_ctx* c, const std::vector<amrfld_pat
   std::string worst_msg;
   for (int step = 0; step < n_steps; ++step) {
     for (int q = 0; q < np; ++q) {
-      const PcgScalars& h = c->h_sc[int64_t(step) * np + q];
-      if (resident && !h.done) aborted = 1;
+      PcgScalars& h = c->h_sc[int64_t(step) * np + q];
+      if (resident && !h.done) {
+        aborted = 1;
+        h = PcgScalars{};  // of another call, or of none
+      }
       amrfld_stats st{};
       st.level = q;
       st.iters = mixed ? h.inner_total : h.iter;

@@ -34,7 +34,10 @@
 // alternate: a block stores into a buffer again only after it has seen every block's
 // sums of the exchange between, and so after every block has read it.  Every wait is
 // bounded; a block that gives up sets the abort flag and leaves, the others then time
-// out in turn, and the iterate in memory is untouched.
+// out in turn, and the iterate in memory is untouched.  While the flag is set the
+// exchange numbers are those of the launch that gave up, and its words may still be
+// there: until the host has cleared the exchange, a share of several ends at its first
+// exchange.  A problem's record has its done flag set only by a launch that completed it.
 #include "resident.h"
 
 #include <algorithm>
@@ -714,7 +717,7 @@ __device__ __forceinline__ bool solve_part(const DevLevel& L, const ResPlanDev& 
   Exchange X{R, me, my_part, epoch0, A.spin_limit, 0u, false};
   for (int u = tid(); u < me.n_units; u += kResThreads) lds.partner[u] = R.partner[me.unit0 + u];
   if (threadIdx.x == 0) {
-    S.failed = 0;
+    S.failed = int(R.epoch[2 * R.n_prob]);  // (looked at where the first exchange ends)
     if (my_part == me.part0) A.sc[me.prob].done = 0;  // set again when the whole record is written
   }
   auto take_halo = [&](double* dst) {  // the received values as the halo part of a vector
@@ -993,6 +996,19 @@ __device__ __forceinline__ bool solve_part(const DevLevel& L, const ResPlanDev& 
   return true;
 }
 
+// A block that gave up at its k-th share leaves: none of the problems it leads from there
+// on is completed by this launch.
+__device__ __forceinline__ void give_up(const ResPlanDev& R, const ResArgs& A, int k) {
+  if (threadIdx.x != 0) return;
+  st_word32(R.epoch + 2 * R.n_prob, 1u);
+  for (; k < R.task0[blockIdx.x + 1]; ++k) {
+    const ResPart& p = R.parts[R.task[k]];
+    PcgScalars& o = A.sc[p.prob];
+    const bool settled = A.resume && (o.converged || o.nonfinite || o.inner_total >= A.max_iter);
+    if (R.task[k] == p.part0 && !settled) o.done = 0;
+  }
+}
+
 template <int NP, ResMode kMode>
 __global__ __launch_bounds__(kResThreads) void k_cg_resident(DevLevel L, ResPlanDev R, ResArgs A) {
   extern __shared__ __align__(16) unsigned char res_lds[];
@@ -1000,7 +1016,7 @@ __global__ __launch_bounds__(kResThreads) void k_cg_resident(DevLevel L, ResPlan
   const int b = int(blockIdx.x);
   for (int k = R.task0[b]; k < R.task0[b + 1]; ++k) {
     if (!solve_part<NP, kMode>(L, R, A, R.task[k], res_lds, S)) {
-      if (threadIdx.x == 0) st_word32(R.epoch + 2 * R.n_prob, 1u);
+      give_up(R, A, k);
       return;
     }
     __syncthreads();
@@ -1026,7 +1042,7 @@ __global__ __launch_bounds__(kResThreads) void k_cg_resident_batch(DevLevel L, R
       default: ok = solve_part<8, kStreamed>(L, R, A, part, res_lds, S);
     }
     if (!ok) {
-      if (threadIdx.x == 0) st_word32(R.epoch + 2 * R.n_prob, 1u);
+      give_up(R, A, k);
       return;
     }
     __syncthreads();

@@ -67,3 +67,51 @@ def test_level_solves_that_give_up_equal_sweeps(precision, mode, coupled):
     assert [x["iters"] for x in st] == [x["iters"] for x in st_ref]
     for a, b in zip(got, ref):
         assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+def test_captured_step_that_gave_up_starts_clean_again(precision):
+    # no launch of a replay takes the words of one that gave up for its own: the step
+    # fails as a whole, every time, and after it the same context makes the step it would
+    # have made, bit for bit
+    from paper_1401_1112_amd import _lib as L
+    from paper_1401_1112_amd.solver import sample_problem_fields, solver_from_problem
+    p = _problem()
+    ref, st_ref = _levels(p, 2, True, 0, precision, steps=2, persistent=True, graph=True)
+    s = solver_from_problem(p, precision=precision, persistent=True, graph=True)
+    s.set_resident(True, 1)
+    for _ in range(3):
+        sample_problem_fields(s, p)
+        assert s.advance(p.dt_coarse, 2, 1e-10, raise_on_error=False) == L.E_DEVICE
+        assert not any(x["converged"] for x in s.stats())
+    s.set_resident(True)
+    sample_problem_fields(s, p)
+    st = []
+    for _ in range(2):
+        s.advance(p.dt_coarse, 2, 1e-10)
+        st += s.stats()
+    assert [x["iters"] for x in st] == [x["iters"] for x in st_ref]
+    for a, b in zip(_fields(s, p), ref):
+        assert np.array_equal(a, b)
+    s.close()
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("graph", [False, True])
+def test_batch_launches_that_gave_up_start_clean_again(precision, graph):
+    from paper_1401_1112_amd import _lib as L
+    from paper_1401_1112_amd.solver import BatchSolver
+    from synth.configs import patch_batch
+    patches, alpha = patch_batch(4100, 5, n_min=4, n_max=48)
+    ref = BatchSolver(robin_alpha=alpha, persistent=True, graph=graph)
+    want, _ = ref.solve(patches, 3, 1e-10, precision=precision)
+    ref.close()
+    b = BatchSolver(robin_alpha=alpha, persistent=True, graph=graph)
+    b.set_resident(True, 1)
+    for _ in range(2):
+        assert b.solve(patches, 3, 1e-10, precision=precision, raise_on_error=False)[1] == L.E_DEVICE
+    b.set_resident(True)
+    got, _ = b.solve(patches, 3, 1e-10, precision=precision)
+    b.close()
+    for x, y in zip(got, want):
+        assert np.array_equal(x, y)
