@@ -1103,6 +1103,10 @@ amrfld_status solve_one(amrfld_ctx* c, int level, double dt, int mode, double to
   if (resident) {
     check(hipEventRecord(c->ev[1], s), "event");
     ResArgs ra = resident_args(c, L, dt, tol, c->sc);
+    // the energy before a solve that may take several launches, of which a later one may
+    // not end (the sweeps' threshold is relative to the first residual): 16 bytes a slot
+    double* const E0 = c->cg.r[0];
+    if (ra.refine) launch_copy_f64(s, E0, L.E, D.n_slots);
     if (run_resident(c, s, D, L.res.d, ra)) {
       if (ra.refine) {
         read_scalars(c, c->h_sc, c->sc, 1);
@@ -1121,7 +1125,15 @@ amrfld_status solve_one(amrfld_ctx* c, int level, double dt, int mode, double to
       check(hipEventRecord(c->ev[3], s), "event");
       read_scalars(c, c->h_sc, c->sc, 1);
       check(hipGetLastError(), "kernels");
-      if (!c->h_sc->done) resident = resident_timed_out(c, s, L.res.d);
+      if (!c->h_sc->done) {
+        if (ra.refine) {
+          reset_exchange(s, L.res.d);
+          launch_copy_f64(s, L.E, E0, D.n_slots);
+          resident = false;
+        } else {
+          resident = resident_timed_out(c, s, L.res.d);
+        }
+      }
       ls.persistent = c->o.persistent != 0;
       ls.launch_blocks = L.res.d.n_parts;
       if (c->o.time_sweeps > 0) {
