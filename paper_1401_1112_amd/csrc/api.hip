@@ -613,6 +613,7 @@ amrfld_status check_level_ready(amrfld_ctx* c, int level) {
 
 struct LoopStats {
   std::vector<int> iters;  // per problem: PCG iterations (inner iterations in mixed precision)
+  const char* elsewhere = nullptr;  // per problem, where given: solved by other launches
   int n_timed = 0;
   double sweep_ms = 0.0;
   bool persistent = false;  // iterations ran in persistent launches
@@ -689,6 +690,17 @@ bool all_done(const PcgScalars* h, int n) {
   return true;
 }
 
+// Adds the records' iterations to the problems' counts; returns the largest count of the
+// problems that these sweeps solve.
+int add_iterations(LoopStats* ls, const PcgScalars* sc, int np) {
+  int most = 0;
+  for (int q = 0; q < np; ++q) {
+    ls->iters[q] += sc[q].iter;
+    if (!ls->elsewhere || !ls->elsewhere[q]) most = std::max(most, sc[q].iter);
+  }
+  return most;
+}
+
 // Iterations of the CG solves of all problems of a plan, whose start sweeps
 // already ran: batches of iteration sweeps, a stopping check after each batch, the
 // next batch size predicted from the slowest problem's observed convergence rate.
@@ -724,11 +736,7 @@ int pcg_iterations(amrfld_ctx* c, const DevLevel& D, const SweepPlan& P, const S
         unsigned aborted = 0;
         check(hipMemcpy(&aborted, c->bar + kBarAbort, sizeof(unsigned), hipMemcpyDeviceToHost), "abort flag");
         if (aborted) throw std::runtime_error("persistent sweep: a grid barrier timed out");
-        int max_done = 0;
-        for (int qq = 0; qq < np; ++qq) {
-          ls->iters[qq] += sc_host[qq].iter;
-          max_done = std::max(max_done, sc_host[qq].iter);
-        }
+        const int max_done = add_iterations(ls, sc_host, np);
         ls->persistent = true;
         ls->launch_blocks = blocks;
         return max_done;
@@ -784,11 +792,7 @@ int pcg_iterations(amrfld_ctx* c, const DevLevel& D, const SweepPlan& P, const S
       chunk = std::max(2, std::min(256, est));
     }
   }
-  int max_done = 0;
-  for (int qq = 0; qq < np; ++qq) {
-    ls->iters[qq] += sc_host[qq].iter;
-    max_done = std::max(max_done, sc_host[qq].iter);
-  }
+  const int max_done = add_iterations(ls, sc_host, np);
   if (period > 0) {
     // timed sweeps that did work for at least one problem (sweep it makes iterate it)
     for (int it = period; it <= max_done && 2 * (it / period) <= int(c->sweep_ev.size()); it += period) {
@@ -2215,6 +2219,7 @@ amrfld_status solve_batch(amrfld_ctx* c, const std::vector<amrfld_patch>& pt, in
       }
     }
     const SweepPlan P = resident ? B.big_plan() : B.plan();
+    if (resident) ls.elsewhere = B.is_resident.data();
     if (P.G > 0) {
       const FaceCoefs<double> Aop = face_coefs(c, B.Cp, B.K, B.mask, 1.0, 1.0, true);
       const ScaledOp<double> Ah = scale_operator(c, s, D, Aop, B.Cp, B.diag, B.rs, B.Ch);

@@ -191,3 +191,26 @@ def test_composite_of_levels_against_oracle(base, top, refine):
 def shares(slots):
     n = -(-slots // 512)  # about 512 slots each, as many on every XCD from nine on
     return n if n <= 8 else -(-n // 8) * 8
+
+
+def test_timed_sweeps_beside_slow_resident_patches():
+    # the timed sweeps are those of the patch that is swept, however many iterations the
+    # resident patches take
+    from paper_1401_1112_amd.solver import BatchSolver
+    from synth.configs import patch_batch
+    small, alpha = patch_batch(5100, 3, n_min=30, n_max=40)
+    big, _ = patch_batch(5200, 1, n_min=136, n_max=136)
+    for p in small:
+        p.dt *= 300.0  # 17 times the iterations
+    big[0].dt *= 0.1
+    for period in (1, 4):
+        s = BatchSolver(robin_alpha=alpha, time_sweeps=period)
+        _, status = s.solve(small + big, 2, 1e-10)
+        st = s.stats()
+        s.close()
+        assert status == 0 and len(st) == 8
+        for k in (0, 4):
+            assert min(x["iters"] for x in st[k:k + 3]) > st[k + 3]["iters"]
+            assert all(x["n_timed"] == 0 for x in st[k:k + 3])
+            assert st[k + 3]["n_timed"] == st[k + 3]["iters"] // period
+            assert st[k + 3]["n_timed"] == 0 or st[k + 3]["sweep_ms"] > 0
