@@ -990,7 +990,8 @@ __device__ __forceinline__ bool solve_part(const DevLevel& L, const ResPlanDev& 
     z.nonfinite = res.fin ? 0 : 1;
     z.max_iter = A.max_iter;
     z.linf_test = A.linf_test;
-    z.loop_ms = double(clk1 - clk0) * 1e-5;  // the constant 100 MHz counter
+    // the constant 100 MHz counter; of all launches of a refined solve
+    z.loop_ms = (A.resume ? A.sc[me.prob].loop_ms : 0.0) + double(clk1 - clk0) * 1e-5;
     A.sc[me.prob] = z;
   }
   return true;

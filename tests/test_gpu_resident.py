@@ -214,3 +214,19 @@ def test_timed_sweeps_beside_slow_resident_patches():
             assert all(x["n_timed"] == 0 for x in st[k:k + 3])
             assert st[k + 3]["n_timed"] == st[k + 3]["iters"] // period
             assert st[k + 3]["n_timed"] == 0 or st[k + 3]["sweep_ms"] > 0
+
+
+def test_time_per_iteration_of_a_resumed_solve():
+    # a threshold below what rounding allows: the refined solve is resumed until its
+    # launches are used up, and its time per iteration is that of a solve of one launch
+    from paper_1401_1112_amd import MIXED
+    p = config_uniform(5, kmode="lp", seed=9)
+    us = {}
+    for precision in (0, MIXED):
+        kw = dict(time_sweeps=1, abs_floor=0.0, precision=precision, linf_test=False)
+        for _ in range(3):
+            _, _, st = _solve(p, 5, 12.0 / 32 ** 2, 1e-10 if precision == 0 else 1e-17, **kw)
+        us[precision] = 1e3 * st["sweep_ms"] / st["n_timed"]
+        assert st["n_timed"] == st["iters"]
+    assert st["converged"] == 0
+    assert 0.6 * us[0] <= us[MIXED] <= 1.7 * us[0], us
