@@ -1011,14 +1011,17 @@ void pcg_mixed(amrfld_ctx* c, const DevLevel& D, const SweepPlan& P, const Sweep
 bool use_resident(const amrfld_ctx* c, const ResPlanDev& R) { return c->resident_on && resident_fits(R); }
 bool use_resident(const amrfld_ctx* c, const LevelState& L) { return use_resident(c, L.res.d); }
 
-// Launches that may resume a refined solve after its first one.
-int resident_resumes(const amrfld_ctx* c, int precision) {
-  if (precision != AMRFLD_MIXED) return 0;
-  return std::min(kResResumes, (c->o.max_outer > 0 ? c->o.max_outer : 30) - 1);
+int max_outer_of(const amrfld_ctx* c) { return c->o.max_outer > 0 ? c->o.max_outer : 30; }
+
+// Launches that are recorded to resume a refined solve after its first one, where the
+// host does not see its record in between.  (One is used where the true residual came out
+// above the threshold that the recursive one met.)
+int recorded_resumes(const amrfld_ctx* c, int precision) {
+  return precision == AMRFLD_MIXED ? std::min(kResResumes, max_outer_of(c) - 1) : 0;
 }
 
 bool resume_wanted(const amrfld_ctx* c, const PcgScalars& h) {
-  return h.done && !h.converged && !h.nonfinite && h.inner_total < c->o.max_iter;
+  return h.done && !h.converged && !h.nonfinite && h.inner_total < c->o.max_iter && h.iter < max_outer_of(c);
 }
 
 ResArgs resident_args(const amrfld_ctx* c, const LevelState& L, double dt, double tol, PcgScalars* sc) {
@@ -1034,6 +1037,8 @@ ResArgs resident_args(const amrfld_ctx* c, const LevelState& L, double dt, doubl
   a.max_iter = c->o.max_iter;
   a.linf_test = c->o.linf_test;
   a.refine = c->o.precision == AMRFLD_MIXED;
+  a.inner_tol = c->o.inner_tol;
+  a.max_outer = max_outer_of(c);
   a.true_residual = c->o.true_residual || a.refine;
   if (!a.refine) a.cp = cparams(c, L);  // (a refined solve's T is updated after its last launch)
   a.rho = L.rho;
@@ -1115,7 +1120,7 @@ amrfld_status solve_one(amrfld_ctx* c, int level, double dt, int mode, double to
       if (ra.refine) {
         read_scalars(c, c->h_sc, c->sc, 1);
         ra.resume = 1;
-        for (int k = resident_resumes(c, c->o.precision); k > 0 && resume_wanted(c, *c->h_sc); --k) {
+        while (resume_wanted(c, *c->h_sc)) {
           if (!run_resident(c, s, D, L.res.d, ra)) break;
           read_scalars(c, c->h_sc, c->sc, 1);
         }
@@ -1260,7 +1265,7 @@ hipError_t record_solve(amrfld_ctx* c, hipStream_t st, int level, double dt, int
     ResArgs ra = resident_args(c, L, dt, tol, sc);
     hipError_t e = launch_resident(st, D, L.res.d, ra);
     ra.resume = 1;
-    for (int k = resident_resumes(c, c->o.precision); k > 0 && e == hipSuccess; --k)
+    for (int k = recorded_resumes(c, c->o.precision); k > 0 && e == hipSuccess; --k)
       e = launch_resident(st, D, L.res.d, ra);
     if (e != hipSuccess) return e;
     if (ra.refine && cp.T)
@@ -1967,6 +1972,8 @@ ResArgs batch_resident_args(const amrfld_ctx* c, const BatchState& B, double tol
   a.max_iter = c->o.max_iter;
   a.linf_test = c->o.linf_test;
   a.refine = precision == AMRFLD_MIXED;
+  a.inner_tol = c->o.inner_tol;
+  a.max_outer = max_outer_of(c);
   a.true_residual = c->o.true_residual || a.refine;
   a.spin_limit = c->wait_limit > 0 ? unsigned(c->wait_limit) : kResSpinLimitBatch;
   return a;
@@ -2011,7 +2018,7 @@ amrfld_status solve_batch_persistent(amrfld_ctx* c, const std::vector<amrfld_pat
         ResArgs ra = batch_resident_args(c, B, tol, precision, sc);
         hipError_t e = launch_resident(st, D, B.res.d, ra);
         ra.resume = 1;
-        for (int k = resident_resumes(c, precision); k > 0 && e == hipSuccess; --k)
+        for (int k = recorded_resumes(c, precision); k > 0 && e == hipSuccess; --k)
           e = launch_resident(st, D, B.res.d, ra);
         if (e != hipSuccess) return e;
         if (P.G == 0) continue;
@@ -2204,7 +2211,7 @@ amrfld_status solve_batch(amrfld_ctx* c, const std::vector<amrfld_patch>& pt, in
             if (resume_wanted(c, c->h_sc[p.id])) return true;
           return false;
         };
-        for (int k = resident_resumes(c, precision); k > 0 && wanted(); --k) {
+        while (precision == AMRFLD_MIXED && wanted()) {
           if (!run_resident(c, s, D, B.res.d, ra)) break;
           read_scalars(c, c->h_sc, c->sc, np);
         }

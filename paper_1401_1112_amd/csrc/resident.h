@@ -24,7 +24,7 @@ constexpr unsigned kResSpinLimit = 1u << 18;
 // of a batch, where a block may wait for others to come to a patch from their earlier ones
 constexpr unsigned kResSpinLimitBatch = 1u << 22;
 constexpr int kResWords = 7;  // a share's partial sums: words of 48 bits and a 16-bit stamp
-constexpr int kResResumes = 4;  // launches after the first of a refined solve, at most
+constexpr int kResResumes = 4;  // launches after the first of a captured refined solve
 constexpr int kResLine = 8;   // words of the line they lie in
 
 // Device tables of a plan and its exchange memory.
@@ -66,10 +66,12 @@ struct ResArgs {
   PcgScalars* sc = nullptr;      // one record per problem, written whole
   double tol = 0.0, abs_floor = 0.0;
   int max_iter = 0, linf_test = 0, true_residual = 0;
-  // refine (the mixed-precision form): the stop is decided on the true residual, counted
-  // as one refinement sweep; a solve that is still above its threshold is resumed from
-  // its iterate by another launch (which does nothing where it is not).
-  int refine = 0, resume = 0;
+  // refine (the mixed-precision form): segments that each reduce the residual by
+  // inner_tol, max_outer of them at most, the stopping rule at their ends; the last one's
+  // stop is decided on the true residual, and a solve that is still above its threshold is
+  // resumed from its iterate by another launch (which does nothing where it is not).
+  int refine = 0, resume = 0, max_outer = 0;
+  double inner_tol = 0.0;
   // post-solve: T update of the coupling term
   CouplingParams cp{};
   const double* rho = nullptr;

@@ -588,16 +588,21 @@ __device__ __forceinline__ bool exchange(Exchange& X, double (&v)[kSums], double
 
 struct CgResult {
   double rn, linf;
-  int iters;
+  int iters, segments;
   bool fin, conv;
 };
 
 // CG iterations from r^ = q.r, p^ in lds.p (own and halo), r^ of the halo in lds.rh.
 // thresh, tol, max_iter, linf_test: the stopping rule of Sect. 3.3.4; dmin: smallest
-// diagonal entry.  false: a wait timed out.
+// diagonal entry.  The rule is looked at where ||r||^2 <= gate2.  inner2 > 0 (a refined
+// solve): only there, where a segment ends, and the next one, of max_segments at most,
+// ends where ||r||^2 has fallen by inner2 again, so that the last residual lies as far
+// below the threshold as that of the refinement with FP32 segments.  false: a wait timed
+// out.
 template <typename T, int NP, ResMode kMode>
 __device__ __forceinline__ bool cg_loop(Exchange& X, Regs<T, NP, kMode>& q, const Lds<T>& lds, Shared& S, double thresh,
-                                        double tol, int max_iter, bool linf_test, double dmin, CgResult& out) {
+                                        double tol, int max_iter, bool linf_test, double dmin, double gate2,
+                                        double inner2, int max_segments, CgResult& out) {
   typedef typename Pair<T>::type T2;
   constexpr int kCap = 2 * NP * kResThreads;
   const int nh = 4 * X.me.n_units;
@@ -610,7 +615,6 @@ __device__ __forceinline__ bool cg_loop(Exchange& X, Regs<T, NP, kMode>& q, cons
     rrd = fma(a0, double(d.x), fma(a1, double(d.y), rrd));
   }
   bool wide = false;  // the next exchange carries the largest relative change too
-  const double stop2 = 1.000001 * thresh * thresh;
   for (int k = 0;; ++k) {
     double v[kSums] = {0.0, 0.0, rr, rrd};
     // (opaque: nothing derived from the places is kept in registers across iterations)
@@ -628,11 +632,15 @@ __device__ __forceinline__ bool cg_loop(Exchange& X, Regs<T, NP, kMode>& q, cons
     if (k >= 1) {
       // (the root only where it can matter: it is a long chain before alpha)
       out.fin = isfinite(v[3]) && isfinite(v[0]) && isfinite(v[2]);
-      if (!out.fin || v[3] <= stop2 || k >= max_iter) {
+      if (!out.fin || v[3] <= gate2 || k >= max_iter) {
         out.rn = sqrt(v[3]);
         out.linf = linf;
         out.iters = k;
         out.conv = out.fin && ((out.rn <= thresh && (!linf_test || (wide && linf < tol))) || out.rn == 0.0);
+        if (inner2 > 0.0) {
+          gate2 = inner2 * v[3];
+          if (++out.segments >= max_segments) return true;
+        }
         if (!out.fin || out.conv || k >= max_iter) return true;
       }
     }
@@ -690,6 +698,11 @@ __device__ __forceinline__ bool cg_loop(Exchange& X, Regs<T, NP, kMode>& q, cons
   }
 }
 
+// Whether a refined solve has ended with an earlier launch.
+__device__ __forceinline__ bool settled(const PcgScalars& o, const ResArgs& A) {
+  return o.converged || o.nonfinite || o.inner_total >= A.max_iter || o.iter >= A.max_outer;
+}
+
 // The solve of one share of one problem.  false: a wait timed out.
 template <int NP, ResMode kMode>
 __device__ __forceinline__ bool solve_part(const DevLevel& L, const ResPlanDev& R, const ResArgs& A, int my_part,
@@ -709,10 +722,8 @@ __device__ __forceinline__ bool solve_part(const DevLevel& L, const ResPlanDev& 
   lds.ex = lds.rh + nh;
   lds.partner = reinterpret_cast<int*>(lds.ex + nh);
   double* const lds_d = reinterpret_cast<double*>(lds.partner + ((me.n_units + 1) & ~1));
-  if (A.resume) {  // nothing left to do: decided by an earlier launch, alike for every share
-    const PcgScalars& o = A.sc[me.prob];
-    if (o.converged || o.nonfinite || o.inner_total >= A.max_iter) return true;
-  }
+  // nothing left to do: decided by an earlier launch, alike for every share
+  if (A.resume && settled(A.sc[me.prob], A)) return true;
   const unsigned epoch0 = R.epoch[me.prob];
   Exchange X{R, me, my_part, epoch0, A.spin_limit, 0u, false};
   for (int u = tid(); u < me.n_units; u += kResThreads) lds.partner[u] = R.partner[me.unit0 + u];
@@ -891,18 +902,19 @@ __device__ __forceinline__ bool solve_part(const DevLevel& L, const ResPlanDev& 
   const double start2 = v[0];
   const double rnorm0 = A.resume ? A.sc[me.prob].rnorm0 : sqrt(v[0]), bnorm = sqrt(v[1]);
   const double floor_b = A.abs_floor * bnorm, thresh = A.resume ? A.sc[me.prob].thresh : fmax(A.tol * rnorm0, floor_b);
-  const int before = A.resume ? A.sc[me.prob].inner_total : 0;
+  const int before = A.resume ? A.sc[me.prob].inner_total : 0, outer = A.resume ? A.sc[me.prob].iter : 0;
   CgResult res;
   res.rn = sqrt(start2);
   res.linf = 0.0;
-  res.iters = 0;
+  res.iters = res.segments = 0;
   res.fin = isfinite(start2) && isfinite(bnorm);
   res.conv = res.fin && res.rn <= floor_b;
   const long long clk0 = wall_clock64();
-  // (a refined solve aims a little below the threshold, so that the true residual, which
-  // differs from the recursive one by rounding, is below it at the first check)
+  const double inner2 = A.refine ? A.inner_tol * A.inner_tol : 0.0;
+  const double gate2 = A.refine ? inner2 * start2 : 1.000001 * thresh * thresh;
   if (res.fin && !res.conv &&
-      !cg_loop(X, q, lds, S, A.refine ? 0.9 * thresh : thresh, A.tol, A.max_iter - before, A.linf_test != 0, dmin, res))
+      !cg_loop(X, q, lds, S, thresh, A.tol, A.max_iter - before, A.linf_test != 0, dmin, gate2, inner2,
+               A.max_outer - outer, res))
     return false;
   const long long clk1 = wall_clock64();
 
@@ -967,7 +979,6 @@ __device__ __forceinline__ bool solve_part(const DevLevel& L, const ResPlanDev& 
   if (threadIdx.x == 0) {
     R.epoch[me.prob] = X.epoch;
     PcgScalars z{};
-    const int outer = A.resume ? A.sc[me.prob].iter : 0;
     if (A.refine && res.iters > 0) {
       // the stop is decided on the true residual; a start at the floor needed no sweep
       res.rn = sqrt(v[0]);
@@ -983,7 +994,7 @@ __device__ __forceinline__ bool solve_part(const DevLevel& L, const ResPlanDev& 
     z.linf = res.linf;
     z.true_rnorm = sqrt(v[0]);
     z.min_E = -m;
-    z.iter = A.refine ? outer + (res.iters > 0 ? 1 : 0) : res.iters;
+    z.iter = A.refine ? outer + res.segments : res.iters;
     z.inner_total = A.refine ? before + res.iters : 0;
     z.done = 1;
     z.converged = res.conv ? 1 : 0;
@@ -1005,8 +1016,7 @@ __device__ __forceinline__ void give_up(const ResPlanDev& R, const ResArgs& A, i
   for (; k < R.task0[blockIdx.x + 1]; ++k) {
     const ResPart& p = R.parts[R.task[k]];
     PcgScalars& o = A.sc[p.prob];
-    const bool settled = A.resume && (o.converged || o.nonfinite || o.inner_total >= A.max_iter);
-    if (R.task[k] == p.part0 && !settled) o.done = 0;
+    if (R.task[k] == p.part0 && !(A.resume && settled(o, A))) o.done = 0;
   }
 }
 

@@ -230,3 +230,30 @@ def test_time_per_iteration_of_a_resumed_solve():
         assert st["n_timed"] == st["iters"]
     assert st["converged"] == 0
     assert 0.6 * us[0] <= us[MIXED] <= 1.7 * us[0], us
+
+
+@pytest.mark.parametrize("inner_tol", [3e-3, 1e-1])
+@pytest.mark.parametrize("form", ["polled", "graph"])
+def test_refined_solve_ends_a_segment_below_its_threshold(inner_tol, form):
+    # every segment of a refined solve reduces the residual by inner_tol, the stopping rule
+    # looks at their ends only, and max_outer caps them: as in the sweeps.  (FP64 segments
+    # overshoot inner_tol by other amounts than FP32 ones: one segment's leave.)
+    from paper_1401_1112_amd import MIXED
+    from paper_1401_1112_amd import _lib as L
+    from paper_1401_1112_amd.solver import solver_from_problem
+    p = config_uniform(5, kmode="lp", seed=13)
+    kw = dict(precision=MIXED, inner_tol=inner_tol, persistent=form == "graph", graph=form == "graph")
+    for max_outer in (30, 2, 1):
+        got = {}
+        for resident in (True, False):
+            s = solver_from_problem(p, max_outer=max_outer, **kw)
+            s.set_resident(resident)
+            status = s.advance(12.0 / 32 ** 2, 0, 1e-10, raise_on_error=False)
+            st = s.stats()[0]
+            s.close()
+            got[resident] = st["outer_iters"]
+            assert st["rel_res"] <= inner_tol ** st["outer_iters"] * (1 + 1e-6)
+            assert status == (L.OK if max_outer == 30 else L.E_NOCONV)
+            assert st["converged"] == (max_outer == 30)
+            assert st["outer_iters"] == max_outer or max_outer == 30
+        assert abs(got[True] - got[False]) <= 1
