@@ -669,8 +669,10 @@ __device__ __forceinline__ bool cg_loop(Exchange& X, Regs<T, NP, kMode>& q, cons
       const T2 po = *reinterpret_cast<const T2*>(lds.p + l);
       const T2 d = q.diag(u);
       if (wide) {
-        const T x0 = fabs(q.x[u][0]), x1 = fabs(q.x[u][1]), e0 = fabs(ta * po.x), e1 = fabs(ta * po.y);
-        linf = fmax(linf, fmax(double(x0 > T(0) ? e0 / x0 : e0), double(x1 > T(0) ? e1 / x1 : e1)));
+        // |dx| / |x|, and |dx| where x = 0 (both scaled by rs = d^-1/2 here)
+        const T x0 = fabs(q.x[u][0]), x1 = fabs(q.x[u][1]);
+        const T q0 = x0 > T(0) ? x0 : sqrt(d.x), q1 = x1 > T(0) ? x1 : sqrt(d.y);
+        linf = fmax(linf, fmax(double(fabs(ta * po.x) / q0), double(fabs(ta * po.y) / q1)));
       }
       q.x[u][0] = fma(ta, po.x, q.x[u][0]);
       q.x[u][1] = fma(ta, po.y, q.x[u][1]);

@@ -257,3 +257,18 @@ def test_refined_solve_ends_a_segment_below_its_threshold(inner_tol, form):
             assert st["converged"] == (max_outer == 30)
             assert st["outer_iters"] == max_outer or max_outer == 30
         assert abs(got[True] - got[False]) <= 1
+
+
+@pytest.mark.parametrize("level", [3, 5])
+@pytest.mark.parametrize("count", [1, 2])
+def test_relative_change_of_cells_at_zero(level, count):
+    # a pulse in one cell of an empty box: the cells it has just reached count with their
+    # absolute change, in the units of the energy
+    p = config_uniform(level, kmode="const", seed=2)
+    p.E = lambda l, c: np.where((np.asarray(c) == 3).all(axis=1), 1e3, 0.0)
+    dt = 12.0 / 4 ** level
+    o = oracle_from_problem(p, max_iter=count, abs_floor=0.0)
+    h = o.solve_level(level, dt, ora.DIRICHLET, 0.0)
+    e, cells, st = _solve(p, level, dt, 0.0, max_iter=count, abs_floor=0.0)
+    assert st["iters"] == h["iters"] == count
+    assert np.isclose(st["linf_change"], h["linf"], rtol=1e-10)
