@@ -53,6 +53,7 @@ typedef unsigned long long u64;
 constexpr int kWaves = kResThreads / 64;
 constexpr int kSums = 4;
 constexpr int kMaxShares = kResThreads;  // of a problem: a thread reads the words of one
+constexpr double kUnderflow = 1e-290;  // sums of squares below it are short of bits
 constexpr u64 kMask48 = 0xffffffffffffull;
 
 __device__ __forceinline__ u64 ld_word(const u64* p) {
@@ -646,14 +647,22 @@ __device__ __forceinline__ bool cg_loop(Exchange& X, Regs<T, NP, kMode>& q, cons
     }
     // alpha = gam / (p^,s^); beta = (alpha^2 (s^,s^) - gam) / gam
     const double gam = v[2];
-    const double inv = 1.0 / v[0], alpha = gam * inv;
-    const double ratio = fma(alpha * inv, v[1], -1.0);
+    const double inv = 1.0 / v[0];
+    double alpha = gam * inv, ratio = fma(alpha * inv, v[1], -1.0);
+    if (!isfinite(alpha) || !isfinite(ratio)) {  // the inverse overflows before the quotients do
+      alpha = gam / v[0];
+      ratio = fma(alpha, v[1] / v[0], -1.0);
+    }
     const double beta = ratio > 0.0 ? ratio : 0.0;
     const double gnext = beta * gam;
     if (!isfinite(alpha) || !isfinite(ratio)) {
       out.rn = sqrt(v[3]);
-      out.fin = out.conv = false;
+      out.linf = 0.0;
       out.iters = k;
+      ++out.segments;
+      // a residual below its threshold whose squares underflow is zero (cells that a pulse
+      // has barely reached keep the relative change above tol until then)
+      out.fin = out.conv = k >= 1 && v[0] == 0.0 && gam < kUnderflow && (out.rn <= thresh || thresh == 0.0);
       return true;
     }
     // ||r_{k+1}||^2 >= dmin (r^,r^)_{k+1}: where that is above the threshold (with a
@@ -886,7 +895,8 @@ __device__ __forceinline__ bool solve_part(const DevLevel& L, const ResPlanDev& 
       q.r[u][1] = q.s[u][1] * b[u].y - av[1];
       keep(q.r[u][0]);
       keep(q.r[u][1]);
-      v[0] += q.r[u][0] * q.r[u][0] * d.x + q.r[u][1] * q.r[u][1] * d.y;
+      const double r0 = q.r[u][0] * sqrt(d.x), r1 = q.r[u][1] * sqrt(d.y);
+      v[0] += r0 * r0 + r1 * r1;
       if (l < ns && ch[u].x == -1) v[1] += b[u].x * b[u].x;
       if (l < ns && ch[u].y == -1) v[1] += b[u].y * b[u].y;
       stage(q, lds.ex, u, q.r[u][0], q.r[u][1]);

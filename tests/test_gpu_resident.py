@@ -272,3 +272,25 @@ def test_relative_change_of_cells_at_zero(level, count):
     e, cells, st = _solve(p, level, dt, 0.0, max_iter=count, abs_floor=0.0)
     assert st["iters"] == h["iters"] == count
     assert np.isclose(st["linf_change"], h["linf"], rtol=1e-10)
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("level", [2, 4, 5])
+@pytest.mark.parametrize("dt,tol", [(1e-9, 1e-10), (12.0, 0.0)])
+def test_residuals_down_to_underflow(level, precision, dt, tol):
+    # a pulse into an empty box in a tiny step, whose relative changes stay above tol until
+    # the residual is zero, and solves to a residual of zero: they end, converged, with the
+    # oracle's energies
+    p = config_uniform(level, kmode="const", seed=2)
+    if tol:
+        p.E = lambda l, c: np.where((np.asarray(c) == 2).all(axis=1), 1e3, 0.0)
+    kw = {} if tol else dict(abs_floor=0.0, linf_test=False)
+    o = oracle_from_problem(p, **kw)
+    o.solve_level(level, dt / 4 ** level, ora.DIRICHLET, 1e-13)
+    e, cells, st = _solve(p, level, dt / 4 ** level, tol, precision=precision, **kw)
+    if precision == 0:
+        assert st["converged"] == 1 and st["status"] == 0
+    else:
+        assert st["status"] in ((0,) if tol else (0, -5))  # a true residual is never zero
+    ref = align(level, o.cells(level), o.E[level], cells)
+    assert np.linalg.norm(e - ref) <= 1e-11 * np.linalg.norm(ref)
