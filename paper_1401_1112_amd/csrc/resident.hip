@@ -667,8 +667,10 @@ __device__ __forceinline__ bool cg_loop(Exchange& X, Regs<T, NP, kMode>& q, cons
     }
     // ||r_{k+1}||^2 >= dmin (r^,r^)_{k+1}: where that is above the threshold (with a
     // margin for the rounding of the prediction) iterate k + 1 cannot be the last, and its
-    // relative change, a division per cell, is not formed
-    wide = k + 1 >= max_iter || !(gnext * dmin > 4.0 * thresh * thresh);
+    // relative change, a division per cell, is not formed (the last segment that a
+    // refined solve may make ends the solve whatever its residual)
+    wide = k + 1 >= max_iter || !(gnext * dmin > 4.0 * thresh * thresh) ||
+           (inner2 > 0.0 && out.segments + 1 >= max_segments);
     const T ta = T(alpha), tb = T(beta);
     rr = rrd = linf = 0.0;
 #pragma unroll

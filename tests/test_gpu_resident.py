@@ -244,7 +244,7 @@ def test_refined_solve_ends_a_segment_below_its_threshold(inner_tol, form):
     p = config_uniform(5, kmode="lp", seed=13)
     kw = dict(precision=MIXED, inner_tol=inner_tol, persistent=form == "graph", graph=form == "graph")
     for max_outer in (30, 2, 1):
-        got = {}
+        got, linf = {}, {}
         for resident in (True, False):
             s = solver_from_problem(p, max_outer=max_outer, **kw)
             s.set_resident(resident)
@@ -252,11 +252,14 @@ def test_refined_solve_ends_a_segment_below_its_threshold(inner_tol, form):
             st = s.stats()[0]
             s.close()
             got[resident] = st["outer_iters"]
+            linf[resident] = st["linf_change"]
             assert st["rel_res"] <= inner_tol ** st["outer_iters"] * (1 + 1e-6)
             assert status == (L.OK if max_outer == 30 else L.E_NOCONV)
             assert st["converged"] == (max_outer == 30)
             assert st["outer_iters"] == max_outer or max_outer == 30
         assert abs(got[True] - got[False]) <= 1
+        # the change that a capped solve reports is that of its last iteration
+        assert max_outer == 30 or np.isclose(linf[True], linf[False], rtol=1e-2)
 
 
 @pytest.mark.parametrize("level", [3, 5])
