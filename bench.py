@@ -259,7 +259,7 @@ def _roofline(stats, bytes_per_cell, kernel, note, traffic=None, active=None):
     summed launch time.  active(st) -> cells of one timed launch (default: the solve's
     leaves)."""
     # (solves that ran resident among them took no part in the sweeps)
-    stats = [st for st in stats if st.get("launch_blocks") == st.get("sweep_blocks")] or stats
+    stats = [st for st in stats if st.get("resident") != 1] or stats
     ms = sum(st["sweep_ms"] for st in stats)
     n = sum(st["n_timed"] for st in stats)
     if ms <= 0 or n == 0:
@@ -707,7 +707,7 @@ def _batched_form(args):
     for k in range(steps):
         its = [st[k * n + q]["iters"] for q in range(n)]
         # (patches solved resident, in registers and LDS, take no part in the timed sweeps)
-        swept = [q for q in range(n) if st[k * n + q]["n_timed"] > 0]
+        swept = [q for q in range(n) if st[k * n + q]["resident"] != 1 and st[k * n + q]["n_timed"] > 0]
         if not swept:
             continue
         rec = st[k * n + swept[0]]
@@ -726,7 +726,7 @@ def _batched_form(args):
                            "alg_bytes_per_cell": ALG_BYTES_FP64, "alg_bytes_per_launch": round(byts / launches),
                            "timed_launches": launches, "avg_launch_us": round(ms * 1e3 / launches, 2),
                            "note": "cells of the patches still iterating in each timed sweep; only the patches "
-                                   "above 1.3 M cells are swept from memory, the others are solved on the chip"}
+                                   "above 2.1 M cells are swept from memory, the others are solved on the chip"}
     if not args.no_cpu_baseline:
         print("bench: batch oracle on the host cores", file=sys.stderr, flush=True)
         out["cpu_baseline"] = _batch_cpu_baseline(patches, alpha, tol)
@@ -960,7 +960,7 @@ def main(argv=None):
                          "the 7-point operator on the new r, two dot products)",
                          "the levels (about 150 MB each) sit in the 256 MB Infinity Cache: cache-assisted, the "
                          "HBM gate is judged on the batch and collapse workloads (roofline_gate)")
-    if roofline is not None and all(st["launch_blocks"] != st["sweep_blocks"] for st in flat):
+    if roofline is not None and all(st["resident"] == 1 for st in flat):
         # resident solves: no iteration reads the system from memory, so the method's bytes
         # over the time are no memory rate and have no fraction of the HBM peak
         roofline.update({
@@ -972,6 +972,7 @@ def main(argv=None):
             "timing": "device clock around the iterations of each resident launch",
             "copy_GBs_achievable": round(_copy_bandwidth(), 1)})
     elif roofline is not None:
+        flat = [st for st in flat if st["resident"] != 1]  # the swept solves
         n_a = roofline["timed_launches"]
         a_ms = sum(st["sweep_ms"] for st in flat)
         moved = sum((SWEEP_BYTES_FORMED if args.form_coefs else SWEEP_BYTES) * slots[st["level"]] * st["n_timed"]

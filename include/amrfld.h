@@ -138,6 +138,8 @@ typedef struct {
   double sweep_ms;       /* summed device time of the timed iteration sweeps (one per CG iteration) */
   double spare_ms;       /* 0: kept for the layout (the iteration is one fused sweep) */
   int launch_mode;       /* 0 host-polled sweeps, 1 persistent launch, 2 persistent launches in a hipGraph */
+  int resident;          /* 1 solved resident (amrfld_solve_level), 0 in sweeps, 2 in sweeps after a resident
+                            launch that gave up */
   double rnorm0;         /* ||r_0|| = ||b - A x_0|| (mixed precision: the first outer residual) */
   double bnorm;          /* ||b||; the stopping threshold is max(tol ||r_0||, abs_floor ||b||) */
   int sweep_blocks;      /* blocks (256-slot tile ranges) of every PCG sweep */

@@ -46,7 +46,7 @@ class amrfld_stats(ctypes.Structure):
         ("linf_change", ctypes.c_double), ("min_E", ctypes.c_double), ("ms", ctypes.c_double),
         ("pcg_ms", ctypes.c_double), ("dt", ctypes.c_double), ("outer_iters", ctypes.c_int),
         ("n_timed", ctypes.c_int), ("sweep_ms", ctypes.c_double), ("spare_ms", ctypes.c_double),
-        ("launch_mode", ctypes.c_int), ("rnorm0", ctypes.c_double), ("bnorm", ctypes.c_double),
+        ("launch_mode", ctypes.c_int), ("resident", ctypes.c_int), ("rnorm0", ctypes.c_double), ("bnorm", ctypes.c_double),
         ("sweep_blocks", ctypes.c_int), ("launch_blocks", ctypes.c_int),
     ]
 

@@ -1108,7 +1108,7 @@ amrfld_status solve_one(amrfld_ctx* c, int level, double dt, int mode, double to
   ls.iters.assign(1, 0);
   const bool registers = Lc && (mode == AMRFLD_BC_NEUMANN || mode == AMRFLD_BC_ROBIN);
   double* reg_c = registers ? ensure_reg(c, *Lc) : nullptr;
-  bool resident = use_resident(c, L);
+  bool resident = use_resident(c, L), gave_up = false;
   if (resident) {
     check(hipEventRecord(c->ev[1], s), "event");
     ResArgs ra = resident_args(c, L, dt, tol, c->sc);
@@ -1135,6 +1135,7 @@ amrfld_status solve_one(amrfld_ctx* c, int level, double dt, int mode, double to
       read_scalars(c, c->h_sc, c->sc, 1);
       check(hipGetLastError(), "kernels");
       if (!c->h_sc->done) {
+        gave_up = true;
         if (ra.refine) {
           reset_exchange(s, L.res.d);
           launch_copy_f64(s, L.E, E0, D.n_slots);
@@ -1198,6 +1199,7 @@ amrfld_status solve_one(amrfld_ctx* c, int level, double dt, int mode, double to
   st.sweep_blocks = P.G;
   st.launch_blocks = resident || ls.persistent ? ls.launch_blocks : P.G;
   st.launch_mode = ls.persistent ? 1 : 0;
+  st.resident = resident ? 1 : gave_up ? 2 : 0;
   float ms = 0.f, pms = 0.f;
   check(hipEventSynchronize(c->ev[3]), "event");  // passed already: the scalars were read after it
   check(hipEventElapsedTime(&ms, c->ev[0], c->ev[3]), "event");
@@ -1422,6 +1424,7 @@ amrfld_status advance_graph(amrfld_ctx* c, double dt_coarse, int mode, double to
                                                           c->o.persistent_per_cu)
                                 : persistent_blocks<double>(P, c->o.persistent_per_cu);
     st.launch_mode = 2;
+    st.resident = resident ? 1 : 0;
     st.status = h.nonfinite ? AMRFLD_E_NONFINITE : (h.converged ? AMRFLD_OK : AMRFLD_E_NOCONV);
     if (st.status != AMRFLD_OK && worst == AMRFLD_OK) {
       worst = amrfld_status(st.status);
@@ -1680,7 +1683,7 @@ amrfld_status solve_composite(amrfld_ctx* c, double dt, double tol) {
   // a single level is that level's system (rows times the volume): solved as it is
   const ResPlanDev& R = C.n_levels == 1 ? c->L(base).res.d : C.res.d;
   const bool fits = use_resident(c, R);
-  bool resident = fits;
+  bool resident = fits, gave_up = false;
   launch_assemble_composite(s, D, C.K, C.x, C.rho, cp, outer_bc(c), dt, C.Cp, C.cif, C.c2f, C.diag, C.b,
                             resident ? C.Ch : nullptr);
   const int n_tiles = tiles_of(C.n_slots);
@@ -1705,7 +1708,10 @@ amrfld_status solve_composite(amrfld_ctx* c, double dt, double tol) {
     check(hipEventRecord(c->ev[1], s), "event");
     if (run_resident(c, s, D, R, a)) {
       read_scalars(c, c->h_sc, c->sc, 1);
-      if (!c->h_sc->done) resident = resident_timed_out(c, s, R);
+      if (!c->h_sc->done) {
+        gave_up = true;
+        resident = resident_timed_out(c, s, R);
+      }
       if (c->o.time_sweeps > 0) {
         ls.n_timed = c->h_sc->iter;
         ls.sweep_ms = c->h_sc->loop_ms;
@@ -1758,6 +1764,7 @@ amrfld_status solve_composite(amrfld_ctx* c, double dt, double tol) {
   st.bnorm = h.bnorm;
   st.sweep_blocks = P.G;
   st.launch_blocks = resident ? R.n_parts : P.G;
+  st.resident = resident ? 1 : gave_up ? 2 : 0;
   float ms = 0.f, pms = 0.f;
   check(hipEventSynchronize(c->ev[3]), "event");  // passed already: the scalars were read after it
   check(hipEventElapsedTime(&ms, c->ev[0], c->ev[3]), "event");
@@ -2117,6 +2124,7 @@ amrfld_status solve_batch_persistent(amrfld_ctx* c, const std::vector<amrfld_pat
       st.ms = total_ms / n_steps;
       st.pcg_ms = -1.0;
       st.launch_mode = mode;
+      st.resident = resident && B.is_resident[q] ? 1 : 0;
       st.rnorm0 = h.rnorm0;
       st.bnorm = h.bnorm;
       st.sweep_blocks = P.G == 0 ? B.res.d.n_blocks : P.G;
@@ -2177,7 +2185,7 @@ amrfld_status solve_batch(amrfld_ctx* c, const std::vector<amrfld_patch>& pt, in
     c->stats.clear();  // the device cannot run it: poll instead
   }
   ensure_scalars(c, np);
-  bool resident = use_resident(c, B.res.d);
+  bool resident = use_resident(c, B.res.d), gave_up = false;
   // the batch's precision for this call only, restored on every way out
   struct PrecisionScope {
     amrfld_opts& o;
@@ -2222,6 +2230,7 @@ amrfld_status solve_batch(amrfld_ctx* c, const std::vector<amrfld_patch>& pt, in
           reset_exchange(s, B.res.d);
           launch_copy_f64(s, B.E, B.E0, B.n_slots);
           resident = false;
+          gave_up = true;
         }
       }
     }
@@ -2280,6 +2289,7 @@ amrfld_status solve_batch(amrfld_ctx* c, const std::vector<amrfld_patch>& pt, in
       st.sweep_blocks = P.G > 0 ? P.G : B.res.d.n_blocks;
       st.launch_blocks = ls.persistent ? ls.launch_blocks : st.sweep_blocks;
       st.launch_mode = ls.persistent ? 1 : 0;
+      st.resident = B.is_resident[q] ? (resident ? 1 : gave_up ? 2 : 0) : 0;
       st.status = h.nonfinite ? AMRFLD_E_NONFINITE : (h.converged ? AMRFLD_OK : AMRFLD_E_NOCONV);
       if (st.status != AMRFLD_OK && worst == AMRFLD_OK) {
         worst = amrfld_status(st.status);

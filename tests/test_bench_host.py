@@ -79,3 +79,14 @@ def test_schedule_is_fine_first_with_restrictions():
     solves = [(l, dt) for k, l, dt in ops if k == "solve"]
     assert solves == [(8, 0.25), (8, 0.25), (7, 0.5), (8, 0.25), (8, 0.25), (7, 0.5), (6, 1.0)]
     assert [l for k, l, _ in ops if k == "restrict"] == [8, 8, 7]
+
+
+def test_roofline_leaves_resident_solves_out():
+    # a resident launch may have as many blocks as the level's sweeps would
+    swept = {"sweep_ms": 2.0, "n_timed": 4, "n_leaf": 1_000_000, "launch_blocks": 256, "sweep_blocks": 256, "resident": 0}
+    chip = {"sweep_ms": 0.1, "n_timed": 9, "n_leaf": 1_000_000, "launch_blocks": 256, "sweep_blocks": 256, "resident": 1}
+    # (nor is a persistent launch of sweeps, with fewer blocks than those, a resident one)
+    for other in (dict(swept, resident=2), dict(swept, launch_blocks=200)):
+        r = bench._roofline([swept, chip, other], 125, "k", "n")
+        assert r["timed_launches"] == 8
+        assert r["achieved"] == pytest.approx(8 * 125e6 / 4e-3 / 1e9, rel=1e-6)

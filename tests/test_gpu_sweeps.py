@@ -68,12 +68,12 @@ def test_the_switch_selects_the_form():
         level = s.stats()[0]
         s.advance_unique(12.0 / 32 ** 2, 1e-10)
         comp = s.stats()[0]
-        assert (level["launch_blocks"] != level["sweep_blocks"]) == on
-        assert (comp["launch_blocks"] != comp["sweep_blocks"]) == on
+        assert level["resident"] == comp["resident"] == int(on)
         b = BatchSolver(robin_alpha=alpha, time_sweeps=1)
         b.set_resident(on)
         res, _ = b.solve(patches, 2, 1e-10)
-        assert all((x["n_timed"] == 0) == on for x in b.stats())  # sweeps are timed, resident patches are not
+        # (sweeps are timed, resident patches are not)
+        assert all(x["resident"] == int(on) and (x["n_timed"] == 0) == on for x in b.stats())
         out.setdefault(on, []).append([to_numpy(s.E(5))] + res)
         s.close()
         b.close()

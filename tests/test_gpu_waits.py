@@ -51,10 +51,6 @@ def _levels(p, mode, resident, wait_limit, precision, unique=False, steps=1, **k
     return out
 
 
-def _swept(st):
-    return [x["launch_blocks"] == x["sweep_blocks"] for x in st]
-
-
 @pytest.mark.parametrize("precision", [0, 1])
 @pytest.mark.parametrize("mode", [0, 2])
 @pytest.mark.parametrize("coupled", [False, True])
@@ -63,7 +59,8 @@ def test_level_solves_that_give_up_equal_sweeps(precision, mode, coupled):
     p = _problem(coupled=coupled)
     ref, st_ref = _levels(p, mode, False, 0, precision)
     got, st = _levels(p, mode, True, 1, precision)
-    assert all(_swept(st_ref)) and all(_swept(st))
+    assert all(x["resident"] == 0 for x in st_ref)
+    assert all(x["resident"] == 2 and x["launch_blocks"] == x["sweep_blocks"] for x in st)
     assert [x["iters"] for x in st] == [x["iters"] for x in st_ref]
     for a, b in zip(got, ref):
         assert np.array_equal(a, b)
@@ -115,3 +112,27 @@ def test_batch_launches_that_gave_up_start_clean_again(precision, graph):
     b.close()
     for x, y in zip(got, want):
         assert np.array_equal(x, y)
+
+
+def test_composite_and_batch_that_give_up_equal_sweeps():
+    from paper_1401_1112_amd.solver import BatchSolver
+    from synth.configs import patch_batch
+    p = _problem(coupled=False)
+    ref, st_ref = _levels(p, 0, False, 0, 0, unique=True)
+    got, st = _levels(p, 0, True, 1, 0, unique=True)
+    assert all(x["resident"] == 0 for x in st_ref) and all(x["resident"] == 2 for x in st)
+    assert [x["iters"] for x in st] == [x["iters"] for x in st_ref]
+    for a, b in zip(got, ref):
+        assert np.array_equal(a, b)
+    patches, alpha = patch_batch(4100, 5, n_min=4, n_max=48)
+    for precision in (0, 1):
+        out = []
+        for resident, wait_limit in ((False, 0), (True, 1), (True, 0)):
+            s = BatchSolver(robin_alpha=alpha)
+            s.set_resident(resident, wait_limit)
+            res, _ = s.solve(patches, 2, 1e-10, precision=precision)
+            out.append((res, {x["resident"] for x in s.stats()}))
+            s.close()
+        assert [x[1] for x in out] == [{0}, {2}, {1}]
+        for a, b in zip(out[0][0], out[1][0]):
+            assert np.array_equal(a, b)
