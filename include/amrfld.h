@@ -323,7 +323,8 @@ amrfld_status amrfld_set_refinement(amrfld_ctx* c, double inner_tol, int max_out
  * all its blocks on the device at once, where they wait for each other, so a caller
  * whose other work holds compute units for long may prefer sweeps.  wait_limit: polls,
  * of about a microsecond each, after which a block of a resident launch gives up a wait
- * (0: the library's own bounds).  Other values: AMRFLD_E_INVALID, nothing changes.  The
+ * (0: the library's own bounds); the blocks of a batch wait longer for blocks that are
+ * still at earlier patches, by what these may take.  Other values: AMRFLD_E_INVALID, nothing changes.  The
  * two forms group their sums differently, so results may differ in the last bits. */
 amrfld_status amrfld_set_resident(amrfld_ctx* c, int resident, int wait_limit);
 

@@ -120,6 +120,7 @@ double* scratch_of(int dev, std::string* why) {
 // Device tables and exchange memory of a resident plan, owned.
 struct ResTables {
   ResPlanDev d;
+  int max_tasks = 0;  // shares of one block, one after another
 
   void release() {
     for (const void* p : {(const void*)d.parts, (const void*)d.places, (const void*)d.partner, (const void*)d.task0,
@@ -127,6 +128,7 @@ struct ResTables {
                           (const void*)d.extra})
       dfree(const_cast<void*>(p));
     d = ResPlanDev{};
+    max_tasks = 0;
   }
 };
 
@@ -453,6 +455,7 @@ ResTables make_res_tables(hipStream_t s, const ResPlanHost& h, int n_prob) {
   r.d.n_near = h.n_near;
   r.d.n_prob = n_prob;
   r.d.n_blocks = int(h.task0.size()) - 1;
+  for (int b = 0; b < r.d.n_blocks; ++b) r.max_tasks = std::max(r.max_tasks, h.task0[b + 1] - h.task0[b]);
   r.d.max_slots = h.max_slots;
   r.d.lds = resident_lds(h.parts, h.max_slots, n_prob);
   if (!resident_fits(r.d)) return ResTables{};
@@ -1024,6 +1027,14 @@ bool resume_wanted(const amrfld_ctx* c, const PcgScalars& h) {
   return h.done && !h.converged && !h.nonfinite && h.inner_total < c->o.max_iter && h.iter < max_outer_of(c);
 }
 
+// The bounds of a launch's waits.  repeatable: a launch that gives up is repeated in sweeps.
+void set_waits(const amrfld_ctx* c, const ResTables& r, bool repeatable, ResArgs* a) {
+  const uint64_t queued = uint64_t(std::max(0, r.max_tasks - 1)) * uint64_t(c->o.max_iter) * kResPollsPerIteration;
+  const uint64_t meet = c->wait_limit > 0 ? unsigned(c->wait_limit) : repeatable ? kResSpinMeet : kResSpinMeetFinal;
+  a->meet_limit = unsigned(std::min<uint64_t>(meet + queued, ~0u));
+  a->spin_limit = c->wait_limit > 0 ? unsigned(c->wait_limit) : kResSpinLoop;
+}
+
 ResArgs resident_args(const amrfld_ctx* c, const LevelState& L, double dt, double tol, PcgScalars* sc) {
   ResArgs a;
   a.Cp = L.Cp;
@@ -1044,7 +1055,6 @@ ResArgs resident_args(const amrfld_ctx* c, const LevelState& L, double dt, doubl
   a.rho = L.rho;
   a.T_out = L.T;
   a.dt = dt;
-  a.spin_limit = c->wait_limit > 0 ? unsigned(c->wait_limit) : kResSpinLimit;
   return a;
 }
 
@@ -1112,6 +1122,7 @@ amrfld_status solve_one(amrfld_ctx* c, int level, double dt, int mode, double to
   if (resident) {
     check(hipEventRecord(c->ev[1], s), "event");
     ResArgs ra = resident_args(c, L, dt, tol, c->sc);
+    set_waits(c, L.res, true, &ra);
     // the energy before a solve that may take several launches, of which a later one may
     // not end (the sweeps' threshold is relative to the first residual): 16 bytes a slot
     double* const E0 = c->cg.r[0];
@@ -1265,6 +1276,7 @@ hipError_t record_solve(amrfld_ctx* c, hipStream_t st, int level, double dt, int
   const bool registers = Lc && (mode == AMRFLD_BC_NEUMANN || mode == AMRFLD_BC_ROBIN);
   if (use_resident(c, L)) {
     ResArgs ra = resident_args(c, L, dt, tol, sc);
+    set_waits(c, L.res, false, &ra);
     hipError_t e = launch_resident(st, D, L.res.d, ra);
     ra.resume = 1;
     for (int k = recorded_resumes(c, c->o.precision); k > 0 && e == hipSuccess; --k)
@@ -1681,7 +1693,8 @@ amrfld_status solve_composite(amrfld_ctx* c, double dt, double tol) {
   cp.T = coupled ? C.T : nullptr;
   const DevLevel D = C.dev();
   // a single level is that level's system (rows times the volume): solved as it is
-  const ResPlanDev& R = C.n_levels == 1 ? c->L(base).res.d : C.res.d;
+  const ResTables& res = C.n_levels == 1 ? c->L(base).res : C.res;
+  const ResPlanDev& R = res.d;
   const bool fits = use_resident(c, R);
   bool resident = fits, gave_up = false;
   launch_assemble_composite(s, D, C.K, C.x, C.rho, cp, outer_bc(c), dt, C.Cp, C.cif, C.c2f, C.diag, C.b,
@@ -1697,6 +1710,7 @@ amrfld_status solve_composite(amrfld_ctx* c, double dt, double tol) {
   ls.iters.assign(1, 0);
   if (resident) {
     ResArgs a = resident_args(c, c->L(base), dt, tol, c->sc);
+    set_waits(c, res, true, &a);
     a.Cp = C.Cp;
     a.Cm = C.Ch;
     a.diag = C.diag;
@@ -1982,7 +1996,6 @@ ResArgs batch_resident_args(const amrfld_ctx* c, const BatchState& B, double tol
   a.inner_tol = c->o.inner_tol;
   a.max_outer = max_outer_of(c);
   a.true_residual = c->o.true_residual || a.refine;
-  a.spin_limit = c->wait_limit > 0 ? unsigned(c->wait_limit) : kResSpinLimitBatch;
   return a;
 }
 
@@ -2023,6 +2036,7 @@ amrfld_status solve_batch_persistent(amrfld_ctx* c, const std::vector<amrfld_pat
                       OuterBC{}, B.Cp, B.mask, B.diag, B.b, resident ? B.Ch : nullptr);
       if (resident) {
         ResArgs ra = batch_resident_args(c, B, tol, precision, sc);
+        set_waits(c, B.res, false, &ra);
         hipError_t e = launch_resident(st, D, B.res.d, ra);
         ra.resume = 1;
         for (int k = recorded_resumes(c, precision); k > 0 && e == hipSuccess; --k)
@@ -2210,6 +2224,7 @@ amrfld_status solve_batch(amrfld_ctx* c, const std::vector<amrfld_patch>& pt, in
     if (resident) {
       launch_copy_f64(s, B.E0, B.E, B.n_slots);
       ResArgs ra = batch_resident_args(c, B, tol, precision, c->sc);
+      set_waits(c, B.res, true, &ra);
       resident = run_resident(c, s, D, B.res.d, ra);
       if (resident) {
         read_scalars(c, c->h_sc, c->sc, np);

@@ -19,10 +19,18 @@ constexpr int kResBlockSlots = 2 * kResPairs * kResThreads;
 constexpr int kResMaxSlots = 16 * kResThreads;
 constexpr int kResStreamDoubles = 11 * kResMaxSlots / 2;  // the coefficients of a block
 constexpr int kResTargetSlots = 512;  // of one share where the level has several
-// polls of a wait before a block gives up (about a microsecond each)
-constexpr unsigned kResSpinLimit = 1u << 18;
-// of a batch, where a block may wait for others to come to a patch from their earlier ones
-constexpr unsigned kResSpinLimitBatch = 1u << 22;
+// Polls (about a microsecond each) before a block gives up.  Once the blocks of a problem
+// have met, in its first exchange, they wait for each other's arithmetic only, unless the
+// device is taken from them as a whole.
+constexpr unsigned kResSpinLoop = 1u << 22;
+// Until then for the last one's place on the device, behind other streams' and processes'
+// kernels: 0.3 s where the solve can be repeated in sweeps, which run beside them on what
+// is left; as long as a grid barrier of the persistent sweeps where it cannot (captured
+// steps, persistent batches).
+constexpr unsigned kResSpinMeet = 1u << 18, kResSpinMeetFinal = 1u << 26;
+// And for blocks that come from earlier patches of a batch: this many for each iteration
+// that those may take (10 us of the largest shares).
+constexpr unsigned kResPollsPerIteration = 16;
 constexpr int kResWords = 7;  // a share's partial sums: words of 48 bits and a 16-bit stamp
 constexpr int kResResumes = 4;  // launches after the first of a captured refined solve
 constexpr int kResLine = 8;   // words of the line they lie in
@@ -77,7 +85,7 @@ struct ResArgs {
   const double* rho = nullptr;
   double* T_out = nullptr;
   double dt = 0.0;
-  unsigned spin_limit = 0;
+  unsigned meet_limit = 0, spin_limit = 0;  // polls of a share's first exchange, of a later one
 };
 
 // Whether a block's share of this plan fits its registers and LDS.

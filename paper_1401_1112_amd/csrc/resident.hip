@@ -738,7 +738,7 @@ __device__ __forceinline__ bool solve_part(const DevLevel& L, const ResPlanDev& 
   // nothing left to do: decided by an earlier launch, alike for every share
   if (A.resume && settled(A.sc[me.prob], A)) return true;
   const unsigned epoch0 = R.epoch[me.prob];
-  Exchange X{R, me, my_part, epoch0, A.spin_limit, 0u, false};
+  Exchange X{R, me, my_part, epoch0, A.meet_limit, 0u, false};
   for (int u = tid(); u < me.n_units; u += kResThreads) lds.partner[u] = R.partner[me.unit0 + u];
   if (threadIdx.x == 0) {
     S.failed = int(R.epoch[2 * R.n_prob]);  // (looked at where the first exchange ends)
@@ -801,6 +801,7 @@ __device__ __forceinline__ bool solve_part(const DevLevel& L, const ResPlanDev& 
   }
   __syncthreads();
   if (!exchange(X, v, m, true, S, lds)) return false;
+  X.spin_limit = A.spin_limit;
   const double dmin = -m;
   take_halo(lds.p + kCap);
   // from here on units between shares on the same XCD go through its L2

@@ -136,3 +136,25 @@ def test_composite_and_batch_that_give_up_equal_sweeps():
         assert [x[1] for x in out] == [{0}, {2}, {1}]
         for a, b in zip(out[0][0], out[1][0]):
             assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("form", ["polled", "persistent", "graph"])
+def test_blocks_wait_for_earlier_patches_of_a_batch(form):
+    # more shares than blocks, one patch that iterates until its residual is zero and the
+    # others at rest: blocks that come to a patch early wait for those still at the slow
+    # one, however short the bound on the waits within a solve
+    from paper_1401_1112_amd.solver import BatchSolver
+    from synth.configs import patch_batch
+    patches, alpha = patch_batch(4300, 200, n_min=18, n_max=26)
+    slow = max(patches, key=lambda p: p.n)  # worked on first
+    for p in patches:
+        if p is not slow:
+            p.E, p.face_mode, p.face_flux = np.ones_like(p.E), np.ones(6, dtype=np.int32), np.zeros(6)
+    s = BatchSolver(robin_alpha=alpha, abs_floor=1e-12, persistent=form != "polled", graph=form == "graph")
+    s.set_resident(True, 300)
+    _, status = s.solve(patches, 1, 0.0, raise_on_error=False)
+    st = s.stats()
+    s.close()
+    assert status in (0, -5) and {x["resident"] for x in st} == {1}
+    its = sorted(x["iters"] for x in st)
+    assert its[-2] <= 1 and its[-1] > 1000  # at 3 us or more each: longer than the bound
