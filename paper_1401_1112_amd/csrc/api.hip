@@ -1126,7 +1126,7 @@ amrfld_status solve_one(amrfld_ctx* c, int level, double dt, int mode, double to
     // the energy before a solve that may take several launches, of which a later one may
     // not end (the sweeps' threshold is relative to the first residual): 16 bytes a slot
     double* const E0 = c->cg.r[0];
-    if (ra.refine) launch_copy_f64(s, E0, L.E, D.n_slots);
+    if (ra.refine && L.res.d.n_blocks > 1) launch_copy_f64(s, E0, L.E, D.n_slots);
     if (run_resident(c, s, D, L.res.d, ra)) {
       if (ra.refine) {
         read_scalars(c, c->h_sc, c->sc, 1);

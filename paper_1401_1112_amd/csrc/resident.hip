@@ -139,6 +139,7 @@ __device__ __forceinline__ double wave_max(double a) {
 struct Shared {
   double part[kWaves][kSums + 1];   // per wave: this share's sums and maximum
   double total[kWaves][kSums + 1];  // per wave: over the shares' words
+  double gate[kWaves];  // per wave (its lanes alone read and write it): cg_loop's gate
   int failed;
   unsigned char xcc[kMaxShares];  // where the problem's shares run, from the first exchange on
 };
@@ -148,7 +149,6 @@ struct Exchange {
   const ResPart& me;
   int my_part;
   unsigned epoch;  // number of the next exchange
-  unsigned spin_limit;
   unsigned near;  // bit k: this thread's k-th word of the halo is among the near ones
   bool one_xcd;   // all shares of the only problem run on one XCD
 
@@ -160,6 +160,57 @@ struct Exchange {
     return R.halo + (size_t(epoch & 1u) * R.all_units() + unit) * 8;
   }
 };
+
+// The arguments of a kernel, read from the launch's memory again wherever this is called.
+// Taken as parameters they are read once, at the start, and what is used after the
+// iterations is moved out of the way and back within them: 146 such moves of a lane in the
+// loop of shares of 1024 slots, 44 so.  An iteration of 4096 slots in one block takes
+// 1.99 us for 2.08, of 33 k slots in 64 blocks 3.4 for 3.5, of 262 k in 256 4.25 for 4.45,
+// two steps of 64 patches (16.8 M slots) 40.8 ms for 43.0.
+struct KernelArgs {
+  DevLevel L;
+  ResPlanDev R;
+  ResArgs A;
+};
+typedef const __attribute__((address_space(4))) char* ArgMemory;
+// (read as what it is, a pointer to device memory, which the compiler takes for granted of
+// arguments that it reads itself)
+template <class T>
+__device__ __forceinline__ void read_pointer(ArgMemory a, size_t at, T*& p) {
+  typedef __attribute__((address_space(1))) T* Global;
+  p = (T*)*(const __attribute__((address_space(4))) Global*)(a + at);
+}
+__device__ __forceinline__ KernelArgs kernel_args() {
+  ArgMemory a = (ArgMemory)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(a));
+  KernelArgs k;
+#pragma unroll
+  for (int i = 0; i < int(sizeof(KernelArgs) / sizeof(int)); ++i)
+    reinterpret_cast<int*>(&k)[i] = ((const __attribute__((address_space(4))) int*)a)[i];
+#define AMRFLD_POINTER(f) read_pointer(a, offsetof(KernelArgs, f), k.f)
+  AMRFLD_POINTER(L.child);
+  AMRFLD_POINTER(L.cif);
+  AMRFLD_POINTER(R.parts);
+  AMRFLD_POINTER(R.places);
+  AMRFLD_POINTER(R.partner);
+  AMRFLD_POINTER(R.task0);
+  AMRFLD_POINTER(R.task);
+  AMRFLD_POINTER(R.lines);
+  AMRFLD_POINTER(R.halo);
+  AMRFLD_POINTER(R.epoch);
+  AMRFLD_POINTER(R.extra);
+  AMRFLD_POINTER(A.Cp);
+  AMRFLD_POINTER(A.Cm);
+  AMRFLD_POINTER(A.diag);
+  AMRFLD_POINTER(A.b);
+  AMRFLD_POINTER(A.x);
+  AMRFLD_POINTER(A.sc);
+  AMRFLD_POINTER(A.cp.T);
+  AMRFLD_POINTER(A.rho);
+  AMRFLD_POINTER(A.T_out);
+#undef AMRFLD_POINTER
+  return k;
+}
 
 // Words of one value in the halo memory, and of the four of a unit.
 template <typename T>
@@ -205,7 +256,7 @@ __device__ __forceinline__ void put_halo(const Exchange& X, const T* ex, const i
 // flight.  Every value is stored by the thread that exported the one at the same place,
 // so sh and ex are the same memory.  false: a wait timed out.
 template <int kBatch, typename T>
-__device__ __forceinline__ bool get_halo(const Exchange& X, T* sh) {
+__device__ __forceinline__ bool get_halo(const Exchange& X, unsigned limit, T* sh) {
   constexpr int kW = kValueWords<T>;
   const int nw = 4 * kW * X.me.n_units;
   const u64* h = X.halo(X.me.unit0);
@@ -230,7 +281,7 @@ __device__ __forceinline__ bool get_halo(const Exchange& X, T* sh) {
         if (miss) c[k] = word(k);
       }
       if (!missing) break;
-      if (++polls > X.spin_limit) return false;
+      if (++polls > limit) return false;
     }
 #pragma unroll
     for (int k = 0; k < kBatch; ++k) {
@@ -248,11 +299,11 @@ __device__ __forceinline__ bool get_halo(const Exchange& X, T* sh) {
   return true;
 }
 template <typename T>
-__device__ __forceinline__ bool get_halo(const Exchange& X, T* sh) {
+__device__ __forceinline__ bool get_halo(const Exchange& X, unsigned limit, T* sh) {
   const int nw = 4 * kValueWords<T> * X.me.n_units;
-  if (nw <= 2 * kResThreads) return get_halo<2>(X, sh);
-  if (nw <= 4 * kResThreads) return get_halo<4>(X, sh);
-  return get_halo<8>(X, sh);
+  if (nw <= 2 * kResThreads) return get_halo<2>(X, limit, sh);
+  if (nw <= 4 * kResThreads) return get_halo<4>(X, limit, sh);
+  return get_halo<8>(X, limit, sh);
 }
 
 // The sums (k < kSums) and the maximum over the first n of the waves' rows, the same in
@@ -322,16 +373,17 @@ __device__ __forceinline__ void put_sums(const Exchange& X, double (&v)[kSums], 
 
 // The sums (and maximum) over the whole problem to every thread, and the halo values
 // that the neighbour shares published for this exchange to sh (null: none).  false: a
-// wait timed out.
+// wait took more than limit polls.
 template <typename T>
-__device__ __forceinline__ bool collect(Exchange& X, double (&v)[kSums], double& m, bool wide, Shared& S, T* sh) {
+__device__ __forceinline__ bool collect(Exchange& X, unsigned limit, double (&v)[kSums], double& m, bool wide, Shared& S,
+                                        T* sh) {
   const int t = tid(), lane = t & 63, wid = t >> 6, G = X.me.group;
   if (G == 1) {
     ++X.epoch;
     return true;
   }
   const int n_waves = (G + 63) >> 6;
-  bool ok = !sh || get_halo(X, sh);
+  bool ok = !sh || get_halo(X, limit, sh);
   if (wid < n_waves) {
     u64 w[kResWords];
 #pragma unroll
@@ -349,7 +401,7 @@ __device__ __forceinline__ bool collect(Exchange& X, double (&v)[kSums], double&
         for (int k = 0; k < kResWords; ++k)
           if (k < kResWords - 1 || wide) all = all && unsigned(w[k] >> 48) == st;
         if (all) break;
-        if (++polls > X.spin_limit) {
+        if (++polls > limit) {
           ok = false;
           break;
         }
@@ -581,10 +633,10 @@ __device__ __forceinline__ void stage(const Regs<T, NP, kMode>& q, T* ex, int u,
 }
 
 template <typename T>
-__device__ __forceinline__ bool exchange(Exchange& X, double (&v)[kSums], double& m, bool wide, Shared& S,
-                                         const Lds<T>& lds) {
+__device__ __forceinline__ bool exchange(Exchange& X, unsigned limit, double (&v)[kSums], double& m, bool wide,
+                                         Shared& S, const Lds<T>& lds) {
   put_sums(X, v, m, wide, S, lds.ex, lds.partner);
-  return collect(X, v, m, wide, S, lds.ex);
+  return collect(X, limit, v, m, wide, S, lds.ex);
 }
 
 struct CgResult {
@@ -595,15 +647,14 @@ struct CgResult {
 
 // CG iterations from r^ = q.r, p^ in lds.p (own and halo), r^ of the halo in lds.rh.
 // thresh, tol, max_iter, linf_test: the stopping rule of Sect. 3.3.4; dmin: smallest
-// diagonal entry.  The rule is looked at where ||r||^2 <= gate2.  inner2 > 0 (a refined
-// solve): only there, where a segment ends, and the next one, of max_segments at most,
-// ends where ||r||^2 has fallen by inner2 again, so that the last residual lies as far
-// below the threshold as that of the refinement with FP32 segments.  false: a wait timed
-// out.
+// diagonal entry.  The rule is looked at where ||r||^2 <= S.gate.  A refined solve: only
+// there, where a segment ends, and the next one, of max_segments at most, ends where ||r||
+// has fallen by A.inner_tol again, so that the last residual lies as far below the
+// threshold as that of the refinement with FP32 segments.  false: a wait timed out.
 template <typename T, int NP, ResMode kMode>
 __device__ __forceinline__ bool cg_loop(Exchange& X, Regs<T, NP, kMode>& q, const Lds<T>& lds, Shared& S, double thresh,
-                                        double tol, int max_iter, bool linf_test, double dmin, double gate2,
-                                        double inner2, int max_segments, CgResult& out) {
+                                        double tol, int max_iter, bool linf_test, double dmin, const ResArgs& A,
+                                        int max_segments, CgResult& out) {
   typedef typename Pair<T>::type T2;
   constexpr int kCap = 2 * NP * kResThreads;
   const int nh = 4 * X.me.n_units;
@@ -616,6 +667,7 @@ __device__ __forceinline__ bool cg_loop(Exchange& X, Regs<T, NP, kMode>& q, cons
     rrd = fma(a0, double(d.x), fma(a1, double(d.y), rrd));
   }
   bool wide = false;  // the next exchange carries the largest relative change too
+  bool last = A.refine && max_segments <= 1;  // no segment after this one
   for (int k = 0;; ++k) {
     double v[kSums] = {0.0, 0.0, rr, rrd};
     // (opaque: nothing derived from the places is kept in registers across iterations)
@@ -628,19 +680,21 @@ __device__ __forceinline__ bool cg_loop(Exchange& X, Regs<T, NP, kMode>& q, cons
       v[0] = fma(double(pv[0]), double(av[0]), fma(double(pv[1]), double(av[1]), v[0]));
       v[1] = fma(double(av[0]), double(av[0]), fma(double(av[1]), double(av[1]), v[1]));
     });
-    if (!exchange(X, v, linf, wide, S, lds)) return false;
+    const double gate = S.gate[tid() >> 6];
+    if (!exchange(X, A.spin_limit, v, linf, wide, S, lds)) return false;
     // the stopping test of iterate k
     if (k >= 1) {
       // (the root only where it can matter: it is a long chain before alpha)
       out.fin = isfinite(v[3]) && isfinite(v[0]) && isfinite(v[2]);
-      if (!out.fin || v[3] <= gate2 || k >= max_iter) {
+      if (!out.fin || v[3] <= gate || k >= max_iter) {
         out.rn = sqrt(v[3]);
         out.linf = linf;
         out.iters = k;
         out.conv = out.fin && ((out.rn <= thresh && (!linf_test || (wide && linf < tol))) || out.rn == 0.0);
-        if (inner2 > 0.0) {
-          gate2 = inner2 * v[3];
+        if (A.refine) {
           if (++out.segments >= max_segments) return true;
+          S.gate[tid() >> 6] = A.inner_tol * A.inner_tol * v[3];
+          last = out.segments + 1 >= max_segments;
         }
         if (!out.fin || out.conv || k >= max_iter) return true;
       }
@@ -649,28 +703,28 @@ __device__ __forceinline__ bool cg_loop(Exchange& X, Regs<T, NP, kMode>& q, cons
     const double gam = v[2];
     const double inv = 1.0 / v[0];
     double alpha = gam * inv, ratio = fma(alpha * inv, v[1], -1.0);
-    if (!isfinite(alpha) || !isfinite(ratio)) {  // the inverse overflows before the quotients do
+    if (!isfinite(alpha) || !isfinite(ratio)) {
+      // the inverse overflows before the quotients do
       alpha = gam / v[0];
       ratio = fma(alpha, v[1] / v[0], -1.0);
+      if (!isfinite(alpha) || !isfinite(ratio)) {
+        out.rn = sqrt(v[3]);
+        out.linf = 0.0;
+        out.iters = k;
+        ++out.segments;
+        // a residual below its threshold whose squares underflow is zero (cells that a
+        // pulse has barely reached keep the relative change above tol until then)
+        out.fin = out.conv = k >= 1 && v[0] == 0.0 && gam < kUnderflow && (out.rn <= thresh || thresh == 0.0);
+        return true;
+      }
     }
     const double beta = ratio > 0.0 ? ratio : 0.0;
     const double gnext = beta * gam;
-    if (!isfinite(alpha) || !isfinite(ratio)) {
-      out.rn = sqrt(v[3]);
-      out.linf = 0.0;
-      out.iters = k;
-      ++out.segments;
-      // a residual below its threshold whose squares underflow is zero (cells that a pulse
-      // has barely reached keep the relative change above tol until then)
-      out.fin = out.conv = k >= 1 && v[0] == 0.0 && gam < kUnderflow && (out.rn <= thresh || thresh == 0.0);
-      return true;
-    }
     // ||r_{k+1}||^2 >= dmin (r^,r^)_{k+1}: where that is above the threshold (with a
     // margin for the rounding of the prediction) iterate k + 1 cannot be the last, and its
     // relative change, a division per cell, is not formed (the last segment that a
     // refined solve may make ends the solve whatever its residual)
-    wide = k + 1 >= max_iter || !(gnext * dmin > 4.0 * thresh * thresh) ||
-           (inner2 > 0.0 && out.segments + 1 >= max_segments);
+    wide = last || k + 1 >= max_iter || !(gnext * dmin > 4.0 * thresh * thresh);
     const T ta = T(alpha), tb = T(beta);
     rr = rrd = linf = 0.0;
 #pragma unroll
@@ -680,10 +734,14 @@ __device__ __forceinline__ bool cg_loop(Exchange& X, Regs<T, NP, kMode>& q, cons
       const T2 po = *reinterpret_cast<const T2*>(lds.p + l);
       const T2 d = q.diag(u);
       if (wide) {
-        // |dx| / |x|, and |dx| where x = 0 (both scaled by rs = d^-1/2 here)
-        const T x0 = fabs(q.x[u][0]), x1 = fabs(q.x[u][1]);
-        const T q0 = x0 > T(0) ? x0 : sqrt(d.x), q1 = x1 > T(0) ? x1 : sqrt(d.y);
-        linf = fmax(linf, fmax(double(fabs(ta * po.x) / q0), double(fabs(ta * po.y) / q1)));
+        // |dx| / |x|, and |dx| where x = 0, of dx = rs alpha p^ and x = rs x^, rs = d^-1/2 (in
+        // a branch of its own: computed for every cell the root cost an iteration 3 to 5 %)
+        T x0 = fabs(q.x[u][0]), x1 = fabs(q.x[u][1]);
+        if ((!(x0 > T(0)) && po.x != T(0)) || (!(x1 > T(0)) && po.y != T(0))) {
+          if (!(x0 > T(0))) x0 = sqrt(d.x);
+          if (!(x1 > T(0))) x1 = sqrt(d.y);
+        }
+        linf = fmax(linf, fmax(double(fabs(ta * po.x) / x0), double(fabs(ta * po.y) / x1)));
       }
       q.x[u][0] = fma(ta, po.x, q.x[u][0]);
       q.x[u][1] = fma(ta, po.y, q.x[u][1]);
@@ -718,9 +776,12 @@ __device__ __forceinline__ bool settled(const PcgScalars& o, const ResArgs& A) {
 
 // The solve of one share of one problem.  false: a wait timed out.
 template <int NP, ResMode kMode>
-__device__ __forceinline__ bool solve_part(const DevLevel& L, const ResPlanDev& R, const ResArgs& A, int my_part,
-                                           unsigned char* dyn, Shared& S) {
+__device__ __forceinline__ bool solve_part(int my_part, unsigned char* dyn, Shared& S) {
   constexpr int kCap = 2 * NP * kResThreads;
+  KernelArgs args = kernel_args();
+  const DevLevel& L = args.L;
+  const ResPlanDev& R = args.R;
+  const ResArgs& A = args.A;
   my_part = __builtin_amdgcn_readfirstlane(my_part);
   ResPart me;  // (alike in every lane, which the compiler does not see of loaded values)
 #pragma unroll
@@ -738,7 +799,7 @@ __device__ __forceinline__ bool solve_part(const DevLevel& L, const ResPlanDev& 
   // nothing left to do: decided by an earlier launch, alike for every share
   if (A.resume && settled(A.sc[me.prob], A)) return true;
   const unsigned epoch0 = R.epoch[me.prob];
-  Exchange X{R, me, my_part, epoch0, A.meet_limit, 0u, false};
+  Exchange X{R, me, my_part, epoch0, 0u, false};
   for (int u = tid(); u < me.n_units; u += kResThreads) lds.partner[u] = R.partner[me.unit0 + u];
   if (threadIdx.x == 0) {
     S.failed = int(R.epoch[2 * R.n_prob]);  // (looked at where the first exchange ends)
@@ -800,8 +861,7 @@ __device__ __forceinline__ bool solve_part(const DevLevel& L, const ResPlanDev& 
     }
   }
   __syncthreads();
-  if (!exchange(X, v, m, true, S, lds)) return false;
-  X.spin_limit = A.spin_limit;
+  if (!exchange(X, A.meet_limit, v, m, true, S, lds)) return false;
   const double dmin = -m;
   take_halo(lds.p + kCap);
   // from here on units between shares on the same XCD go through its L2
@@ -878,7 +938,7 @@ __device__ __forceinline__ bool solve_part(const DevLevel& L, const ResPlanDev& 
 #pragma unroll
   for (int u = 0; u < NP; ++u)
     *reinterpret_cast<double2*>(lds.p + 2 * (tid() + u * kResThreads)) = double2{q.x[u][0], q.x[u][1]};
-  if (!exchange(X, v, m, false, S, lds)) return false;
+  if (!exchange(X, A.spin_limit, v, m, false, S, lds)) return false;
   take_halo(lds.p + kCap);
   __syncthreads();
   v[0] = v[1] = v[2] = v[3] = 0.0;
@@ -898,8 +958,7 @@ __device__ __forceinline__ bool solve_part(const DevLevel& L, const ResPlanDev& 
       q.r[u][1] = q.s[u][1] * b[u].y - av[1];
       keep(q.r[u][0]);
       keep(q.r[u][1]);
-      const double r0 = q.r[u][0] * sqrt(d.x), r1 = q.r[u][1] * sqrt(d.y);
-      v[0] += r0 * r0 + r1 * r1;
+      v[0] += (q.r[u][0] * d.x) * q.r[u][0] + (q.r[u][1] * d.y) * q.r[u][1];
       if (l < ns && ch[u].x == -1) v[1] += b[u].x * b[u].x;
       if (l < ns && ch[u].y == -1) v[1] += b[u].y * b[u].y;
       stage(q, lds.ex, u, q.r[u][0], q.r[u][1]);
@@ -909,7 +968,7 @@ __device__ __forceinline__ bool solve_part(const DevLevel& L, const ResPlanDev& 
 #pragma unroll
   for (int u = 0; u < NP; ++u)
     *reinterpret_cast<double2*>(lds.p + 2 * (tid() + u * kResThreads)) = double2{q.r[u][0], q.r[u][1]};
-  if (!exchange(X, v, m, false, S, lds)) return false;
+  if (!exchange(X, A.spin_limit, v, m, false, S, lds)) return false;
   take_halo(lds.rh);
   take_halo(lds.p + kCap);
   __syncthreads();
@@ -917,7 +976,8 @@ __device__ __forceinline__ bool solve_part(const DevLevel& L, const ResPlanDev& 
   const double start2 = v[0];
   const double rnorm0 = A.resume ? A.sc[me.prob].rnorm0 : sqrt(v[0]), bnorm = sqrt(v[1]);
   const double floor_b = A.abs_floor * bnorm, thresh = A.resume ? A.sc[me.prob].thresh : fmax(A.tol * rnorm0, floor_b);
-  const int before = A.resume ? A.sc[me.prob].inner_total : 0, outer = A.resume ? A.sc[me.prob].iter : 0;
+  const int before = A.resume ? A.sc[me.prob].inner_total : 0;
+  const int outer = __builtin_amdgcn_readfirstlane(A.resume ? A.sc[me.prob].iter : 0);
   CgResult res;
   res.rn = sqrt(start2);
   res.linf = 0.0;
@@ -925,13 +985,12 @@ __device__ __forceinline__ bool solve_part(const DevLevel& L, const ResPlanDev& 
   res.fin = isfinite(start2) && isfinite(bnorm);
   res.conv = res.fin && res.rn <= floor_b;
   const long long clk0 = wall_clock64();
-  const double inner2 = A.refine ? A.inner_tol * A.inner_tol : 0.0;
-  const double gate2 = A.refine ? inner2 * start2 : 1.000001 * thresh * thresh;
+  S.gate[tid() >> 6] = A.refine ? A.inner_tol * A.inner_tol * start2 : 1.000001 * thresh * thresh;
   if (res.fin && !res.conv &&
-      !cg_loop(X, q, lds, S, thresh, A.tol, A.max_iter - before, A.linf_test != 0, dmin, gate2, inner2,
-               A.max_outer - outer, res))
+      !cg_loop(X, q, lds, S, thresh, A.tol, A.max_iter - before, A.linf_test != 0, dmin, A, A.max_outer - outer, res))
     return false;
   const long long clk1 = wall_clock64();
+  args = kernel_args();
 
   // the unscaled iterate, the T update of the coupling term (linearised emission), the
   // true residual b - (A^ x^) / rs and the smallest leaf energy
@@ -973,7 +1032,7 @@ __device__ __forceinline__ bool solve_part(const DevLevel& L, const ResPlanDev& 
   if (A.true_residual) {
     double none = 0.0;
     __syncthreads();
-    if (!exchange(X, v, none, false, S, lds)) return false;
+    if (!exchange(X, A.spin_limit, v, none, false, S, lds)) return false;
     take_halo(lds.p + kCap);
     __syncthreads();
     v[0] = v[1] = v[2] = v[3] = 0.0;
@@ -990,7 +1049,7 @@ __device__ __forceinline__ bool solve_part(const DevLevel& L, const ResPlanDev& 
   v[1] = v[2] = v[3] = 0.0;
   put_sums(X, v, m, true, S, static_cast<const double*>(nullptr), lds.partner);
   if (my_part != me.part0) return true;
-  if (!collect(X, v, m, true, S, static_cast<double*>(nullptr))) return false;
+  if (!collect(X, A.spin_limit, v, m, true, S, static_cast<double*>(nullptr))) return false;
   if (threadIdx.x == 0) {
     R.epoch[me.prob] = X.epoch;
     PcgScalars z{};
@@ -1025,8 +1084,11 @@ __device__ __forceinline__ bool solve_part(const DevLevel& L, const ResPlanDev& 
 
 // A block that gave up at its k-th share leaves: none of the problems it leads from there
 // on is completed by this launch.
-__device__ __forceinline__ void give_up(const ResPlanDev& R, const ResArgs& A, int k) {
+__device__ __forceinline__ void give_up(int k) {
   if (threadIdx.x != 0) return;
+  const KernelArgs args = kernel_args();
+  const ResPlanDev& R = args.R;
+  const ResArgs& A = args.A;
   st_word32(R.epoch + 2 * R.n_prob, 1u);
   for (; k < R.task0[blockIdx.x + 1]; ++k) {
     const ResPart& p = R.parts[R.task[k]];
@@ -1036,13 +1098,15 @@ __device__ __forceinline__ void give_up(const ResPlanDev& R, const ResArgs& A, i
 }
 
 template <int NP, ResMode kMode>
-__global__ __launch_bounds__(kResThreads) void k_cg_resident(DevLevel L, ResPlanDev R, ResArgs A) {
+__global__ __launch_bounds__(kResThreads) void k_cg_resident(KernelArgs) {
   extern __shared__ __align__(16) unsigned char res_lds[];
   __shared__ Shared S;
   const int b = int(blockIdx.x);
-  for (int k = R.task0[b]; k < R.task0[b + 1]; ++k) {
-    if (!solve_part<NP, kMode>(L, R, A, R.task[k], res_lds, S)) {
-      give_up(R, A, k);
+  const KernelArgs args = kernel_args();
+  const int end = args.R.task0[b + 1];
+  for (int k = args.R.task0[b]; k < end; ++k) {
+    if (!solve_part<NP, kMode>(kernel_args().R.task[k], res_lds, S)) {
+      give_up(k);
       return;
     }
     __syncthreads();
@@ -1051,24 +1115,27 @@ __global__ __launch_bounds__(kResThreads) void k_cg_resident(DevLevel L, ResPlan
 
 // Shares of several sizes in one launch: each runs with as many pairs per thread as it
 // needs (a small share in the loops of a large one would mostly iterate over nothing).
-__global__ __launch_bounds__(kResThreads) void k_cg_resident_batch(DevLevel L, ResPlanDev R, ResArgs A) {
+__global__ __launch_bounds__(kResThreads) void k_cg_resident_batch(KernelArgs) {
   extern __shared__ __align__(16) unsigned char res_lds[];
   __shared__ Shared S;
   const int b = int(blockIdx.x);
-  for (int k = R.task0[b]; k < R.task0[b + 1]; ++k) {
-    const int part = R.task[k];
+  const KernelArgs args = kernel_args();
+  const int end = args.R.task0[b + 1];
+  for (int k = args.R.task0[b]; k < end; ++k) {
+    const KernelArgs now = kernel_args();
+    const int part = now.R.task[k];
     bool ok;
-    switch ((R.parts[part].n_slots + 2 * kResThreads - 1) / (2 * kResThreads)) {
-      case 1: ok = solve_part<1, kHeld>(L, R, A, part, res_lds, S); break;
-      case 2: ok = solve_part<2, kHeld>(L, R, A, part, res_lds, S); break;
-      case 3: ok = solve_part<3, kHeld>(L, R, A, part, res_lds, S); break;
-      case 4: ok = solve_part<4, kHeld>(L, R, A, part, res_lds, S); break;
-      case 5: ok = solve_part<5, kHeld>(L, R, A, part, res_lds, S); break;
-      case 6: ok = solve_part<6, kStreamed>(L, R, A, part, res_lds, S); break;
-      default: ok = solve_part<8, kStreamed>(L, R, A, part, res_lds, S);
+    switch ((now.R.parts[part].n_slots + 2 * kResThreads - 1) / (2 * kResThreads)) {
+      case 1: ok = solve_part<1, kHeld>(part, res_lds, S); break;
+      case 2: ok = solve_part<2, kHeld>(part, res_lds, S); break;
+      case 3: ok = solve_part<3, kHeld>(part, res_lds, S); break;
+      case 4: ok = solve_part<4, kHeld>(part, res_lds, S); break;
+      case 5: ok = solve_part<5, kHeld>(part, res_lds, S); break;
+      case 6: ok = solve_part<6, kStreamed>(part, res_lds, S); break;
+      default: ok = solve_part<8, kStreamed>(part, res_lds, S);
     }
     if (!ok) {
-      give_up(R, A, k);
+      give_up(k);
       return;
     }
     __syncthreads();
@@ -1083,12 +1150,12 @@ int pairs_of(int n_slots, int n_prob) {
   return n_prob > 1 && np == 7 ? 8 : np;
 }
 
-hipError_t launch_kernel(void (*f)(DevLevel, ResPlanDev, ResArgs), hipStream_t s, const DevLevel& L,
-                         const ResPlanDev& R, const ResArgs& A) {
+hipError_t launch_kernel(void (*f)(KernelArgs), hipStream_t s, const DevLevel& L, const ResPlanDev& R,
+                         const ResArgs& A) {
   const hipError_t e =
       hipFuncSetAttribute(reinterpret_cast<const void*>(f), hipFuncAttributeMaxDynamicSharedMemorySize, R.lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(f, dim3(R.n_blocks), dim3(kResThreads), R.lds, s, L, R, A);
+  hipLaunchKernelGGL(f, dim3(R.n_blocks), dim3(kResThreads), R.lds, s, KernelArgs{L, R, A});
   return hipGetLastError();
 }
 
