@@ -789,13 +789,13 @@ __device__ __forceinline__ bool solve_part(int my_part, unsigned char* dyn, Shar
     reinterpret_cast<int*>(&me)[k] = __builtin_amdgcn_readfirstlane(reinterpret_cast<const int*>(R.parts + my_part)[k]);
   const int ns = me.n_slots, n = L.n_slots;
   const int nh = 4 * me.n_units;
+  double* const dl = reinterpret_cast<double*>(dyn);
+  const ResLds at_lds(kCap, size_t(me.n_units), kMode == kCoupled ? size_t(me.n_coarse) : 0, kMode != kStreamed);
   Lds<double> lds;
-  lds.p = reinterpret_cast<double*>(dyn);
-
-  lds.rh = lds.p + kCap + nh;
-  lds.ex = lds.rh + nh;
-  lds.partner = reinterpret_cast<int*>(lds.ex + nh);
-  double* const lds_d = reinterpret_cast<double*>(lds.partner + ((me.n_units + 1) & ~1));
+  lds.p = dl + at_lds.p;
+  lds.rh = dl + at_lds.rh;
+  lds.ex = dl + at_lds.ex;
+  lds.partner = reinterpret_cast<int*>(dl + at_lds.partner);
   // nothing left to do: decided by an earlier launch, alike for every share
   if (A.resume && settled(A.sc[me.prob], A)) return true;
   const unsigned epoch0 = R.epoch[me.prob];
@@ -816,9 +816,9 @@ __device__ __forceinline__ bool solve_part(int my_part, unsigned char* dyn, Shar
   q.face = 0;
   if constexpr (kMode == kStreamed)
     q.cs = reinterpret_cast<double2*>(static_cast<double*>(R.extra) + size_t(blockIdx.x) * kResStreamDoubles);
-  else q.d = lds_d;
+  else q.d = dl + at_lds.diag;
   if constexpr (kMode == kCoupled) {
-    q.cv = lds_d + kCap;
+    q.cv = dl + at_lds.coarse;
     q.uc0 = 4 * (me.n_units - me.n_coarse);
   }
   double v[kSums] = {0.0, 0.0, 0.0, 0.0}, m = -DBL_MAX;
@@ -1161,17 +1161,12 @@ hipError_t launch_kernel(void (*f)(KernelArgs), hipStream_t s, const DevLevel& L
 
 }  // namespace
 
-// Of one share: the places of a vector and its halo, r^ and exchanged values of the halo,
-// the partner units and, where the coefficients are in registers, the diagonal; the
-// coefficients of the finer cells.  The
-// shares of one problem run with as many pairs as its largest.
+// The shares of one problem run with as many pairs as its largest.
 int resident_lds(const std::vector<ResPart>& parts, int max_slots, int n_prob) {
   size_t most = 0;
   for (const ResPart& p : parts) {
     const int np = pairs_of(n_prob > 1 ? p.n_slots : max_slots, n_prob);
-    const size_t cap = 2 * size_t(np) * kResThreads, nh = 4 * size_t(p.n_units);
-    most = std::max(most, (cap + 3 * nh + (np <= kResPairs ? cap : 0) + 4 * size_t(p.n_coarse)) * sizeof(double) +
-                              size_t((p.n_units + 1) & ~1) * sizeof(int));
+    most = std::max(most, ResLds(2 * size_t(np) * kResThreads, p.n_units, p.n_coarse, np <= kResPairs).bytes);
   }
   return int(std::min<size_t>(most, 1u << 30));
 }

@@ -2,6 +2,7 @@
 // (host side, no device code): contiguous shares of octs, and the faces between them.
 #pragma once
 
+#include <cstddef>
 #include <cstdint>
 #include <vector>
 
@@ -16,6 +17,22 @@ struct ResPart {
   int prob;            // the problem
   int part0, group;    // the problem's shares are [part0, part0 + group)
   int n_coarse;        // the last of its units: its cells' faces towards finer cells
+};
+
+// Where a share's arrays lie in LDS, in doubles from a 16-byte boundary: p^ and r^ of the
+// slots and the halo, the exchanged values, the diagonal (held shares), the coefficients
+// of the finer cells, and last the partner units, the only ones that are not read in pairs
+// of 16 bytes.  cap: places of the slots (even).
+struct ResLds {
+  size_t p, rh, ex, diag, coarse, partner, bytes;
+  constexpr ResLds(size_t cap, size_t units, size_t n_coarse, bool held)
+      : p(0),
+        rh(cap + 4 * units),
+        ex(rh + 4 * units),
+        diag(ex + 4 * units),
+        coarse(diag + (held ? cap : 0)),
+        partner(coarse + 4 * n_coarse),
+        bytes(partner * sizeof(double) + ((units + 1) & ~size_t(1)) * sizeof(int32_t)) {}
 };
 
 struct ResPlanHost {
