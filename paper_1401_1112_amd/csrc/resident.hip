@@ -97,10 +97,6 @@ __device__ __forceinline__ double dpp(double old, double v) {
       unsigned(__builtin_amdgcn_update_dpp(int(unsigned(o)), int(unsigned(w)), kCtrl, 0xf, 0xf, false)),
       unsigned(__builtin_amdgcn_update_dpp(int(unsigned(o >> 32)), int(unsigned(w >> 32)), kCtrl, 0xf, 0xf, false)));
 }
-template <int kCtrl>
-__device__ __forceinline__ float dpp(float old, float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(old), __float_as_int(v), kCtrl, 0xf, 0xf, false));
-}
 constexpr int kQuadXor1 = 0xB1, kQuadXor2 = 0x4E, kRowShr1 = 0x111, kRowShr2 = 0x112, kRowShr4 = 0x114,
               kRowShr8 = 0x118;
 
@@ -213,11 +209,9 @@ __device__ __forceinline__ KernelArgs kernel_args() {
 }
 
 // Words of one value in the halo memory, and of the four of a unit.
-template <typename T>
-constexpr int kValueWords = int(sizeof(T) / 4);
+constexpr int kValueWords = 2, kUnitWords = 4 * kValueWords;
 
 __device__ __forceinline__ unsigned half(double v, int h) { return unsigned(bits_of(v) >> (32 * h)); }
-__device__ __forceinline__ unsigned half(float v, int) { return unsigned(__float_as_int(v)); }
 
 // The export list to the partners' halo memory: consecutive lanes store consecutive
 // words, so that one store fills a unit's line.  Units whose partner runs on the same XCD
@@ -225,26 +219,24 @@ __device__ __forceinline__ unsigned half(float v, int) { return unsigned(__float
 // 3.0 us so and 5.7 through memory, 600 units 3.4 and 7.2.  (The two kinds never share a
 // cache line, nor do near units of two shares: a line is written from one XCD only.)
 // A step of four levels to 1.25 M slots: 12.1 ms with all units through memory, 10.9 so.
-template <typename T>
-__device__ __forceinline__ void put_halo(const Exchange& X, const T* ex, const int* partner) {
-  constexpr int kW = kValueWords<T>, kUnit = 4 * kW;
+__device__ __forceinline__ void put_halo(const Exchange& X, const double* ex, const int* partner) {
   const u64 st = u64(X.epoch) << 32;
   u64* const h = X.halo(0);
   const int far = X.R.far_units();
   constexpr int kBatch = 4;  // words of a thread at a time, so that their LDS reads overlap
-  const int nw = kUnit * X.me.n_units;
+  const int nw = kUnitWords * X.me.n_units;
   for (int w0 = tid(); w0 < nw; w0 += kBatch * kResThreads) {
     int to[kBatch];
     unsigned d[kBatch];
 #pragma unroll
     for (int k = 0; k < kBatch; ++k) {
       const int w = min(w0 + k * kResThreads, nw - 1);
-      to[k] = partner[w / kUnit];
-      d[k] = half(ex[w / kW], w % kW);
+      to[k] = partner[w / kUnitWords];
+      d[k] = half(ex[w / kValueWords], w % kValueWords);
     }
 #pragma unroll
     for (int k = 0; k < kBatch; ++k) {
-      u64* const p = h + (size_t(to[k]) * 8 + w0 % kUnit);
+      u64* const p = h + (size_t(to[k]) * 8 + w0 % kUnitWords);
       if (w0 + k * kResThreads >= nw) break;
       if (to[k] >= far) st_word_near(p, st | d[k]);
       else st_word(p, st | d[k]);
@@ -255,10 +247,9 @@ __device__ __forceinline__ void put_halo(const Exchange& X, const T* ex, const i
 // The halo values of this exchange to sh, a word per lane, kBatch words of a thread in
 // flight.  Every value is stored by the thread that exported the one at the same place,
 // so sh and ex are the same memory.  false: a wait timed out.
-template <int kBatch, typename T>
-__device__ __forceinline__ bool get_halo(const Exchange& X, unsigned limit, T* sh) {
-  constexpr int kW = kValueWords<T>;
-  const int nw = 4 * kW * X.me.n_units;
+template <int kBatch>
+__device__ __forceinline__ bool get_halo(const Exchange& X, unsigned limit, double* sh) {
+  const int nw = kUnitWords * X.me.n_units;
   const u64* h = X.halo(X.me.unit0);
   // from a unit's place among the far ones to that among the near ones (near_base)
   const unsigned to_near = 8u * unsigned(X.R.far_units() + ((X.me.unit0 + X.my_part + 1) & ~1) - X.me.unit0);
@@ -287,20 +278,16 @@ __device__ __forceinline__ bool get_halo(const Exchange& X, unsigned limit, T* s
     for (int k = 0; k < kBatch; ++k) {
       const int w = w0 + k * kResThreads;
       const unsigned mine = unsigned(c[k]);
-      if constexpr (kW == 1) {
-        if (w < nw) sh[w] = __int_as_float(int(mine));
-      } else {  // the other half is in the neighbour lane
-        const unsigned other = unsigned(__builtin_amdgcn_update_dpp(0, int(mine), kQuadXor1, 0xf, 0xf, false));
-        if (w < nw && !(w & 1)) sh[w >> 1] = of_words(mine, other);
-      }
+      // the other half is in the neighbour lane
+      const unsigned other = unsigned(__builtin_amdgcn_update_dpp(0, int(mine), kQuadXor1, 0xf, 0xf, false));
+      if (w < nw && !(w & 1)) sh[w >> 1] = of_words(mine, other);
     }
     near >>= kBatch;
   }
   return true;
 }
-template <typename T>
-__device__ __forceinline__ bool get_halo(const Exchange& X, unsigned limit, T* sh) {
-  const int nw = 4 * kValueWords<T> * X.me.n_units;
+__device__ __forceinline__ bool get_halo(const Exchange& X, unsigned limit, double* sh) {
+  const int nw = kUnitWords * X.me.n_units;
   if (nw <= 2 * kResThreads) return get_halo<2>(X, limit, sh);
   if (nw <= 4 * kResThreads) return get_halo<4>(X, limit, sh);
   return get_halo<8>(X, limit, sh);
@@ -334,9 +321,8 @@ __device__ __forceinline__ void row_totals(const double (&rows)[kWaves][kSums + 
 
 // This share's sums v and (wide) maximum m published, and its export list ex (null:
 // none); a problem of one share: the sums returned to every thread.
-template <typename T>
 __device__ __forceinline__ void put_sums(const Exchange& X, double (&v)[kSums], double& m, bool wide, Shared& S,
-                                         const T* ex, const int* partner) {
+                                         const double* ex, const int* partner) {
   const int t = tid(), lane = t & 63, wid = t >> 6;
   const double a = wave_sums(v);
   if ((lane & 15) == 15) S.part[wid][((lane >> 5) & 1) | ((lane >> 3) & 2)] = a;
@@ -374,9 +360,8 @@ __device__ __forceinline__ void put_sums(const Exchange& X, double (&v)[kSums], 
 // The sums (and maximum) over the whole problem to every thread, and the halo values
 // that the neighbour shares published for this exchange to sh (null: none).  false: a
 // wait took more than limit polls.
-template <typename T>
 __device__ __forceinline__ bool collect(Exchange& X, unsigned limit, double (&v)[kSums], double& m, bool wide, Shared& S,
-                                        T* sh) {
+                                        double* sh) {
   const int t = tid(), lane = t & 63, wid = t >> 6, G = X.me.group;
   if (G == 1) {
     ++X.epoch;
@@ -429,30 +414,18 @@ __device__ __forceinline__ bool collect(Exchange& X, unsigned limit, double (&v)
 }
 
 
-template <typename T>
-struct Pair;
-template <>
-struct Pair<double> {
-  typedef double2 type;
-};
-template <>
-struct Pair<float> {
-  typedef float2 type;
-};
-
 // Scaled face coefficients of a pair: within the oct cix (the same for both slots), ciy,
 // ciz; out of the oct cox, coy, coz.
-template <typename T>
 struct Coefs {
-  T cix, ciy[2], ciz[2], cox[2], coy[2], coz[2];
+  double cix, ciy[2], ciz[2], cox[2], coy[2], coz[2];
 };
 
 // A share's state in registers, NP pairs of slots per thread (thread t holds pairs
 // t + 512 u of the share).  Places in p: of the out-of-oct neighbours in x of both slots
 // (px, 16 bits each) and of the pairs in y and z (pyz).
-template <typename T, int NP>
+template <int NP>
 struct State {
-  T x[NP][2], r[NP][2], s[NP][2];
+  double x[NP][2], r[NP][2], s[NP][2];
   unsigned px[NP], pyz[NP];
   unsigned face;  // bit u: pair u has a cell on a face between shares
 };
@@ -467,19 +440,18 @@ enum ResMode { kHeld, kStreamed, kCoupled };
 // sweep.  What ends it at 8192 slots is the register file.  64 patches of 16.9 M cells,
 // the 7.8 M of five of them in streamed shares (128^3 and less): 42.8 ms for two steps
 // against 69 with sweeps of those five.
-template <typename T, int NP, ResMode kMode>
+template <int NP, ResMode kMode>
 struct Regs;
 
-template <typename T, int NP>
-struct Regs<T, NP, kHeld> : State<T, NP> {
-  typedef typename Pair<T>::type T2;
-  Coefs<T> c[NP];
-  T* d;
+template <int NP>
+struct Regs<NP, kHeld> : State<NP> {
+  Coefs c[NP];
+  double* d;
 
-  __device__ __forceinline__ Coefs<T> coefs(int u) const { return c[u]; }
-  __device__ __forceinline__ void put_axis(int u, int a, T ci0, T ci1, T co0, T co1) {
-    T(&ci)[2] = a == 1 ? c[u].ciy : c[u].ciz;
-    T(&co)[2] = a == 0 ? c[u].cox : a == 1 ? c[u].coy : c[u].coz;
+  __device__ __forceinline__ Coefs coefs(int u) const { return c[u]; }
+  __device__ __forceinline__ void put_axis(int u, int a, double ci0, double ci1, double co0, double co1) {
+    double(&ci)[2] = a == 1 ? c[u].ciy : c[u].ciz;
+    double(&co)[2] = a == 0 ? c[u].cox : a == 1 ? c[u].coy : c[u].coz;
     if (a == 0) {
       c[u].cix = ci0;
       keep(c[u].cix);
@@ -494,35 +466,34 @@ struct Regs<T, NP, kHeld> : State<T, NP> {
     keep(co[0]);
     keep(co[1]);
   }
-  __device__ __forceinline__ T2 diag(int u) const {
-    return *reinterpret_cast<const T2*>(d + 2 * (tid() + u * kResThreads));
+  __device__ __forceinline__ double2 diag(int u) const {
+    return *reinterpret_cast<const double2*>(d + 2 * (tid() + u * kResThreads));
   }
-  __device__ __forceinline__ void put_diag(int u, T2 v) {
-    *reinterpret_cast<T2*>(d + 2 * (tid() + u * kResThreads)) = v;
+  __device__ __forceinline__ void put_diag(int u, double2 v) {
+    *reinterpret_cast<double2*>(d + 2 * (tid() + u * kResThreads)) = v;
   }
 };
 
-template <typename T, int NP>
-struct Regs<T, NP, kStreamed> : State<T, NP> {
-  typedef typename Pair<T>::type T2;
-  T dr[NP][2];
-  T2* cs;  // five arrays of NP * 512 pairs (ciy, ciz, cox, coy, coz), then cix
+template <int NP>
+struct Regs<NP, kStreamed> : State<NP> {
+  double dr[NP][2];
+  double2* cs;  // five arrays of NP * 512 pairs (ciy, ciz, cox, coy, coz), then cix
 
-  __device__ __forceinline__ T2* at(int k, int u) const { return cs + (k * NP + u) * kResThreads + tid(); }
-  __device__ __forceinline__ T* x_at(int u) const {
-    return reinterpret_cast<T*>(cs + 5 * NP * kResThreads) + u * kResThreads + tid();
+  __device__ __forceinline__ double2* at(int k, int u) const { return cs + (k * NP + u) * kResThreads + tid(); }
+  __device__ __forceinline__ double* x_at(int u) const {
+    return reinterpret_cast<double*>(cs + 5 * NP * kResThreads) + u * kResThreads + tid();
   }
-  __device__ __forceinline__ Coefs<T> coefs(int u) const {
-    const T2 iy = *at(0, u), iz = *at(1, u), ox = *at(2, u), oy = *at(3, u), oz = *at(4, u);
-    return Coefs<T>{*x_at(u), {iy.x, iy.y}, {iz.x, iz.y}, {ox.x, ox.y}, {oy.x, oy.y}, {oz.x, oz.y}};
+  __device__ __forceinline__ Coefs coefs(int u) const {
+    const double2 iy = *at(0, u), iz = *at(1, u), ox = *at(2, u), oy = *at(3, u), oz = *at(4, u);
+    return Coefs{*x_at(u), {iy.x, iy.y}, {iz.x, iz.y}, {ox.x, ox.y}, {oy.x, oy.y}, {oz.x, oz.y}};
   }
-  __device__ __forceinline__ void put_axis(int u, int a, T ci0, T ci1, T co0, T co1) {
+  __device__ __forceinline__ void put_axis(int u, int a, double ci0, double ci1, double co0, double co1) {
     if (a == 0) *x_at(u) = ci0;
-    else *at(a - 1, u) = T2{ci0, ci1};
-    *at(2 + a, u) = T2{co0, co1};
+    else *at(a - 1, u) = double2{ci0, ci1};
+    *at(2 + a, u) = double2{co0, co1};
   }
-  __device__ __forceinline__ T2 diag(int u) const { return T2{dr[u][0], dr[u][1]}; }
-  __device__ __forceinline__ void put_diag(int u, T2 v) {
+  __device__ __forceinline__ double2 diag(int u) const { return double2{dr[u][0], dr[u][1]}; }
+  __device__ __forceinline__ void put_diag(int u, double2 v) {
     dr[u][0] = v.x;
     dr[u][1] = v.y;
     keep(dr[u][0]);
@@ -531,36 +502,34 @@ struct Regs<T, NP, kStreamed> : State<T, NP> {
 };
 
 // As kHeld, and couplings to finer cells.
-template <typename T, int NP>
-struct Regs<T, NP, kCoupled> : Regs<T, NP, kHeld> {
+template <int NP>
+struct Regs<NP, kCoupled> : Regs<NP, kHeld> {
   unsigned cu[NP];  // of a pair: first of its coarse units (16 bits), units of either slot (8 bits each)
-  T* cv;            // [4 coarse units]: scaled coefficients of their finer cells (in LDS)
+  double* cv;       // [4 coarse units]: scaled coefficients of their finer cells (in LDS)
   int uc0;          // halo position of the first coarse unit
 };
 
 // LDS arrays of a share.
-template <typename T>
 struct Lds {
-  T* p;         // [cap + 4 units]: p^ of the share, then of its halo cells
-  T* rh;        // [4 units]: r^ of the halo cells
-  T* ex;        // [4 units]: this share's cells on the same faces, then the halo cells'
+  double* p;    // [cap + 4 units]: p^ of the share, then of its halo cells
+  double* rh;   // [4 units]: r^ of the halo cells
+  double* ex;   // [4 units]: this share's cells on the same faces, then the halo cells'
                 // values of the current exchange
   int* partner; // [units]
 };
 
 // (A^ v) of pair u, v in p.
-template <typename T, int NP>
-__device__ __forceinline__ void apply(const State<T, NP>& q, const Coefs<T>& c, const T* p, int u, T (&pv)[2],
-                                      T (&av)[2]) {
-  typedef typename Pair<T>::type T2;
+template <int NP>
+__device__ __forceinline__ void apply(const State<NP>& q, const Coefs& c, const double* p, int u, double (&pv)[2],
+                                      double (&av)[2]) {
   const int l = 2 * (tid() + u * kResThreads);
-  const T2 own = *reinterpret_cast<const T2*>(p + l);
-  const T2 ny = *reinterpret_cast<const T2*>(p + (q.pyz[u] & 0xffffu));
-  const T2 nz = *reinterpret_cast<const T2*>(p + (q.pyz[u] >> 16));
-  const T nx0 = p[q.px[u] & 0xffffu], nx1 = p[q.px[u] >> 16];
+  const double2 own = *reinterpret_cast<const double2*>(p + l);
+  const double2 ny = *reinterpret_cast<const double2*>(p + (q.pyz[u] & 0xffffu));
+  const double2 nz = *reinterpret_cast<const double2*>(p + (q.pyz[u] >> 16));
+  const double nx0 = p[q.px[u] & 0xffffu], nx1 = p[q.px[u] >> 16];
   pv[0] = own.x;
   pv[1] = own.y;
-  T a0 = own.x, a1 = own.y;
+  double a0 = own.x, a1 = own.y;
   a0 = fma(-c.cix, own.y, a0);
   a1 = fma(-c.cix, own.x, a1);
   a0 = fma(-c.ciy[0], dpp<kQuadXor1>(own.x, own.x), a0);
@@ -578,22 +547,22 @@ __device__ __forceinline__ void apply(const State<T, NP>& q, const Coefs<T>& c, 
 }
 
 // f(u, v, A^ v) for every pair; streamed coefficients are loaded one pair ahead.
-template <typename T, int NP, ResMode kMode, class F>
-__device__ __forceinline__ void apply_all(const Regs<T, NP, kMode>& q, const T* p, F f) {
-  Coefs<T> c = q.coefs(0);
+template <int NP, ResMode kMode, class F>
+__device__ __forceinline__ void apply_all(const Regs<NP, kMode>& q, const double* p, F f) {
+  Coefs c = q.coefs(0);
 #pragma unroll
   for (int u = 0; u < NP; ++u) {
     __builtin_amdgcn_sched_barrier(0);
-    Coefs<T> next;
+    Coefs next;
     if (kMode == kStreamed && u + 1 < NP) next = q.coefs(u + 1);
-    T pv[2], av[2];
+    double pv[2], av[2];
     apply(q, c, p, u, pv, av);
     if constexpr (kMode == kCoupled) {
       if (q.cu[u]) {
         const int k1 = int(q.cu[u] & 0xffffu) + int((q.cu[u] >> 16) & 0xffu), k2 = k1 + int(q.cu[u] >> 24);
-        const T* ph = p + 2 * NP * kResThreads + q.uc0;
+        const double* ph = p + 2 * NP * kResThreads + q.uc0;
         for (int k = int(q.cu[u] & 0xffffu); k < k2; ++k) {
-          T t = T(0);
+          double t = 0.0;
 #pragma unroll
           for (int e = 0; e < 4; ++e) t = fma(q.cv[4 * k + e], ph[4 * k + e], t);
           if (k < k1) av[0] -= t;
@@ -608,10 +577,9 @@ __device__ __forceinline__ void apply_all(const Regs<T, NP, kMode>& q, const T* 
 
 // The values of pair u that lie on faces between shares to the block's export list
 // (ordered like its halo cells).
-template <typename T, int NP, ResMode kMode>
-__device__ __forceinline__ void stage(const Regs<T, NP, kMode>& q, T* ex, int u, T v0, T v1) {
+template <int NP, ResMode kMode>
+__device__ __forceinline__ void stage(const Regs<NP, kMode>& q, double* ex, int u, double v0, double v1) {
   constexpr int kCap = 2 * NP * kResThreads;
-  typedef typename Pair<T>::type T2;
   if constexpr (kMode == kCoupled) {
     if (q.cu[u]) {
       const int k1 = int(q.cu[u] & 0xffffu) + int((q.cu[u] >> 16) & 0xffu), k2 = k1 + int(q.cu[u] >> 24);
@@ -625,16 +593,15 @@ __device__ __forceinline__ void stage(const Regs<T, NP, kMode>& q, T* ex, int u,
   const int y = int(q.pyz[u] & 0xffffu) - kCap, z = int(q.pyz[u] >> 16) - kCap;
   if (x0 >= 0) ex[x0] = v0;
   if (x1 >= 0) ex[x1] = v1;
-  T2 w;
+  double2 w;
   w.x = v0;
   w.y = v1;
-  if (y >= 0) *reinterpret_cast<T2*>(ex + y) = w;
-  if (z >= 0) *reinterpret_cast<T2*>(ex + z) = w;
+  if (y >= 0) *reinterpret_cast<double2*>(ex + y) = w;
+  if (z >= 0) *reinterpret_cast<double2*>(ex + z) = w;
 }
 
-template <typename T>
 __device__ __forceinline__ bool exchange(Exchange& X, unsigned limit, double (&v)[kSums], double& m, bool wide,
-                                         Shared& S, const Lds<T>& lds) {
+                                         Shared& S, const Lds& lds) {
   put_sums(X, v, m, wide, S, lds.ex, lds.partner);
   return collect(X, limit, v, m, wide, S, lds.ex);
 }
@@ -651,20 +618,19 @@ struct CgResult {
 // there, where a segment ends, and the next one, of max_segments at most, ends where ||r||
 // has fallen by A.inner_tol again, so that the last residual lies as far below the
 // threshold as that of the refinement with FP32 segments.  false: a wait timed out.
-template <typename T, int NP, ResMode kMode>
-__device__ __forceinline__ bool cg_loop(Exchange& X, Regs<T, NP, kMode>& q, const Lds<T>& lds, Shared& S, double thresh,
+template <int NP, ResMode kMode>
+__device__ __forceinline__ bool cg_loop(Exchange& X, Regs<NP, kMode>& q, const Lds& lds, Shared& S, double thresh,
                                         double tol, int max_iter, bool linf_test, double dmin, const ResArgs& A,
                                         int max_segments, CgResult& out) {
-  typedef typename Pair<T>::type T2;
   constexpr int kCap = 2 * NP * kResThreads;
   const int nh = 4 * X.me.n_units;
   double rr = 0.0, rrd = 0.0, linf = 0.0;
 #pragma unroll
   for (int u = 0; u < NP; ++u) {
-    const T2 d = q.diag(u);
-    const double a0 = double(q.r[u][0]) * double(q.r[u][0]), a1 = double(q.r[u][1]) * double(q.r[u][1]);
+    const double2 d = q.diag(u);
+    const double a0 = q.r[u][0] * q.r[u][0], a1 = q.r[u][1] * q.r[u][1];
     rr += a0 + a1;
-    rrd = fma(a0, double(d.x), fma(a1, double(d.y), rrd));
+    rrd = fma(a0, d.x, fma(a1, d.y, rrd));
   }
   bool wide = false;  // the next exchange carries the largest relative change too
   bool last = A.refine && max_segments <= 1;  // no segment after this one
@@ -673,12 +639,12 @@ __device__ __forceinline__ bool cg_loop(Exchange& X, Regs<T, NP, kMode>& q, cons
     // (opaque: nothing derived from the places is kept in registers across iterations)
 #pragma unroll
     for (int u = 0; u < NP; ++u) asm volatile("" : "+v"(q.px[u]), "+v"(q.pyz[u]));
-    apply_all(q, lds.p, [&](int u, const T(&pv)[2], const T(&av)[2]) {
+    apply_all(q, lds.p, [&](int u, const double(&pv)[2], const double(&av)[2]) {
       q.s[u][0] = av[0];
       q.s[u][1] = av[1];
       stage(q, lds.ex, u, av[0], av[1]);
-      v[0] = fma(double(pv[0]), double(av[0]), fma(double(pv[1]), double(av[1]), v[0]));
-      v[1] = fma(double(av[0]), double(av[0]), fma(double(av[1]), double(av[1]), v[1]));
+      v[0] = fma(pv[0], av[0], fma(pv[1], av[1], v[0]));
+      v[1] = fma(av[0], av[0], fma(av[1], av[1], v[1]));
     });
     const double gate = S.gate[tid() >> 6];
     if (!exchange(X, A.spin_limit, v, linf, wide, S, lds)) return false;
@@ -725,45 +691,44 @@ __device__ __forceinline__ bool cg_loop(Exchange& X, Regs<T, NP, kMode>& q, cons
     // relative change, a division per cell, is not formed (the last segment that a
     // refined solve may make ends the solve whatever its residual)
     wide = last || k + 1 >= max_iter || !(gnext * dmin > 4.0 * thresh * thresh);
-    const T ta = T(alpha), tb = T(beta);
     rr = rrd = linf = 0.0;
 #pragma unroll
     for (int u = 0; u < NP; ++u) {
       __builtin_amdgcn_sched_barrier(0);
       const int l = 2 * (tid() + u * kResThreads);
-      const T2 po = *reinterpret_cast<const T2*>(lds.p + l);
-      const T2 d = q.diag(u);
+      const double2 po = *reinterpret_cast<const double2*>(lds.p + l);
+      const double2 d = q.diag(u);
       if (wide) {
         // |dx| / |x|, and |dx| where x = 0, of dx = rs alpha p^ and x = rs x^, rs = d^-1/2 (in
         // a branch of its own: computed for every cell the root cost an iteration 3 to 5 %)
-        T x0 = fabs(q.x[u][0]), x1 = fabs(q.x[u][1]);
-        if ((!(x0 > T(0)) && po.x != T(0)) || (!(x1 > T(0)) && po.y != T(0))) {
-          if (!(x0 > T(0))) x0 = sqrt(d.x);
-          if (!(x1 > T(0))) x1 = sqrt(d.y);
+        double x0 = fabs(q.x[u][0]), x1 = fabs(q.x[u][1]);
+        if ((!(x0 > 0.0) && po.x != 0.0) || (!(x1 > 0.0) && po.y != 0.0)) {
+          if (!(x0 > 0.0)) x0 = sqrt(d.x);
+          if (!(x1 > 0.0)) x1 = sqrt(d.y);
         }
-        linf = fmax(linf, fmax(double(fabs(ta * po.x) / x0), double(fabs(ta * po.y) / x1)));
+        linf = fmax(linf, fmax(fabs(alpha * po.x) / x0, fabs(alpha * po.y) / x1));
       }
-      q.x[u][0] = fma(ta, po.x, q.x[u][0]);
-      q.x[u][1] = fma(ta, po.y, q.x[u][1]);
-      q.r[u][0] = fma(-ta, q.s[u][0], q.r[u][0]);
-      q.r[u][1] = fma(-ta, q.s[u][1], q.r[u][1]);
-      T2 pn;
-      pn.x = fma(tb, po.x, q.r[u][0]);
-      pn.y = fma(tb, po.y, q.r[u][1]);
-      *reinterpret_cast<T2*>(lds.p + l) = pn;
-      const double a0 = double(q.r[u][0]) * double(q.r[u][0]), a1 = double(q.r[u][1]) * double(q.r[u][1]);
+      q.x[u][0] = fma(alpha, po.x, q.x[u][0]);
+      q.x[u][1] = fma(alpha, po.y, q.x[u][1]);
+      q.r[u][0] = fma(-alpha, q.s[u][0], q.r[u][0]);
+      q.r[u][1] = fma(-alpha, q.s[u][1], q.r[u][1]);
+      double2 pn;
+      pn.x = fma(beta, po.x, q.r[u][0]);
+      pn.y = fma(beta, po.y, q.r[u][1]);
+      *reinterpret_cast<double2*>(lds.p + l) = pn;
+      const double a0 = q.r[u][0] * q.r[u][0], a1 = q.r[u][1] * q.r[u][1];
       rr += a0 + a1;
-      rrd = fma(a0, double(d.x), fma(a1, double(d.y), rrd));
+      rrd = fma(a0, d.x, fma(a1, d.y, rrd));
     }
     for (int h = 2 * tid(); h < nh; h += 2 * kResThreads) {
-      const T2 sn = *reinterpret_cast<const T2*>(lds.ex + h);
-      T2 rn = *reinterpret_cast<const T2*>(lds.rh + h), pn = *reinterpret_cast<const T2*>(lds.p + kCap + h);
-      rn.x = fma(-ta, sn.x, rn.x);
-      rn.y = fma(-ta, sn.y, rn.y);
-      pn.x = fma(tb, pn.x, rn.x);
-      pn.y = fma(tb, pn.y, rn.y);
-      *reinterpret_cast<T2*>(lds.rh + h) = rn;
-      *reinterpret_cast<T2*>(lds.p + kCap + h) = pn;
+      const double2 sn = *reinterpret_cast<const double2*>(lds.ex + h);
+      double2 rn = *reinterpret_cast<const double2*>(lds.rh + h), pn = *reinterpret_cast<const double2*>(lds.p + kCap + h);
+      rn.x = fma(-alpha, sn.x, rn.x);
+      rn.y = fma(-alpha, sn.y, rn.y);
+      pn.x = fma(beta, pn.x, rn.x);
+      pn.y = fma(beta, pn.y, rn.y);
+      *reinterpret_cast<double2*>(lds.rh + h) = rn;
+      *reinterpret_cast<double2*>(lds.p + kCap + h) = pn;
     }
     __syncthreads();
   }
@@ -791,7 +756,7 @@ __device__ __forceinline__ bool solve_part(int my_part, unsigned char* dyn, Shar
   const int nh = 4 * me.n_units;
   double* const dl = reinterpret_cast<double*>(dyn);
   const ResLds at_lds(kCap, size_t(me.n_units), kMode == kCoupled ? size_t(me.n_coarse) : 0, kMode != kStreamed);
-  Lds<double> lds;
+  Lds lds;
   lds.p = dl + at_lds.p;
   lds.rh = dl + at_lds.rh;
   lds.ex = dl + at_lds.ex;
@@ -812,7 +777,7 @@ __device__ __forceinline__ bool solve_part(int my_part, unsigned char* dyn, Shar
   // start: rs = diag^-1/2 exchanged, the scaled operator; x^_0 = x_0 / rs exchanged,
   // r^_0 = rs b - A^ x^_0 exchanged.  Every array is read once, in order; a thread's pairs
   // past the share's end read its first pair and get rs = 0, hence a zero operator.
-  Regs<double, NP, kMode> q;
+  Regs<NP, kMode> q;
   q.face = 0;
   if constexpr (kMode == kStreamed)
     q.cs = reinterpret_cast<double2*>(static_cast<double*>(R.extra) + size_t(blockIdx.x) * kResStreamDoubles);
