@@ -350,7 +350,9 @@ __device__ __forceinline__ void put_sums(const Exchange& X, double (&v)[kSums], 
     word = lane == 5 ? (d3 >> 48) | (e << 16) : word;
     word = lane == 6 ? (e >> 32) | (u64(xcc_id()) << 32) : word;
     word = (word & kMask48) | (u64(X.epoch & 0xffffu) << 48);
-    if (lane < (wide ? kResWords : kResWords - 1)) {
+    // (also the last word, which is read with the maximum only: its stamp of 16 bits then
+    // differs from any that is awaited, however many exchanges lie between two maxima)
+    if (lane < kResWords) {
       if (X.one_xcd) st_word_near(X.words(X.my_part) + lane, word);
       else st_word(X.words(X.my_part) + lane, word);
     }
