@@ -16,7 +16,8 @@ int res_group(int64_t n_oct, int max_blocks, int max_slots, int target_slots) {
 int res_blocks(int g, int n_cu) {
   const int per = std::max(1, n_cu / 8);  // compute units of an XCD
   const int n_xcd = (g + per - 1) / per;
-  return g == 1 ? 1 : std::min(n_cu, 8 * ((g + n_xcd - 1) / n_xcd));
+  // (never fewer than shares: units that are no multiple of 8 leave an XCD over)
+  return g == 1 ? 1 : std::max(g, std::min(n_cu, 8 * ((g + n_xcd - 1) / n_xcd)));
 }
 
 double res_cost(int n_slots, int group) {
