@@ -1109,7 +1109,9 @@ __global__ __launch_bounds__(kResThreads) void k_cg_resident_batch(KernelArgs) {
   }
 }
 
-constexpr size_t kLdsLimit = 160 * 1024 - sizeof(Shared) - 256;
+// What a launch may ask for beside Shared and the 256 bytes of __syncthreads_and.  (That
+// much is a function's default: its attribute is left alone, which all threads share.)
+constexpr size_t kLdsLimit = 160 * 1024 - ((sizeof(Shared) + 15) & ~size_t(15)) - 256;
 
 // Pairs of slots per thread of a share (a batch has no loops of 7: see its kernel).
 int pairs_of(int n_slots, int n_prob) {
@@ -1119,9 +1121,6 @@ int pairs_of(int n_slots, int n_prob) {
 
 hipError_t launch_kernel(void (*f)(KernelArgs), hipStream_t s, const DevLevel& L, const ResPlanDev& R,
                          const ResArgs& A) {
-  const hipError_t e =
-      hipFuncSetAttribute(reinterpret_cast<const void*>(f), hipFuncAttributeMaxDynamicSharedMemorySize, R.lds);
-  if (e != hipSuccess) return e;
   hipLaunchKernelGGL(f, dim3(R.n_blocks), dim3(kResThreads), R.lds, s, KernelArgs{L, R, A});
   return hipGetLastError();
 }

@@ -297,3 +297,33 @@ def test_residuals_down_to_underflow(level, precision, dt, tol):
         assert st["status"] in ((0,) if tol else (0, -5))  # a true residual is never zero
     ref = align(level, o.cells(level), o.E[level], cells)
     assert np.linalg.norm(e - ref) <= 1e-11 * np.linalg.norm(ref)
+
+
+def test_threads_whose_launches_need_other_amounts_of_lds():
+    # the same kernel for shares with few and with many halo units, launched from threads at
+    # the same time: no launch fails (it would be made in sweeps instead)
+    import torch
+    from paper_1401_1112_amd.solver import solver_from_problem
+    ps = [_problem(k, seed=31 + k, compact=c) for k, c in ((700, True), (3000, False), (4096, True), (2000, False))]
+    streams = [torch.cuda.Stream() for _ in ps]
+    solvers = []
+    for p, st in zip(ps, streams):
+        with torch.cuda.stream(st):
+            solvers.append(solver_from_problem(p, stream=st))
+    torch.cuda.synchronize()
+    forms = [[] for _ in ps]
+
+    def work(k):
+        with torch.cuda.stream(streams[k]):
+            for _ in range(40):
+                solvers[k].solve_level(5, 1e-3 / 32 ** 2, 0, 1e-6, raise_on_error=False)
+                forms[k].append(solvers[k].stats()[0]["resident"])
+
+    threads = [threading.Thread(target=work, args=(k,)) for k in range(len(ps))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for s in solvers:
+        s.close()
+    assert all(f == [1] * 40 for f in forms)
