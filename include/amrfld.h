@@ -198,7 +198,8 @@ amrfld_status amrfld_set_coeffs(amrfld_ctx* c, int level, const double* rho, con
  * form_coefs, persistent and inner_tol say (stats: launch_blocks = its blocks,
  * launch_mode as asked for); the other levels run in sweeps.  Should that launch
  * not end because its blocks do not reach the device together, the solve is repeated in
- * sweeps. */
+ * sweeps, and so are the next 16 solves (after further such launches more, up to 1024)
+ * without trying. */
 amrfld_status amrfld_solve_level(amrfld_ctx* c, int level, double dt, int bc_mode, double tol);
 
 /* For callers that cannot allocate device memory (tight serving loops, harnesses

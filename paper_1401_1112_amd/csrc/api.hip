@@ -281,6 +281,8 @@ struct amrfld_ctx {
   int n_cu = 0;    // its compute units
   bool resident_on = true;  // solves that fit run resident
   int wait_limit = 0;       // polls of a wait between blocks; 0: the launch's own
+  int res_skip = 0;         // solves of several blocks still to be made in sweeps
+  int res_backoff = 0;      // of them after the last launch that gave up
   uint64_t param_epoch = 0;  // bumped by every call that changes what a captured step bakes in
   StepGraph step_graph;
   int finest = -1;
@@ -1058,6 +1060,26 @@ ResArgs resident_args(const amrfld_ctx* c, const LevelState& L, double dt, doubl
   return a;
 }
 
+// Whether a host-driven solve runs resident.  After a launch that gave up, because its
+// blocks could not meet within their bound (another process's or stream's kernels hold
+// compute units), the next 16 solves of several blocks are made in sweeps without
+// waiting, after the next such launch 32, up to 1024: beside a lasting holder a solve in
+// sixteen, and soon one in a thousand, spends the 0.3 s.
+constexpr int kResSkipFirst = 16, kResSkipMost = 1024;
+bool take_resident(amrfld_ctx* c, const ResPlanDev& R) {
+  if (!use_resident(c, R)) return false;
+  if (R.n_blocks == 1 || c->res_skip == 0) return true;
+  --c->res_skip;
+  return false;
+}
+void resident_gave_up(amrfld_ctx* c) {
+  c->res_backoff = std::min(kResSkipMost, std::max(kResSkipFirst, 2 * c->res_backoff));
+  c->res_skip = c->res_backoff;
+}
+void resident_ended(amrfld_ctx* c, const ResPlanDev& R) {
+  if (R.n_blocks > 1) c->res_backoff = 0;
+}
+
 // Launches a resident solve in its turn; false: not launchable here.
 bool run_resident(amrfld_ctx* c, hipStream_t s, const DevLevel& D, const ResPlanDev& R, const ResArgs& a) {
   if (R.n_blocks == 1) {  // waits for nobody
@@ -1104,7 +1126,8 @@ amrfld_status solve_one(amrfld_ctx* c, int level, double dt, int mode, double to
   launch_cell_K(s, D, L.E, L.rho, Lc ? Lc->E : nullptr, kparams(L), outer_bc(c), L.K);
   const double w = mode == AMRFLD_BC_DIRICHLET ? 1.0 : mode == AMRFLD_BC_NEUMANN ? 0.0 : c->o.robin_alpha;
   const CouplingParams cp = cparams(c, L);
-  double* Cm = use_resident(c, L) ? L.Ch : nullptr;  // the sweeps' scaled operator is not formed then
+  bool resident = take_resident(c, L.res.d), gave_up = false;
+  double* Cm = resident ? L.Ch : nullptr;  // the sweeps' scaled operator is not formed then
   launch_assemble(s, D, L.K, Lc ? Lc->K : nullptr, L.E, Lc ? Lc->E : nullptr, L.rho, L.reg, dt, w,
                   c->o.robin_alpha, cp, kparams(L), outer_bc(c), L.Cp, L.mask, L.diag, L.b, Cm);
   const double scale = dt / (D.dx * D.dx);
@@ -1118,7 +1141,6 @@ amrfld_status solve_one(amrfld_ctx* c, int level, double dt, int mode, double to
   ls.iters.assign(1, 0);
   const bool registers = Lc && (mode == AMRFLD_BC_NEUMANN || mode == AMRFLD_BC_ROBIN);
   double* reg_c = registers ? ensure_reg(c, *Lc) : nullptr;
-  bool resident = use_resident(c, L), gave_up = false;
   if (resident) {
     check(hipEventRecord(c->ev[1], s), "event");
     ResArgs ra = resident_args(c, L, dt, tol, c->sc);
@@ -1145,8 +1167,11 @@ amrfld_status solve_one(amrfld_ctx* c, int level, double dt, int mode, double to
       check(hipEventRecord(c->ev[3], s), "event");
       read_scalars(c, c->h_sc, c->sc, 1);
       check(hipGetLastError(), "kernels");
-      if (!c->h_sc->done) {
+      if (c->h_sc->done) {
+        resident_ended(c, L.res.d);
+      } else {
         gave_up = true;
+        resident_gave_up(c);
         if (ra.refine) {
           reset_exchange(s, L.res.d);
           launch_copy_f64(s, L.E, E0, D.n_slots);
@@ -1695,7 +1720,7 @@ amrfld_status solve_composite(amrfld_ctx* c, double dt, double tol) {
   // a single level is that level's system (rows times the volume): solved as it is
   const ResTables& res = C.n_levels == 1 ? c->L(base).res : C.res;
   const ResPlanDev& R = res.d;
-  const bool fits = use_resident(c, R);
+  const bool fits = take_resident(c, R);
   bool resident = fits, gave_up = false;
   launch_assemble_composite(s, D, C.K, C.x, C.rho, cp, outer_bc(c), dt, C.Cp, C.cif, C.c2f, C.diag, C.b,
                             resident ? C.Ch : nullptr);
@@ -1722,8 +1747,11 @@ amrfld_status solve_composite(amrfld_ctx* c, double dt, double tol) {
     check(hipEventRecord(c->ev[1], s), "event");
     if (run_resident(c, s, D, R, a)) {
       read_scalars(c, c->h_sc, c->sc, 1);
-      if (!c->h_sc->done) {
+      if (c->h_sc->done) {
+        resident_ended(c, R);
+      } else {
         gave_up = true;
+        resident_gave_up(c);
         resident = resident_timed_out(c, s, R);
       }
       if (c->o.time_sweeps > 0) {
@@ -2199,7 +2227,7 @@ amrfld_status solve_batch(amrfld_ctx* c, const std::vector<amrfld_patch>& pt, in
     c->stats.clear();  // the device cannot run it: poll instead
   }
   ensure_scalars(c, np);
-  bool resident = use_resident(c, B.res.d), gave_up = false;
+  bool resident = take_resident(c, B.res.d), gave_up = false;
   // the batch's precision for this call only, restored on every way out
   struct PrecisionScope {
     amrfld_opts& o;
@@ -2241,7 +2269,10 @@ amrfld_status solve_batch(amrfld_ctx* c, const std::vector<amrfld_patch>& pt, in
         // a launch that did not end: the step again in sweeps, from its first energies
         bool ended = true;
         for (const ResProblem& p : B.res_probs) ended = ended && c->h_sc[p.id].done;
-        if (!ended) {
+        if (ended) {
+          resident_ended(c, B.res.d);
+        } else {
+          resident_gave_up(c);
           reset_exchange(s, B.res.d);
           launch_copy_f64(s, B.E, B.E0, B.n_slots);
           resident = false;
@@ -2786,6 +2817,7 @@ amrfld_status amrfld_set_resident(amrfld_ctx* c, int resident, int wait_limit) {
   }
   c->resident_on = resident != 0;
   c->wait_limit = wait_limit;
+  c->res_skip = c->res_backoff = 0;
   ++c->param_epoch;
   c->err.clear();
   return AMRFLD_OK;

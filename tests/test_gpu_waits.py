@@ -35,13 +35,18 @@ def _fields(s, p):
     return out
 
 
-def _levels(p, mode, resident, wait_limit, precision, unique=False, steps=1, **kw):
+def _levels(p, mode, resident, wait_limit, precision, unique=False, steps=1, level=None, **kw):
     from paper_1401_1112_amd.solver import solver_from_problem
     s = solver_from_problem(p, precision=precision, **kw)
+    if level is not None:
+        s.set_resident(False)
+        s.advance(p.dt_coarse, mode, 1e-10)
     s.set_resident(resident, wait_limit)
     st = []
     for _ in range(steps):
-        if unique:
+        if level is not None:
+            s.solve_level(level, p.dt_coarse, mode, 1e-10)
+        elif unique:
             s.advance_unique(p.dt_coarse, 1e-10)
         else:
             s.advance(p.dt_coarse, mode, 1e-10)
@@ -60,10 +65,18 @@ def test_level_solves_that_give_up_equal_sweeps(precision, mode, coupled):
     ref, st_ref = _levels(p, mode, False, 0, precision)
     got, st = _levels(p, mode, True, 1, precision)
     assert all(x["resident"] == 0 for x in st_ref)
-    assert all(x["resident"] == 2 and x["launch_blocks"] == x["sweep_blocks"] for x in st)
+    assert [x["resident"] for x in st] == [2] + [0] * (len(st) - 1)  # the others do not try
+    assert all(x["launch_blocks"] == x["sweep_blocks"] for x in st)
     assert [x["iters"] for x in st] == [x["iters"] for x in st_ref]
     for a, b in zip(got, ref):
         assert np.array_equal(a, b)
+    # one level's solve alone, after a step in sweeps (and with its register)
+    for level in p.hierarchy.levels:
+        ref, st_ref = _levels(p, mode, False, 0, precision, level=level)
+        got, st = _levels(p, mode, True, 1, precision, level=level)
+        assert [x["resident"] for x in st] == [2] and st[0]["iters"] == st_ref[0]["iters"]
+        for a, b in zip(got, ref):
+            assert np.array_equal(a, b)
 
 
 @pytest.mark.parametrize("precision", [0, 1])
@@ -120,7 +133,8 @@ def test_composite_and_batch_that_give_up_equal_sweeps():
     p = _problem(coupled=False)
     ref, st_ref = _levels(p, 0, False, 0, 0, unique=True)
     got, st = _levels(p, 0, True, 1, 0, unique=True)
-    assert all(x["resident"] == 0 for x in st_ref) and all(x["resident"] == 2 for x in st)
+    assert all(x["resident"] == 0 for x in st_ref)
+    assert [x["resident"] for x in st] == [2] + [0] * (len(st) - 1)
     assert [x["iters"] for x in st] == [x["iters"] for x in st_ref]
     for a, b in zip(got, ref):
         assert np.array_equal(a, b)
@@ -158,3 +172,22 @@ def test_blocks_wait_for_earlier_patches_of_a_batch(form):
     assert status in (0, -5) and {x["resident"] for x in st} == {1}
     its = sorted(x["iters"] for x in st)
     assert its[-2] <= 1 and its[-1] > 1000  # at 3 us or more each: longer than the bound
+
+
+def test_solves_after_one_that_gave_up_do_not_try_again_at_once():
+    from paper_1401_1112_amd.solver import solver_from_problem
+    p = config_uniform(5, kmode="lp", seed=3)
+    s = solver_from_problem(p)
+
+    def forms(n):
+        out = []
+        for _ in range(n):
+            s.solve_level(5, 1e-3 / 32 ** 2, 0, 1e-6)
+            out.append(s.stats()[0]["resident"])
+        return out
+
+    s.set_resident(True, 1)
+    assert forms(1 + 16 + 1 + 32 + 1) == [2] + [0] * 16 + [2] + [0] * 32 + [2]
+    s.set_resident(True)  # starts anew
+    assert forms(3) == [1] * 3
+    s.close()
