@@ -199,7 +199,10 @@ amrfld_status amrfld_set_coeffs(amrfld_ctx* c, int level, const double* rho, con
  * launch_mode as asked for); the other levels run in sweeps.  Should that launch
  * not end because its blocks do not reach the device together, the solve is repeated in
  * sweeps, and so are the next 16 solves (after further such launches more, up to 1024)
- * without trying. */
+ * without trying.  A captured step (opts.graph) and a persistent or captured batch are not
+ * followed by the host and not repeated: they wait longer, as long as for a grid barrier of
+ * persistent sweeps (about a minute), and then return AMRFLD_E_DEVICE with their fields
+ * partly advanced. */
 amrfld_status amrfld_solve_level(amrfld_ctx* c, int level, double dt, int bc_mode, double tol);
 
 /* For callers that cannot allocate device memory (tight serving loops, harnesses

@@ -1080,6 +1080,10 @@ void resident_ended(amrfld_ctx* c, const ResPlanDev& R) {
   if (R.n_blocks > 1) c->res_backoff = 0;
 }
 
+// Of a captured step or a persistent batch, which the host does not follow and repeat.
+constexpr const char* kGaveUp = "resident solve: its blocks did not meet on the device in time; the fields are "
+                                "those of a step that was not finished";
+
 // Launches a resident solve in its turn; false: not launchable here.
 bool run_resident(amrfld_ctx* c, hipStream_t s, const DevLevel& D, const ResPlanDev& R, const ResArgs& a) {
   if (R.n_blocks == 1) {  // waits for nobody
@@ -1427,6 +1431,7 @@ amrfld_status advance_graph(amrfld_ctx* c, double dt_coarse, int mode, double to
   unsigned aborted = 0;
   check(hipMemcpy(&aborted, c->bar + kBarAbort, sizeof(unsigned), hipMemcpyDeviceToHost), "abort flag");
   read_scalars(c, c->h_sc, c->sc, n);
+  bool gave_up = false;
   amrfld_status worst = AMRFLD_OK;
   std::string worst_msg;
   for (int k = 0; k < n; ++k) {
@@ -1436,7 +1441,7 @@ amrfld_status advance_graph(amrfld_ctx* c, double dt_coarse, int mode, double to
     const SweepPlan P = level_plan(c, nt);
     const bool resident = use_resident(c, L);
     if (resident && !h.done) {
-      aborted = 1;
+      gave_up = true;
       h = PcgScalars{};  // of another replay, or of none
       reset_exchange(us, L.res.d);
     }
@@ -1471,6 +1476,7 @@ amrfld_status advance_graph(amrfld_ctx* c, double dt_coarse, int mode, double to
     }
     c->stats.push_back(st);
   }
+  if (gave_up) return fail(c, AMRFLD_E_DEVICE, kGaveUp);
   if (aborted) return fail(c, AMRFLD_E_DEVICE, "persistent sweep: a grid barrier timed out");
   if (worst != AMRFLD_OK) return fail(c, worst, worst_msg);
   return AMRFLD_OK;
@@ -2142,13 +2148,14 @@ amrfld_status solve_batch_persistent(amrfld_ctx* c, const std::vector<amrfld_pat
   unsigned aborted = 0;
   check(hipMemcpy(&aborted, abort_flag, sizeof(unsigned), hipMemcpyDeviceToHost), "abort flag");
   read_scalars(c, c->h_sc, c->sc, n_steps * np);
+  bool gave_up = false;
   amrfld_status worst = AMRFLD_OK;
   std::string worst_msg;
   for (int step = 0; step < n_steps; ++step) {
     for (int q = 0; q < np; ++q) {
       PcgScalars& h = c->h_sc[int64_t(step) * np + q];
-      if (resident && !h.done) {
-        aborted = 1;
+      if (resident && B.is_resident[q] && !h.done) {
+        gave_up = true;
         h = PcgScalars{};  // of another call, or of none
       }
       amrfld_stats st{};
@@ -2180,7 +2187,10 @@ amrfld_status solve_batch_persistent(amrfld_ctx* c, const std::vector<amrfld_pat
       c->stats.push_back(st);
     }
   }
-  if (aborted && resident) reset_exchange(us, B.res.d);
+  if (gave_up) {
+    reset_exchange(us, B.res.d);
+    return fail(c, AMRFLD_E_DEVICE, kGaveUp);
+  }
   if (aborted) return fail(c, AMRFLD_E_DEVICE, "persistent sweep: a grid barrier timed out");
   if (worst != AMRFLD_OK) return fail(c, worst, worst_msg);
   return AMRFLD_OK;

@@ -93,6 +93,7 @@ def test_captured_step_that_gave_up_starts_clean_again(precision):
     for _ in range(3):
         sample_problem_fields(s, p)
         assert s.advance(p.dt_coarse, 2, 1e-10, raise_on_error=False) == L.E_DEVICE
+        assert "did not meet" in s.last_error() and "not finished" in s.last_error()
         assert not any(x["converged"] for x in s.stats())
     s.set_resident(True)
     sample_problem_fields(s, p)
@@ -120,6 +121,7 @@ def test_batch_launches_that_gave_up_start_clean_again(precision, graph):
     b.set_resident(True, 1)
     for _ in range(2):
         assert b.solve(patches, 3, 1e-10, precision=precision, raise_on_error=False)[1] == L.E_DEVICE
+        assert "did not meet" in b.last_error()
     b.set_resident(True)
     got, _ = b.solve(patches, 3, 1e-10, precision=precision)
     b.close()
