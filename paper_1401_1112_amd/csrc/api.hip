@@ -488,6 +488,17 @@ ResTables make_res_tables(hipStream_t s, const ResPlanHost& h, int n_prob) {
   return r;
 }
 
+// Runs f, which makes tables that solves can do without (in sweeps): no failure where the
+// device has no memory for them.  Called after everything else has its memory.
+template <class F>
+void optional_tables(F f) {
+  try {
+    f();
+  } catch (const NoMem&) {
+    (void)hipGetLastError();
+  }
+}
+
 // The resident plan of one level, one share per compute unit at most.
 ResTables level_res_tables(const amrfld_ctx* c, const LevelTables& t) {
   const int g = res_group(t.n_oct, c->n_cu, kResBlockSlots, kResTargetSlots);
@@ -1682,7 +1693,7 @@ void build_composite_into(amrfld_ctx* c, CompositeState* C) {
     const int g = std::max(2, res_group(C->n_oct, c->n_cu, 0, kResTargetSlots));
     const ResPlanHost h =
         build_res_plan({p}, {g}, res_blocks(g, c->n_cu), nbr.data(), C->n_oct, cnb.data(), child.data());
-    if (h.max_slots <= kResBlockSlots) C->res = make_res_tables(c->stream(), h, 1);
+    if (h.max_slots <= kResBlockSlots) optional_tables([&] { C->res = make_res_tables(c->stream(), h, 1); });
   }
   launch_fill(c->stream(), C->x, n, 0.0);  // padding slots keep x = 0 (identity rows)
   launch_fill(c->stream(), C->rho, n, 1.0);
@@ -1922,6 +1933,23 @@ void build_batch_into(amrfld_ctx* c, BatchState* B, const std::vector<int>& size
       }
     }
   }
+  std::vector<int32_t> cnb(6 * B->n_oct, -1);
+  upload(c, &B->nbr, nbr, "batch tables");
+  upload(c, &B->cnb, cnb, "batch tables");
+  upload(c, &B->child, child, "batch tables");
+  upload(c, &B->oct_prob, oct_prob, "batch tables");
+  upload(c, &B->idx, idx, "batch tables");
+  B->E = dalloc<double>(B->n_slots, "batch fields");
+  B->rho = dalloc<double>(B->n_slots, "batch fields");
+  B->K = dalloc<double>(B->n_slots, "batch fields");
+  B->Cp = dalloc<double>(3 * B->n_slots, "batch fields");
+  B->mask = dalloc<uint8_t>(B->n_slots, "batch fields");
+  B->diag = dalloc<double>(B->n_slots, "batch fields");
+  B->b = dalloc<double>(B->n_slots, "batch fields");
+  B->Ch = dalloc<double>(3 * B->n_slots, "batch fields");
+  B->rs = dalloc<double>(B->n_slots, "batch fields");
+  B->pp = dalloc<PatchParams>(B->n_prob, "batch params");
+  B->src = reinterpret_cast<const double**>(dalloc<const double*>(B->n_prob, "batch pointers"));
   // patches that fit a resident solve, the largest first (without those of streamed
   // coefficients should the halo of one be too large for LDS); in shares as large as a
   // block holds once the patches fill the device, else about even
@@ -1954,7 +1982,11 @@ void build_batch_into(amrfld_ctx* c, BatchState* B, const std::vector<int>& size
       shares += group.back();
     }
     const int n_blocks = int(std::min<int64_t>(c->n_cu, shares));
-    B->res = make_res_tables(c->stream(), build_res_plan(probs, group, n_blocks, nbr.data(), B->n_oct), B->n_prob);
+    optional_tables([&] {
+      B->res = make_res_tables(c->stream(), build_res_plan(probs, group, n_blocks, nbr.data(), B->n_oct), B->n_prob);
+      if (B->res.d.parts) B->E0 = dalloc<double>(B->n_slots, "batch fields");
+    });
+    if (!B->E0) B->res.release();
     if (B->res.d.parts) {
       for (int q : order) is_res[q] = 1;
       B->res_probs = probs;
@@ -1987,30 +2019,12 @@ void build_batch_into(amrfld_ctx* c, BatchState* B, const std::vector<int>& size
   B->G_big = big_blk0[B->n_prob];
   B->n_big = B->n_prob - int(std::count(is_res.begin(), is_res.end(), char(1)));
   B->tpb_max = tpb_max;
-  std::vector<int32_t> cnb(6 * B->n_oct, -1);
-  upload(c, &B->nbr, nbr, "batch tables");
-  upload(c, &B->cnb, cnb, "batch tables");
-  upload(c, &B->child, child, "batch tables");
-  upload(c, &B->oct_prob, oct_prob, "batch tables");
-  upload(c, &B->idx, idx, "batch tables");
   upload(c, &B->blk_prob, blk_prob, "batch tables");
   upload(c, &B->blk0, blk0, "batch tables");
   upload(c, &B->big_blk_prob, big_blk_prob, "batch tables");
   upload(c, &B->big_blk0, big_blk0, "batch tables");
   upload(c, &B->tile0, t0v, "batch tables");
   upload(c, &B->d_out_off, B->out_off, "batch tables");
-  B->E = dalloc<double>(B->n_slots, "batch fields");
-  if (B->res.d.parts) B->E0 = dalloc<double>(B->n_slots, "batch fields");
-  B->rho = dalloc<double>(B->n_slots, "batch fields");
-  B->K = dalloc<double>(B->n_slots, "batch fields");
-  B->Cp = dalloc<double>(3 * B->n_slots, "batch fields");
-  B->mask = dalloc<uint8_t>(B->n_slots, "batch fields");
-  B->diag = dalloc<double>(B->n_slots, "batch fields");
-  B->b = dalloc<double>(B->n_slots, "batch fields");
-  B->Ch = dalloc<double>(3 * B->n_slots, "batch fields");
-  B->rs = dalloc<double>(B->n_slots, "batch fields");
-  B->pp = dalloc<PatchParams>(B->n_prob, "batch params");
-  B->src = reinterpret_cast<const double**>(dalloc<const double*>(B->n_prob, "batch pointers"));
   check(hipStreamSynchronize(c->stream()), "batch tables");
 }
 
@@ -2554,7 +2568,7 @@ amrfld_status amrfld_build_level(amrfld_ctx* c, int level, int64_t n_oct, const 
       fresh.Ch = dalloc<double>(3 * n, "fields");
       fresh.rs = dalloc<double>(n, "fields");
       upload_tables(c, fresh);
-      fresh.res = level_res_tables(c, fresh.t);
+      optional_tables([&] { fresh.res = level_res_tables(c, fresh.t); });
     } catch (...) {
       (void)hipStreamSynchronize(c->stream());
       fresh.release();
