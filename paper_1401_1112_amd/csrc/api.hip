@@ -121,14 +121,16 @@ double* scratch_of(int dev, std::string* why) {
 struct ResTables {
   ResPlanDev d;
   int max_tasks = 0;  // shares of one block, one after another
+  // the plan's tables and exchange memory, the exchange numbers, the streamed coefficients
+  unsigned char* mem = nullptr;
+  unsigned* epoch = nullptr;
+  double* coefs = nullptr;
 
   void release() {
-    for (const void* p : {(const void*)d.parts, (const void*)d.places, (const void*)d.partner, (const void*)d.task0,
-                          (const void*)d.task, (const void*)d.lines, (const void*)d.halo, (const void*)d.epoch,
-                          (const void*)d.extra})
-      dfree(const_cast<void*>(p));
-    d = ResPlanDev{};
-    max_tasks = 0;
+    dfree(mem);
+    dfree(epoch);
+    dfree(coefs);
+    *this = ResTables{};
   }
 };
 
@@ -433,19 +435,11 @@ void ensure_workspace32(amrfld_ctx* c, int64_t n) {
 
 // Exchange numbers start at 1 over a cleared exchange memory (stamp 0 is never awaited).
 void reset_exchange(hipStream_t s, const ResPlanDev& d) {
-  launch_fill_u32(s, reinterpret_cast<unsigned*>(d.lines), int64_t(4) * d.n_parts * kResLine, 0u);
-  launch_fill_u32(s, reinterpret_cast<unsigned*>(d.halo), 32 * d.all_units(), 0u);
+  // (the lines and after them the halo memory)
+  unsigned* const lines = reinterpret_cast<unsigned*>(d.lines);
+  launch_fill_u32(s, lines, reinterpret_cast<unsigned*>(d.halo + 16 * d.all_units()) - lines, 0u);
   launch_fill_u32(s, d.epoch, d.n_prob, 1u);
   launch_fill_u32(s, d.epoch + d.n_prob, d.n_prob + 1, 0u);
-}
-
-template <class T>
-const T* upload_const(const std::vector<T>& v, const char* what, hipStream_t s) {
-  T* p = dalloc<T>(int64_t(v.size()), what);
-  const hipError_t e = hipMemcpyAsync(p, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice, s);
-  if (e != hipSuccess) dfree(p);
-  check(e, what);
-  return p;
 }
 
 // Device tables of a resident plan (none where it does not fit a resident launch); the
@@ -461,23 +455,56 @@ ResTables make_res_tables(hipStream_t s, const ResPlanHost& h, int n_prob) {
   r.d.max_slots = h.max_slots;
   r.d.lds = resident_lds(h.parts, h.max_slots, n_prob);
   if (!resident_fits(r.d)) return ResTables{};
+  // one allocation, and one copy where the tables are small: two levels of 4 k slots are set
+  // up in 2.5 ms so, and were in 2.7 with nine allocations and six copies each
+  struct Table {
+    const void* src;
+    size_t bytes, at;
+  };
+  std::vector<Table> tables;
+  size_t end = 0;
+  auto room = [&](size_t bytes) {
+    const size_t at = end;
+    end += (bytes + 255) & ~size_t(255);
+    return at;
+  };
+  auto table = [&](const auto& v) {
+    tables.push_back({v.data(), v.size() * sizeof(v[0]), room(v.size() * sizeof(v[0]))});
+    return tables.back().at;
+  };
+  std::vector<int32_t> pp(h.partner);
+  pp.resize(r.d.far_units());
+  pp.insert(pp.end(), h.peers.begin(), h.peers.end());
+  std::vector<uint32_t> cpl(h.couplings);
+  cpl.insert(cpl.end(), h.coarse.begin(), h.coarse.end());
+  r.d.coupled = !cpl.empty();
+  const size_t parts = table(h.parts), places = table(h.places), partner = table(pp), task0 = table(h.task0),
+               task = table(h.task), extra = table(cpl), copied = end;
+  const size_t lines = room(size_t(2) * r.d.n_parts * kResLine * sizeof(unsigned long long)),
+               halo = room(size_t(16) * r.d.all_units() * sizeof(unsigned long long));
+  std::vector<unsigned char> staged;
   try {
-    r.d.parts = upload_const(h.parts, "resident plan", s);
-    r.d.places = reinterpret_cast<const uint2*>(upload_const(h.places, "resident plan", s));
-    std::vector<int32_t> pp(h.partner);
-    pp.resize(r.d.far_units());
-    pp.insert(pp.end(), h.peers.begin(), h.peers.end());
-    r.d.partner = upload_const(pp, "resident plan", s);
-    std::vector<uint32_t> c(h.couplings);
-    c.insert(c.end(), h.coarse.begin(), h.coarse.end());
-    r.d.coupled = !c.empty();
-    if (r.d.coupled) r.d.extra = const_cast<uint32_t*>(upload_const(c, "resident plan", s));
-    r.d.task0 = upload_const(h.task0, "resident plan", s);
-    r.d.task = upload_const(h.task, "resident plan", s);
-    r.d.lines = dalloc<unsigned long long>(int64_t(2) * r.d.n_parts * kResLine, "resident exchange");
-    r.d.halo = dalloc<unsigned long long>(16 * r.d.all_units(), "resident exchange");
-    r.d.epoch = dalloc<unsigned>(2 * n_prob + 1, "resident exchange");
-    if (const size_t nc = resident_coefs(r.d)) r.d.extra = dalloc<double>(int64_t(nc), "resident coefficients");
+    r.mem = dalloc<unsigned char>(int64_t(end), "resident plan");
+    r.epoch = dalloc<unsigned>(2 * n_prob + 1, "resident exchange");
+    if (const size_t nc = resident_coefs(r.d)) r.coefs = dalloc<double>(int64_t(nc), "resident coefficients");
+    if (copied <= size_t(1) << 20) {
+      staged.resize(copied);
+      for (const Table& t : tables) std::copy_n(static_cast<const unsigned char*>(t.src), t.bytes, &staged[t.at]);
+      check(hipMemcpyAsync(r.mem, staged.data(), copied, hipMemcpyHostToDevice, s), "resident plan");
+    } else {
+      for (const Table& t : tables)
+        if (t.bytes) check(hipMemcpyAsync(r.mem + t.at, t.src, t.bytes, hipMemcpyHostToDevice, s), "resident plan");
+    }
+    r.d.parts = reinterpret_cast<const ResPart*>(r.mem + parts);
+    r.d.places = reinterpret_cast<const uint2*>(r.mem + places);
+    r.d.partner = reinterpret_cast<const int32_t*>(r.mem + partner);
+    r.d.task0 = reinterpret_cast<const int32_t*>(r.mem + task0);
+    r.d.task = reinterpret_cast<const int32_t*>(r.mem + task);
+    r.d.lines = reinterpret_cast<unsigned long long*>(r.mem + lines);
+    r.d.halo = reinterpret_cast<unsigned long long*>(r.mem + halo);
+    r.d.epoch = r.epoch;
+    r.d.extra = r.coefs;
+    if (r.d.coupled) r.d.extra = r.mem + extra;
     reset_exchange(s, r.d);
     check(hipStreamSynchronize(s), "resident plan");
   } catch (...) {
@@ -505,7 +532,9 @@ ResTables level_res_tables(const amrfld_ctx* c, const LevelTables& t) {
   if ((t.n_oct + g - 1) / g * 8 > kResMaxSlots) return ResTables{};
   ResProblem p;
   p.n_oct = t.n_oct;
-  return make_res_tables(c->stream(), build_res_plan({p}, {g}, res_blocks(g, c->n_cu), t.nbr.data(), t.n_oct), 1);
+  const ResPlanHost h =
+      build_res_plan({p}, {g}, res_blocks(g, c->n_cu), t.nbr.data(), t.n_oct, nullptr, nullptr, false);
+  return make_res_tables(c->stream(), h, 1);
 }
 
 // The level's device tables: allocated all together (a failed allocation leaves
@@ -1691,8 +1720,8 @@ void build_composite_into(amrfld_ctx* c, CompositeState* C) {
     p.n_oct = C->n_oct;
     // (at least two blocks: couplings go through the exchange, also those within a share)
     const int g = std::max(2, res_group(C->n_oct, c->n_cu, 0, kResTargetSlots));
-    const ResPlanHost h =
-        build_res_plan({p}, {g}, res_blocks(g, c->n_cu), nbr.data(), C->n_oct, cnb.data(), child.data());
+    const ResPlanHost h = build_res_plan({p}, {g}, res_blocks(g, c->n_cu), nbr.data(), C->n_oct, cnb.data(),
+                                         child.data(), false);
     if (h.max_slots <= kResBlockSlots) optional_tables([&] { C->res = make_res_tables(c->stream(), h, 1); });
   }
   launch_fill(c->stream(), C->x, n, 0.0);  // padding slots keep x = 0 (identity rows)
@@ -1983,7 +2012,8 @@ void build_batch_into(amrfld_ctx* c, BatchState* B, const std::vector<int>& size
     }
     const int n_blocks = int(std::min<int64_t>(c->n_cu, shares));
     optional_tables([&] {
-      B->res = make_res_tables(c->stream(), build_res_plan(probs, group, n_blocks, nbr.data(), B->n_oct), B->n_prob);
+      const ResPlanHost h = build_res_plan(probs, group, n_blocks, nbr.data(), B->n_oct, nullptr, nullptr, false);
+      B->res = make_res_tables(c->stream(), h, B->n_prob);
       if (B->res.d.parts) B->E0 = dalloc<double>(B->n_slots, "batch fields");
     });
     if (!B->E0) B->res.release();

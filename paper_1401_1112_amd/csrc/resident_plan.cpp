@@ -2,8 +2,83 @@
 #include "resident_plan.h"
 
 #include <algorithm>
+#include <atomic>
+#include <condition_variable>
+#include <mutex>
+#include <system_error>
+#include <thread>
 
 namespace amrfld {
+
+namespace {
+
+// Threads that work on the shares of a plan, pass after pass, the calling one among them.
+class Team {
+ public:
+  explicit Team(int threads) {
+    more_.reserve(size_t(std::max(0, threads - 1)));
+    try {
+      while (int(more_.size()) < threads - 1) more_.emplace_back([this] { follow(); });
+    } catch (const std::system_error&) {  // no more threads to be had: those there are will do
+    }
+  }
+  ~Team() {
+    {
+      std::lock_guard<std::mutex> lk(mu_);
+      pass_ = -1;
+    }
+    begin_.notify_all();
+    for (std::thread& t : more_) t.join();
+  }
+  // f(k) for k = 0 .. n - 1.  f throws nothing and writes nothing that another call reads.
+  template <class F>
+  void each(int n, const F& f) {
+    if (more_.empty()) {
+      for (int k = 0; k < n; ++k) f(k);
+      return;
+    }
+    next_ = 0;
+    {
+      std::lock_guard<std::mutex> lk(mu_);
+      call_ = [](const void* g, int k) { (*static_cast<const F*>(g))(k); };
+      f_ = &f;
+      n_ = n;
+      busy_ = int(more_.size());
+      ++pass_;
+    }
+    begin_.notify_all();
+    work();
+    std::unique_lock<std::mutex> lk(mu_);
+    end_.wait(lk, [this] { return busy_ == 0; });
+  }
+
+ private:
+  void work() {
+    for (int k = next_.fetch_add(1); k < n_; k = next_.fetch_add(1)) call_(f_, k);
+  }
+  void follow() {
+    std::unique_lock<std::mutex> lk(mu_);
+    for (int64_t seen = 0;;) {
+      begin_.wait(lk, [&] { return pass_ != seen; });
+      if (pass_ < 0) return;
+      seen = pass_;
+      lk.unlock();
+      work();
+      lk.lock();
+      if (--busy_ == 0) end_.notify_one();
+    }
+  }
+  std::vector<std::thread> more_;
+  std::mutex mu_;
+  std::condition_variable begin_, end_;
+  std::atomic<int> next_{0};
+  int64_t pass_ = 0;
+  int n_ = 0, busy_ = 0;
+  void (*call_)(const void*, int) = nullptr;
+  const void* f_ = nullptr;
+};
+
+}  // namespace
 
 int res_group(int64_t n_oct, int max_blocks, int max_slots, int target_slots) {
   if (8 * n_oct <= max_slots) return 1;
@@ -25,9 +100,12 @@ double res_cost(int n_slots, int group) {
 }
 
 ResPlanHost build_res_plan(const std::vector<ResProblem>& probs, const std::vector<int>& group, int n_blocks,
-                           const int32_t* nbr, int64_t n_oct_table, const int32_t* cnb, const int32_t* child) {
+                           const int32_t* nbr, int64_t n_oct_table, const int32_t* cnb, const int32_t* child,
+                           bool faces, int threads) {
   ResPlanHost h;
-  std::vector<int32_t> part_of(n_oct_table, -1);
+  if (threads <= 0)
+    threads = int(std::min<int64_t>({kResPlanThreads, int64_t(std::max(1u, std::thread::hardware_concurrency())),
+                                     1 + n_oct_table / kResPlanThreadOcts}));
   for (size_t q = 0; q < probs.size(); ++q) {
     const int64_t m = probs[q].n_oct;
     const int g = group[q], p0 = int(h.parts.size());
@@ -57,89 +135,130 @@ ResPlanHost build_res_plan(const std::vector<ResProblem>& probs, const std::vect
       p.prob = probs[q].id;
       p.part0 = p0;
       p.group = g;
-      for (int64_t o = o0; o < o1; ++o) part_of[o] = int32_t(h.parts.size());
       h.max_slots = std::max(h.max_slots, p.n_slots);
       h.parts.push_back(p);
     }
   }
-  h.unit_of.assign(6 * n_oct_table, -1);
+  const int n_parts = int(h.parts.size());
+  Team team(std::min(threads, n_parts));
+  auto oct0 = [&](const ResPart& p) { return int64_t(p.slot0) / 8; };
+  auto oct1 = [&](const ResPart& p) { return (int64_t(p.slot0) + p.n_slots) / 8; };
+  // f(slot, direction, finer oct) for the share's leaves' faces towards finer cells, slot by slot
+  auto towards_finer = [&](const ResPart& p, auto f) {
+    for (int64_t i = p.slot0; i < int64_t(p.slot0) + p.n_slots; ++i) {
+      if (child[i] != -1) continue;
+      const int pos = int(i & 7);
+      for (int d = 0; d < 6; ++d) {
+        const int a = d >> 1, bit = 1 << a;
+        const int32_t nb = nbr[6 * (i >> 3) + d];
+        const int64_t j = ((pos >> a) & 1) != (d & 1) ? i ^ bit : nb >= 0 ? (int64_t(nb) << 3) | (pos ^ bit) : -1;
+        if (j >= 0 && child[j] >= 0) f(i, d, child[j]);
+      }
+    }
+  };
+  // the units counted, then numbered share by share
+  ResArray<uint8_t> outer(n_oct_table);  // bit d: the oct's face d has a halo unit
+  team.each(n_parts, [&](int k) {
+    ResPart& p = h.parts[k];
+    const int64_t o0 = oct0(p), o1 = oct1(p);
+    int32_t n = 0;
+    for (int64_t o = o0; o < o1; ++o) {
+      unsigned m = 0;
+      for (int d = 0; d < 6; ++d) {
+        const int32_t nb = nbr[6 * o + d];
+        m |= unsigned(nb >= 0 ? nb < o0 || nb >= o1 : cnb && cnb[6 * o + d] >= 0) << d;
+      }
+      outer[o] = uint8_t(m);
+      n += __builtin_popcount(m);
+    }
+    if (cnb) towards_finer(p, [&](int64_t, int, int32_t) { ++p.n_coarse; });
+    p.n_units = n + p.n_coarse;
+  });
   int32_t n_units = 0;
   for (ResPart& p : h.parts) {
     p.unit0 = n_units;
-    const int32_t me = part_of[p.slot0 / 8];
-    for (int64_t o = p.slot0 / 8; o < (int64_t(p.slot0) + p.n_slots) / 8; ++o)
-      for (int d = 0; d < 6; ++d) {
-        const int32_t nb = nbr[6 * o + d];
-        if (nb >= 0 ? part_of[nb] != me : cnb && cnb[6 * o + d] >= 0) h.unit_of[6 * o + d] = n_units++;
-      }
-    if (cnb) {
-      // the leaves' faces towards finer cells, slot by slot
-      const int32_t first = n_units;
-      h.couplings.resize(4 * n_oct_table, 0u);
-      for (int64_t i = p.slot0; i < int64_t(p.slot0) + p.n_slots; ++i) {
-        if (child[i] != -1) continue;
-        const int pos = int(i & 7);
-        for (int d = 0; d < 6; ++d) {
-          const int a = d >> 1, bit = 1 << a;
-          const int32_t nb = nbr[6 * (i >> 3) + d];
-          const int64_t j = ((pos >> a) & 1) != (d & 1) ? i ^ bit : nb >= 0 ? (int64_t(nb) << 3) | (pos ^ bit) : -1;
-          if (j < 0 || child[j] < 0) continue;
-          uint32_t& c = h.couplings[i >> 1];
-          if (c == 0) c = uint32_t(n_units - first);
-          c += i & 1 ? 1u << 24 : 1u << 16;
-          h.coarse.resize(2 * size_t(n_units) + 2, 0);
-          h.coarse[2 * size_t(n_units)] = int32_t(i - p.slot0);
-          h.coarse[2 * size_t(n_units) + 1] = 8 * child[j] + (d ^ 1);
-          ++n_units;
-        }
-      }
-      p.n_coarse = n_units - first;
-    }
-    p.n_units = n_units - p.unit0;
+    n_units += p.n_units;
     h.max_units = std::max(h.max_units, p.n_units);
   }
-  h.partner.assign(n_units, -1);
-  for (const ResPart& p : h.parts)
-    for (int64_t o = p.slot0 / 8; o < (int64_t(p.slot0) + p.n_slots) / 8; ++o)
+  ResArray<int32_t> unit0(n_oct_table);  // first unit of an oct
+  auto unit_of = [&](int64_t face) {
+    const int64_t o = face / 6;
+    return unit0[o] + __builtin_popcount(outer[o] & ((1u << (face % 6)) - 1u));
+  };
+  std::vector<int32_t> share_of(n_units);
+  h.places.resize(8 * n_oct_table);
+  if (faces) h.unit_of.assign(6 * n_oct_table, -1);
+  if (cnb) {
+    h.couplings.resize(4 * n_oct_table, 0u);
+    h.coarse.resize(2 * size_t(n_units), 0);
+  }
+  team.each(n_parts, [&](int k) {
+    const ResPart& p = h.parts[k];
+    std::fill_n(share_of.begin() + p.unit0, p.n_units, int32_t(k));
+    int32_t next = p.unit0;
+    for (int64_t o = oct0(p); o < oct1(p); ++o) {
+      int32_t unit[6];
+      unit0[o] = next;
       for (int d = 0; d < 6; ++d) {
-        const int32_t u = h.unit_of[6 * o + d];
-        if (u >= 0 && nbr[6 * o + d] >= 0) h.partner[u] = h.unit_of[6 * int64_t(nbr[6 * o + d]) + (d ^ 1)];
+        unit[d] = (outer[o] >> d) & 1 ? next++ : -1;
+        if (faces) h.unit_of[6 * o + d] = unit[d];
       }
-  if (cnb) h.coarse.resize(2 * size_t(n_units), 0);
-  for (const ResPart& p : h.parts)
+      for (int q = 0; q < 4; ++q) {  // pair q of the oct: y = q & 1, z = q >> 1
+        const unsigned own = unsigned(8 * o + 2 * q - p.slot0);
+        auto place = [&](int d, unsigned self, unsigned inside, unsigned cell) -> unsigned {
+          if (unit[d] >= 0) return kResHalo | unsigned(4 * (unit[d] - p.unit0)) + cell;
+          const int32_t nb = nbr[6 * o + d];
+          return nb < 0 ? self : unsigned(8 * int64_t(nb) - p.slot0) + inside;
+        };
+        const int y = q & 1, z = q >> 1;
+        const unsigned x0 = place(0, own, unsigned(2 * q + 1), unsigned(q));
+        const unsigned x1 = place(1, own + 1, unsigned(2 * q), unsigned(q));
+        const unsigned py = place(2 + y, own, unsigned(2 * (q ^ 1)), unsigned(2 * z));
+        const unsigned pz = place(4 + z, own, unsigned(2 * (q ^ 2)), unsigned(2 * y));
+        h.places[8 * o + 2 * q] = x0 | (x1 << 16);
+        h.places[8 * o + 2 * q + 1] = py | (pz << 16);
+      }
+    }
+    if (cnb) {
+      const int32_t first = next;
+      towards_finer(p, [&](int64_t i, int d, int32_t finer) {
+        uint32_t& c = h.couplings[i >> 1];
+        if (c == 0) c = uint32_t(next - first);
+        c += i & 1 ? 1u << 24 : 1u << 16;
+        h.coarse[2 * size_t(next)] = int32_t(i - p.slot0);
+        h.coarse[2 * size_t(next) + 1] = 8 * finer + (d ^ 1);
+        ++next;
+      });
+    }
+  });
+  h.partner.assign(n_units, -1);
+  team.each(n_parts, [&](int k) {
+    const ResPart& p = h.parts[k];
+    for (int64_t o = oct0(p); o < oct1(p); ++o)
+      for (int d = 0, u = unit0[o]; outer[o] >> d; ++d)
+        if ((outer[o] >> d) & 1) {
+          const int32_t nb = nbr[6 * o + d];
+          if (nb >= 0) h.partner[u] = unit_of(6 * int64_t(nb) + (d ^ 1));
+          ++u;
+        }
+    // (a finer oct's face towards a coarser leaf has that leaf's unit for its only partner)
     for (int32_t u = p.unit0 + p.n_units - p.n_coarse; u < p.unit0 + p.n_units; ++u) {
-      const int32_t f = h.unit_of[6 * int64_t(h.coarse[2 * u + 1] >> 3) + (h.coarse[2 * u + 1] & 7)];
+      const int32_t c = h.coarse[2 * size_t(u) + 1], f = unit_of(6 * int64_t(c >> 3) + (c & 7));
       h.partner[u] = f;
       h.partner[f] = u;
     }
-  std::vector<int32_t> share_of(n_units);
-  for (size_t k = 0; k < h.parts.size(); ++k)
-    std::fill_n(share_of.begin() + h.parts[k].unit0, h.parts[k].n_units, int32_t(k));
-  h.n_near = ResPlanHost::near_base(n_units, int32_t(h.parts.size()));
+  });
+  h.n_near = ResPlanHost::near_base(n_units, n_parts);
   h.peers.resize(2 * size_t(n_units));
-  for (int32_t u = 0; u < n_units; ++u) {
-    const int32_t k = share_of[h.partner[u]];
-    const ResPart& p = h.parts[k];
-    h.peers[2 * size_t(u)] = ResPlanHost::near_base(p.unit0, k) + (h.partner[u] - p.unit0);
-    h.peers[2 * size_t(u) + 1] = k - p.part0;
-  }
-  h.places.assign(8 * n_oct_table, 0);
-  for (const ResPart& p : h.parts)
-    for (int64_t o = p.slot0 / 8; o < (int64_t(p.slot0) + p.n_slots) / 8; ++o)
-      for (int k = 0; k < 4; ++k) {  // pair k of the oct: y = k & 1, z = k >> 1
-        const unsigned own = unsigned(8 * o + 2 * k - p.slot0);
-        auto place = [&](int d, unsigned self, unsigned inside, unsigned cell) -> unsigned {
-          const int32_t nb = nbr[6 * o + d], u = h.unit_of[6 * o + d];
-          if (u >= 0) return kResHalo | unsigned(4 * (u - p.unit0)) + cell;
-          return nb < 0 ? self : unsigned(8 * int64_t(nb) - p.slot0) + inside;
-        };
-        const int y = k & 1, z = k >> 1;
-        const unsigned x0 = place(0, own, unsigned(2 * k + 1), unsigned(k)), x1 = place(1, own + 1, unsigned(2 * k), unsigned(k));
-        const unsigned py = place(2 + y, own, unsigned(2 * (k ^ 1)), unsigned(2 * z));
-        const unsigned pz = place(4 + z, own, unsigned(2 * (k ^ 2)), unsigned(2 * y));
-        h.places[8 * o + 2 * k] = x0 | (x1 << 16);
-        h.places[8 * o + 2 * k + 1] = py | (pz << 16);
-      }
+  team.each(n_parts, [&](int me) {
+    const ResPart& mine = h.parts[me];
+    for (int32_t u = mine.unit0; u < mine.unit0 + mine.n_units; ++u) {
+      const int32_t k = share_of[h.partner[u]];
+      const ResPart& p = h.parts[k];
+      h.peers[2 * size_t(u)] = ResPlanHost::near_base(p.unit0, k) + (h.partner[u] - p.unit0);
+      h.peers[2 * size_t(u) + 1] = k - p.part0;
+    }
+  });
   // Blocks: each problem goes to the `group` least loaded blocks.  Every block works on
   // its shares in the order of the problems, so the first unfinished problem always has
   // all its blocks on it: no block waits for one that waits for it.

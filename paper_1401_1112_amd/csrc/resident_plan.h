@@ -4,11 +4,36 @@
 
 #include <cstddef>
 #include <cstdint>
+#include <memory>
+#include <utility>
 #include <vector>
 
 namespace amrfld {
 
 constexpr unsigned kResHalo = 0x8000u;
+
+// Entries that are not set when an array is made: a large plan is written by several
+// threads, each of which so is the first to touch its part.
+template <class T>
+struct ResNoInit : std::allocator<T> {
+  template <class U>
+  struct rebind {
+    typedef ResNoInit<U> other;
+  };
+  ResNoInit() = default;
+  template <class U>
+  ResNoInit(const ResNoInit<U>&) {}
+  template <class U>
+  void construct(U* p) {
+    ::new (static_cast<void*>(p)) U;
+  }
+  template <class U, class... A>
+  void construct(U* p, A&&... a) {
+    ::new (static_cast<void*>(p)) U(std::forward<A>(a)...);
+  }
+};
+template <class T>
+using ResArray = std::vector<T, ResNoInit<T>>;
 
 // One block's share of a problem: a contiguous range of its slots.
 struct ResPart {
@@ -37,15 +62,15 @@ struct ResLds {
 
 struct ResPlanHost {
   std::vector<ResPart> parts;
-  // unit_of[6 o + d]: number of the halo unit of oct o's face d, or -1.  Units are
-  // numbered share by share, so a share's units are contiguous.
+  // unit_of[6 o + d]: number of the halo unit of oct o's face d, or -1 (where asked for).
+  // Units are numbered share by share, so a share's units are contiguous.
   std::vector<int32_t> unit_of;
   // places[2 k], places[2 k + 1] of the slots 2 k and 2 k + 1, neighbours in x: where a
   // share's block finds their out-of-oct neighbours, 16 bits each.  Low and high half of
   // the first word: the neighbour in x of either slot; of the second: the pair of
   // neighbours in y, in z.  A position in the share, or kResHalo and a position among
   // its halo cells (four per unit); the slot or pair itself where there is none.
-  std::vector<uint32_t> places;
+  ResArray<uint32_t> places;
   // partner[u]: the unit of the same face seen from the other side (the neighbour
   // share writes its four cells there)
   std::vector<int32_t> partner;
@@ -96,8 +121,13 @@ double res_cost(int n_slots, int group);
 // n_oct_table: rows of nbr.  cnb, child (not null: a system with couplings between levels):
 // the coarser leaf behind each face without a neighbour oct, -1 where there is none; the
 // oct that refines each slot, negative where there is none, -1 where the slot is a leaf.
+// faces: unit_of as well.  threads: 0 for one per kResPlanThreadOcts octs, at most
+// kResPlanThreads; the plan is the same whatever their number.  Two million octs take 126 ms
+// in one thread, 48 in four and 36 in eight; for 40 thousand (2 ms) starting threads costs
+// what they save.
+constexpr int64_t kResPlanThreads = 8, kResPlanThreadOcts = 65536;
 ResPlanHost build_res_plan(const std::vector<ResProblem>& probs, const std::vector<int>& group, int n_blocks,
                            const int32_t* nbr, int64_t n_oct_table, const int32_t* cnb = nullptr,
-                           const int32_t* child = nullptr);
+                           const int32_t* child = nullptr, bool faces = true, int threads = 0);
 
 }  // namespace amrfld
