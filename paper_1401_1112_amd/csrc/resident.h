@@ -86,6 +86,10 @@ struct ResArgs {
   double* T_out = nullptr;
   double dt = 0.0;
   unsigned meet_limit = 0, spin_limit = 0;  // polls of a share's first exchange, of a later one
+  // Of one problem, beside other launches: block b works on share b, and there is no other
+  // block.  (Alone the shares lie on as few XCDs as hold them, which takes a grid over all of
+  // them: 32 shares take 3.7 us an iteration so and 4.5 spread.)  The same bits either way.
+  int spread = 0;
 };
 
 // Whether a block's share of this plan fits its registers and LDS.
@@ -94,8 +98,8 @@ int resident_lds(const std::vector<ResPart>& parts, int max_slots, int n_prob);
 // Doubles of the streamed coefficients of a plan (0: none of its shares streams them).
 size_t resident_coefs(const ResPlanDev& R);
 // All blocks have to be on the device together (at most one per compute unit): no other
-// kernel whose blocks wait for each other may run meanwhile.  An ordinary launch: a
-// cooperative one goes through a hardware queue of its own, which costs 20 to 130 us of
+// kernel whose blocks wait for each other may run meanwhile, but for such as leave a unit
+// for each block.  An ordinary launch: a cooperative one goes through a hardware queue of its own, which costs 20 to 130 us of
 // waits between the queues on a solve of 300 us.
 hipError_t launch_resident(hipStream_t s, const DevLevel& L, const ResPlanDev& R, const ResArgs& A);
 

@@ -1049,18 +1049,30 @@ __device__ __forceinline__ bool solve_part(int my_part, unsigned char* dyn, Shar
   return true;
 }
 
-// A block that gave up at its k-th share leaves: none of the problems it leads from there
-// on is completed by this launch.
-__device__ __forceinline__ void give_up(int k) {
+// The tasks of a block, [first, end), and the share of one.
+struct Tasks {
+  int first, end;
+};
+__device__ __forceinline__ Tasks tasks_of_block(const KernelArgs& k) {
+  const int b = int(blockIdx.x);
+  if (k.A.spread) return Tasks{b, b + 1};
+  return Tasks{k.R.task0[b], k.R.task0[b + 1]};
+}
+__device__ __forceinline__ int share_of(const KernelArgs& k, int task) { return k.A.spread ? task : k.R.task[task]; }
+
+// A block that gave up at a task leaves: none of the problems it leads from there on is
+// completed by this launch.
+__device__ __forceinline__ void give_up(int task) {
   if (threadIdx.x != 0) return;
   const KernelArgs args = kernel_args();
   const ResPlanDev& R = args.R;
   const ResArgs& A = args.A;
   st_word32(R.epoch + 2 * R.n_prob, 1u);
-  for (; k < R.task0[blockIdx.x + 1]; ++k) {
-    const ResPart& p = R.parts[R.task[k]];
+  for (const int end = tasks_of_block(args).end; task < end; ++task) {
+    const int part = share_of(args, task);
+    const ResPart& p = R.parts[part];
     PcgScalars& o = A.sc[p.prob];
-    if (R.task[k] == p.part0 && !(A.resume && settled(o, A))) o.done = 0;
+    if (part == p.part0 && !(A.resume && settled(o, A))) o.done = 0;
   }
 }
 
@@ -1068,11 +1080,9 @@ template <int NP, ResMode kMode>
 __global__ __launch_bounds__(kResThreads) void k_cg_resident(KernelArgs) {
   extern __shared__ __align__(16) unsigned char res_lds[];
   __shared__ Shared S;
-  const int b = int(blockIdx.x);
-  const KernelArgs args = kernel_args();
-  const int end = args.R.task0[b + 1];
-  for (int k = args.R.task0[b]; k < end; ++k) {
-    if (!solve_part<NP, kMode>(kernel_args().R.task[k], res_lds, S)) {
+  const Tasks t = tasks_of_block(kernel_args());
+  for (int k = t.first; k < t.end; ++k) {
+    if (!solve_part<NP, kMode>(share_of(kernel_args(), k), res_lds, S)) {
       give_up(k);
       return;
     }
@@ -1085,12 +1095,10 @@ __global__ __launch_bounds__(kResThreads) void k_cg_resident(KernelArgs) {
 __global__ __launch_bounds__(kResThreads) void k_cg_resident_batch(KernelArgs) {
   extern __shared__ __align__(16) unsigned char res_lds[];
   __shared__ Shared S;
-  const int b = int(blockIdx.x);
-  const KernelArgs args = kernel_args();
-  const int end = args.R.task0[b + 1];
-  for (int k = args.R.task0[b]; k < end; ++k) {
+  const Tasks t = tasks_of_block(kernel_args());
+  for (int k = t.first; k < t.end; ++k) {
     const KernelArgs now = kernel_args();
-    const int part = now.R.task[k];
+    const int part = share_of(now, k);
     bool ok;
     switch ((now.R.parts[part].n_slots + 2 * kResThreads - 1) / (2 * kResThreads)) {
       case 1: ok = solve_part<1, kHeld>(part, res_lds, S); break;
@@ -1121,7 +1129,7 @@ int pairs_of(int n_slots, int n_prob) {
 
 hipError_t launch_kernel(void (*f)(KernelArgs), hipStream_t s, const DevLevel& L, const ResPlanDev& R,
                          const ResArgs& A) {
-  hipLaunchKernelGGL(f, dim3(R.n_blocks), dim3(kResThreads), R.lds, s, KernelArgs{L, R, A});
+  hipLaunchKernelGGL(f, dim3(A.spread ? R.n_parts : R.n_blocks), dim3(kResThreads), R.lds, s, KernelArgs{L, R, A});
   return hipGetLastError();
 }
 

@@ -327,3 +327,45 @@ def test_threads_whose_launches_need_other_amounts_of_lds():
     for s in solvers:
         s.close()
     assert all(f == [1] * 40 for f in forms)
+
+
+def test_contexts_side_by_side_are_the_same_bits():
+    # eight contexts on threads of their own with levels of 8 to 96 shares: their launches
+    # run side by side or in turn, in the form for company or alone, with the bits of the
+    # context alone, and none gives up
+    import torch
+    from paper_1401_1112_amd.solver import solver_from_problem, to_numpy
+    ps = [_problem(k, seed=50 + k) for k in (650, 900, 1400, 2000, 3000, 4000, 4096)] + \
+        [config_uniform(5, kmode="lp", seed=4)]
+    lv = [5] * len(ps)
+    alone = [_solve(p, l, 12.0 / 32 ** 2, 1e-10)[0] for p, l in zip(ps, lv)]
+    streams = [torch.cuda.Stream() for _ in ps]
+    solvers = []
+    for p, st in zip(ps, streams):
+        with torch.cuda.stream(st):
+            solvers.append(solver_from_problem(p, stream=st))
+    torch.cuda.synchronize()
+    out, forms = [[] for _ in ps], [[] for _ in ps]
+
+    def work(k):
+        p, s = ps[k], solvers[k]
+        with torch.cuda.stream(streams[k]):
+            for _ in range(12):
+                for l in p.hierarchy.levels:
+                    c = s.cells(l)
+                    s.set_fields(l, p.rho(l, c), p.E(l, c), kmode=1)
+                s.solve_level(lv[k], 12.0 / 32 ** 2, 0, 1e-10)
+                forms[k].append(s.stats()[0]["resident"])
+                out[k].append(s.E(lv[k]))
+        streams[k].synchronize()
+
+    threads = [threading.Thread(target=work, args=(k,)) for k in range(len(ps))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for k, s in enumerate(solvers):
+        assert forms[k] == [1] * 12
+        for e in out[k]:
+            assert np.array_equal(to_numpy(e), alone[k]), k
+        s.close()
