@@ -70,8 +70,10 @@ typedef enum { AMRFLD_BC_DIRICHLET = 0, AMRFLD_BC_NEUMANN = 1, AMRFLD_BC_ROBIN =
  * rule of Sect. 3.3.4 on that residual.  Between two refinement sweeps the FP32 CG
  * reduces its residual by inner_tol; after each sweep it continues from the new
  * residual with its search direction kept (residual replacement).  Levels and patches that
- * are solved resident on the chip (see amrfld_solve_level) keep the refinement and its
- * stopping rule, with an inner CG in FP64. */
+ * are solved resident on the chip (see amrfld_solve_level) keep the refinement, inner_tol,
+ * max_outer and the stopping rule, with an inner CG in FP64 whose segments are counted as
+ * refinement sweeps; the true residual is formed where the last one met its threshold.  (A
+ * captured solve makes five such checks at most.) */
 typedef enum { AMRFLD_FP64 = 0, AMRFLD_MIXED = 1 } amrfld_precision;
 typedef enum { AMRFLD_K_CONST = 0, AMRFLD_K_LP = 1, AMRFLD_K_MINERBO = 2, AMRFLD_K_POWER = 3 } amrfld_kmode;
 
@@ -195,7 +197,7 @@ amrfld_status amrfld_set_coeffs(amrfld_ctx* c, int level, const double* rho, con
  * Returns AMRFLD_E_NOCONV if max_iter was reached.
  * A solve whose level fits the device's registers and LDS (about 2.1 million slots) runs
  * resident: one launch that keeps the whole CG state on the chip, whatever max_blocks,
- * form_coefs, persistent and inner_tol say (stats: launch_blocks = its blocks,
+ * form_coefs and persistent say (stats: resident = 1, launch_blocks = its blocks,
  * launch_mode as asked for); the other levels run in sweeps.  Should that launch
  * not end because its blocks do not reach the device together, the solve is repeated in
  * sweeps, and so are the next 16 solves (after further such launches more, up to 1024)

@@ -179,7 +179,7 @@ def run_unique(steps: int) -> None:
 
 
 def _short(name: str) -> str:
-    for pre in ("amrfld::(anonymous namespace)::", "void "):
+    for pre in ("amrfld::(anonymous namespace)::", "void ", "(ResMode)"):
         name = name.replace(pre, "")
     return name.split("(")[0][:60]
 
