@@ -99,8 +99,8 @@ int resident_lds(const std::vector<ResPart>& parts, int max_slots, int n_prob);
 size_t resident_coefs(const ResPlanDev& R);
 // All blocks have to be on the device together (at most one per compute unit): no other
 // kernel whose blocks wait for each other may run meanwhile, but for such as leave a unit
-// for each block.  An ordinary launch: a cooperative one goes through a hardware queue of its own, which costs 20 to 130 us of
-// waits between the queues on a solve of 300 us.
+// for each block.  An ordinary launch: a cooperative one goes through a hardware queue of
+// its own, which costs 20 to 130 us of waits between the queues on a solve of 300 us.
 hipError_t launch_resident(hipStream_t s, const DevLevel& L, const ResPlanDev& R, const ResArgs& A);
 
 }  // namespace amrfld

@@ -25,8 +25,8 @@
 // towards finer cells is a unit with their four values, added to its row by its thread
 // with coefficients from LDS.  All couplings go through the exchange, also those within
 // a share.  Four levels of 353 k slots, 400 iterations in four solves: 13.1 ms with
-// sweeps and a kernel for the couplings, 4.2 so (9.3 us per iteration: shares of 1400
-// slots have 340 to 520 units, as many as shares of 4880 slots of one level).
+// sweeps and a kernel for the couplings, 4.1 so (8.3 us per iteration: shares of 1400
+// slots have 207 to 658 units, as many as shares of 4880 slots of one level).
 //
 // Every exchanged word carries the number of its exchange (a 64-bit word holds data
 // and stamp), so a reader polls the data itself: no barrier, no flag after the data and
@@ -440,7 +440,7 @@ enum ResMode { kHeld, kStreamed, kCoupled };
 // the coefficients read in every iteration, from memory that this block alone uses: 44
 // bytes per slot that L2 and the last-level cache largely hold, against the 115 of a
 // sweep.  What ends it at 8192 slots is the register file.  64 patches of 16.9 M cells,
-// the 7.8 M of five of them in streamed shares (128^3 and less): 42.8 ms for two steps
+// the 7.8 M of five of them in streamed shares (128^3 and less): 40 ms for two steps
 // against 69 with sweeps of those five.
 template <int NP, ResMode kMode>
 struct Regs;
